@@ -97,7 +97,8 @@ def draw(rng):
     if kind == "quantize":
         return dict(kind="quantize", m=_log(rng, 1, 4096), k=_log(rng, 1024, 28672, 256), x=rng.choice(["f32", "bf16"]),
                     group=group, gsum=rng.random() < 0.3)
-    return dict(kind="prepack", k=_log(rng, 1024, 28672, 256), n=_log(rng, 1024, 16384, 8), group=group, codec=codec)
+    # (K in steps of 1024: the blob then ends with its last scale, without alignment bytes of undefined content)
+    return dict(kind="prepack", k=_log(rng, 1024, 28672, 1024), n=_log(rng, 1024, 16384, 8), group=group, codec=codec)
 
 
 def _projections(case):
