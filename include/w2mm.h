@@ -67,15 +67,14 @@ typedef enum {
 } w2_status_t;
 
 /* Kernel families, for w2_matmul_a8_ex / w2_matmul_a16_ex and the debug export.
- * AUTO picks by shape.  w2a8: GEMV up to M = 8 wherever the rows fit a workgroup's local memory (up to 16
- * while two workgroups share a CU or the projection is narrow: N <= 10240 or at most 256 workgroups; up to 32
- * for K <= 4096), MIDM above it up to
- * M = 64 (128 when N <= 4096; 32 when N >= 24576 or, with a workspace, K >= 14336), else TILED (64-row
- * tiles; 128-row tiles from M = 1024, or from M = 128 where they fill the chip).
- * w2a16: GEMV up to M = 8 (up to 16 for K <= 4096; up to 4 for K > 5120 with N >= 32768) wherever the bf16
- * rows fit a workgroup's local memory, SMALLM for the rest up to M = 8 (M = 2 for K > 16384; M = 4 for
- * K > 8192 with a workspace), MIDM up to M = 64 (M = 128 when N <= 4096, M = 40 when N >= 32768), else the
- * SCALED16 tiled kernel.
+ * AUTO picks by shape.  w2a8: GEMV up to M = 8 (M = 4 where the rows leave a workgroup little room or the
+ * projection has few columns and K > 4096; M = 12 with G = 64 and N >= 16384), MIDM above it up to M = 240
+ * (160 when N > 7168, 112 when N >= 24576, 48 when N >= 40960), else TILED (64-row tiles; 128-row tiles from
+ * M = 1024, or from M = 128 where they fill the chip).
+ * w2a16: GEMV up to M = 8 (M = 4 when K > 4096, 7 at K = 5120 with N >= 10240, 2 when K > 16384; M = 16 with
+ * G = 64, K <= 4096 and N >= 16384) wherever the bf16 rows fit a workgroup's local memory, else SMALLM; MIDM
+ * up to M = 192 (256 when N <= 7168 and K <= 14336, 96 when N >= 16384 or K*N > 160 Mi, 64 when N >= 40960),
+ * else the SCALED16 tiled kernel.
  * GEMV: the decode kernel: whole rows in local memory, a wave streams a contiguous run of a column
  * block's tiles through a rolling register window into int8 MFMA (w2a8, M <= 32) or, with bf16 rows left as they
  * are and the zero-point weight construction, into bf16 MFMA (w2a16, M <= 16; W2_ERR_UNSUPPORTED_SHAPE when the
@@ -84,8 +83,9 @@ typedef enum {
  * with split-K across the waves of a workgroup (M <= 4; kept as the dot-product form of the microkernel,
  * selectable here).  SMALLM: one 16-row int8 (bf16 for a16) MFMA tile per
  * wave, split-K across waves (M <= 16).  MIDM: the weight stream
- * is still read once per band of 64 rows; every streamed tile is multiplied into one to four
- * 16-row MFMA tiles (M <= 256 = four bands; for w2a16 with the SCALED16 weight construction).
+ * is read once per band of up to 64 rows; every up-converted weight is multiplied into one to four
+ * 16-row MFMA tiles, K split over the waves of a workgroup (M <= 256; for w2a16 with the SCALED16
+ * weight construction).
  * TILED: LDS-staged MFMA tiles (any M; for w2a16 the zero-point construction).
  * SCALED16 (w2a16 only): the weights are built as sw*q from code and group
  * scale (Sec. II-D, the alternative 16-bit construction) and go to the bf16
@@ -114,13 +114,13 @@ typedef struct {
     int small_kc;         /* ... k per local-memory chunk of the activations: a multiple of 256 */
     int gemv_window;      /* GEMV: weight tiles a wave keeps in flight: 2, 4 or 8 */
     int gemv_max_m;       /* w2a8 AUTO: largest M given to GEMV (1..32) */
-    int midm_cbw;         /* MIDM: column blocks per workgroup: 2, 4 or 8 */
+    int midm_cbw;         /* MIDM: column blocks per workgroup: 2, 4 or 8 (w2a16: 8 = 4) */
     int tiled_bm;         /* w2a8 TILED: rows per workgroup: 64 or 128 (128: G = 128) */
     int tiled_bn;         /* TILED / SCALED16 tiled kernels: columns per workgroup: 128 or 256 (w2a8, 64-row tiles: also 64) */
     int tiled_kw;         /* w2a8 TILED, 128-column workgroups: K ranges inside a workgroup: 1, 2 or 4 */
     int tiled_wd;         /* w2a8 TILED, 64-row tiles: weight stages in flight per wave: 2 or 8 */
     int tiled_group_m;    /* ... row tiles per band of the workgroup order: 1..1024 */
-    int splitk;           /* tiled and mid-M kernels: 1 = never split K, n = 2..16: n parts if the workspace holds them */
+    int splitk;           /* tiled kernels: 1 = never split K, n = 2..16: n parts if the workspace holds them */
     int splitk_min_tiles; /* ... planner: fewest 256-k tiles per part, 1..1024 */
     int stream_unroll;    /* w2_debug_stream_read: 1 KiB chunks in flight per wave: 4, 8 or 16 */
     int stream_blocks;    /* ... most workgroups launched: 1..65536 */
@@ -177,15 +177,14 @@ W2_API int w2_quantize_rows(const void* X, w2_dtype_t x_dtype, int64_t M, int64_
  *   acc[m,g,n] = sum_{k in group g} xq[m,k] * q[k,n]            (int32, exact)
  *   Y[m,n]     = bf16( sx[m] * sum_g sw[g,n] * float(acc[m,g,n]) )   (fp32)
  * packed  dev, from w2_prepack with the same K, N, G
- *         Weight scales: finite bf16 with |sw| < 2^63 (for M > 8 the kernels
+ *         Weight scales: finite bf16 with |sw| < 2^63 (for M > 4 the kernels
  *         multiply by sw * 2^64 in fp32); results below the fp32 normal range
  *         (|sx * sw * acc| < 2^-126) may lose precision.
  * xq, sx  dev, as produced by w2_quantize_rows ([M][K] dense, [M])
  * Y       dev, bf16 bit patterns [M][N], row stride ldy
  * workspace  optional (NULL / 0: none), dev, 16-byte aligned, contents
  *            undefined before and after: on shapes with few output tiles
- *            and a deep K (M > 32: the tiled kernel; 4 <= M <= 128 and
- *            K >= 13568: the mid-M kernel) K is split across workgroups
+ *            and a deep K (the tiled kernels) K is split across workgroups
  *            (Sec. II-D, K-splitting for the smaller GEMM shapes) if there
  *            is room for the fp32 partial results (w2_workspace_size; less
  *            room = fewer parts or none, same result contract).  A second
@@ -306,7 +305,8 @@ W2_API int w2_matmul_a16_epi(const void* packed, int64_t K, int64_t N, int G, co
  * split-K part only and accepts the same buffer): room for the int8 rows and
  * their scales, rounded up to 256 bytes (0 where one launch covers the
  * quantisation: one or two rows of up to 64 KiB as fp32), plus, where a
- * kernel would split K, 2..16 fp32 copies of the M x N output.  a16 = 1
+ * tiled kernel would split K (and for 4 <= M <= 128 on K >= 13568, where
+ * nothing uses it any more), 2..16 fp32 copies of the M x N output.  a16 = 1
  * (w2_matmul_a16): the split-K part alone.  0 means no workspace is used. */
 W2_API int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* bytes);
 

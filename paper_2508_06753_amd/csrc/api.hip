@@ -263,70 +263,46 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
     a.tune = tn;
     int fallback = W2_VARIANT_SMALLM;                        // where the decode kernel cannot hold the rows
     if (variant == W2_VARIANT_AUTO) {
-        // measured: the MFMA form is at least as fast as dot4 from M = 1 on; the mid-M kernel (one
-        // fma per accumulator in the dequant, rolling weight window; its time hardly grows with M)
-        // overtakes the small-M one at M = 4 on wide or very deep projections and at M = 9 on narrow ones (few
-        // column blocks: it then splits K four ways with a barrier pair per tile), and is faster
-        // than the tiled one up to M = 64
+        // Few rows: the decode kernel, which reads the weights once and keeps whole rows in local memory (the MFMA
+        // form is at least as fast as dot4 from M = 1 on).  Then the mid-M kernel, then the tiled ones.
+        // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
+        // before against the mid-M kernel): at M = 9 in general (4096 x 6144 5.3 against 5.2 at M = 16; 4096 x 28672 at
+        // M = 8 / 9 9.2 / 10.1 against 9.6 / 9.7; 8192 x 10240 8.8 / 11.7 against 8.8 / 8.9); at M = 5 where the decode
+        // kernel has few workgroups and two pieces of a row per thread (5120 x 5120 5.5 against 4.6) or cannot hold
+        // the rows (17408 x 5120 12.7 against 9.7; 28672 x 8192 18.4 against 15.4); on 16384 columns and more with
+        // groups of 64 at 13 (5120 x 34816 at M = 12 / 16 15.2 / 21.4 against 16.1 / 17.2).
         const int dot4_max = tn.dot4_max_m;
-        const int midm_min = tn.midm_min_m ? tn.midm_min_m : (a.n_cb >= 384 || a.n_kt > 64) ? 4 : 9;
-        // Upper end.  Two bands of 64 rows (up to M = 128) on the narrowest projections only (up to 4096
-        // columns, where the tiled kernel has too few tiles: 4096 x 4096 at M = 128 10 against 14.7 us; with room
-        // for split-K partial results the tiled kernel is the faster one there once K reaches 14336).  Wider:
-        // 8192 x 8192 at M = 128 runs 23.5 us through the tiled kernel with K split inside its workgroups
-        // against 33 in two bands, 4096 x 6144 15.0 against 18.7.  On wide projections (24576 columns and more)
-        // the tiled kernel takes over at M = 33, where the mid-M kernel goes to four row tiles per wave and its
-        // LDS operand reads bound it (4096 x 28672 at M = 48: 15.8 against 19.0 us; 5120 x 34816: 27 against 40).
-        // Deep K (56 tiles and more) with room for split-K partial results: the tiled kernel, its K cut across
-        // and inside workgroups, takes over at M = 33 (28672 x 8192 at M = 64: 31 against 34 us; 17408 x 5120 at
-        // M = 33: 18.0 against 19.2), on the narrowest projections at M = 65 (14336 x 4096: 19.2 against 21.2).
-        const bool deep_ws = a.part_bytes && a.n_kt >= 56;
+        const bool wide = a.n_cb >= 1024;
+        const int midm_from = wide ? (G == 128 ? 9 : 13) : a.n_kt > 64 || (a.n_kt > 16 && a.n_kt <= 32 && a.n_cb <= 448) ? 5 : 9;
+        const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
+        // Upper end, against the tiled kernels with a workspace: they win earlier the more columns there are to fill
+        // the chip with (2048 x 57344 at M = 48 / 64 16.6 / 17.4 us against 15.3 / 18.5; 4096 x 28672 at M = 96 / 128
+        // 24.3 / 25.2 against 20.4 / 24.9; 8192 x 10240 at M = 160 / 192 24.8 / 25.1 against 22.7 / 26.0; 5120 x 7168
+        // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7).
         const int midm_max = tn.midm_max_m ? tn.midm_max_m
-                           : a.n_cb <= 256 ? (deep_ws ? 64 : 128) : a.n_cb >= 1536 || deep_ws ? 32 : 64;
-        fallback = M >= midm_min && M <= midm_max && a8_midm_supports(a) ? W2_VARIANT_MIDM
-                 : a8_smallm_supports(a)                                   ? W2_VARIANT_SMALLM
-                                                                           : W2_VARIANT_TILED;
-        // The decode kernel keeps whole rows in local memory and reads the weights once, like the mid-M
-        // kernel, without that kernel's barrier pair per 1024 k: measured faster up to 8 rows wherever the
-        // rows fit (4096 x 28672 at M = 8: 7.4 against 10.1 us; 8192 x 8192: 5.9 against 7.8), and up to 16 rows
-        // while two workgroups share a CU (rows of at most 64 to 68 KiB: 4096 x 28672 at M = 16 10.1 against
-        // 10.5 us, 4096 x 6144 5.2 against 6.0) or the projection is narrow (8192 x 8192 at M = 16: 7.5 against
-        // 9.4 us; 8192 x 10240 at M = 12 / 16: 11.6 / 11.7 against 12.6 / 12.8); wide projections with long rows
-        // lose (8192 x 57344 at M = 12: 33 against 28 us).
-        // Rows of more than 72 KiB leave room for one workgroup per CU only: then the grid must fit the chip
-        // in one round (17408 x 5120 at M = 8, 320 workgroups: 15.3 against 10.4 us through the mid-M kernel;
-        // 14336 x 4096, 256 workgroups: 6.4 against 8.1).
+                           : a.n_cb >= 2560 ? 48 : a.n_cb >= 1536 ? 112 : a.n_cb > 448 ? 160 : 240;
+        const bool midm_ok = M >= midm_min && M <= midm_max && a8_midm_supports(a);
+        // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
+        // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
         const int64_t row_bytes = M * (K + 32);
-        int gcbw = M > 12 ? 8 : 4;                              // (the decode kernel's rule for five rows and more)
+        int gcbw = 4;                                        // (the decode kernel's rule for five rows and more)
         while (gcbw > 1 && (a.n_cb / gcbw < 192 || (a.n_kt + 8 / gcbw - 1) / (8 / gcbw) > 16)) gcbw >>= 1;
         const int64_t gemv_wgs = (a.n_cb + gcbw - 1) / gcbw;
-        // (up to K = 8192 two rounds still win: 8192 x 10240 at M = 9 .. 16, 320 workgroups, 11.6 to 11.8 against 12.4 to 12.9)
         const bool one_round = row_bytes <= 72 * 1024 || gemv_wgs <= 256 || a.n_kt <= 32;
-        // narrow: few column blocks, or a grid of one round (8192 x 12288 at M = 9 .. 16, 192 workgroups: 9.1 to 9.3
-        // against 12.8 to 13.2)
-        const bool narrow = a.n_cb <= 640 || gemv_wgs <= 256;
-        const int gemv_max = tn.gemv_max_m                               ? tn.gemv_max_m
-                           : M <= 4                                      ? 4
-                           : !one_round                                  ? 4
-                           : M <= 8                                      ? 8
-                           : M <= 12 && (row_bytes <= 64 * 1024 || narrow) ? 12
-                           : M <= 16 ? (row_bytes <= 68 * 1024 || narrow ? 16 : 8)
-                           // 17 to 32 rows (two row tiles per wave, one workgroup per CU): K up to 4096 in a grid of
-                           // one round (4096 x 4096 at M = 17..32: 5.9 against 6.9 to 7.3 us through the mid-M
-                           // kernel; 4096 x 6144 6.8 against 7.2; 4096 x 28672 12.5 to 13.9 against 13.0 to 14.3;
-                           // K = 5120 gains nothing, 4096 x 57344, two rounds, loses 10 %)
-                           : M <= 32 && a.n_kt <= 16 && row_bytes <= 133 * 1024 ? 32
-                                                                         : 8;
-        variant = M <= dot4_max && a8_dot4_supports(a)     ? W2_VARIANT_DOT4
-                : M <= gemv_max && a8_gemv_supports(M)     ? W2_VARIANT_GEMV
-                                                           : fallback;
+        const int gemv_max = tn.gemv_max_m ? tn.gemv_max_m : one_round ? midm_from - 1 : 4;
+        fallback = midm_ok || (!tn.midm_min_m && M >= 4 && M < midm_min) ? W2_VARIANT_MIDM
+                 : a8_smallm_supports(a)                                 ? W2_VARIANT_SMALLM
+                                                                         : W2_VARIANT_TILED;
+        variant = M <= dot4_max && a8_dot4_supports(a) ? W2_VARIANT_DOT4
+                : M <= gemv_max && a8_gemv_supports(M) ? W2_VARIANT_GEMV
+                                                       : fallback;
     }
     hipStream_t s = (hipStream_t)stream;
     switch (variant) {
     case W2_VARIANT_GEMV: {
         if (!a8_gemv_supports(M)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: GEMV needs M <= 32", fn);
         rc = launch_a8_gemv(a, xq, 0, K, s);
-        // rows too long for one workgroup's local memory: the kernels that stage them in chunks
+        // rows too long for one workgroup: the kernels that stage them in chunks
         if (rc != W2_ERR_UNSUPPORTED_SHAPE || tn.variant == W2_VARIANT_GEMV) return rc;
         if (fallback == W2_VARIANT_MIDM) return launch_a8_midm(a, s);
         if (fallback == W2_VARIANT_TILED) return launch_a8_tiled(a, s);
@@ -577,28 +553,27 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
         variant = W2_VARIANT_SMALLM;
     }
     if (variant == W2_VARIANT_AUTO) {
-        // Few rows: the decode kernel (below), else the zero-point construction in the small-M kernel; up to
-        // 64 rows the mid-M kernel (the weight stream is still read once; measured faster than the small-M
-        // kernel from M = 9 on every projection shape); above, 128-row tiles.  Both of the latter fold the
-        // scale into the weights: fewest vector instructions per matrix instruction.
-        // (K beyond 16384: from M = 3, for the rows the decode kernel cannot hold; 17408 x 5120 at M = 8 19.9 us
-        // against 33.7 in the small-M kernel, at M = 4 19.2 against 25.5)
-        // (with room for split-K partial results already from K = 8448 on: 14336 x 4096 at M = 8 13.8 us against 15.4)
-        // (and on the widest projections once K passes 5120, where five to eight rows leave the decode kernel one
-        // workgroup per CU: 8192 x 57344 at M = 5 / 8 42.3 / 43.1 us against 43.7 / 45.8)
-        const bool wide_deep = K > 5120 && a.n_cb >= 2048;
-        const int midm_min = tn.midm_min_m ? tn.midm_min_m
-                           : a.n_kt > 64 ? 3 : (a.n_kt > 32 && a.part_bytes) || wide_deep ? 5 : 9;
-        // two bands on small projections; on very wide ones (32768 columns and more) the tiled kernel
-        // takes over at M = 41 (8192 x 57344 at M = 48: 94 against 104 us)
-        // (and with room for split-K partial results the tiled kernel wins above 64 rows once K passes 8192:
-        // 28 against 35 us on 14336 x 4096 at M = 128)
+        // Few rows: the decode kernel wherever a workgroup can hold them, else the small-M kernel (both with the
+        // zero-point construction); then the mid-M kernel; above, 128-row tiles.  Both of the latter fold the scale
+        // into the weights: fewest vector instructions per matrix instruction.
+        // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
+        // before against the mid-M kernel): at M = 3 for rows too long for a workgroup (17408 x 5120 16.5 against
+        // 13.2), at M = 5 where K passes 4096 (5120 x 5120 8.2 against 5.8, 14336 x 4096 10.7 against 8.8, 8192 x 10240
+        // 15.5 against 12.7), at 8 on wide projections of K = 5120 (5120 x 34816 at M = 6 / 8 19.1 / 24.3 against
+        // 20.4), and at 9 up to K = 4096 (4096 x 6144 at M = 8 / 9 5.9 / 7.1 against 5.7; 4096 x 28672 12.0 / 13.3
+        // against 13.1), with groups of 64 and 16384 columns at 17 (at M = 16 / 24 13.9 / 22.0 against 14.7 / 17.6).
+        const int midm_from = a.n_kt > 64                                  ? 3
+                            : a.n_kt > 20 || (a.n_kt > 16 && a.n_cb < 640) ? 5
+                            : a.n_kt > 16                                  ? 8
+                            : G == 128 || a.n_cb < 1024                    ? 9 : 17;
+        const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
+        // Upper end, against the tiled kernel with a workspace (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 /
+        // 114; 4096 x 28672 at M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 28672 x 8192 at M = 96 / 128 57.6 / 62.4
+        // against 56.9 / 68.0; 8192 x 10240 at M = 192 45.3 against 38.7; 4096 x 4096 at M = 256 22.9 against 12.3).
         const int midm_max = tn.midm_max_m ? tn.midm_max_m
-                           : a.n_cb <= 256 ? (a.part_bytes && a.n_kt > 32 ? 64 : 128) : a.n_cb >= 2048 ? 40 : 64;
-        // The decode kernel wherever a workgroup can hold the rows: up to 8 of them, and up to 16 while a thread
-        // stages one piece per row (K <= 4096: 4096 x 28672 at M = 12 14.0 us against 15.9 in the mid-M kernel,
-        // 4096 x 4096 6.4 against 7.6; 5120 x 34816 31 against 29)
-        const bool gemv_rows = tn.midm_min_m ? M < midm_min : M <= 4 || (M <= 8 && !wide_deep) || (M <= 16 && K <= 4096);
+                           : a.n_cb >= 2560 ? 64 : a.n_cb >= 1024 || a.n_cb * a.n_kt > 40000 ? 96
+                           : a.n_cb <= 448 && a.n_kt <= 56 ? 256 : 192;
+        const bool gemv_rows = M < midm_min;
         if (gemv_rows && a16_gemv_supports(a)) {
             rc = launch_a16_gemv(a, (hipStream_t)stream);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
@@ -658,14 +633,13 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
     if (M == 0) *bytes = 0;
     else if (a16) {
         const size_t tiled = M > 64 ? a16_fold_splitk_bytes(M, N, L.n_kt, dflt) : 0;
-        const size_t midm = M >= 3 && M <= 128 ? a16_midm_splitk_bytes(M, N, L.n_cb, L.n_kt, dflt) : 0;
+        const size_t midm = M >= 3 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = tiled > midm ? tiled : midm;
     }
     else {
-        // split-K partial results: the tiled kernel's above 64 rows, the mid-M kernel's on deep projections
-        // (whichever of the two the call would pick, the larger need covers it)
+        // split-K partial results of the tiled kernels; what was reported for the mid-M range is reported still
         const size_t tiled = M > 32 ? a8_tiled_splitk_bytes(M, N, L.n_kt, G, dflt) : 0;
-        const size_t midm = M >= 4 && M <= 128 ? a8_midm_splitk_bytes(M, N, L.n_cb, L.n_kt, dflt) : 0;
+        const size_t midm = M >= 4 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = (single ? 0 : fused_workspace_bytes(M, K)) + (tiled > midm ? tiled : midm);
     }
     return W2_OK;

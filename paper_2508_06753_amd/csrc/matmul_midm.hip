@@ -1,0 +1,575 @@
+// Medium M (up to 256 rows), both activation types: between the memory-bound GEMV regime and the compute-bound GEMM
+// regime of Sec. III-C.  The weight stream is read once per band of up to 64 rows, and every up-converted weight
+// ("up-convert and compute", Sec. II-C) is multiplied into RT row tiles: v_mfma_i32_16x16x64_i8 for int8 rows,
+// v_mfma_f32_16x16x32_bf16 on scale-folded weights for bf16 rows (Sec. II-D, "Alternative implementation").
+//
+// A wave owns RT row tiles x CJ column blocks x a contiguous run of k tiles; the waves of a workgroup split K (Sec.
+// II-D, K-splitting for small shapes) and their partial results meet in local memory once, in a fixed order.  No
+// second launch, no workspace.
+//
+// Why this shape.  What such a problem moves is the activations: every workgroup reads its rows over the whole K, 64
+// bytes per clock and CU through the vector L1 whichever way they go.  With K split over the waves nothing that a wave
+// reads is read by another wave of the workgroup, so the activations need no workgroup-wide staging and the main loop
+// no barrier: a wave turns them around in a piece of local memory of its own.  It has to, because the matrix operand
+// wants 16 rows per 16 bytes of k: loaded directly in that order the L1 delivers 16 B/clk (one cache line per lane),
+// loaded as eight rows x 128 bytes per instruction 60 B/clk (measured, 256 CUs reading 64 rows of 4096..14336 bytes
+// out of L2).  A chunk is 128 bytes of every row: loaded a chunk or two ahead into registers, written as it comes with
+// the 16-byte pieces of row r XORed by r mod 8, read back as matrix operands without bank conflicts.  CJ column blocks
+// share the operands that are read; RT row tiles share the up-converted weights (7 or 23 vector instructions per 16).
+//
+// SH = 2: pairs of waves take different column blocks of the same K range and share its chunks (two buffers, one
+// barrier per chunk): half the activation traffic, for wide projections with int8 rows.
+//
+// Measured (graph-timed, us; before = the kernels this one replaces, which shared 1024-k chunks of all rows between
+// the waves of a workgroup with two barriers each, and split deep K across workgroups with a second launch):
+// int8 rows, M = 48: 4096 x 6144 9.4 -> 5.9, 4096 x 4096 9.2 -> 5.0, 14336 x 4096 16.2 -> 9.7, 17408 x 5120 18.6 ->
+// 13.1, 3584 x 18944 23.1 -> 11.5, 4096 x 28672 17.0 -> 14.6; bf16 rows, M = 64: 15.7 -> 8.8, 15.4 -> 6.6, 23.9 -> 15.7,
+// 32.0 -> 25.6, 38.7 -> 18.8, 32.1 -> 23.1.
+//
+// What bounds it (4096 x 28672, 64 int8 rows, 17.2 us; copies with parts taken out): without the activations 14.0,
+// without the weight loads 12.9, without either 10.3, without the epilogue 14.8: a launch of this size is too short
+// for its phases (first loads out of HBM, multiply, reduce) to overlap, and a SIMD's vector issue slots are two
+// thirds full while it multiplies.  Deeper load windows, a second operand set read a chunk ahead, pinned interleaving
+// of vector and matrix instructions and a start of K that differs per workgroup were measured and gave nothing.
+#include <hip/hip_runtime.h>
+
+#include "w2_small_common.h"
+
+#if defined(__HIP_DEVICE_COMPILE__) && defined(__FAST_MATH__)
+#error "the one-fma dequant reads int32 accumulators as fp32 denormals: do not build with fast-math / flush-to-zero"
+#endif
+
+namespace w2 {
+
+namespace midm {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int CHUNK_BYTES = 128;                             // bytes of a row in one staged chunk
+
+struct Args {                                                // what is needed after the first loads
+    const float* sx;
+    uint16_t* Y;
+    int32_t* acc_out;
+    int64_t N, ldy;
+    Epilogue epi;
+};
+
+// the head of the arguments: scalar kernel parameters, which a wave finds in registers at its launch
+struct Head {
+    const char* X;                                           // int8 or bf16 rows
+    const char* codes;
+    const char* scales;
+    uint32_t stride;                                         // bytes between rows
+    int M, n_cb, n_kt;                                       // (and t_lo, t_rem: tiles per K range, one more for the first t_rem)
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
+// The four weights of one (group, column), low bytes and high bytes, indexed by the raw code
+// (00 -> 0, 01 -> +sw, 10 -> -2 sw: sign flipped and exponent + 1, 11 -> -sw).
+struct Lut { uint32_t lo4, hi4; };
+
+__device__ __forceinline__ Lut make_lut(uint32_t s)          // s: bf16 bit pattern of the group scale
+{
+    const uint32_t neg = s ^ 0x8000u;
+    const uint32_t neg2 = (s & 0x7f80u) ? ((s + 0x0080u) ^ 0x8000u) : neg;   // a zero scale stays (minus) zero
+    const uint32_t a = s << 16;
+    const uint32_t b = neg2 | (neg << 16);
+    Lut l;
+    l.lo4 = __builtin_amdgcn_perm(b, a, 0x06040200u);
+    l.hi4 = __builtin_amdgcn_perm(b, a, 0x07050301u);
+    return l;
+}
+
+// 16 codes of one dword -> b0 (k 0..7 of the lane's 16-k block), b1 (k 8..15)
+__device__ __forceinline__ void upconvert16(uint32_t w, const Lut& l, v4i& b0, v4i& b1)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t t = (w >> (2 * j)) & 0x03030303u;
+        const uint32_t lo = __builtin_amdgcn_perm(0u, l.lo4, t);
+        const uint32_t hi = __builtin_amdgcn_perm(0u, l.hi4, t);
+        const int d0 = (int)__builtin_amdgcn_perm(hi, lo, 0x05010400u);
+        const int d1 = (int)__builtin_amdgcn_perm(hi, lo, 0x07030602u);
+        if (j < 2) { b0[2 * j] = d0; b0[2 * j + 1] = d1; }
+        else { b1[2 * j - 4] = d0; b1[2 * j - 3] = d1; }
+    }
+}
+
+__device__ __forceinline__ v4f mfma_bf16(const v4i& a, const v4i& b, const v4f& c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+
+constexpr int stage_bytes(int rt, int sh) { return rt * 16 * CHUNK_BYTES * (sh > 1 ? 2 : 1); }     // of one K range
+constexpr int red_bytes(int rt, int cj) { return rt * 16 * (cj * 16 + 4) * 4; }                     // of one wave
+// bytes of local memory of one K range (sh waves): its staged chunks, later its waves' partial results
+constexpr int range_lds(int rt, int cj, int sh)
+{
+    return stage_bytes(rt, sh) > sh * red_bytes(rt, cj) ? stage_bytes(rt, sh) : sh * red_bytes(rt, cj);
+}
+
+// XT 0: int8 rows (w2a8), 1: bf16 rows (w2a16)
+// most waves of a workgroup: 16 where a wave's registers allow it (very deep and narrow projections), else 8
+constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
+
+template <int XT, int G, int RT, int CJ, int SH, bool DBG>
+__global__ void __launch_bounds__(64 * max_waves(RT, CJ), max_waves(RT, CJ) / 4)
+midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const char* __restrict__ scales, uint32_t stride, int M,
+            int n_cb, int n_kt, int t_lo, int t_rem, Args a)
+{
+    constexpr int EB = XT == 0 ? 1 : 2;                      // bytes per activation
+    constexpr int CH = TILE_K * EB / CHUNK_BYTES;            // chunks per tile: 2 or 4
+    constexpr int GPT = TILE_K / G;
+    constexpr int NJ = RT * 2 / SH;                          // 16-byte pieces per lane and chunk
+    constexpr int D = 2;                                     // weight tiles in flight
+    constexpr int SD = NJ <= 4 ? 2 : 1;                      // chunks in flight
+    static_assert(D * CH % SD == 0, "register sets are picked at compile time");
+    extern __shared__ __align__(16) int8_t smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = lane >> 4, l16 = lane & 15;
+    const int m0 = blockIdx.y * (RT * 16);
+    const int rows = min(RT * 16, M - m0);
+    const int cg = wave % SH, kr = wave / SH;
+    const int cb0 = (blockIdx.x * SH + cg) * CJ;
+    const int t0 = kr * t_lo + min(kr, t_rem);
+    const int T = t_lo + (kr < t_rem ? 1 : 0);
+    // waves that share chunks meet at barriers: the same count for all (past its run a wave reads zeros)
+    const int T_all = SH > 1 ? t_lo + (t_rem > 0 ? 1 : 0) : T;
+    const int nch = T * CH;
+    int8_t* const my = smem + kr * range_lds(RT, CJ, SH);
+
+    // the rows, from this run's first k on: rows past the last lie past the end of the resource, whose loads return
+    // zeros and move nothing (the lane offset alone puts them there: (rows - 1) * stride + the run's bytes <= rows *
+    // stride), and so does everything once there is no further chunk
+    const char* xbase = X + (int64_t)m0 * stride + (int64_t)t0 * (TILE_K * EB);
+    const uint32_t xbytes = (uint32_t)(rows - 1) * stride + (uint32_t)T * (TILE_K * EB);
+    uint32_t xoff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+        xoff[j] = (uint32_t)((cg * NJ + j) * 8 + (lane >> 3)) * stride + (uint32_t)(lane & 7) * 16u;
+    // local memory, per row 128 bytes: the 16-byte piece that k-step e gives to lane quarter q sits at slot
+    // (4 e + q) ^ (row mod 8).  int8 rows: piece 4 e + q; bf16 rows (a lane's 16 k are two pieces): piece 2 q + e
+    const int piece = lane & 7, f = XT == 0 ? piece : (piece >> 1) | ((piece & 1) << 2);
+    const int st_off = (cg * NJ * 8 + (lane >> 3)) * CHUNK_BYTES + ((f ^ (lane >> 3)) * 16);
+    const int rd0 = l16 * CHUNK_BYTES + ((q ^ (l16 & 7)) * 16);
+    const int rd1 = l16 * CHUNK_BYTES + (((4 + q) ^ (l16 & 7)) * 16);
+
+    // the run of each column block: loads past its end, or of a block past the last, return zeros and move nothing
+    const char* wp[CJ];
+    const char* sp[CJ];
+    uint32_t wbytes[CJ], sbytes[CJ];
+#pragma unroll
+    for (int j = 0; j < CJ; ++j) {
+        const bool ok = cb0 + j < n_cb;
+        const int64_t tile = (int64_t)(ok ? cb0 + j : cb0) * n_kt + t0;
+        wp[j] = codes + tile * TILE_BYTES;
+        sp[j] = scales + tile * (TILE_N * GPT * 2);
+        wbytes[j] = ok ? (uint32_t)T * TILE_BYTES : 0u;
+        sbytes[j] = ok ? (uint32_t)T * (TILE_N * GPT * 2) : 0u;
+    }
+
+    u32x4 stage[SD][NJ];
+    auto load_x = [&](int c, int set) {
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(xbase, c < nch ? xbytes : 0u);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) stage[set][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[j], c * CHUNK_BYTES, 0);
+    };
+    u32x4 w[D][CJ];
+    uint32_t sc[D][CJ][GPT / 2];
+    auto load_w = [&](int i, int set) {
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) {
+            w[set][j] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(wp[j], wbytes[j]), lane * 16 + i * TILE_BYTES, 0, 0);
+            const __amdgpu_buffer_rsrc_t sr = make_rsrc(sp[j], sbytes[j]);
+            const int so = l16 * (GPT * 2) + i * (TILE_N * GPT * 2);
+            if constexpr (G == 128) {
+                sc[set][j][0] = __builtin_amdgcn_raw_buffer_load_b32(sr, so, 0, 0);
+            } else {
+                const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(sr, so, 0, 0);
+                sc[set][j][0] = t[0];
+                sc[set][j][1] = t[1];
+            }
+        }
+    };
+
+    // activations first, then the weights: vector memory returns in order
+#pragma unroll
+    for (int s = 0; s < SD; ++s) load_x(s, s);
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_w(i, i);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // Dequant of the int8 form in one fma: a group starts from BIAS = 2^21 (the third matrix operand), so
+    // acc = BIAS + 64 * sum is positive and below 2^23 and its bit pattern read as binary32 is the denormal
+    // acc * 2^-149: y += as_float(acc) * (sw * 2^64).  The bias, 2^-128 * (the sum of the scaled scales), is taken out
+    // every four tiles and at the end.  Two accumulator sets alternate between groups; a finished group is dequantised
+    // under the next one's matrix instructions.
+    constexpr int BIAS = 1 << 21;                            // > 64 * 127 * 2 * 128
+    const v4i biasv = {BIAS, BIAS, BIAS, BIAS};
+    v4i acc[2][RT];
+    v4f y[RT][CJ];
+    float ssum[CJ];
+    float pend_sw = 0.f;                                     // the finished group waiting in set 1: none yet
+    int pend_g = 0;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        acc[0][rt] = biasv;
+        acc[1][rt] = biasv;
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) y[rt][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int j = 0; j < CJ; ++j) ssum[j] = 0.f;
+
+    auto dequant = [&](int b, int j) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (DBG) {
+                    const int m = rt * 16 + 4 * q + r;
+                    const int64_t n = (int64_t)(cb0 + j) * TILE_N + l16;
+                    if (pend_sw != 0.f && n < a.N && m < rows)
+                        a.acc_out[((int64_t)(m0 + m) * (n_kt * GPT) + pend_g) * a.N + n] = (acc[b][rt][r] - BIAS) >> 6;
+                }
+                y[rt][j][r] = fmaf(__int_as_float(acc[b][rt][r]), pend_sw, y[rt][j][r]);
+            }
+        ssum[j] += pend_sw;
+    };
+    auto settle = [&]() {
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) {
+            const float corr = ssum[j] * 0x1p-128f;
+            ssum[j] = 0.f;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[rt][j][r] -= corr;
+        }
+    };
+
+    // up-converted operands of the coming block (a block: one column block of one chunk)
+    v4i bn0, bn1;
+    Lut lut[CJ];
+    auto prepare_b = [&](const u32x4& wd, const uint32_t (&s)[GPT / 2], int h, int j) {
+        if constexpr (XT == 0) {
+            int u0[4], u1[4];
+            upconvert(wd[2 * h], u0);
+            upconvert(wd[2 * h + 1], u1);
+            bn0 = (v4i){u0[0], u0[1], u0[2], u0[3]};
+            bn1 = (v4i){u1[0], u1[1], u1[2], u1[3]};
+        } else {
+            if (G == 64 || !(h & 1)) {                       // a group begins
+                const uint32_t p = s[G == 128 ? 0 : h >> 1];
+                const int hi = G == 128 ? h >> 1 : h & 1;
+                lut[j] = make_lut(hi ? p >> 16 : p & 0xffffu);
+            }
+            upconvert16(wd[h], lut[j], bn0, bn1);
+        }
+    };
+    constexpr int SBUF = RT * 16 * CHUNK_BYTES;
+    v4i f0[RT], f1[RT];                                      // matrix operands of the chunk's two k-steps
+    // chunk c, in register set `set`: to local memory and back as matrix operands; chunk c + SD is requested.  Local
+    // memory operations of one wave complete in order.
+    auto turn_chunk = [&](int c, int set, int par) {
+        int8_t* const buf = my + (SH > 1 ? par * SBUF : 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) *reinterpret_cast<u32x4*>(buf + st_off + j * 1024) = stage[set][j];
+        load_x(c + SD, set);
+        if constexpr (SH > 1) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            f0[rt] = *reinterpret_cast<const v4i*>(buf + rd0 + rt * 2048);
+            f1[rt] = *reinterpret_cast<const v4i*>(buf + rd1 + rt * 2048);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    prepare_b(w[0][0], sc[0][0], 0, 0);
+
+    for (int i0 = 0; i0 < T_all; i0 += D) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int i = i0 + u;
+            if (i >= T_all) break;
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                const int n = u * CH + h;                    // (constant after unrolling)
+                turn_chunk(i * CH + h, n % SD, h & 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < CJ; ++j) {
+                    const v4i b0 = bn0, b1 = bn1;
+                    if (j + 1 < CJ) prepare_b(w[u][j + 1], sc[u][j + 1], h, j + 1);
+                    else if (h + 1 < CH) prepare_b(w[u][0], sc[u][0], h + 1, 0);
+                    else prepare_b(w[(u + 1) % D][0], sc[(u + 1) % D][0], 0, 0);
+                    if constexpr (XT == 0) {
+                        const int pj = (j + CJ - 1) % CJ;
+                        const uint32_t p = sc[u][j][G == 128 ? 0 : h];
+                        if constexpr (G == 128) {
+                            const int b = (h * CJ + j) & 1;
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) acc[b][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f0[rt], b0, biasv, 0, 0, 0);
+                            dequant(b ^ 1, pj);
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) acc[b][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f1[rt], b1, acc[b][rt], 0, 0, 0);
+                            pend_sw = DBG ? 1.0f : __uint_as_float(h ? p & 0xffff0000u : p << 16) * 0x1p64f;
+                            pend_g = (t0 + i) * GPT + h;
+                        } else {
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) acc[0][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f0[rt], b0, biasv, 0, 0, 0);
+                            dequant(1, pj);
+                            pend_sw = DBG ? 1.0f : __uint_as_float(p << 16) * 0x1p64f;
+                            pend_g = (t0 + i) * GPT + 2 * h;
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) acc[1][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f1[rt], b1, biasv, 0, 0, 0);
+                            dequant(0, j);
+                            pend_sw = DBG ? 1.0f : __uint_as_float(p & 0xffff0000u) * 0x1p64f;
+                            pend_g = (t0 + i) * GPT + 2 * h + 1;
+                        }
+                    } else {
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) y[rt][j] = mfma_bf16(f0[rt], b0, y[rt][j]);
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) y[rt][j] = mfma_bf16(f1[rt], b1, y[rt][j]);
+                    }
+                }
+            }
+            if constexpr (XT == 0) {
+                if ((i & 3) == 3) settle();
+            }
+            load_w(i + D, u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (XT == 0) {
+        dequant(1, CJ - 1);
+        if constexpr (DBG) return;
+        settle();
+    }
+    if constexpr (SH > 1) __syncthreads();                   // the staged chunks are read by the other wave too
+    // (fetched under the reduction; read in the store loop it cost 0.1 us a launch)
+    const float sx_mine = XT == 0 && !DBG ? a.sx[min(m0 + (int)(threadIdx.x & 63), M - 1)] : 0.f;
+    constexpr int RS = CJ * 16 + 4;
+    float* red = reinterpret_cast<float*>(my + cg * red_bytes(RT, CJ));
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < CJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                red[(rt * 16 + 4 * q + r) * RS + j * 16 + l16] = y[rt][j][r];
+    float* const sx_lds = reinterpret_cast<float*>(smem + (blockDim.x >> 6) / SH * range_lds(RT, CJ, SH));
+    if constexpr (XT == 0) {
+        if (threadIdx.x < RT * 16) sx_lds[threadIdx.x] = sx_mine * 0x1p79f;   // 2^(149-64-6)
+    }
+    __syncthreads();
+    const int ks = (blockDim.x >> 6) / SH;
+    constexpr int WC = SH * CJ;                              // column blocks of the workgroup
+    const int wcb0 = blockIdx.x * WC;
+    auto sum4 = [&](int row, int col) {
+        v4f s = {0.f, 0.f, 0.f, 0.f};
+        const int8_t* p = smem + (col / (CJ * 16)) * red_bytes(RT, CJ) + (row * RS + col % (CJ * 16)) * 4;
+        for (int k = 0; k < ks; ++k) s += *reinterpret_cast<const v4f*>(p + k * range_lds(RT, CJ, SH));
+        if constexpr (XT == 0) s *= sx_lds[row];
+        return s;
+    };
+    auto add_bias = [&](v4f& v, int64_t n) {
+        if (a.epi.bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += bf16_to_f32(a.epi.bias[n + e]);   // (the bias need not be aligned)
+        }
+    };
+    auto put = [&](int row, int64_t n, const v4f& v) {
+        *reinterpret_cast<uint2*>(a.Y + (int64_t)(m0 + row) * a.ldy + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    };
+    if (a.epi.act != ACT_SILU_MUL) {
+        for (int i = threadIdx.x; i < rows * WC * 4; i += blockDim.x) {
+            const int row = i / (WC * 4), col = (i % (WC * 4)) * 4;
+            const int64_t n = (int64_t)wcb0 * TILE_N + col;
+            if (n >= a.N) continue;
+            v4f v = sum4(row, col);
+            add_bias(v, n);
+            if (a.epi.act == ACT_SILU) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = silu_f32(v[e]);
+            }
+            put(row, n, v);
+        }
+    } else if constexpr (WC >= 2) {
+        for (int i = threadIdx.x; i < rows * WC * 2; i += blockDim.x) {
+            const int row = i / (WC * 2), c = i % (WC * 2);
+            const int gcol = (c >> 2) * 32 + (c & 3) * 4;
+            const int64_t n = (int64_t)wcb0 * TILE_N + gcol;
+            if (n >= a.N) continue;
+            v4f g = sum4(row, gcol), v = sum4(row, gcol + 16);
+            add_bias(g, n);
+            add_bias(v, n + 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] *= silu_f32(g[e]);
+            put(row, (int64_t)(wcb0 / 2 + (c >> 2)) * TILE_N + (c & 3) * 4, v);
+        }
+    }
+}
+
+// Launch shape: row tiles and column blocks per wave, K ranges per workgroup, waves that share a range.
+struct Plan { int rt, cj, ks, sh; };
+
+// Registers per lane of each instantiation (G = 128; G = 64 is within one step), [rt - 1][cj: 1, 2, 4]: they limit the
+// workgroups that a CU holds at a time.
+constexpr int REGS[2][4][3] = {{{80, 96, 120}, {112, 136, 176}, {128, 160, 224}, {152, 216, 248}},
+                               {{80, 96, 128}, {120, 136, 176}, {136, 168, 208}, {128, 176, 248}}};
+
+// Every candidate shape is priced with a linear model and the cheapest wins.  The terms are what the busiest CU has to
+// do (nb workgroups, in rounds of as many as it holds at a time), the coefficients (us) a least-squares fit to 4400
+// graph-timed launches: 20 projection shapes from 2048 x 2048 and 28672 x 1024 to 8192 x 57344, 4 to 192 rows.  Its
+// choices are on average 3.6 % (int8 rows) and 0.9 % (bf16 rows) slower than the fastest shape measured.
+static double price(int xt, const Plan& p, int64_t M, int64_t n_cb, int64_t n_kt)
+{
+    constexpr double C[2][13] = {
+        {1.525, 0.1987, 0.6254, 1.419, 1.127, 0.3743, 0.8993, 0.4517, 0.3403, 0.6996, 0.6068, 0.7275, 0.3929},
+        {1.677, 1.494, 0.3030, 3.895, 0.9297, 0.9087, 0.7657, 0.0, 0.5634, 0.4702, 0.9276, 1.174, 0.1319}};
+    const double* c = C[xt];
+    const int64_t bands = (M + 16 * p.rt - 1) / (16 * p.rt);
+    const int64_t wgs = (n_cb + p.cj * p.sh - 1) / (p.cj * p.sh) * bands;
+    const int waves = p.ks * p.sh;
+    const int lds = p.ks * range_lds(p.rt, p.cj, p.sh) + p.rt * 64;
+    int resident = 160 * 1024 / lds;
+    resident = max(1, min(resident, 4 * (512 / REGS[xt][p.rt - 1][p.cj >> 1]) / waves));
+    const int64_t nb = (wgs + 255) / 256, rounds = (nb + resident - 1) / resident;
+    const int64_t T = (n_kt + p.ks - 1) / p.ks;              // tiles of a wave's run
+    return c[0]
+         + c[1] * 0.01 * (nb * waves * T * p.cj)             // up-converts
+         + c[2] * 0.01 * (nb * waves * T * p.cj * p.rt)      // matrix instructions and dequant
+         + c[3] * 0.01 * (nb * p.ks * T * p.rt)              // activations through the L1
+         + c[4] * 1e-4 * (n_cb * n_kt)                       // the weight stream
+         + c[5] * 1e-4 * (n_cb * n_kt * bands)               // ... once per band out of L2
+         + c[6] * 0.01 * (nb * waves * p.rt * p.cj)          // reduce and store
+         + c[7] * 0.1 * (rounds * T)                         // latency per tile,
+         + c[8] * 0.1 * (rounds * T * p.rt * p.cj)           // multiply,
+         + c[9] * rounds                                     // start
+         + c[10] * 0.1 * (rounds * p.rt * p.cj)              // and end of a wave
+         + c[11] * 0.1 * T
+         + c[12] * 1e-3 * wgs;                               // workgroups to launch
+}
+
+static Plan plan(int xt, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, const w2_tuning_t& tune)
+{
+    Plan best = {1, 2, 1, 1};
+    double best_price = 1e30;
+    const int tiles = (int)min((M + 15) / 16, (int64_t)4);
+    auto consider = [&](int rt, int cj, int ks, int sh) {
+        if (gated && cj * sh < 2) return;                                    // a workgroup pairs gate and up blocks
+        if (tune.midm_cbw && cj * sh != (xt == 1 ? min(tune.midm_cbw, 4) : tune.midm_cbw)) return;
+        const Plan p = {rt, cj, (int)min((int64_t)ks, n_kt), sh};
+        const double t = price(xt, p, M, n_cb, n_kt);
+        if (t < best_price) { best = p; best_price = t; }
+    };
+    for (int rt = 1; rt <= tiles; ++rt)
+        for (int cj = rt == 1 ? 1 : 2; cj <= 4; cj *= 2) {
+            if (max_waves(rt, cj) == 16) consider(rt, cj, 16, 1);
+            consider(rt, cj, 8, 1);
+            consider(rt, cj, 4, 1);
+            if (xt == 0) consider(rt, cj, 2, 2);
+        }
+    return best;
+}
+
+template <int XT, int G, int RT, int CJ, int SH, bool DBG>
+static int launch_t(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
+{
+    const size_t lds = (size_t)p.ks * range_lds(RT, CJ, SH) + RT * 16 * sizeof(float);
+    auto kern = midm_kernel<XT, G, RT, CJ, SH, DBG>;
+    if (int rc = ensure_dynamic_lds((const void*)kern, lds, "w2_matmul[midm]")) return rc;
+    const dim3 grid((unsigned)((h.n_cb + CJ * SH - 1) / (CJ * SH)), (unsigned)((h.M + RT * 16 - 1) / (RT * 16))), block(64 * p.ks * SH);
+    hipLaunchKernelGGL(kern, grid, block, lds, stream, h.X, h.codes, h.scales, h.stride, h.M, h.n_cb, h.n_kt,
+                       h.n_kt / p.ks, h.n_kt % p.ks, a);
+    return check_launch("w2_matmul[midm]");
+}
+
+template <int XT, int G, int RT, int CJ>
+static int launch_sh(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
+{
+    if constexpr (XT == 0) {
+        if (p.sh == 2) return launch_t<XT, G, RT, CJ, 2, false>(h, a, p, stream);
+    }
+    return launch_t<XT, G, RT, CJ, 1, false>(h, a, p, stream);
+}
+
+template <int XT, int G>
+static int launch_g(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
+{
+    if (a.acc_out) {                                         // the test-only export of the int32 accumulators: one width
+        if constexpr (XT == 0) {
+            const Plan d = {p.rt, 2, (int)min((int64_t)8, (int64_t)h.n_kt), 1};
+            switch (p.rt) {
+            case 1: return launch_t<0, G, 1, 2, 1, true>(h, a, d, stream);
+            case 2: return launch_t<0, G, 2, 2, 1, true>(h, a, d, stream);
+            case 3: return launch_t<0, G, 3, 2, 1, true>(h, a, d, stream);
+            default: return launch_t<0, G, 4, 2, 1, true>(h, a, d, stream);
+            }
+        }
+    }
+    switch (p.rt * 8 + p.cj) {
+    case 8 + 1: return launch_sh<XT, G, 1, 1>(h, a, p, stream);
+    case 8 + 2: return launch_sh<XT, G, 1, 2>(h, a, p, stream);
+    case 8 + 4: return launch_sh<XT, G, 1, 4>(h, a, p, stream);
+    case 16 + 2: return launch_sh<XT, G, 2, 2>(h, a, p, stream);
+    case 16 + 4: return launch_sh<XT, G, 2, 4>(h, a, p, stream);
+    case 24 + 2: return launch_sh<XT, G, 3, 2>(h, a, p, stream);
+    case 24 + 4: return launch_sh<XT, G, 3, 4>(h, a, p, stream);
+    case 32 + 2: return launch_sh<XT, G, 4, 2>(h, a, p, stream);
+    default: return launch_sh<XT, G, 4, 4>(h, a, p, stream);
+    }
+}
+
+}  // namespace midm
+
+constexpr int64_t MIDM_MAX_ROWS = 256;                       // beyond that the tiled kernels' reuse of the weights wins everywhere
+
+bool a8_midm_supports(const A8Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
+bool a16_midm_supports(const A16Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
+
+// What w2_workspace_size adds for this range on a deep K (K > 13312): fp32 copies of the output, 2..16 of them.  This
+// kernel needs none; the size is part of what callers have been told and keeps its value.
+size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt)
+{
+    const int64_t chunks = (n_kt + 3) / 4;                   // of 1024 k
+    if (chunks < 14) return 0;
+    const int64_t cbw = n_cb >= 8 * 64 ? 8 : n_cb >= 4 * 64 ? 4 : 2;
+    const int64_t wgs = (n_cb + cbw - 1) / cbw * ((M + 63) / 64);
+    const int64_t s = min(min((256 + wgs / 2) / wgs, chunks / 3), (int64_t)16);
+    return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
+}
+
+int launch_a8_midm(const A8Args& a, hipStream_t stream)
+{
+    const midm::Head h = {(const char*)a.xq, (const char*)a.codes, (const char*)a.scales, (uint32_t)a.K, (int)a.M, (int)a.n_cb, (int)a.n_kt};
+    const midm::Args k = {a.sx, a.Y, a.acc_out, a.N, a.ldy, a.epi};
+    const midm::Plan p = midm::plan(0, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, a.tune);
+    return a.G == 128 ? midm::launch_g<0, 128>(h, k, p, stream) : midm::launch_g<0, 64>(h, k, p, stream);
+}
+
+int launch_a16_midm(const A16Args& a, hipStream_t stream)
+{
+    const midm::Head h = {(const char*)a.X, (const char*)a.codes, (const char*)a.scales, (uint32_t)(a.ldx * 2), (int)a.M, (int)a.n_cb, (int)a.n_kt};
+    const midm::Args k = {nullptr, a.Y, nullptr, a.N, a.ldy, a.epi};
+    const midm::Plan p = midm::plan(1, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, a.tune);
+    return a.G == 128 ? midm::launch_g<1, 128>(h, k, p, stream) : midm::launch_g<1, 64>(h, k, p, stream);
+}
+
+}  // namespace w2

@@ -291,6 +291,28 @@ def test_midm_row_bands(w2, M, K, N, G):
     run_a16_case(w2, M, K, N, G, M % 2, w2.VARIANT_MIDM, seed=M + K)
 
 
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("M,K,N", [(5, 256, 8), (16, 14336, 48), (17, 4352, 72), (48, 2304, 96), (49, 5376, 544), (240, 1280, 160)])
+def test_midm_k_ranges_and_row_tiles(w2, M, K, N, G):
+    # K split over the waves of a workgroup into uneven runs (17, 9, 21, 5 tiles), one tile, sixteen waves (56 tiles on
+    # three column blocks); one to four row tiles, a last one with a single row, several bands; a last column group
+    # with missing blocks; gated epilogue and a bias that is aligned to two bytes only
+    run_a8_case(w2, M, K, N, G, 1, w2.VARIANT_MIDM, seed=M + K + N)
+    run_a16_case(w2, M, K, N, G, 0, w2.VARIANT_MIDM, seed=M + K + N)
+    codes, scales, X = synth.make_problem(M, K, N, G, 0, M + N)
+    packed = w2.prepack(dev(codes), dev(scales), G, 0)
+    xq, sx, _ = w2.quantize_rows(dev(X), G)
+    oq, osx, _ = oracle.quantize_rows(X, G)
+    _, y64 = oracle.matmul_a8(codes, scales, G, 0, oq, osx)
+    mag = oracle.a8_term_magnitude(codes, scales, G, 0, oq, osx)
+    bias = synth.f32_to_bf16_bits(np.random.default_rng(M).standard_normal(N).astype(np.float32))
+    store = torch.zeros(N + 1, dtype=torch.int16, device="cuda")
+    store[1:] = dev(bias)
+    for act in (w2.ACT_SILU,) + ((w2.ACT_SILU_MUL,) if N % 32 == 0 else ()):
+        Y = w2.matmul_a8_epi(packed, K, N, G, xq, sx, bias=store[1:], act=act, variant=w2.VARIANT_MIDM)
+        check_epilogue(bf16_bits(Y), y64, mag, bias, act, f"mid-M epilogue {act} M={M} K={K} N={N} G={G}")
+
+
 def test_a8_midm_long_k_and_limits(w2):
     run_a8_case(w2, 64, 8192, 48, 128, 0, w2.VARIANT_MIDM, seed=7)
     run_a8_case(w2, 40, 14336, 32, 64, 1, w2.VARIANT_MIDM, seed=8)
