@@ -63,6 +63,28 @@ def test_prepack_roundtrip(w2, codec, K, N, G):
     assert np.array_equal(s2.cpu().numpy().view(np.uint16), scales)
 
 
+@pytest.mark.parametrize("offset", [0, 8, 1])
+@pytest.mark.parametrize("K,N,G", [(256, 8, 128), (512, 256, 64), (256, 264, 128), (768, 520, 64)])
+def test_prepack_alignments_and_illegal_codes(w2, K, N, G, offset):
+    # rows that start at a multiple of 16, of 8 or of 1 byte; a whole group of column blocks, one block more, half a
+    # block; codes outside the alphabet anywhere (also above 3): counted, and read back as the code of value 0
+    for codec, top in ((0, 3), (1, 2)):
+        codes, scales = synth.make_weights(K, N, G, codec, seed=K + N + offset)
+        rng = np.random.default_rng(K + N)
+        at = rng.choice(K * N, 9, replace=False)
+        want = codes.copy()
+        codes.reshape(-1)[at] = [top + 1, 4, 7, 64, 128, 200, 252, 255, 3 + 4 * 5]
+        want.reshape(-1)[at] = 2 if codec == 0 else 1
+        store = torch.zeros(K * N + offset, dtype=torch.uint8, device="cuda")
+        store[offset:] = dev(codes).reshape(-1)
+        flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+        packed = w2.prepack(store[offset:].view(K, N), dev(scales), G, codec, bad_codes=flag)
+        assert int(flag.item()) == 9
+        c2, s2 = w2.debug_unpack(packed, K, N, G, codec)
+        assert np.array_equal(c2.cpu().numpy(), want)
+        assert np.array_equal(s2.cpu().numpy().view(np.uint16), scales)
+
+
 def test_prepack_counts_bad_codes(w2):
     codes, scales = synth.make_weights(256, 32, 128, 1, seed=3)
     codes[5, 7] = 3
