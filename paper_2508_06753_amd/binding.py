@@ -80,11 +80,19 @@ def _check(fn, status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# The current stream's handle, looked up on every call.  torch.cuda.current_stream() builds a Stream object for it:
+# 2.8 us of a 9.7 us call (one row, 2048 x 2048) where these two take 0.2; without them, the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is not None and _raw_device is not None:
+    def _stream():
+        return _raw_stream(_raw_device())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, name):
