@@ -652,15 +652,21 @@ int launch_a8_tiled(const A8Args& a, hipStream_t stream)
         // 71 against 84 us; 4096 x 28672 at M = 384, 1.3 rounds: 66 against 57)
         const int64_t t128 = (a.M + 127) / 128 * ((a.N + 255) / 256);
         const bool fill_ok = t128 >= 768 || t128 % 256 == 0 || t128 % 256 >= 128;
+        // Groups of 64 (twice the dequant fmas, so less to gain per matrix instruction): where the rounds come out
+        // nearly whole and the rows fill their tiles (4096 x 28672 at M = 256 / 512 / 2048, 0.9 / 1.8 / 7 rounds: 43.5 /
+        // 82 / 293 us in 64-row tiles against 41.3 / 78 / 280; 28672 x 8192 at M = 768 / 1024, 0.75 / 1 rounds: 288 /
+        // 283 against 240 / 256; but at M = 1000, 3.5 rounds of 4096 x 28672, 148 against 155)
+        const int64_t tail = t128 % 256;
+        const bool rows_full = a.M * 20 >= (a.M + 127) / 128 * 128 * 17;
+        const bool whole64 = t128 <= 256 ? t128 >= 144 : (t128 >= 1792 || tail == 0 || tail >= 159) && rows_full;
         const bool want128 = a.tune.tiled_bm ? a.tune.tiled_bm == 128
+                           : a.G == 64       ? a.M >= 128 && whole64
                                              : a.M >= 1024 || (a.M >= 128 && t128 >= 224 && fill_ok);
         const int s_deep = a.acc_out ? 1 : deep128_splits(a.M, a.N, a.n_kt, a.G, cap, a.tune);
-        if (a8_tiled128_supports(a)) {
-            // forced 128-row tiles: that kernel's own rule for K ranges (or the forced count)
-            if (a.tune.tiled_bm == 128) return launch_a8_tiled128(a, a8_tiled128_splits(a.M, a.N, a.n_kt, cap, a.tune), stream);
-            if (s_deep >= 2) return launch_a8_tiled128(a, s_deep, stream);
-            if (want128 && splits < 2) return launch_a8_tiled128(a, 1, stream);
-        }
+        // forced 128-row tiles: that kernel's own rule for K ranges (or the forced count)
+        if (a.tune.tiled_bm == 128) return launch_a8_tiled128(a, a8_tiled128_splits(a.M, a.N, a.n_kt, cap, a.tune), stream);
+        if (s_deep >= 2) return launch_a8_tiled128(a, s_deep, stream);
+        if (want128 && splits < 2) return launch_a8_tiled128(a, 1, stream);
     }
     if (a.G == 128)
         return a.acc_out ? launch_tiled_bn<128, true>(a, stream) : launch_tiled_bn<128, false>(a, stream);

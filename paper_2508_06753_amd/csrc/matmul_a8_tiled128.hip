@@ -26,11 +26,16 @@
 //     instructions it reads the second k-step's operands and the next stage's
 //     first ones, up-converts one operand ahead, and dequantises a finished
 //     column block in two halves (16 fmas per eight matrix instructions);
+//   - groups of 64 (G = 64): a k-step is a group, so every block of eight matrix
+//     instructions leaves a finished group in one of two accumulator sets and
+//     folds the other one in (32 fmas): 5.2 vector instructions per matrix
+//     instruction against 6.1 in 64-row tiles (8192 x 57344 at M = 2048: 1118 ->
+//     1051 us; 28672 x 8192 at M = 1024: 283 -> 256);
 //   - dequant in ONE fma per accumulator: a group starts from BIAS = 2^21 (the
 //     third MFMA operand), so acc = BIAS + 64*sum is positive and below 2^23 and
 //     its bit pattern read as binary32 is the denormal acc * 2^-149:
 //     y += as_float(acc) * (sw * 2^64); the bias term is taken out every 16
-//     stages and at the end.  Requires fp32 denormals (the build keeps them and
+//     groups and at the end.  Requires fp32 denormals (the build keeps them and
 //     the source refuses fast-math) and |sw| < 2^63.  (Starting from the bit
 //     pattern of 1.5 * 2^23 instead, a normal number, is no faster -- denormal
 //     operands cost the fma nothing here -- and carries six times the bias,
@@ -255,6 +260,23 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             }
         }
     };
+    // G = 64: the group in accumulator set `set`, all rows, into column block j
+    auto dequant_set = [&](int set, int j, float swS, int64_t g) {
+#pragma unroll
+        for (int i = 0; i < RI; ++i) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (DBG) {
+                    const int64_t m = m0 + i * 16 + 4 * q + r;
+                    const int64_t n = n0 + wn * WN + j * 16 + l16;
+                    if (g >= 0 && m < a.M && n < a.N)
+                        a.acc_out[(m * (a.K / G) + g) * a.N + n] = (acc[i][set][r] - BIAS) >> 6;
+                }
+                y[i][j][r] = fmaf(__int_as_float(acc[i][set][r]), swS, y[i][j][r]);
+            }
+        }
+        ssum[j] += swS;
+    };
     auto scale_of = [&](const WTile<G>& w, int j, int h, int t) -> float {
         // G = 128: the stage's group is group h of the tile; G = 64: k-step t of stage h is group 2h + t
         const uint32_t pair = G == 128 ? w.s[j][0] : w.s[j][h];
@@ -296,7 +318,6 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         const int8_t* ab = a_base + buf * A_BUF;
         const int8_t* abn = a_base + buf1 * A_BUF;
         const WTile<G>& wn_tile = h == 1 ? wnx : wc;         // where the next stage finds its weights
-        static_assert(G == 128, "this schedule is written for one group per stage");
         const float sw0 = scale_of(wc, 0, h, 0), sw1 = scale_of(wc, 1, h, 0);
         const int64_t g = it;                                // group index = stage index (G = 128)
 
@@ -306,15 +327,49 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         // region the scheduler pulled the fmas up to right behind the matrix instruction that produces their
         // operand, and every such pair stalls the wave until the matrix pipe has written the result (measured:
         // 2070 TOP/s; 4290 with the same fmas reading other registers).
-        auto interleave = [&](bool with_lds) {               // per matrix instruction: [one LDS read] three vector instructions
+        auto interleave = [&](bool with_lds) {               // per matrix instruction: [one LDS read] three (five) vector instructions
 #pragma unroll
             for (int k = 0; k < RI; ++k) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (with_lds) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, G == 128 ? 3 : 5, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
+        if constexpr (G == 64) {
+            // A k-step is a group: every block leaves a whole group in one of two accumulator sets (acc[.][0] and
+            // acc[.][1]), which the next block folds in row by row, eight matrix instructions behind.
+            const float sw01 = scale_of(wc, 0, h, 1), sw11 = scale_of(wc, 1, h, 1);
+#pragma unroll
+            for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_STRIDE + 64);
+            const v4i b10 = upconvert4(dword_of(wc, 0, h, 1));
+#pragma unroll
+            for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b00, biasv, 0, 0, 0);
+            dequant_set(1, 1, pend_sw, pend_g);              // column 1's second group of the previous stage
+            interleave(true);
+            const v4i b01 = upconvert4(dword_of(wc, 1, h, 0));
+#pragma unroll
+            for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b10, biasv, 0, 0, 0);
+            dequant_set(0, 0, sw0, 2 * g);
+            interleave(false);
+            const v4i b11 = upconvert4(dword_of(wc, 1, h, 1));
+#pragma unroll
+            for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b01, biasv, 0, 0, 0);
+            dequant_set(1, 0, sw01, 2 * g + 1);
+            interleave(false);
+#pragma unroll
+            for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
+            b_next = upconvert4(dword_of(wn_tile, 0, h ^ 1, 0));
+#pragma unroll
+            for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b11, biasv, 0, 0, 0);
+            dequant_set(0, 1, sw1, 2 * g);
+            pend_sw = DBG ? 1.0f : sw11;
+            pend_g = 2 * g + 1;
+            interleave(true);
+            buf = buf1;
+            if constexpr (NBUF == 3 || h == 1) __syncthreads();
+            return;
+        }
         // block A
 #pragma unroll
         for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_STRIDE + 64);
@@ -358,9 +413,9 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         stage(kt * 2, std::integral_constant<int, 0>{}, w0, w1);
         stage(kt * 2 + 1, std::integral_constant<int, 1>{}, w0, w1);
         w0 = w1;
-        if ((kt & 7) == 7) {
-            // take the accumulated bias term out every 16 stages, so that the running sums never carry
-            // more than 16 stages of it (the rounding error stays near 2^-14 of the result, whatever K is)
+        if ((kt & (G == 128 ? 7 : 3)) == (G == 128 ? 7 : 3)) {
+            // take the accumulated bias term out every 16 groups, so that the running sums never carry
+            // more than 16 groups of it (the rounding error stays near 2^-14 of the result, whatever K is)
 #pragma unroll
             for (int j = 0; j < CJ; ++j) {
                 // column 1 of the stage just finished is still pending: its scale is not in ssum[1] yet
@@ -374,9 +429,13 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         }
     }
     // the very last stage's column block 1
-    dequant_half(1, 0, pend_sw, pend_g);
-    dequant_half(1, RI / 2, pend_sw, pend_g);
-    ssum[1] += pend_sw;
+    if constexpr (G == 64) {
+        dequant_set(1, 1, pend_sw, pend_g);
+    } else {
+        dequant_half(1, 0, pend_sw, pend_g);
+        dequant_half(1, RI / 2, pend_sw, pend_g);
+        ssum[1] += pend_sw;
+    }
     if constexpr (DBG) return;
 
     // y_true = (y - BIAS*2^-149 * ssum) * 2^(149-64) * 2^-6 * sx.  The wave's 128 x 32 result goes through
@@ -470,7 +529,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     }
 }
 
-template <bool DBG, int BN, bool SPLIT = false>
+template <int G, bool DBG, int BN, bool SPLIT = false>
 static int launch(const A8Args& a, int splits, hipStream_t stream)
 {
     constexpr int WAVES = waves_of(BN);
@@ -481,7 +540,7 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
     // moves the least through the XCD's L2 (measured as fast as 8 at M = 2048, 2 % faster at M = 4096).
     const int group_m = a.tune.tiled_group_m ? a.tune.tiled_group_m : 4;
     constexpr int lds = lds_bytes(BN) + SX_BYTES;
-    auto kern = a8_tiled128_kernel<128, DBG, BN, SPLIT>;
+    auto kern = a8_tiled128_kernel<G, DBG, BN, SPLIT>;
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, "w2_matmul_a8[tiled 128]")) return rc;
     const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n), (unsigned)(SPLIT ? splits : 1)), block(64 * WAVES);
     hipLaunchKernelGGL(kern, grid, block, lds, stream, a, tiles_m, tiles_n, group_m, (int)(a.n_kt / (SPLIT ? splits : 1)),
@@ -493,8 +552,6 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
 
 }  // namespace t128
 
-// G = 128 only (a stage is one group).
-bool a8_tiled128_supports(const A8Args& a) { return a.G == 128; }
 
 // K ranges across workgroups for the 128-row kernel: with room for partial results, 256-column workgroups
 // (one per CU) times floor(256 / tiles) ranges -- one round, never more -- up to 8, at least two 256-k tiles
@@ -517,14 +574,18 @@ int launch_a8_tiled128(const A8Args& a, int splits, hipStream_t stream)
 {
     const int64_t wgs256 = ((a.M + 127) / 128) * ((a.N + 255) / 256);
     const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    if (a.acc_out || splits > cap || splits > a.n_kt) splits = 1;
+    if (a.acc_out || splits > cap || splits > a.n_kt || a.G != 128) splits = 1;
     if (splits >= 2) {
-        if (a.tune.tiled_bn == 128) return t128::launch<false, 128, true>(a, splits, stream);
-        return t128::launch<false, 256, true>(a, splits, stream);
+        if (a.tune.tiled_bn == 128) return t128::launch<128, false, 128, true>(a, splits, stream);
+        return t128::launch<128, false, 256, true>(a, splits, stream);
     }
     const int bn = a.tune.tiled_bn == 128 || a.tune.tiled_bn == 256 ? a.tune.tiled_bn : wgs256 <= 128 ? 128 : 256;
-    if (a.acc_out) return bn == 128 ? t128::launch<true, 128>(a, 1, stream) : t128::launch<true, 256>(a, 1, stream);
-    return bn == 128 ? t128::launch<false, 128>(a, 1, stream) : t128::launch<false, 256>(a, 1, stream);
+    if (a.G == 64) {
+        if (a.acc_out) return bn == 128 ? t128::launch<64, true, 128>(a, 1, stream) : t128::launch<64, true, 256>(a, 1, stream);
+        return bn == 128 ? t128::launch<64, false, 128>(a, 1, stream) : t128::launch<64, false, 256>(a, 1, stream);
+    }
+    if (a.acc_out) return bn == 128 ? t128::launch<128, true, 128>(a, 1, stream) : t128::launch<128, true, 256>(a, 1, stream);
+    return bn == 128 ? t128::launch<128, false, 128>(a, 1, stream) : t128::launch<128, false, 256>(a, 1, stream);
 }
 
 }  // namespace w2

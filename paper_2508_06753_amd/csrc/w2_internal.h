@@ -82,7 +82,6 @@ int launch_a8_smallm(const A8Args& a, hipStream_t stream);
 bool a8_midm_supports(const A8Args& a);
 int launch_a8_midm(const A8Args& a, hipStream_t stream);
 int launch_a8_tiled(const A8Args& a, hipStream_t stream);
-bool a8_tiled128_supports(const A8Args& a);
 int launch_a8_tiled128(const A8Args& a, int splits, hipStream_t stream);
 int a8_tiled128_splits(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune);
 

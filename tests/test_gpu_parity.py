@@ -455,6 +455,14 @@ def test_a8_tiled_128_row_tiles_split_k(w2, M, K, N, splitk, bn, act):
         check_epilogue(bf16_bits(Y), y64, mag, None, act, f"a8 128-row tiles split-K {splitk} gated bn={bn} M={M} K={K} N={N}")
 
 
+@pytest.mark.parametrize("bn", [128, 256])
+@pytest.mark.parametrize("M,K,N", [(1, 256, 8), (127, 256, 16), (129, 2304, 272), (256, 1024, 1032)])
+def test_a8_128_row_tiles_groups_of_64(w2, M, K, N, bn):
+    # two groups per stage, accumulator sets alternating between blocks: one tile of K, a K that ends between two
+    # settlements of the bias (nine tiles), ragged rows and columns, both workgroup widths; accumulators bit for bit
+    run_a8_case(w2, M, K, N, 64, M % 2, w2.VARIANT_TILED, seed=M + K + N, tune={"tiled_bm": 128, "tiled_bn": bn})
+
+
 @pytest.mark.parametrize("M", [20, 100, 300])
 def test_a8_one_fma_dequant_keeps_denormals(w2, M):
     # the mid-M and prefill kernels read BIAS + 64*sum as an fp32 denormal and multiply by sw * 2^64: a build
