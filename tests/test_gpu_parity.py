@@ -136,6 +136,23 @@ def test_quantize_ties_and_bf16_and_stride(w2):
     assert np.array_equal(xq.cpu().numpy(), oq)
 
 
+@pytest.mark.parametrize("bf16_in", [False, True])
+@pytest.mark.parametrize("M,K", [(2, 256), (1, 2304), (3, 8448), (1, 33024), (1, 66048), (65, 768), (65, 4352), (66, 17408)])
+def test_quantize_row_lengths(w2, M, K, bf16_in):
+    # one to eight vectors per thread and rows that need a second reading, last vectors partly or wholly past the end,
+    # one wave and several, few rows and many; a row whose largest value comes last, one that is constant
+    X = synth.make_activations(M, K, seed=M + K)
+    X[0, -1] = 9.0
+    X[M - 1, :] = -0.5 if M > 1 else X[M - 1, :]
+    Xb = synth.f32_to_bf16_bits(X)
+    oq, os_, og = oracle.quantize_rows(Xb if bf16_in else X, 64, x_is_bf16=bf16_in)
+    for want in (True, False):
+        xq, sx, gs = w2.quantize_rows(dev(Xb).view(torch.bfloat16) if bf16_in else dev(X), 64, want_gsum=want)
+        assert np.array_equal(xq.cpu().numpy(), oq)
+        assert np.array_equal(sx.cpu().numpy().view(np.uint32), os_.view(np.uint32))
+        assert not want or np.array_equal(gs.cpu().numpy(), og)
+
+
 @pytest.mark.parametrize("G", [64, 128])
 @pytest.mark.parametrize("M", [1, 3])
 def test_quantize_bf16_single_tile_row_with_group_sums(w2, M, G):
