@@ -57,33 +57,41 @@ constexpr int max_waves(int RL, int XT = 0) { return RL > 4 || XT == 3 ? 8 : 16;
 
 // ---- w2a16 in the same kernel (XT 3; Sec. II-D, "Alternative implementation": the activations stay bf16, the
 // weights become 16-bit values in registers and go to the 16-bit matrix instruction, fp32 accumulation).
-// The up-convert is the one of the other w2a16 kernels: XOR 0xAAAAAAAA turns every field into s = q + 2, OR-ing a
-// field into the mantissa of the bf16 constant 128 gives 130 + q, two weights per (shift, and-or); the matrix
-// instruction then sums x * (130 + q) and a group's accumulator STARTS from -130 * (sum of the group's x), which
-// the staging pass leaves in local memory, so that the group ends as sum x * q and the dequant is one fma.
+// The up-convert: bf16 has seven mantissa bits, so the 2-bit field at bit 2 j of a number whose exponent is that of
+// 128 / 4^j weighs exactly 1.  XOR with the mask's share of 0xAAAA.. turns a field into s = q + 2 and sets the exponent
+// in the same instruction (the bits are disjoint): (w & mask_j) ^ base_j is two weights 128 / 4^j + s, s = 0 .. 3, for
+// j = 0, 1, 2 of the even bytes; two shifts (by 6 and 12) bring the other five pairs to those places: ten instructions
+// for 16 weights (one shift and one and-or per pair, all at the offset 128, before: 4096 x 28672 at
+// M = 1 / 4 / 8 9.9 / 10.6 / 12.5 -> 8.8 / 10.0 / 11.6 us, 14336 x 4096 at M = 1 6.6 -> 6.2; the smaller offsets also
+// leave less to cancel).
+// The matrix instruction then sums x * (offset + 2 + q), and a group's accumulator STARTS from the sum of the group's
+// -(offset + 2) * x, which the staging pass leaves in local memory, so that the group ends as sum x * q and the
+// dequant is one fma.
 // Operand dwords 0..3 take their two weights from bytes 0 and 2 of the code word (even k of the lane's 16-k
 // block), dwords 4..7 from bytes 1 and 3 (odd k); the rows are staged de-interleaved the same way.
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-constexpr float ZP16 = 130.0f;
-struct Bf16Consts { uint32_t mask, base; };
+// offset + 2 of k = 4 j + b within a 16-k block: even b {130, 34, 10, 130}[j], odd b {34, 10, 130, 34}[j]
+constexpr float ZP_A = 130.0f, ZP_B = 34.0f, ZP_C = 10.0f;
+struct Bf16Consts { uint32_t mask[3], base[3]; };
 __device__ __forceinline__ Bf16Consts bf16_consts()
 {
-    Bf16Consts c = {0x00030003u, 0x43004300u};
-    asm volatile("" : "+v"(c.mask), "+v"(c.base));           // in vector registers: (x & mask) | base is one instruction
+    Bf16Consts c = {{0x00030003u, 0x000C000Cu, 0x00300030u}, {0x43024302u, 0x42084208u, 0x41204120u}};
+#pragma unroll
+    for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(c.mask[e]), "+v"(c.base[e]));   // in vector registers: (x & mask) ^ base is one instruction
     return c;
 }
 __device__ __forceinline__ void upconvert_bf16(uint32_t w, const Bf16Consts& c, v4i& b0, v4i& b1)
 {
-    const uint32_t x = w ^ 0xAAAAAAAAu;
-    b0[0] = (int)((x & c.mask) | c.base);
-    b0[1] = (int)(((x >> 2) & c.mask) | c.base);
-    b0[2] = (int)(((x >> 4) & c.mask) | c.base);
-    b0[3] = (int)(((x >> 6) & c.mask) | c.base);
-    b1[0] = (int)(((x >> 8) & c.mask) | c.base);
-    b1[1] = (int)(((x >> 10) & c.mask) | c.base);
-    b1[2] = (int)(((x >> 12) & c.mask) | c.base);
-    b1[3] = (int)(((x >> 14) & c.mask) | c.base);
+    const uint32_t w6 = w >> 6, w12 = w >> 12;
+    b0[0] = (int)((w & c.mask[0]) ^ c.base[0]);
+    b0[1] = (int)((w & c.mask[1]) ^ c.base[1]);
+    b0[2] = (int)((w & c.mask[2]) ^ c.base[2]);
+    b0[3] = (int)((w6 & c.mask[0]) ^ c.base[0]);
+    b1[0] = (int)((w6 & c.mask[1]) ^ c.base[1]);
+    b1[1] = (int)((w6 & c.mask[2]) ^ c.base[2]);
+    b1[2] = (int)((w12 & c.mask[0]) ^ c.base[0]);
+    b1[3] = (int)((w12 & c.mask[1]) ^ c.base[1]);
 }
 __device__ __forceinline__ v4f mfma_bf16(const v4i& a, const v4i& b, const v4f& c)
 {
@@ -106,7 +114,7 @@ struct Args {
     int outs_magic;               // ceil(2^20 / outputs per row of a workgroup): item / outputs for items below 4096
     int red_off;                  // LDS offset of the reduction scratch
     int sc_off;                   // LDS offset of the waves' scale slices
-    int xg_off;                   // XT 3: LDS offset of -130 * (group sums of the rows), [K / G][4 rows] fp32
+    int xg_off;                   // XT 3: LDS offset of the group sums of -(offset + 2) * x, [K / G][4 rows] fp32
     const float* sx;              // XT 0: activation scales [M]
     uint16_t* Y;
     int32_t* acc_out;             // debug export (XT 0)
@@ -283,19 +291,26 @@ a8_gemv_kernel(const void* p_X, int64_t p_ldx, const uint32_t* p_codes, const ui
         if (!DBG && !SX_IN_REGS && tid < a.M) s_red[SX_SLOT + tid] = sx_mine;
     } else if constexpr (A16) {
         // bf16 rows as they are, de-interleaved per 16-k block ([8 even k | 8 odd k]: the two matrix operands of
-        // a lane are then one 16-byte read each), and -130 x the sum of every group of every row.  A piece
-        // is 8 values; the G / 8 pieces of a group sit in consecutive lanes of one row of 16 lanes.
+        // a lane are then one 16-byte read each), and the sum of -(offset + 2) * x over every group of every row.
+        // A piece is 8 values, j = 0, 1 or j = 2, 3 of its block by the thread's parity; the G / 8 pieces of a group
+        // sit in consecutive lanes of one row of 16 lanes.
         constexpr int PPG = G / 8;
         float* xg = reinterpret_cast<float*>(smem + a.xg_off);
+        const bool upper = tid & 1;                          // (threads is even: so is the piece's index, or not, for every j)
+        const float z0 = upper ? -ZP_C : -ZP_A, z1 = upper ? -ZP_A : -ZP_B;     // even and odd k of the piece's first four
+        const float z2 = upper ? -ZP_A : -ZP_B, z3 = upper ? -ZP_B : -ZP_C;     // ... and of its last four
 #pragma unroll
         for (int r = 0; r < RL; ++r)
 #pragma unroll
             for (int j = 0; j < PR; ++j) {
                 const int i = tid + j * threads;
                 const uint32_t d[4] = {pc[r][j].x, pc[r][j].y, pc[r][j].z, pc[r][j].w};
-                float sum = 0.f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum += __uint_as_float(d[e] << 16) + __uint_as_float(d[e] & 0xffff0000u);
+                auto lo = [&](int e) { return __uint_as_float(d[e] << 16); };
+                auto hi = [&](int e) { return __uint_as_float(d[e] & 0xffff0000u); };
+                float sum = z0 * (lo(0) + lo(1));
+                sum = fmaf(z1, hi(0) + hi(1), sum);
+                sum = fmaf(z2, lo(2) + lo(3), sum);
+                sum = fmaf(z3, hi(2) + hi(3), sum);
                 sum += dpp_move_f32<0xB1>(sum);              // pairs, quads, eights, (sixteen) lanes: every lane
                 sum += dpp_move_f32<0x4E>(sum);              // ends with its group's sum, added in one fixed order
                 sum += dpp_move_f32<0x141>(sum);
@@ -306,7 +321,7 @@ a8_gemv_kernel(const void* p_X, int64_t p_ldx, const uint32_t* p_codes, const ui
                     int8_t* blk = xs + r * row_stride + (i >> 1) * 32 + (i & 1) * 8;
                     *reinterpret_cast<uint2*>(blk) = ev;
                     *reinterpret_cast<uint2*>(blk + 16) = od;
-                    if ((i & (PPG - 1)) == 0) xg[(i / PPG) * XGS + r] = -ZP16 * sum;
+                    if ((i & (PPG - 1)) == 0) xg[(i / PPG) * XGS + r] = sum;
                 }
             }
         // no activation scale: the epilogue's sx * 2^-6 is exactly 1
