@@ -467,6 +467,18 @@ static double price(int xt, const Plan& p, int64_t M, int64_t n_cb, int64_t n_kt
          + c[12] * 1e-3 * wgs;                               // workgroups to launch
 }
 
+// Row tiles (16 rows x 256 k, 4 KB of int8) that all workgroups together read.  With two column blocks per wave every 32
+// columns read all rows, and on a deep K that stream out of the L2s, about 50 bytes a nanosecond and CU, is what the launch
+// waits for; the linear model has no such limit.  Above 172 MB shapes of two column blocks are left out, which leaves
+// four, half the stream (28672 x 8192 at M = 32 / 48 / 144 23.2 / 29.5 / 66.8 -> 21.3 / 25.2 / 53.5 us, 17408 x 7168 at
+// M = 48 18.3 -> 16.0).  The line: 17408 x 6144 at M = 48, 160 MB, takes 14.3 with two and 14.8 with four; with groups of
+// 64 four also lose 3 to 6 % where the last row tile holds one row (28672 x 8192 at M = 33 26.8 -> 27.7).
+static int64_t row_tiles_read(const Plan& p, int64_t M, int64_t n_cb, int64_t n_kt)
+{
+    return (n_cb + p.cj * p.sh - 1) / (p.cj * p.sh) * ((M + 16 * p.rt - 1) / (16 * p.rt)) * p.rt * n_kt;
+}
+constexpr int64_t ROW_TILES_FROM_L2 = 42000;                 // 172 MB
+
 static Plan plan(int xt, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, const w2_tuning_t& tune)
 {
     Plan best = {1, 2, 1, 1};
@@ -476,6 +488,7 @@ static Plan plan(int xt, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, cons
         if (gated && cj * sh < 2) return;                                    // a workgroup pairs gate and up blocks
         if (tune.midm_cbw && cj * sh != (xt == 1 ? min(tune.midm_cbw, 4) : tune.midm_cbw)) return;
         const Plan p = {rt, cj, (int)min((int64_t)ks, n_kt), sh};
+        if (xt == 0 && cj == 2 && sh == 1 && !tune.midm_cbw && row_tiles_read(p, M, n_cb, n_kt) > ROW_TILES_FROM_L2) return;
         const double t = price(xt, p, M, n_cb, n_kt);
         if (t < best_price) { best = p; best_price = t; }
     };

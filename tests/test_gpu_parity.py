@@ -352,6 +352,14 @@ def test_midm_k_ranges_and_row_tiles(w2, M, K, N, G):
         check_epilogue(bf16_bits(Y), y64, mag, bias, act, f"mid-M epilogue {act} M={M} K={K} N={N} G={G}")
 
 
+@pytest.mark.parametrize("N", [1312, 1344])
+@pytest.mark.parametrize("M", [241, 256])
+def test_midm_row_stream_limit(w2, M, N):
+    # 64 k-tiles x 16 row tiles x 41 / 42 pairs of column blocks: just below and just above the 42000 row tiles from
+    # which four column blocks per wave are taken; a last row tile of one row, a last column group with missing blocks
+    run_a8_case(w2, M, 16384, N, 128, 1, w2.VARIANT_MIDM, seed=M + N)
+
+
 def test_a8_midm_long_k_and_limits(w2):
     run_a8_case(w2, 64, 8192, 48, 128, 0, w2.VARIANT_MIDM, seed=7)
     run_a8_case(w2, 40, 14336, 32, 64, 1, w2.VARIANT_MIDM, seed=8)
