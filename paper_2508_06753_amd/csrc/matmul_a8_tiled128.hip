@@ -452,9 +452,11 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     }
     // (one copy of the loop per epilogue, picked here: a choice per element would have the compiler
     // evaluate the SiLU for every output and select afterwards)
+    // (y - bias) * 2^79 in one fma (powers of two: exact products), then sx: in this order a row scale may be as large as
+    // fp32 holds
     float cj[CJ];
 #pragma unroll
-    for (int j = 0; j < CJ; ++j) cj[j] = ssum[j] * BIAS_F;
+    for (int j = 0; j < CJ; ++j) cj[j] = ssum[j] * -(BIAS_F * 0x1p79f);
     if constexpr (SPLIT) {
         // this range's results, dequantised, as fp32 rows of the workspace: the wave's 128 x 32 tile goes
         // through LDS 64 rows at a time (rows padded by 16 bytes: conflict-free both ways; the wave reads
@@ -476,7 +478,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 #pragma unroll
                     for (int j = 0; j < CJ; ++j)
                         *reinterpret_cast<float*>(pbase + (i * 16 + 4 * q + r) * P_STRIDE + (j * 16 + l16) * 4) =
-                            (y[h * 4 + i][j][r] - cj[j]) * (sr[r] * 0x1p79f);
+                            fmaf(y[h * 4 + i][j][r], 0x1p79f, cj[j]) * sr[r];
             }
 #pragma unroll
             for (int p = 0; p < 8; ++p) {
@@ -497,10 +499,9 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = i * 16 + 4 * q + r;
-                const float t = sr[r] * 0x1p79f;
                 float z[CJ];
 #pragma unroll
-                for (int j = 0; j < CJ; ++j) z[j] = (y[i][j][r] - cj[j]) * t + bias[j];
+                for (int j = 0; j < CJ; ++j) z[j] = fmaf(y[i][j][r], 0x1p79f, cj[j]) * sr[r] + bias[j];
                 if constexpr (MODE == ACT_SILU_MUL) {
                     eb[row * (E_STRIDE / 2) + l16] = f32_to_bf16_rne(silu_f32(z[0]) * z[1]);
                 } else {

@@ -375,7 +375,7 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
                 red[(rt * 16 + 4 * q + r) * RS + j * 16 + l16] = y[rt][j][r];
     float* const sx_lds = reinterpret_cast<float*>(smem + (blockDim.x >> 6) / SH * range_lds(RT, CJ, SH));
     if constexpr (XT == 0) {
-        if (threadIdx.x < RT * 16) sx_lds[threadIdx.x] = sx_mine * 0x1p79f;   // 2^(149-64-6)
+        if (threadIdx.x < RT * 16) sx_lds[threadIdx.x] = sx_mine;
     }
     __syncthreads();
     const int ks = (blockDim.x >> 6) / SH;
@@ -385,7 +385,8 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
         v4f s = {0.f, 0.f, 0.f, 0.f};
         const int8_t* p = smem + (col / (CJ * 16)) * red_bytes(RT, CJ) + (row * RS + col % (CJ * 16)) * 4;
         for (int k = 0; k < ks; ++k) s += *reinterpret_cast<const v4f*>(p + k * range_lds(RT, CJ, SH));
-        if constexpr (XT == 0) s *= sx_lds[row];
+        // 2^79 = 2^(149-64-6) on the sums, not on sx: a row scale may be as large as fp32 holds
+        if constexpr (XT == 0) s = s * 0x1p79f * sx_lds[row];
         return s;
     };
     auto add_bias = [&](v4f& v, int64_t n) {

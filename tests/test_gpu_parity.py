@@ -507,6 +507,31 @@ def test_a8_one_fma_dequant_keeps_denormals(w2, M):
         assert np.array_equal(bits_to_f64(bf16_bits(Y)), want), (variant, tune)
 
 
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("M", [4, 8, 16, 32, 48, 128, 240, 300, 1024])
+def test_a8_large_row_scales(w2, M, G):
+    # row scales near 2^60 (rows of 1e20): finite results through every kernel that AUTO picks, a column of zero weights
+    # exactly zero; the last size also with K split across workgroups (128-row tiles)
+    K, N = 1024, 528
+    codes, scales = synth.make_weights(K, N, G, 0, seed=M + G)
+    codes[:, 5] = 2
+    rng = np.random.default_rng(M)
+    xq = rng.integers(-127, 128, (M, K)).astype(np.int8)
+    sx = (rng.uniform(0.5, 1.0, M) * 2.0 ** 60).astype(np.float32)
+    packed = w2.prepack(dev(codes), dev(scales), G, 0)
+    Yo, y64 = oracle.matmul_a8(codes, scales, G, 0, xq, sx)
+    mag = oracle.a8_term_magnitude(codes, scales, G, 0, xq, sx)
+    ways = [{}]
+    if M == 1024 and G == 128:
+        ways.append({"tiled_bm": 128, "splitk": 2})
+    for tune in ways:
+        ws = torch.empty(2 * M * N * 4, dtype=torch.uint8, device="cuda") if tune else None
+        Y = bf16_bits(w2.matmul_a8(packed, K, N, G, dev(xq), dev(sx), workspace=ws, tune=tune or None))
+        assert np.isfinite(bits_to_f64(Y)).all()
+        assert not bits_to_f64(Y[:, 5]).any()
+        check_y(Y, Yo, y64, mag, f"large row scales M={M} G={G} {tune}")
+
+
 @pytest.mark.parametrize("M", [1, 4, 8, 9, 16, 17, 64, 65, 130])
 def test_a8_auto_dispatch(w2, M):
     run_a8_case(w2, M, 1024, 528, 128, 0, w2.VARIANT_AUTO, seed=M)
