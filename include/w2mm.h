@@ -177,8 +177,10 @@ W2_API int w2_quantize_rows(const void* X, w2_dtype_t x_dtype, int64_t M, int64_
  *   acc[m,g,n] = sum_{k in group g} xq[m,k] * q[k,n]            (int32, exact)
  *   Y[m,n]     = bf16( sx[m] * sum_g sw[g,n] * float(acc[m,g,n]) )   (fp32)
  * packed  dev, from w2_prepack with the same K, N, G
- *         Weight scales: finite bf16 with |sw| < 2^63 (for M > 4 the kernels
- *         multiply by sw * 2^64 in fp32); results below the fp32 normal range
+ *         Weight scales: finite bf16, for M > 32 (and the TILED family forced)
+ *         with |sw| < 2^63 (those kernels multiply by sw * 2^64 in fp32 and sum
+ *         with an error of 2^-14 of the largest scale; up to M = 32 every group's
+ *         int32 sum is converted exactly); results below the fp32 normal range
  *         (|sx * sw * acc| < 2^-126) may lose precision.
  * xq, sx  dev, as produced by w2_quantize_rows ([M][K] dense, [M])
  * Y       dev, bf16 bit patterns [M][N], row stride ldy

@@ -120,7 +120,8 @@ constexpr int range_lds(int rt, int cj, int sh)
 // most waves of a workgroup: 16 where a wave's registers allow it (very deep and narrow projections), else 8
 constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
 
-template <int XT, int G, int RT, int CJ, int SH, bool DBG>
+// EX (int8 rows): every group's int32 sum is converted exactly before it is scaled; see the dequant below
+template <int XT, int G, int RT, int CJ, int SH, bool EX, bool DBG>
 __global__ void __launch_bounds__(64 * max_waves(RT, CJ), max_waves(RT, CJ) / 4)
 midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const char* __restrict__ scales, uint32_t stride, int M,
             int n_cb, int n_kt, int t_lo, int t_rem, Args a)
@@ -208,12 +209,15 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
     for (int i = 0; i < D; ++i) load_w(i, i);
     __builtin_amdgcn_sched_barrier(0);
 
-    // Dequant of the int8 form in one fma: a group starts from BIAS = 2^21 (the third matrix operand), so
+    // Dequant of the int8 form above EXACT_ROWS in one fma: a group starts from BIAS = 2^21 (the third matrix operand), so
     // acc = BIAS + 64 * sum is positive and below 2^23 and its bit pattern read as binary32 is the denormal
     // acc * 2^-149: y += as_float(acc) * (sw * 2^64).  The bias, 2^-128 * (the sum of the scaled scales), is taken out
     // every four tiles and at the end.  Two accumulator sets alternate between groups; a finished group is dequantised
     // under the next one's matrix instructions.
-    constexpr int BIAS = 1 << 21;                            // > 64 * 127 * 2 * 128
+    // EX: no bias; the sum is converted (one more instruction) and scaled as the decode kernel does it, which takes the
+    // same row counts on other shapes: fp32 sums of exact products, any finite scale.
+    constexpr int BIAS = EX ? 0 : 1 << 21;                   // > 64 * 127 * 2 * 128
+    constexpr float SWS = EX ? 1.0f : 0x1p64f;
     const v4i biasv = {BIAS, BIAS, BIAS, BIAS};
     v4i acc[2][RT];
     v4f y[RT][CJ];
@@ -241,11 +245,12 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
                     if (pend_sw != 0.f && n < a.N && m < rows)
                         a.acc_out[((int64_t)(m0 + m) * (n_kt * GPT) + pend_g) * a.N + n] = (acc[b][rt][r] - BIAS) >> 6;
                 }
-                y[rt][j][r] = fmaf(__int_as_float(acc[b][rt][r]), pend_sw, y[rt][j][r]);
+                y[rt][j][r] = fmaf(EX ? (float)acc[b][rt][r] : __int_as_float(acc[b][rt][r]), pend_sw, y[rt][j][r]);
             }
-        ssum[j] += pend_sw;
+        if constexpr (!EX) ssum[j] += pend_sw;
     };
     auto settle = [&]() {
+        if constexpr (EX) return;
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
             const float corr = ssum[j] * 0x1p-128f;
@@ -327,18 +332,18 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
                             dequant(b ^ 1, pj);
 #pragma unroll
                             for (int rt = 0; rt < RT; ++rt) acc[b][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f1[rt], b1, acc[b][rt], 0, 0, 0);
-                            pend_sw = DBG ? 1.0f : __uint_as_float(h ? p & 0xffff0000u : p << 16) * 0x1p64f;
+                            pend_sw = DBG ? 1.0f : __uint_as_float(h ? p & 0xffff0000u : p << 16) * SWS;
                             pend_g = (t0 + i) * GPT + h;
                         } else {
 #pragma unroll
                             for (int rt = 0; rt < RT; ++rt) acc[0][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f0[rt], b0, biasv, 0, 0, 0);
                             dequant(1, pj);
-                            pend_sw = DBG ? 1.0f : __uint_as_float(p << 16) * 0x1p64f;
+                            pend_sw = DBG ? 1.0f : __uint_as_float(p << 16) * SWS;
                             pend_g = (t0 + i) * GPT + 2 * h;
 #pragma unroll
                             for (int rt = 0; rt < RT; ++rt) acc[1][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f1[rt], b1, biasv, 0, 0, 0);
                             dequant(0, j);
-                            pend_sw = DBG ? 1.0f : __uint_as_float(p & 0xffff0000u) * 0x1p64f;
+                            pend_sw = DBG ? 1.0f : __uint_as_float(p & 0xffff0000u) * SWS;
                             pend_g = (t0 + i) * GPT + 2 * h + 1;
                         }
                     } else {
@@ -385,8 +390,8 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
         v4f s = {0.f, 0.f, 0.f, 0.f};
         const int8_t* p = smem + (col / (CJ * 16)) * red_bytes(RT, CJ) + (row * RS + col % (CJ * 16)) * 4;
         for (int k = 0; k < ks; ++k) s += *reinterpret_cast<const v4f*>(p + k * range_lds(RT, CJ, SH));
-        // 2^79 = 2^(149-64-6) on the sums, not on sx: a row scale may be as large as fp32 holds
-        if constexpr (XT == 0) s = s * 0x1p79f * sx_lds[row];
+        // 2^79 = 2^(149-64-6) (EX: 2^-6) on the sums, not on sx: a row scale may be as large as fp32 holds
+        if constexpr (XT == 0) s = s * (EX ? 0x1p-6f : 0x1p79f) * sx_lds[row];
         return s;
     };
     auto add_bias = [&](v4f& v, int64_t n) {
@@ -503,11 +508,16 @@ static Plan plan(int xt, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, cons
     return best;
 }
 
-template <int XT, int G, int RT, int CJ, int SH, bool DBG>
+// Int8 rows: up to 32 rows the decode kernel takes every group's sum exactly, and so does this kernel, whichever of the
+// two a shape goes to (the conversion costs 1 % on average over 2048 x 2048 .. 28672 x 8192, 4096 x 6144 at M = 16
+// 5.10 -> 5.13 us, 3584 x 18944 with groups of 64 7.9 -> 8.5 at worst); above, the prefill kernels' one-fma form.
+constexpr int64_t EXACT_ROWS = 32;
+
+template <int XT, int G, int RT, int CJ, int SH, bool EX, bool DBG>
 static int launch_t(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
 {
     const size_t lds = (size_t)p.ks * range_lds(RT, CJ, SH) + RT * 16 * sizeof(float);
-    auto kern = midm_kernel<XT, G, RT, CJ, SH, DBG>;
+    auto kern = midm_kernel<XT, G, RT, CJ, SH, EX, DBG>;
     if (int rc = ensure_dynamic_lds((const void*)kern, lds, "w2_matmul[midm]")) return rc;
     const dim3 grid((unsigned)((h.n_cb + CJ * SH - 1) / (CJ * SH)), (unsigned)((h.M + RT * 16 - 1) / (RT * 16))), block(64 * p.ks * SH);
     hipLaunchKernelGGL(kern, grid, block, lds, stream, h.X, h.codes, h.scales, h.stride, h.M, h.n_cb, h.n_kt,
@@ -519,9 +529,13 @@ template <int XT, int G, int RT, int CJ>
 static int launch_sh(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
 {
     if constexpr (XT == 0) {
-        if (p.sh == 2) return launch_t<XT, G, RT, CJ, 2, false>(h, a, p, stream);
+        if constexpr (RT <= 2) {
+            if (h.M <= EXACT_ROWS)
+                return p.sh == 2 ? launch_t<XT, G, RT, CJ, 2, true, false>(h, a, p, stream) : launch_t<XT, G, RT, CJ, 1, true, false>(h, a, p, stream);
+        }
+        if (p.sh == 2) return launch_t<XT, G, RT, CJ, 2, false, false>(h, a, p, stream);
     }
-    return launch_t<XT, G, RT, CJ, 1, false>(h, a, p, stream);
+    return launch_t<XT, G, RT, CJ, 1, false, false>(h, a, p, stream);
 }
 
 template <int XT, int G>
@@ -531,10 +545,10 @@ static int launch_g(const Head& h, const Args& a, const Plan& p, hipStream_t str
         if constexpr (XT == 0) {
             const Plan d = {p.rt, 2, (int)min((int64_t)8, (int64_t)h.n_kt), 1};
             switch (p.rt) {
-            case 1: return launch_t<0, G, 1, 2, 1, true>(h, a, d, stream);
-            case 2: return launch_t<0, G, 2, 2, 1, true>(h, a, d, stream);
-            case 3: return launch_t<0, G, 3, 2, 1, true>(h, a, d, stream);
-            default: return launch_t<0, G, 4, 2, 1, true>(h, a, d, stream);
+            case 1: return launch_t<0, G, 1, 2, 1, true, true>(h, a, d, stream);
+            case 2: return launch_t<0, G, 2, 2, 1, true, true>(h, a, d, stream);
+            case 3: return launch_t<0, G, 3, 2, 1, false, true>(h, a, d, stream);
+            default: return launch_t<0, G, 4, 2, 1, false, true>(h, a, d, stream);
             }
         }
     }

@@ -532,6 +532,29 @@ def test_a8_large_row_scales(w2, M, G):
         check_y(Y, Yo, y64, mag, f"large row scales M={M} G={G} {tune}")
 
 
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("M,K", [(5, 17408), (5, 5120), (8, 8192), (9, 1024), (12, 5120), (16, 4096), (17, 2304), (24, 4096), (32, 4096)])
+def test_a8_exact_sums_up_to_32_rows(w2, M, K, G):
+    # up to 32 rows every kernel that AUTO picks converts a group's int32 sum exactly before it is scaled: a group of a
+    # scale 2^23 times the others' whose weights are all zero leaves no trace in the result, and scales beyond 2^63 (the
+    # limit of the one-fma dequant) are as good as any.  check_y's floor is on the terms that are there.
+    N = 80
+    codes, scales, X = synth.make_problem(M, K, N, G, 0, seed=M + K)
+    oq, _, _ = oracle.quantize_rows(X, G)
+    codes[G:2 * G] = 2
+    mixed = scales.copy()
+    mixed[1] = 0x4780                                        # 2^16
+    huge = scales + np.uint16(70 << 7)                       # x 2^70
+    for what, sc, e in (("mixed", mixed, 0), ("huge", huge, -70)):
+        sx = np.full(M, 0.01 * 2.0 ** e, np.float32)
+        packed = w2.prepack(dev(codes), dev(sc), G, 0)
+        Yo, y64 = oracle.matmul_a8(codes, sc, G, 0, oq, sx)
+        mag = oracle.a8_term_magnitude(codes, sc, G, 0, oq, sx)
+        for variant in (w2.VARIANT_AUTO, w2.VARIANT_MIDM):
+            Y = w2.matmul_a8(packed, K, N, G, dev(oq), dev(sx), variant=variant)
+            check_y(bf16_bits(Y), Yo, y64, mag, f"{what} scales M={M} K={K} G={G} variant={variant}")
+
+
 @pytest.mark.parametrize("M", [1, 4, 8, 9, 16, 17, 64, 65, 130])
 def test_a8_auto_dispatch(w2, M):
     run_a8_case(w2, M, 1024, 528, 128, 0, w2.VARIANT_AUTO, seed=M)
