@@ -84,8 +84,8 @@ typedef enum {
  * selectable here).  SMALLM: one 16-row int8 (bf16 for a16) MFMA tile per
  * wave, split-K across waves (M <= 16).  MIDM: the weight stream
  * is read once per band of up to 64 rows; every up-converted weight is multiplied into one to four
- * 16-row MFMA tiles, K split over the waves of a workgroup (M <= 256; for w2a16 with the SCALED16
- * weight construction).
+ * 16-row MFMA tiles, K split over the waves of a workgroup (M <= 256; for w2a16 the weights are q or,
+ * where a wave holds two row tiles and more, the SCALED16 construction).
  * TILED: LDS-staged MFMA tiles (any M; for w2a16 the zero-point construction).
  * SCALED16 (w2a16 only): the weights are built as sw*q from code and group
  * scale (Sec. II-D, the alternative 16-bit construction) and go to the bf16
@@ -94,7 +94,8 @@ typedef enum {
  * with this construction (never picked by AUTO: the zero-point form is faster
  * there); M <= 64: the MIDM kernel; above: a 128-row tiled kernel of its own,
  * AUTO's choice for prefill.  Needs bf16 scales with an exponent field below
- * 254 (-2 sw is made by raising the exponent by one). */
+ * 254 (-2 sw is made by raising the exponent by one); AUTO takes this construction
+ * from M = 17 on. */
 typedef enum { W2_VARIANT_AUTO = 0, W2_VARIANT_DOT4 = 1, W2_VARIANT_SMALLM = 2,
                W2_VARIANT_TILED = 3, W2_VARIANT_MIDM = 4, W2_VARIANT_SCALED16 = 5,
                W2_VARIANT_GEMV = 6 } w2_variant_t;

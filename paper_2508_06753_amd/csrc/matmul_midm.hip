@@ -1,7 +1,8 @@
 // Medium M (up to 256 rows), both activation types: between the memory-bound GEMV regime and the compute-bound GEMM
 // regime of Sec. III-C.  The weight stream is read once per band of up to 64 rows, and every up-converted weight
 // ("up-convert and compute", Sec. II-C) is multiplied into RT row tiles: v_mfma_i32_16x16x64_i8 for int8 rows,
-// v_mfma_f32_16x16x32_bf16 on scale-folded weights for bf16 rows (Sec. II-D, "Alternative implementation").
+// v_mfma_f32_16x16x32_bf16 for bf16 rows (Sec. II-D, "Alternative implementation"), on scale-folded weights from two row
+// tiles per wave on, on the weights q and with a dequant per 64 k below.
 //
 // A wave owns RT row tiles x CJ column blocks x a contiguous run of k tiles; the waves of a workgroup split K (Sec.
 // II-D, K-splitting for small shapes) and their partial results meet in local memory once, in a fixed order.  No
@@ -129,6 +130,7 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
     constexpr int EB = XT == 0 ? 1 : 2;                      // bytes per activation
     constexpr int CH = TILE_K * EB / CHUNK_BYTES;            // chunks per tile: 2 or 4
     constexpr int GPT = TILE_K / G;
+    constexpr bool FOLD = XT == 1 && RT > 1;                 // bf16 rows: the scale folded into the weights, or as they are
     constexpr int NJ = RT * 2 / SH;                          // 16-byte pieces per lane and chunk
     constexpr int D = 2;                                     // weight tiles in flight
     constexpr int SD = NJ <= 4 ? 2 : 1;                      // chunks in flight
@@ -249,6 +251,11 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
             }
         if constexpr (!EX) ssum[j] += pend_sw;
     };
+    v4f accf[2] = {(v4f){0.f, 0.f, 0.f, 0.f}, (v4f){0.f, 0.f, 0.f, 0.f}};      // bf16 rows, not folded: the same alternation
+    auto dequant_f = [&](int b, int j) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[0][j][r] = fmaf(accf[b][r], pend_sw, y[0][j][r]);
+    };
     auto settle = [&]() {
         if constexpr (EX) return;
 #pragma unroll
@@ -272,13 +279,15 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
             upconvert(wd[2 * h + 1], u1);
             bn0 = (v4i){u0[0], u0[1], u0[2], u0[3]};
             bn1 = (v4i){u1[0], u1[1], u1[2], u1[3]};
-        } else {
+        } else if constexpr (FOLD) {
             if (G == 64 || !(h & 1)) {                       // a group begins
                 const uint32_t p = s[G == 128 ? 0 : h >> 1];
                 const int hi = G == 128 ? h >> 1 : h & 1;
                 lut[j] = make_lut(hi ? p >> 16 : p & 0xffffu);
             }
             upconvert16(wd[h], lut[j], bn0, bn1);
+        } else {
+            upconvert16(wd[h], Lut{0x80008000u, 0xbbbc3b00u}, bn0, bn1);     // 2^-8 * (0, 1, -2, -1)
         }
     };
     constexpr int SBUF = RT * 16 * CHUNK_BYTES;
@@ -346,6 +355,17 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
                             pend_sw = DBG ? 1.0f : __uint_as_float(p & 0xffff0000u) * SWS;
                             pend_g = (t0 + i) * GPT + 2 * h + 1;
                         }
+                    } else if constexpr (!FOLD) {
+                        // One row tile (up to 16 rows): 2^-8 * sum x * q of every 64 k apart, then y += sw * sum: any
+                        // finite scale, as in the decode kernel, which takes the same row counts on other shapes (the
+                        // folded weight -2 sw does not exist from 2^127 on), and no finite row overflows a sum.  Four
+                        // fmas per 64 k where the folded table takes ten instructions a group.
+                        const uint32_t p = sc[u][j][G == 128 ? 0 : h >> 1];
+                        const int b = (h * CJ + j) & 1;
+                        accf[b] = mfma_bf16(f0[0], b0, (v4f){0.f, 0.f, 0.f, 0.f});
+                        dequant_f(b ^ 1, (j + CJ - 1) % CJ);
+                        accf[b] = mfma_bf16(f1[0], b1, accf[b]);
+                        pend_sw = __uint_as_float((G == 128 ? h >> 1 : h & 1) ? p & 0xffff0000u : p << 16);
                     } else {
 #pragma unroll
                         for (int rt = 0; rt < RT; ++rt) y[rt][j] = mfma_bf16(f0[rt], b0, y[rt][j]);
@@ -365,6 +385,8 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
         dequant(1, CJ - 1);
         if constexpr (DBG) return;
         settle();
+    } else if constexpr (!FOLD) {
+        dequant_f(1, CJ - 1);
     }
     if constexpr (SH > 1) __syncthreads();                   // the staged chunks are read by the other wave too
     // (fetched under the reduction; read in the store loop it cost 0.1 us a launch)
@@ -390,6 +412,7 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
         v4f s = {0.f, 0.f, 0.f, 0.f};
         const int8_t* p = smem + (col / (CJ * 16)) * red_bytes(RT, CJ) + (row * RS + col % (CJ * 16)) * 4;
         for (int k = 0; k < ks; ++k) s += *reinterpret_cast<const v4f*>(p + k * range_lds(RT, CJ, SH));
+        if constexpr (XT == 1 && !FOLD) s *= 256.0f;
         // 2^79 = 2^(149-64-6) (EX: 2^-6) on the sums, not on sx: a row scale may be as large as fp32 holds
         if constexpr (XT == 0) s = s * (EX ? 0x1p-6f : 0x1p79f) * sx_lds[row];
         return s;

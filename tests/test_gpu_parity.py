@@ -1020,6 +1020,29 @@ def test_a16_midm_long_k_and_limits(w2):
         w2.matmul_a16(packed, K, N, G, dev(synth.f32_to_bf16_bits(X)).view(torch.bfloat16), variant=w2.VARIANT_MIDM)
 
 
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("M,K", [(1, 512), (3, 17408), (5, 5120), (8, 14336), (9, 1024), (16, 4096), (16, 8192)])
+def test_a16_any_finite_scale_up_to_16_rows(w2, M, K, G):
+    # up to 16 rows no kernel that AUTO picks folds the scale into the weights: subnormal scales and those whose
+    # exponent leaves no room for -2 sw; on every shape rows near the top of bf16 where the mid-M kernel runs
+    N = 80
+    codes, _, X = synth.make_problem(M, K, N, G, 0, seed=M + K)
+    rng = np.random.default_rng(M + K + G)
+    top = rng.integers(0x7F00, 0x7F80, (K // G, N)).astype(np.uint16)
+    sub = rng.integers(1, 0x80, (K // G, N)).astype(np.uint16)
+    plain = synth.f32_to_bf16_bits(rng.uniform(0.0005, 0.005, (K // G, N)).astype(np.float32))
+    big = X / np.abs(X).max() * 2.0 ** 127
+    for what, sc, x in (("top", top, X * 2.0 ** -40), ("subnormal", sub, X * 2.0 ** 100), ("big rows", plain, big)):
+        Xb = synth.f32_to_bf16_bits(x.astype(np.float32))
+        packed = w2.prepack(dev(codes), dev(sc), G, 0)
+        Yo, y64, mag = oracle.matmul_a16(codes, sc, G, 0, Xb)
+        for variant in (w2.VARIANT_AUTO, w2.VARIANT_MIDM):
+            if what == "big rows" and variant == w2.VARIANT_AUTO:
+                continue                                     # (the decode kernel's zero-point form sums 130 x)
+            Y = w2.matmul_a16(packed, K, N, G, dev(Xb).view(torch.bfloat16), variant=variant)
+            check_y(bf16_bits(Y), Yo, y64, mag, f"{what} M={M} K={K} G={G} variant={variant}")
+
+
 @pytest.mark.parametrize("M", [1, 16, 17, 64, 65, 130])
 def test_a16_auto_dispatch(w2, M):
     run_a16_case(w2, M, 1024, 528, 128, 0, w2.VARIANT_AUTO, seed=M)
