@@ -76,8 +76,8 @@ __device__ __forceinline__ FoldLut fold_lut(uint32_t s)      // s: bf16 bit patt
 {
     FoldLut l;
     const uint32_t neg = s ^ 0x8000u;
-    // -2 sw: exponent + 1; a zero (or denormal) scale keeps its exponent field: -0 stays -0
-    const uint32_t neg2 = (s & 0x7f80u) ? ((s + 0x0080u) ^ 0x8000u) : neg;
+    // -2 sw: exponent + 1, or of a subnormal scale (a zero: -0) the mantissa twice
+    const uint32_t neg2 = (s + min(s & 0x7fffu, 0x0080u)) ^ 0x8000u;
     l.lo = s << 16;                                          // [0, +sw]
     l.hi = neg2 | (neg << 16);                               // [-2 sw, -sw]
     return l;

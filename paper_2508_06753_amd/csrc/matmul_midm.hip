@@ -80,7 +80,8 @@ struct Lut { uint32_t lo4, hi4; };
 __device__ __forceinline__ Lut make_lut(uint32_t s)          // s: bf16 bit pattern of the group scale
 {
     const uint32_t neg = s ^ 0x8000u;
-    const uint32_t neg2 = (s & 0x7f80u) ? ((s + 0x0080u) ^ 0x8000u) : neg;   // a zero scale stays (minus) zero
+    // -2 sw: exponent + 1, or of a subnormal scale (a zero: -0) the mantissa twice
+    const uint32_t neg2 = (s + min(s & 0x7fffu, 0x0080u)) ^ 0x8000u;
     const uint32_t a = s << 16;
     const uint32_t b = neg2 | (neg << 16);
     Lut l;

@@ -1043,6 +1043,23 @@ def test_a16_any_finite_scale_up_to_16_rows(w2, M, K, G):
             check_y(bf16_bits(Y), Yo, y64, mag, f"{what} M={M} K={K} G={G} variant={variant}")
 
 
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("M", [4, 17, 48, 64, 130, 300])
+def test_a16_folded_subnormal_scales(w2, M, G):
+    # every subnormal scale, either sign and zero among them, folded into the weights: -2 sw doubles the mantissa, up
+    # to the smallest normal numbers
+    K, N = 1024, 272
+    codes, _, X = synth.make_problem(M, K, N, G, 0, seed=M + G)
+    rng = np.random.default_rng(M + G)
+    sc = (rng.integers(0, 0x82, (K // G, N)) + 0x8000 * rng.integers(0, 2, (K // G, N))).astype(np.uint16)
+    Xb = synth.f32_to_bf16_bits((X * 2.0 ** 100).astype(np.float32))
+    packed = w2.prepack(dev(codes), dev(sc), G, 0)
+    Yo, y64, mag = oracle.matmul_a16(codes, sc, G, 0, Xb)
+    for variant in (w2.VARIANT_AUTO, w2.VARIANT_SCALED16):
+        Y = w2.matmul_a16(packed, K, N, G, dev(Xb).view(torch.bfloat16), variant=variant)
+        check_y(bf16_bits(Y), Yo, y64, mag, f"subnormal scales M={M} G={G} variant={variant}")
+
+
 @pytest.mark.parametrize("M", [1, 16, 17, 64, 65, 130])
 def test_a16_auto_dispatch(w2, M):
     run_a16_case(w2, M, 1024, 528, 128, 0, w2.VARIANT_AUTO, seed=M)
