@@ -34,6 +34,7 @@
 // of vector and matrix instructions and a start of K that differs per workgroup were measured and gave nothing.
 #include <hip/hip_runtime.h>
 
+#include "midm_plan.h"
 #include "w2_small_common.h"
 
 #if defined(__HIP_DEVICE_COMPILE__) && defined(__FAST_MATH__)
@@ -48,8 +49,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int CHUNK_BYTES = 128;                             // bytes of a row in one staged chunk
 
 struct Args {                                                // what is needed after the first loads
     const float* sx;
@@ -110,18 +109,7 @@ __device__ __forceinline__ v4f mfma_bf16(const v4i& a, const v4i& b, const v4f& 
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-constexpr int stage_bytes(int rt, int sh) { return rt * 16 * CHUNK_BYTES * (sh > 1 ? 2 : 1); }     // of one K range
-constexpr int red_bytes(int rt, int cj) { return rt * 16 * (cj * 16 + 4) * 4; }                     // of one wave
-// bytes of local memory of one K range (sh waves): its staged chunks, later its waves' partial results
-constexpr int range_lds(int rt, int cj, int sh)
-{
-    return stage_bytes(rt, sh) > sh * red_bytes(rt, cj) ? stage_bytes(rt, sh) : sh * red_bytes(rt, cj);
-}
-
 // XT 0: int8 rows (w2a8), 1: bf16 rows (w2a16)
-// most waves of a workgroup: 16 where a wave's registers allow it (very deep and narrow projections), else 8
-constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
-
 // EX (int8 rows): every group's int32 sum is converted exactly before it is scaled; see the dequant below
 template <int XT, int G, int RT, int CJ, int SH, bool EX, bool DBG>
 __global__ void __launch_bounds__(64 * max_waves(RT, CJ), max_waves(RT, CJ) / 4)
@@ -454,82 +442,6 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
             put(row, (int64_t)(wcb0 / 2 + (c >> 2)) * TILE_N + (c & 3) * 4, v);
         }
     }
-}
-
-// Launch shape: row tiles and column blocks per wave, K ranges per workgroup, waves that share a range.
-struct Plan { int rt, cj, ks, sh; };
-
-// Registers per lane of each instantiation (G = 128; G = 64 is within one step), [rt - 1][cj: 1, 2, 4]: they limit the
-// workgroups that a CU holds at a time.
-constexpr int REGS[2][4][3] = {{{80, 96, 120}, {112, 136, 176}, {128, 160, 224}, {152, 216, 248}},
-                               {{80, 96, 128}, {120, 136, 176}, {136, 168, 208}, {128, 176, 248}}};
-
-// Every candidate shape is priced with a linear model and the cheapest wins.  The terms are what the busiest CU has to
-// do (nb workgroups, in rounds of as many as it holds at a time), the coefficients (us) a least-squares fit to 4400
-// graph-timed launches: 20 projection shapes from 2048 x 2048 and 28672 x 1024 to 8192 x 57344, 4 to 192 rows.  Its
-// choices are on average 3.6 % (int8 rows) and 0.9 % (bf16 rows) slower than the fastest shape measured.
-static double price(int xt, const Plan& p, int64_t M, int64_t n_cb, int64_t n_kt)
-{
-    constexpr double C[2][13] = {
-        {1.525, 0.1987, 0.6254, 1.419, 1.127, 0.3743, 0.8993, 0.4517, 0.3403, 0.6996, 0.6068, 0.7275, 0.3929},
-        {1.677, 1.494, 0.3030, 3.895, 0.9297, 0.9087, 0.7657, 0.0, 0.5634, 0.4702, 0.9276, 1.174, 0.1319}};
-    const double* c = C[xt];
-    const int64_t bands = (M + 16 * p.rt - 1) / (16 * p.rt);
-    const int64_t wgs = (n_cb + p.cj * p.sh - 1) / (p.cj * p.sh) * bands;
-    const int waves = p.ks * p.sh;
-    const int lds = p.ks * range_lds(p.rt, p.cj, p.sh) + p.rt * 64;
-    int resident = 160 * 1024 / lds;
-    resident = max(1, min(resident, 4 * (512 / REGS[xt][p.rt - 1][p.cj >> 1]) / waves));
-    const int64_t nb = (wgs + 255) / 256, rounds = (nb + resident - 1) / resident;
-    const int64_t T = (n_kt + p.ks - 1) / p.ks;              // tiles of a wave's run
-    return c[0]
-         + c[1] * 0.01 * (nb * waves * T * p.cj)             // up-converts
-         + c[2] * 0.01 * (nb * waves * T * p.cj * p.rt)      // matrix instructions and dequant
-         + c[3] * 0.01 * (nb * p.ks * T * p.rt)              // activations through the L1
-         + c[4] * 1e-4 * (n_cb * n_kt)                       // the weight stream
-         + c[5] * 1e-4 * (n_cb * n_kt * bands)               // ... once per band out of L2
-         + c[6] * 0.01 * (nb * waves * p.rt * p.cj)          // reduce and store
-         + c[7] * 0.1 * (rounds * T)                         // latency per tile,
-         + c[8] * 0.1 * (rounds * T * p.rt * p.cj)           // multiply,
-         + c[9] * rounds                                     // start
-         + c[10] * 0.1 * (rounds * p.rt * p.cj)              // and end of a wave
-         + c[11] * 0.1 * T
-         + c[12] * 1e-3 * wgs;                               // workgroups to launch
-}
-
-// Row tiles (16 rows x 256 k, 4 KB of int8) that all workgroups together read.  With two column blocks per wave every 32
-// columns read all rows, and on a deep K that stream out of the L2s, about 50 bytes a nanosecond and CU, is what the launch
-// waits for; the linear model has no such limit.  Above 172 MB shapes of two column blocks are left out, which leaves
-// four, half the stream (28672 x 8192 at M = 32 / 48 / 144 23.2 / 29.5 / 66.8 -> 21.3 / 25.2 / 53.5 us, 17408 x 7168 at
-// M = 48 18.3 -> 16.0).  The line: 17408 x 6144 at M = 48, 160 MB, takes 14.3 with two and 14.8 with four; with groups of
-// 64 four also lose 3 to 6 % where the last row tile holds one row (28672 x 8192 at M = 33 26.8 -> 27.7).
-static int64_t row_tiles_read(const Plan& p, int64_t M, int64_t n_cb, int64_t n_kt)
-{
-    return (n_cb + p.cj * p.sh - 1) / (p.cj * p.sh) * ((M + 16 * p.rt - 1) / (16 * p.rt)) * p.rt * n_kt;
-}
-constexpr int64_t ROW_TILES_FROM_L2 = 42000;                 // 172 MB
-
-static Plan plan(int xt, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, const w2_tuning_t& tune)
-{
-    Plan best = {1, 2, 1, 1};
-    double best_price = 1e30;
-    const int tiles = (int)min((M + 15) / 16, (int64_t)4);
-    auto consider = [&](int rt, int cj, int ks, int sh) {
-        if (gated && cj * sh < 2) return;                                    // a workgroup pairs gate and up blocks
-        if (tune.midm_cbw && cj * sh != (xt == 1 ? min(tune.midm_cbw, 4) : tune.midm_cbw)) return;
-        const Plan p = {rt, cj, (int)min((int64_t)ks, n_kt), sh};
-        if (xt == 0 && cj == 2 && sh == 1 && !tune.midm_cbw && row_tiles_read(p, M, n_cb, n_kt) > ROW_TILES_FROM_L2) return;
-        const double t = price(xt, p, M, n_cb, n_kt);
-        if (t < best_price) { best = p; best_price = t; }
-    };
-    for (int rt = 1; rt <= tiles; ++rt)
-        for (int cj = rt == 1 ? 1 : 2; cj <= 4; cj *= 2) {
-            if (max_waves(rt, cj) == 16) consider(rt, cj, 16, 1);
-            consider(rt, cj, 8, 1);
-            consider(rt, cj, 4, 1);
-            if (xt == 0) consider(rt, cj, 2, 2);
-        }
-    return best;
 }
 
 // Int8 rows: up to 32 rows the decode kernel takes every group's sum exactly, and so does this kernel, whichever of the

@@ -352,12 +352,11 @@ def test_midm_k_ranges_and_row_tiles(w2, M, K, N, G):
         check_epilogue(bf16_bits(Y), y64, mag, bias, act, f"mid-M epilogue {act} M={M} K={K} N={N} G={G}")
 
 
-@pytest.mark.parametrize("N", [1312, 1344])
-@pytest.mark.parametrize("M", [241, 256])
+@pytest.mark.parametrize("M,N", [(241, 672), (241, 704), (256, 640), (256, 672)])
 def test_midm_row_stream_limit(w2, M, N):
-    # 64 k-tiles x 16 row tiles x 41 / 42 pairs of column blocks: just below and just above the 42000 row tiles from
-    # which four column blocks per wave are taken; a last row tile of one row, a last column group with missing blocks
-    run_a8_case(w2, M, 16384, N, 128, 1, w2.VARIANT_MIDM, seed=M + N)
+    # just below and just above the 172 MB of rows (241 x 32768 x 21 / 22 pairs of column blocks) from which four column
+    # blocks per wave are taken (test_midm_plan.py holds the choice); a last row tile of one row
+    run_a8_case(w2, M, 32768, N, 128, 1, w2.VARIANT_MIDM, seed=M + N)
 
 
 def test_a8_midm_long_k_and_limits(w2):
