@@ -121,7 +121,7 @@ typedef struct {
     int tiled_kw;         /* w2a8 TILED, 128-column workgroups: K ranges inside a workgroup: 1, 2 or 4 */
     int tiled_wd;         /* w2a8 TILED, 64-row tiles: weight stages in flight per wave: 2 or 8 */
     int tiled_group_m;    /* ... row tiles per band of the workgroup order: 1..1024 */
-    int splitk;           /* tiled kernels: 1 = never split K, n = 2..16: n parts if the workspace holds them */
+    int splitk;           /* tiled kernels, MIDM: 1 = never split K, n = 2..16: n parts if the workspace holds them */
     int splitk_min_tiles; /* ... planner: fewest 256-k tiles per part, 1..1024 */
     int stream_unroll;    /* w2_debug_stream_read: 1 KiB chunks in flight per wave: 4, 8 or 16 */
     int stream_blocks;    /* ... most workgroups launched: 1..65536 */
@@ -187,7 +187,7 @@ W2_API int w2_quantize_rows(const void* X, w2_dtype_t x_dtype, int64_t M, int64_
  * Y       dev, bf16 bit patterns [M][N], row stride ldy
  * workspace  optional (NULL / 0: none), dev, 16-byte aligned, contents
  *            undefined before and after: on shapes with few output tiles
- *            and a deep K (the tiled kernels) K is split across workgroups
+ *            and a deep K (the tiled and mid-M kernels) K is split across workgroups
  *            (Sec. II-D, K-splitting for the smaller GEMM shapes) if there
  *            is room for the fp32 partial results (w2_workspace_size; less
  *            room = fewer parts or none, same result contract).  A second
@@ -308,9 +308,9 @@ W2_API int w2_matmul_a16_epi(const void* packed, int64_t K, int64_t N, int G, co
  * split-K part only and accepts the same buffer): room for the int8 rows and
  * their scales, rounded up to 256 bytes (0 where one launch covers the
  * quantisation: one or two rows of up to 64 KiB as fp32), plus, where a
- * tiled kernel would split K (and for 4 <= M <= 128 on K >= 13568, where
- * nothing uses it any more), 2..16 fp32 copies of the M x N output.  a16 = 1
- * (w2_matmul_a16): the split-K part alone.  0 means no workspace is used. */
+ * tiled kernel would split K, and for the mid-M kernel for 4 <= M <= 128 on
+ * K >= 13568, 2..16 fp32 copies of the M x N output.  a16 = 1 (w2_matmul_a16):
+ * the split-K part alone (mid-M: from M = 3 on).  0 means no workspace is used. */
 W2_API int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* bytes);
 
 /* ------------------------------------------------------------------------

@@ -5,8 +5,10 @@
 // tiles per wave on, on the weights q and with a dequant per 64 k below.
 //
 // A wave owns RT row tiles x CJ column blocks x a contiguous run of k tiles; the waves of a workgroup split K (Sec.
-// II-D, K-splitting for small shapes) and their partial results meet in local memory once, in a fixed order.  No
-// second launch, no workspace.
+// II-D, K-splitting for small shapes) and their partial results meet in local memory once, in a fixed order.  Where the
+// column blocks are too few for the chip and K is deep, K is also split across workgroups, whose fp32 results go to the
+// caller's workspace and are added by a second launch (28672 x 1024, 16 bf16 rows 13.6 -> 9.8 us, 28672 x 2048 18.4 ->
+// 12.1; 28672 x 5120 at M = 64 33 -> 28).
 //
 // Why this shape.  What such a problem moves is the activations: every workgroup reads its rows over the whole K, 64
 // bytes per clock and CU through the vector L1 whichever way they go.  With K split over the waves nothing that a wave
@@ -54,6 +56,7 @@ struct Args {                                                // what is needed a
     const float* sx;
     uint16_t* Y;
     int32_t* acc_out;
+    float* part;                                             // K split across workgroups too: [blockIdx.z][M][N] fp32
     int64_t N, ldy;
     Epilogue epi;
 };
@@ -111,11 +114,15 @@ __device__ __forceinline__ v4f mfma_bf16(const v4i& a, const v4i& b, const v4f& 
 
 // XT 0: int8 rows (w2a8), 1: bf16 rows (w2a16)
 // EX (int8 rows): every group's int32 sum is converted exactly before it is scaled; see the dequant below
-template <int XT, int G, int RT, int CJ, int SH, bool EX, bool DBG>
+// MODE: the product, a part of it (K split across workgroups), or
+// the test-only export of the int32 group sums
+constexpr int WHOLE = 0, PART = 1, GROUP_SUMS = 2;
+template <int XT, int G, int RT, int CJ, int SH, bool EX, int MODE>
 __global__ void __launch_bounds__(64 * max_waves(RT, CJ), max_waves(RT, CJ) / 4)
 midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const char* __restrict__ scales, uint32_t stride, int M,
             int n_cb, int n_kt, int t_lo, int t_rem, Args a)
 {
+    constexpr bool DBG = MODE == GROUP_SUMS;
     constexpr int EB = XT == 0 ? 1 : 2;                      // bytes per activation
     constexpr int CH = TILE_K * EB / CHUNK_BYTES;            // chunks per tile: 2 or 4
     constexpr int GPT = TILE_K / G;
@@ -132,8 +139,11 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
     const int rows = min(RT * 16, M - m0);
     const int cg = wave % SH, kr = wave / SH;
     const int cb0 = (blockIdx.x * SH + cg) * CJ;
-    const int t0 = kr * t_lo + min(kr, t_rem);
-    const int T = t_lo + (kr < t_rem ? 1 : 0);
+    // of the whole K (the dimensions of the workgroup come out of memory, and a 13th parameter would too: 0.2 us ahead of
+    // the first loads, which only the parts of a deep K pay)
+    const int range = MODE == PART ? blockIdx.z * ((blockDim.x >> 6) / SH) + kr : kr;
+    const int t0 = range * t_lo + min(range, t_rem);
+    const int T = t_lo + (range < t_rem ? 1 : 0);
     // waves that share chunks meet at barriers: the same count for all (past its run a wave reads zeros)
     const int T_all = SH > 1 ? t_lo + (t_rem > 0 ? 1 : 0) : T;
     const int nch = T * CH;
@@ -415,6 +425,15 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
     auto put = [&](int row, int64_t n, const v4f& v) {
         *reinterpret_cast<uint2*>(a.Y + (int64_t)(m0 + row) * a.ldy + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
     };
+    if constexpr (MODE == PART) {                            // the epilogue belongs to the launch that adds the parts
+        float* dst = a.part + ((int64_t)blockIdx.z * M + m0) * a.N;
+        for (int i = threadIdx.x; i < rows * WC * 4; i += blockDim.x) {
+            const int row = i / (WC * 4), col = (i % (WC * 4)) * 4;
+            const int64_t n = (int64_t)wcb0 * TILE_N + col;
+            if (n < a.N) *reinterpret_cast<v4f*>(dst + row * a.N + n) = sum4(row, col);
+        }
+        return;
+    }
     if (a.epi.act != ACT_SILU_MUL) {
         for (int i = threadIdx.x; i < rows * WC * 4; i += blockDim.x) {
             const int row = i / (WC * 4), col = (i % (WC * 4)) * 4;
@@ -449,16 +468,23 @@ midm_kernel(const char* __restrict__ X, const char* __restrict__ codes, const ch
 // 5.10 -> 5.13 us, 3584 x 18944 with groups of 64 7.9 -> 8.5 at worst); above, the prefill kernels' one-fma form.
 constexpr int64_t EXACT_ROWS = 32;
 
-template <int XT, int G, int RT, int CJ, int SH, bool EX, bool DBG>
+template <int XT, int G, int RT, int CJ, int SH, bool EX, int MODE>
 static int launch_t(const Head& h, const Args& a, const Plan& p, hipStream_t stream)
 {
+    if constexpr (MODE == WHOLE) {
+        if (p.sp > 1) return launch_t<XT, G, RT, CJ, SH, EX, PART>(h, a, p, stream);
+    }
     const size_t lds = (size_t)p.ks * range_lds(RT, CJ, SH) + RT * 16 * sizeof(float);
-    auto kern = midm_kernel<XT, G, RT, CJ, SH, EX, DBG>;
+    auto kern = midm_kernel<XT, G, RT, CJ, SH, EX, MODE>;
     if (int rc = ensure_dynamic_lds((const void*)kern, lds, "w2_matmul[midm]")) return rc;
-    const dim3 grid((unsigned)((h.n_cb + CJ * SH - 1) / (CJ * SH)), (unsigned)((h.M + RT * 16 - 1) / (RT * 16))), block(64 * p.ks * SH);
+    const dim3 grid((unsigned)((h.n_cb + CJ * SH - 1) / (CJ * SH)), (unsigned)((h.M + RT * 16 - 1) / (RT * 16)), (unsigned)p.sp),
+               block(64 * p.ks * SH);
+    const int ranges = p.ks * p.sp;
     hipLaunchKernelGGL(kern, grid, block, lds, stream, h.X, h.codes, h.scales, h.stride, h.M, h.n_cb, h.n_kt,
-                       h.n_kt / p.ks, h.n_kt % p.ks, a);
-    return check_launch("w2_matmul[midm]");
+                       h.n_kt / ranges, h.n_kt % ranges, a);
+    const int rc = check_launch("w2_matmul[midm]");
+    if (rc || MODE != PART) return rc;
+    return launch_splitk_reduce(a.part, p.sp, h.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
 template <int XT, int G, int RT, int CJ>
@@ -467,11 +493,11 @@ static int launch_sh(const Head& h, const Args& a, const Plan& p, hipStream_t st
     if constexpr (XT == 0) {
         if constexpr (RT <= 2) {
             if (h.M <= EXACT_ROWS)
-                return p.sh == 2 ? launch_t<XT, G, RT, CJ, 2, true, false>(h, a, p, stream) : launch_t<XT, G, RT, CJ, 1, true, false>(h, a, p, stream);
+                return p.sh == 2 ? launch_t<XT, G, RT, CJ, 2, true, WHOLE>(h, a, p, stream) : launch_t<XT, G, RT, CJ, 1, true, WHOLE>(h, a, p, stream);
         }
-        if (p.sh == 2) return launch_t<XT, G, RT, CJ, 2, false, false>(h, a, p, stream);
+        if (p.sh == 2) return launch_t<XT, G, RT, CJ, 2, false, WHOLE>(h, a, p, stream);
     }
-    return launch_t<XT, G, RT, CJ, 1, false, false>(h, a, p, stream);
+    return launch_t<XT, G, RT, CJ, 1, false, WHOLE>(h, a, p, stream);
 }
 
 template <int XT, int G>
@@ -479,12 +505,12 @@ static int launch_g(const Head& h, const Args& a, const Plan& p, hipStream_t str
 {
     if (a.acc_out) {                                         // the test-only export of the int32 accumulators: one width
         if constexpr (XT == 0) {
-            const Plan d = {p.rt, 2, (int)min((int64_t)8, (int64_t)h.n_kt), 1};
+            const Plan d = {p.rt, 2, (int)min((int64_t)8, (int64_t)h.n_kt), 1, 1};
             switch (p.rt) {
-            case 1: return launch_t<0, G, 1, 2, 1, true, true>(h, a, d, stream);
-            case 2: return launch_t<0, G, 2, 2, 1, true, true>(h, a, d, stream);
-            case 3: return launch_t<0, G, 3, 2, 1, false, true>(h, a, d, stream);
-            default: return launch_t<0, G, 4, 2, 1, false, true>(h, a, d, stream);
+            case 1: return launch_t<0, G, 1, 2, 1, true, GROUP_SUMS>(h, a, d, stream);
+            case 2: return launch_t<0, G, 2, 2, 1, true, GROUP_SUMS>(h, a, d, stream);
+            case 3: return launch_t<0, G, 3, 2, 1, false, GROUP_SUMS>(h, a, d, stream);
+            default: return launch_t<0, G, 4, 2, 1, false, GROUP_SUMS>(h, a, d, stream);
             }
         }
     }
@@ -508,8 +534,8 @@ constexpr int64_t MIDM_MAX_ROWS = 256;                       // beyond that the 
 bool a8_midm_supports(const A8Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
 bool a16_midm_supports(const A16Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
 
-// What w2_workspace_size adds for this range on a deep K (K > 13312): fp32 copies of the output, 2..16 of them.  This
-// kernel needs none; the size is part of what callers have been told and keeps its value.
+// What w2_workspace_size adds for this range on a deep K (K > 13312): fp32 copies of the output, 2..16 of them, as many
+// parts as about 64 workgroups across the columns need for one workgroup per CU.
 size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt)
 {
     const int64_t chunks = (n_kt + 3) / 4;                   // of 1024 k
@@ -523,16 +549,18 @@ size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt)
 int launch_a8_midm(const A8Args& a, hipStream_t stream)
 {
     const midm::Head h = {(const char*)a.xq, (const char*)a.codes, (const char*)a.scales, (uint32_t)a.K, (int)a.M, (int)a.n_cb, (int)a.n_kt};
-    const midm::Args k = {a.sx, a.Y, a.acc_out, a.N, a.ldy, a.epi};
-    const midm::Plan p = midm::plan(0, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, a.tune);
+    const midm::Args k = {a.sx, a.Y, a.acc_out, a.acc_out ? nullptr : a.part, a.N, a.ldy, a.epi};
+    const int64_t cap = k.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
+    const midm::Plan p = midm::plan(0, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, cap, a.tune);
     return a.G == 128 ? midm::launch_g<0, 128>(h, k, p, stream) : midm::launch_g<0, 64>(h, k, p, stream);
 }
 
 int launch_a16_midm(const A16Args& a, hipStream_t stream)
 {
     const midm::Head h = {(const char*)a.X, (const char*)a.codes, (const char*)a.scales, (uint32_t)(a.ldx * 2), (int)a.M, (int)a.n_cb, (int)a.n_kt};
-    const midm::Args k = {nullptr, a.Y, nullptr, a.N, a.ldy, a.epi};
-    const midm::Plan p = midm::plan(1, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, a.tune);
+    const midm::Args k = {nullptr, a.Y, nullptr, a.part, a.N, a.ldy, a.epi};
+    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
+    const midm::Plan p = midm::plan(1, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, cap, a.tune);
     return a.G == 128 ? midm::launch_g<1, 128>(h, k, p, stream) : midm::launch_g<1, 64>(h, k, p, stream);
 }
 

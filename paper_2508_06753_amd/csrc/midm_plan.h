@@ -23,8 +23,9 @@ constexpr int range_lds(int rt, int cj, int sh)
 // most waves of a workgroup: 16 where a wave's registers allow it (very deep and narrow projections), else 8
 constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
 
-// Launch shape: row tiles and column blocks per wave, K ranges per workgroup, waves that share a range.
-struct Plan { int rt, cj, ks, sh; };
+// Launch shape: row tiles and column blocks per wave, K ranges per workgroup, waves that share a range, workgroups that
+// K is split across (parts).
+struct Plan { int rt, cj, ks, sh, sp; };
 
 // Waves of each instantiation that a SIMD's registers hold (int8, bf16 rows; [rt - 1][cj: 1, 2, 4]).
 constexpr int SIMD_WAVES[2][4][3] = {{{6, 5, 4}, {4, 3, 2}, {4, 3, 2}, {3, 2, 2}},
@@ -69,21 +70,27 @@ constexpr double COEF[2][13] = {
 // to 250 MB, and 27 to 30 % at worst.
 constexpr int64_t ROW_BYTES_FROM_L2 = 172000000;
 
-inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, const w2_tuning_t& tune)
+// K split across workgroups: a second launch adds the parts.  3 us and the parts' way to memory and back.
+constexpr double PARTS_US = 3.0, PARTS_US_PER_VALUE = 2e-6;
+
+// `cap`: fp32 copies of the output that the workspace holds.
+inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune)
 {
     const double* c = COEF[xt];
     const int M = (int)M64, n_cb = (int)n_cb64, n_kt = (int)n_kt64;
     const double tiles = (double)n_cb * n_kt;
+    const double part_us = PARTS_US_PER_VALUE * 16 * M * (double)n_cb;
     const int cbw = xt == 1 ? std::min(tune.midm_cbw, 4) : tune.midm_cbw;
-    Plan best = {1, 2, 1, 1};
+    const int forced = tune.splitk > 1 ? (int)std::min<int64_t>(std::min(tune.splitk, n_kt), cap) : 0;
+    Plan best = {1, 2, 1, 1, 1};
     double best_price = 1e30;
     // (this runs on every call of up to 256 rows: no division but by powers of two, where it can be had)
     auto price = [&](const Plan& p, int bands, int groups, int T, int resident) {
-        const int wgs = groups * bands, waves = p.ks * p.sh;
+        const int wgs = groups * bands * p.sp, waves = p.ks * p.sh;
         const int nb = (wgs + 255) >> 8;
         const int rounds = nb <= resident ? 1 : (nb + resident - 1) / resident;
         const int rc = p.rt * p.cj;
-        return c[0]
+        double t = c[0]
                  + (double)(nb * waves) * T * (c[1] * p.cj               // up-converts
                                                + c[2] * rc)             // matrix instructions and dequant
                  + c[3] * ((double)(nb * p.ks) * T * p.rt)               // activations through the L1
@@ -93,6 +100,8 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                  + rounds * (c[9] + c[10] * rc)                          // start and end of a wave
                  + c[11] * T
                  + c[12] * wgs;                                          // workgroups to launch
+        if (p.sp > 1) t = 1.04 * (t + PARTS_US + part_us * p.sp);      // (it has to win by more than the model errs)
+        return t;
     };
     const int row_tiles = std::min((M + 15) / 16, 4);
     for (int rt = 1; rt <= row_tiles; ++rt) {
@@ -104,14 +113,26 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 if (cbw && 1 << lw != cbw) continue;
                 const int groups = (n_cb + (1 << lw) - 1) >> lw;
                 if (xt == 0 && lw <= 1 && !cbw && (int64_t)groups * M * n_kt * 256 > ROW_BYTES_FROM_L2) continue;
-                auto offer = [&](int ks, int T, int resident) {
-                    const Plan p = {rt, cj, ks, sh};
-                    const double t = price(p, bands, groups, T, resident);
+                const int resident = RESIDENT.n[xt][rt - 1][cj >> 1][f];
+                auto offer = [&](int ks, int sp, int T, int res) {
+                    const Plan p = {rt, cj, ks, sh, sp};
+                    const double t = price(p, bands, groups, T, res);
                     if (t < best_price) { best = p; best_price = t; }
                 };
                 const int lk = 4 - f;                                    // FORMS[f][0] == 1 << lk
-                if (n_kt >= 1 << lk) offer(1 << lk, (n_kt + (1 << lk) - 1) >> lk, RESIDENT.n[xt][rt - 1][lj][f]);
-                else offer(n_kt, 1, resident_of(xt, rt, cj, n_kt, sh));
+                if (forced > 1) {
+                    const int ks = std::max(1, std::min(1 << lk, n_kt / forced));
+                    offer(ks, forced, (n_kt + ks * forced - 1) / (ks * forced), resident);
+                    continue;
+                }
+                if (n_kt >= 1 << lk) offer(1 << lk, 1, (n_kt + (1 << lk) - 1) >> lk, resident);
+                else offer(n_kt, 1, 1, resident_of(xt, rt, cj, n_kt, sh));
+                // Across workgroups only from K = 8192 on, for grids that leave half the chip idle, into as many parts as
+                // still run in one round: other numbers of parts were hardly ever faster by more than 3 %.
+                const int wgs = groups * bands;
+                if (cap < 2 || n_kt < 32 || wgs > 128 || lw == 0 || f == 0 || tune.splitk == 1) continue;
+                const int sp = (int)std::min<int64_t>(std::min(256 / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
+                if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);
             }
     }
     return best;

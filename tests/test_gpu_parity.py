@@ -785,26 +785,40 @@ def test_tiled_split_k(w2, M, K, N, G, splitk):
 
 @pytest.mark.parametrize("cbw,splitk", [(2, 2), (4, 3), (8, 2), (2, 5), (0, 0)])
 @pytest.mark.parametrize("G", [64, 128])
-@pytest.mark.parametrize("M,K,N", [(9, 2304, 272), (33, 5376, 48), (64, 3072, 1032), (100, 2048, 272), (16, 14336, 64)])
+@pytest.mark.parametrize("M,K,N", [(9, 2304, 272), (33, 5376, 48), (64, 3072, 1032), (100, 2048, 272), (16, 14336, 64), (16, 28672, 64)])
 def test_midm_split_k(w2, M, K, N, G, cbw, splitk):
-    # the mid-M kernel with K cut into ranges of whole 1024-k chunks across workgroups: every workgroup
-    # width, forced part counts (uneven ranges, more parts than chunks: clamped), a ragged last chunk that
-    # overlaps its predecessor (2304, 5376), two bands of rows, and the planner's own choice (deep K: splits)
+    # the mid-M kernel with K cut across workgroups as well, into ranges of whole k tiles: every workgroup width, forced
+    # part counts (uneven ranges: 9, 21 and 12 tiles over the waves of 2, 3 and 5 workgroups), two bands of rows, the
+    # planner's own choice (0; bf16 rows split on 28672 x 64), which parts of the workspace are written, and the epilogues, which
+    # belong to the second launch then
     tune = {"midm_cbw": cbw, "splitk": splitk}
     codes, scales, X = synth.make_problem(M, K, N, G, 0, M + K + N + G + cbw)
     packed = w2.prepack(dev(codes), dev(scales), G, 0)
     ws = torch.empty(16 * M * N * 4, dtype=torch.uint8, device="cuda")
     xq, sx, _ = w2.quantize_rows(dev(X), G)
+    ws.fill_(0xA5)
     Y = w2.matmul_a8(packed, K, N, G, xq, sx, variant=w2.VARIANT_MIDM, workspace=ws, tune=tune)
+    touched = (ws.view(torch.int32) != -0x5A5A5A5B).view(16, M * N).cpu().numpy()
+    if splitk:
+        parts = min(splitk, K // 256)
+        assert touched[:parts].any(axis=1).all() and not touched[parts:].any()
     Y2 = w2.matmul_a8(packed, K, N, G, xq, sx, variant=w2.VARIANT_MIDM, workspace=ws, tune=tune)
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16)), "not deterministic"
     oq, osx, _ = oracle.quantize_rows(X, G)
     assert np.array_equal(xq.cpu().numpy(), oq)
     Yo, y64 = oracle.matmul_a8(codes, scales, G, 0, oq, osx)
     mag = oracle.a8_term_magnitude(codes, scales, G, 0, oq, osx)
+    if N % 32 == 0:
+        bias = synth.f32_to_bf16_bits(np.random.default_rng(M).standard_normal(N).astype(np.float32))
+        Yg = w2.matmul_a8_epi(packed, K, N, G, xq, sx, bias=dev(bias), act=w2.ACT_SILU_MUL, variant=w2.VARIANT_MIDM,
+                              workspace=ws, tune=tune)
+        check_epilogue(bf16_bits(Yg), y64, mag, bias, 2, f"a8 mid-M split-K {splitk} gated M={M} K={K} N={N} G={G}")
     check_y(bf16_bits(Y), Yo, y64, mag, f"a8 mid-M split-K {splitk} cbw={cbw} M={M} K={K} N={N} G={G}")
     Xb = synth.f32_to_bf16_bits(X)
+    ws.fill_(0xA5)
     Y16 = w2.matmul_a16(packed, K, N, G, dev(Xb).view(torch.bfloat16), variant=w2.VARIANT_MIDM, workspace=ws, tune=tune)
+    touched = (ws.view(torch.int32) != -0x5A5A5A5B).view(16, M * N).cpu().numpy()
+    assert touched[1].any() == (splitk > 1 or K == 28672)
     Yo, y64, mag = oracle.matmul_a16(codes, scales, G, 0, Xb)
     check_y(bf16_bits(Y16), Yo, y64, mag, f"a16 mid-M split-K {splitk} cbw={cbw} M={M} K={K} N={N} G={G}")
     if splitk >= 2:

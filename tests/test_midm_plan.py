@@ -11,13 +11,14 @@ PROGRAM = r"""
 #include <stdio.h>
 int main()
 {
-    int xt, gated, cbw;
-    long long M, n_cb, n_kt;
-    while (scanf("%%d %%lld %%lld %%lld %%d %%d", &xt, &M, &n_cb, &n_kt, &gated, &cbw) == 6) {
+    int xt, gated, cbw, splitk;
+    long long M, n_cb, n_kt, cap;
+    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d", &xt, &M, &n_cb, &n_kt, &gated, &cbw, &cap, &splitk) == 8) {
         w2_tuning_t tune = {};
         tune.midm_cbw = cbw;
-        const w2::midm::Plan p = w2::midm::plan(xt, M, n_cb, n_kt, gated != 0, tune);
-        printf("%%d %%d %%d %%d\n", p.rt, p.cj, p.ks, p.sh);
+        tune.splitk = splitk;
+        const w2::midm::Plan p = w2::midm::plan(xt, M, n_cb, n_kt, gated != 0, cap, tune);
+        printf("%%d %%d %%d %%d %%d\n", p.rt, p.cj, p.ks, p.sh, p.sp);
     }
 }
 """
@@ -32,8 +33,10 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
 
     def ask(problems):
-        """problems: (rows int8 0 / bf16 1, M, K, N, gated, midm_cbw) -> (rt, cj, ks, sh) each"""
-        text = "".join(f"{xt} {M} {(N + 15) // 16} {K // 256} {int(g)} {cbw}\n" for xt, M, K, N, g, cbw in problems)
+        """problems: (rows int8 0 / bf16 1, M, K, N, gated, midm_cbw[, copies of the output that fit, splitk])
+        -> (rt, cj, ks, sh, sp) each"""
+        text = "".join("{} {} {} {} {} {} {} {}\n".format(xt, M, (N + 15) // 16, K // 256, g, cbw, *(more or (0, 0)))
+                       for xt, M, K, N, g, cbw, *more in problems)
         out = subprocess.run([str(d / "p")], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, l.split())) for l in out.splitlines()]
 
@@ -45,11 +48,13 @@ ROWS = (1, 5, 16, 17, 33, 64, 65, 99, 173, 241, 256)
 
 
 def test_shapes_fit_the_kernel(plans):
-    problems = [(xt, M, K, N, g, cbw) for xt in (0, 1) for K, N in SHAPES for M in ROWS for g in (0, 1) if not (g and N % 32)
-                for cbw in (0, 2, 4, 8)]
-    for (xt, M, K, N, g, cbw), (rt, cj, ks, sh) in zip(problems, plans(problems)):
+    problems = [(xt, M, K, N, g, cbw, cap, splitk) for xt in (0, 1) for K, N in SHAPES for M in ROWS for g in (0, 1)
+                if not (g and N % 32) for cbw in (0, 2, 4, 8) for cap, splitk in ((0, 0), (1, 3), (2, 3), (16, 0), (16, 1), (16, 16))]
+    for (xt, M, K, N, g, cbw, cap, splitk), (rt, cj, ks, sh, sp) in zip(problems, plans(problems)):
         assert 1 <= rt <= min((M + 15) // 16, 4) and cj in ((1, 2, 4) if rt == 1 else (2, 4))
-        assert 1 <= ks <= K // 256 and sh in (1, 2) and (sh == 1 or xt == 0)
+        assert ks >= 1 and 1 <= sp <= max(1, min(cap, 16)) and ks * sp <= K // 256     # every range holds a tile
+        assert splitk == 0 or sp == max(1, min(splitk, cap, K // 256))
+        assert sh in (1, 2) and (sh == 1 or xt == 0)
         assert ks * sh <= (16 if rt == 1 and cj <= 2 else 8)
         assert not g or cj * sh >= 2
         assert not cbw or cj * sh == (cbw if xt == 0 else min(cbw, 4))
@@ -72,3 +77,15 @@ def test_row_stream_limit(plans):
     # two column blocks are not replaced by one, which reads twice as much
     (p,) = plans([(0, 173, 23040, 1488, 0, 0)])
     assert streamed(173, 23040, 1488, p) < 110000000
+
+
+def test_k_across_workgroups(plans):
+    # only with room for two copies of the output, on a deep K, for a grid that leaves half the chip idle, in one round
+    problems = [(xt, M, K, N, 0, 0, cap, 0) for xt in (0, 1) for K, N in SHAPES for M in ROWS for cap in (0, 1, 2, 5, 16)]
+    split = 0
+    for (xt, M, K, N, _, _, cap, _), (rt, cj, ks, sh, sp) in zip(problems, plans(problems)):
+        if sp > 1:
+            split += 1
+            wgs = -(-((N + 15) // 16) // (cj * sh)) * -(-M // (16 * rt))
+            assert cap >= 2 and K >= 8192 and wgs * sp <= 256 and ks * sp <= K // 512
+    assert split > 50
