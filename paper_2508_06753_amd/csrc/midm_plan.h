@@ -70,8 +70,9 @@ constexpr double COEF[2][13] = {
 // to 250 MB, and 27 to 30 % at worst.
 constexpr int64_t ROW_BYTES_FROM_L2 = 172000000;
 
-// K split across workgroups: a second launch adds the parts.  3 us and the parts' way to memory and back.
-constexpr double PARTS_US = 3.0, PARTS_US_PER_VALUE = 2e-6;
+// K split across workgroups: a second launch adds the parts, which go to memory and back (us, and us per value of a part;
+// fitted on 36 shapes from 8192 x 1024 to 28672 x 10240, int8 and bf16 rows), and it has to win by more than the model errs.
+constexpr double PARTS_US[2] = {1.0, 2.0}, PARTS_US_PER_VALUE[2] = {3e-6, 2e-6}, PARTS_MARGIN = 1.04;
 
 // `cap`: fp32 copies of the output that the workspace holds.
 inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune)
@@ -79,7 +80,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
     const double* c = COEF[xt];
     const int M = (int)M64, n_cb = (int)n_cb64, n_kt = (int)n_kt64;
     const double tiles = (double)n_cb * n_kt;
-    const double part_us = PARTS_US_PER_VALUE * 16 * M * (double)n_cb;
+    const double part_us = PARTS_US_PER_VALUE[xt] * 16 * M * (double)n_cb;
     const int cbw = xt == 1 ? std::min(tune.midm_cbw, 4) : tune.midm_cbw;
     const int forced = tune.splitk > 1 ? (int)std::min<int64_t>(std::min(tune.splitk, n_kt), cap) : 0;
     Plan best = {1, 2, 1, 1, 1};
@@ -100,7 +101,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                  + rounds * (c[9] + c[10] * rc)                          // start and end of a wave
                  + c[11] * T
                  + c[12] * wgs;                                          // workgroups to launch
-        if (p.sp > 1) t = 1.04 * (t + PARTS_US + part_us * p.sp);      // (it has to win by more than the model errs)
+        if (p.sp > 1) t = PARTS_MARGIN * (t + PARTS_US[xt] + part_us * p.sp);
         return t;
     };
     const int row_tiles = std::min((M + 15) / 16, 4);
