@@ -789,7 +789,7 @@ def test_tiled_split_k(w2, M, K, N, G, splitk):
 def test_midm_split_k(w2, M, K, N, G, cbw, splitk):
     # the mid-M kernel with K cut across workgroups as well, into ranges of whole k tiles: every workgroup width, forced
     # part counts (uneven ranges: 9, 21 and 12 tiles over the waves of 2, 3 and 5 workgroups), two bands of rows, the
-    # planner's own choice (0; bf16 rows split on 28672 x 64), which parts of the workspace are written, and the epilogues, which
+    # planner's own choice (0; bf16 rows split on the deepest), which parts of the workspace are written, and the epilogues, which
     # belong to the second launch then
     tune = {"midm_cbw": cbw, "splitk": splitk}
     codes, scales, X = synth.make_problem(M, K, N, G, 0, M + K + N + G + cbw)
@@ -818,7 +818,7 @@ def test_midm_split_k(w2, M, K, N, G, cbw, splitk):
     ws.fill_(0xA5)
     Y16 = w2.matmul_a16(packed, K, N, G, dev(Xb).view(torch.bfloat16), variant=w2.VARIANT_MIDM, workspace=ws, tune=tune)
     touched = (ws.view(torch.int32) != -0x5A5A5A5B).view(16, M * N).cpu().numpy()
-    assert touched[1].any() == (splitk > 1 or K == 28672)
+    assert touched[1].any() == (splitk > 1 or K >= 14336)
     Yo, y64, mag = oracle.matmul_a16(codes, scales, G, 0, Xb)
     check_y(bf16_bits(Y16), Yo, y64, mag, f"a16 mid-M split-K {splitk} cbw={cbw} M={M} K={K} N={N} G={G}")
     if splitk >= 2:
