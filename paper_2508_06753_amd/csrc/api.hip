@@ -267,21 +267,36 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
         // form is at least as fast as dot4 from M = 1 on).  Then the mid-M kernel, then the tiled ones.
         // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
         // before against the mid-M kernel): at M = 9 in general (4096 x 6144 5.3 against 5.2 at M = 16; 4096 x 28672 at
-        // M = 8 / 9 9.2 / 10.1 against 9.6 / 9.7; 8192 x 10240 8.8 / 11.7 against 8.8 / 8.9); at M = 5 where the decode
-        // kernel has few workgroups and two pieces of a row per thread (5120 x 5120 5.5 against 4.6) or cannot hold
-        // the rows (17408 x 5120 12.7 against 9.7; 28672 x 8192 18.4 against 15.4); on 16384 columns and more with
-        // groups of 64 at 13 (5120 x 34816 at M = 12 / 16 15.2 / 21.4 against 16.1 / 17.2).
+        // M = 8 / 9 9.2 / 10.1 against 9.6 / 9.7; 8192 x 10240 8.8 / 11.7 against 8.8 / 8.9).  At M = 5 where the decode
+        // kernel has few workgroups and two pieces of a row per thread (decode / mid-M at M = 5 and 8, 192 to 512 column
+        // blocks: K = 4096 0.91 .. 1.05, but 1.20 on 320 blocks; K = 5120 1.08 .. 1.24, 6144 1.03 .. 1.20, 7168 0.91 .. 1.10,
+        // 8192 0.93 .. 1.01), on a deep K of few columns (17408 x 1024 1.19, x 2048 0.98), and below where it cannot hold the
+        // rows in one round of workgroups (17408 x 5120 1.35, x 4096 0.94).  At 13 on 16384 columns and more with groups of
+        // 64 (5120 x 34816 at M = 12 / 16 15.2 / 21.4 against 16.1 / 17.2).  At 17 where K near 8192 keeps its whole grid
+        // busy in one round, 768 to 1024 column blocks (K = 8192 at M = 9 .. 16 0.91 .. 0.97, 7168 1.00 .. 1.05).
         const int dot4_max = tn.dot4_max_m;
         const bool wide = a.n_cb >= 1024;
-        const int midm_from = wide ? (G == 128 ? 9 : 13) : a.n_kt > 64 || (a.n_kt > 16 && a.n_kt <= 32 && a.n_cb <= 448) ? 5 : 9;
+        const int midm_from = a.n_kt > 28 && a.n_kt <= 32 && a.n_cb >= 768 && a.n_cb <= 1024 ? 17
+                            : wide                                                           ? (G == 128 ? 9 : 13)
+                            : (a.n_kt > 64 && a.n_cb < 128) || (a.n_kt > 16 && a.n_kt <= 26 && a.n_cb <= 512) ? 5 : 9;
         const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
         // Upper end, against the tiled kernels with a workspace: they win earlier the more columns there are to fill
         // the chip with (2048 x 57344 at M = 48 / 64 16.6 / 17.4 us against 15.3 / 18.5; 4096 x 28672 at M = 96 / 128
-        // 24.3 / 25.2 against 20.4 / 24.9; 8192 x 10240 at M = 160 / 192 24.8 / 25.1 against 22.7 / 26.0; 5120 x 7168
-        // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7).
+        // 24.3 / 25.2 against 20.4 / 24.9; 8192 x 10240 at M = 160 / 192 24.8 / 25.1 against 24.3 / 26.0; 5120 x 7168
+        // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7; 28672 x 5120 at M = 240 50.2 against 54.5).
         const int midm_max = tn.midm_max_m ? tn.midm_max_m
-                           : a.n_cb >= 2560 ? 48 : a.n_cb >= 1536 ? 112 : a.n_cb > 448 ? 160 : 240;
-        const bool midm_ok = M >= midm_min && M <= midm_max && a8_midm_supports(a);
+                           : a.n_cb >= 2560 ? 48 : a.n_cb >= 1536 ? 112 : a.n_cb > 448 ? 160 : G == 128 && a.n_kt > 104 && a.n_cb > 256 ? 192 : 240;
+        // A little more than 512 (1024) column blocks, in groups of two (four), are a little more than one round of 256
+        // workgroups; on a very deep K the tiled kernels with K split across workgroups are then ahead where the rows fill
+        // their tiles: 49 to 64 rows up to 640 blocks from K = 17920 (tiled / mid-M at M = 64: 20480 0.91 .. 0.96, 24576
+        // 0.86 .. 0.90, 28672 0.92 .. 0.96; on 704 to 896 blocks 0.98 .. 1.29, at M = 48 0.95 .. 1.04), 33 to 64 up to 1280
+        // (M = 40 / 64: K = 16384 0.89 .. 0.98, 18432 1.02 .. 1.07, 22528 0.76 .. 0.89, 26624 0.72 .. 0.86), 113 to 128 from K = 25600 (28672 at M = 128 0.78 .. 0.87; 24576 1.00 .. 1.22).
+        const bool two_parts = a.part_bytes >= (size_t)(2 * M * N) * sizeof(float);
+        const bool full_tiles = two_parts && !tn.midm_max_m && G == 128 &&
+                                ((a.n_kt >= 70 && a.n_cb > 512 && a.n_cb <= 640 && M > 48 && M <= 64) ||
+                                 (a.n_kt >= 60 && a.n_cb > 1024 && a.n_cb <= 1280 && M > 32 && M <= 64) ||
+                                 (a.n_kt >= 100 && a.n_cb > 512 && a.n_cb < 1024 && M > 112 && M <= 128));
+        const bool midm_ok = M >= midm_min && M <= midm_max && !full_tiles && a8_midm_supports(a);
         // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
         // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
         const int64_t row_bytes = M * (K + 32);
@@ -290,7 +305,7 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
         const int64_t gemv_wgs = (a.n_cb + gcbw - 1) / gcbw;
         const bool one_round = row_bytes <= 72 * 1024 || gemv_wgs <= 256 || a.n_kt <= 32;
         const int gemv_max = tn.gemv_max_m ? tn.gemv_max_m : one_round ? midm_from - 1 : 4;
-        fallback = midm_ok || (!tn.midm_min_m && M >= 4 && M < midm_min) ? W2_VARIANT_MIDM
+        fallback = midm_ok || (!tn.midm_min_m && M >= 4 && M < midm_min && M <= midm_max) ? W2_VARIANT_MIDM
                  : a8_smallm_supports(a)                                 ? W2_VARIANT_SMALLM
                                                                          : W2_VARIANT_TILED;
         variant = M <= dot4_max && a8_dot4_supports(a) ? W2_VARIANT_DOT4
@@ -559,26 +574,42 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
         // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
         // before against the mid-M kernel): at M = 3 for rows too long for a workgroup (17408 x 5120 16.5 against
         // 13.2), at M = 5 where K passes 4096 (5120 x 5120 8.2 against 5.8, 14336 x 4096 10.7 against 8.8, 8192 x 10240
-        // 15.5 against 12.7), at 8 on wide projections of K = 5120 (5120 x 34816 at M = 6 / 8 19.1 / 24.3 against
-        // 20.4), and at 9 up to K = 4096 (4096 x 6144 at M = 8 / 9 5.9 / 7.1 against 5.7; 4096 x 28672 12.0 / 13.3
+        // 15.5 against 12.7) but for 768 to 1024 column blocks up to K = 8192, whose grid fills one round (decode / mid-M
+        // at M = 5 and 8 0.85 .. 0.98; K = 9216 1.41 .. 1.53), at 8 on wide projections of K = 5120 (5120 x 34816 at M =
+        // 6 / 8 19.1 / 24.3 against 20.4), and at 9 up to K = 4096 (4096 x 6144 at M = 8 / 9 5.9 / 7.1 against 5.7; 4096 x 28672 12.0 / 13.3
         // against 13.1), with groups of 64 and 16384 columns at 17 (at M = 16 / 24 13.9 / 22.0 against 14.7 / 17.6).
         const int midm_from = a.n_kt > 64                                  ? 3
+                            : a.n_kt > 20 && a.n_kt <= 32 && a.n_cb >= 768 && a.n_cb <= 1024 ? 9
                             : a.n_kt > 20 || (a.n_kt > 16 && a.n_cb < 640) ? 5
                             : a.n_kt > 16                                  ? 8
                             : G == 128 || a.n_cb < 1024                    ? 9 : 17;
         const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
-        // Upper end, against the tiled kernel with a workspace (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 /
-        // 114; 4096 x 28672 at M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 28672 x 8192 at M = 96 / 128 57.6 / 62.4
-        // against 56.9 / 68.0; 8192 x 10240 at M = 192 45.3 against 38.7; 4096 x 4096 at M = 256 22.9 against 12.3).
-        const int midm_max = tn.midm_max_m ? tn.midm_max_m
-                           : a.n_cb >= 2560 ? 64 : a.n_cb >= 1024 || a.n_cb * a.n_kt > 40000 ? 96
-                           : a.n_cb <= 448 && a.n_kt <= 56 ? 256 : 192;
+        // Upper end, against the tiled kernel of 128-row tiles (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096
+        // x 28672 at M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  With room for
+        // two parts of a split K that kernel wins earlier, by the number of tiles P of the matrix (its time / the mid-M
+        // kernel's): at M = 96 once P passes 40000 (25000 for 641 to 768 column blocks, 50000 up to 1023, 60000 above; never up
+        // to 512): 14336 x 10240, P = 35840, 1.01; 17408 x 10240 0.96; 24576 x 10240 0.82; 8192 x 11264, P = 22528, 1.03; 11008
+        // x 12288, P = 33024, 0.88; 16384 x 14336, P = 57344, 0.98; 14336 x 16384, P = 57344, 1.00; 24576 x 8192 1.04.  From 97
+        // to 128, a tile full of rows, past 27000 (35000 up to 512 blocks): P = 27520 on 640 blocks 0.97, 35840 0.88; on 512 and
+        // fewer 26112 1.01, 34816 1.06, 36864 0.91.  Up to 192 its second row tile is half empty (24576 x 6144 at M = 160
+        // 1.13); up to 256 past 17000 (P = 16512 at M = 240 0.99, 17920 0.91).
+        const int64_t P = a.n_cb * a.n_kt;
+        const bool two_parts = a.part_bytes >= (size_t)(2 * M * N) * sizeof(float);
+        const int64_t midm_max = tn.midm_max_m                        ? tn.midm_max_m
+                               : a.n_cb >= 2560                       ? 64
+                               : a.n_cb >= 1024 || P > 40000          ? 96
+                               : a.n_cb <= 448 && a.n_kt <= 56        ? 256 : 192;
+        const int64_t p_max = M <= 64  ? P
+                            : M <= 96  ? (a.n_cb <= 512 ? P : a.n_cb <= 640 ? 40000 : a.n_cb <= 768 ? 25000 : a.n_cb < 1024 ? 50000 : 60000)
+                            : M <= 128 ? (a.n_cb <= 512 ? 35000 : 27000)
+                            : M <= 192 ? 40000 : 17000;
+        const bool below_max = M <= midm_max && (tn.midm_max_m || !two_parts || P <= p_max);
         const bool gemv_rows = M < midm_min;
         if (gemv_rows && a16_gemv_supports(a)) {
             rc = launch_a16_gemv(a, (hipStream_t)stream);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
         }
-        if (M >= midm_min && M <= midm_max && a16_midm_supports(a)) return launch_a16_midm(a, (hipStream_t)stream);
+        if (M >= midm_min && below_max && a16_midm_supports(a)) return launch_a16_midm(a, (hipStream_t)stream);
         if (a16_gemv_supports(a)) {
             rc = launch_a16_gemv(a, (hipStream_t)stream);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the small-M kernel)

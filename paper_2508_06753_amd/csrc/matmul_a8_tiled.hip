@@ -605,7 +605,7 @@ static TiledPlan tiled_plan(int64_t M, int64_t N, int64_t n_kt, int64_t cap, con
 // M = 256: 27.5 against 29.4), and so it does below 256 rows at K = 17408.
 static int deep128_splits(int64_t M, int64_t N, int64_t n_kt, int64_t G, int64_t cap, const w2_tuning_t& tune)
 {
-    if (tune.tiled_bm || G != 128 || !((n_kt >= 100 && M >= 128) || (n_kt >= 64 && M >= 256))) return 1;
+    if (tune.tiled_bm || G != 128 || !((n_kt >= 100 && M > 112) || (n_kt >= 64 && M >= 256))) return 1;
     const int s = a8_tiled128_splits(M, N, n_kt, cap, tune);
     const int64_t t256 = ((M + 127) / 128) * ((N + 255) / 256);
     return s >= 2 && t256 * s >= 192 ? s : 1;

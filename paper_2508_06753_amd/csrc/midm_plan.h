@@ -128,11 +128,14 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 }
                 if (n_kt >= 1 << lk) offer(1 << lk, 1, (n_kt + (1 << lk) - 1) >> lk, resident);
                 else offer(n_kt, 1, 1, resident_of(xt, rt, cj, n_kt, sh));
-                // Across workgroups only from K = 8192 on, for grids that leave half the chip idle, into as many parts as
-                // still run in one round: other numbers of parts were hardly ever faster by more than 3 %.
+                // Across workgroups: grids that leave half the chip idle, in as many parts as still run at once, one per CU, and
+                // with bf16 rows (whose workgroups take longer) grids of one round in two per CU, where two fit; other
+                // numbers of parts were hardly ever faster by more than 3 %.  From K = 8192 on, with int8 rows from 20480 (17408 x
+                // 1024 at M = 5 7.1 us in parts, 5.6 in one piece).
                 const int wgs = groups * bands;
-                if (cap < 2 || n_kt < 32 || wgs > 128 || lw == 0 || f == 0 || tune.splitk == 1) continue;
-                const int sp = (int)std::min<int64_t>(std::min(256 / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
+                if (cap < 2 || n_kt < (xt == 0 ? 80 : 32) || lw == 0 || f == 0 || tune.splitk == 1) continue;
+                const int at_once = wgs <= 128 ? 256 : xt == 1 && wgs <= 256 && resident >= 2 ? 512 : 0;
+                const int sp = (int)std::min<int64_t>(std::min(at_once / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
                 if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);
             }
     }
