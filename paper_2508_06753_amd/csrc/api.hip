@@ -609,10 +609,11 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
             rc = launch_a16_gemv(a, (hipStream_t)stream);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
         }
-        if (M >= midm_min && below_max && a16_midm_supports(a)) return launch_a16_midm(a, (hipStream_t)stream);
-        if (a16_gemv_supports(a)) {
+        // (from three rows on the mid-M kernel, not the small-M one, also takes what the decode kernel turns down)
+        if ((M >= midm_min || (!tn.midm_min_m && M >= 3)) && below_max && a16_midm_supports(a)) return launch_a16_midm(a, (hipStream_t)stream);
+        if (!gemv_rows && a16_gemv_supports(a)) {            // (only where tuning fields leave rows to neither of the two)
             rc = launch_a16_gemv(a, (hipStream_t)stream);
-            if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the small-M kernel)
+            if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;
         }
         if (!a16_smallm_supports(a)) return launch_a16_fold_tiled(a, (hipStream_t)stream);
         variant = W2_VARIANT_SMALLM;

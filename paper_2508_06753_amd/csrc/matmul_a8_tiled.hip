@@ -599,7 +599,7 @@ static TiledPlan tiled_plan(int64_t M, int64_t N, int64_t n_kt, int64_t cap, con
 }
 
 // Deep K with room for partial results: the 128-row kernel with its own K ranges (half the up-convert work per
-// matrix instruction) instead of 64-row tiles.  Measured against the priced 64-row plan: 28672 x 8192 at
+// matrix instruction) instead of 64-row tiles, from 113 rows, which fill its tile.  Measured against the priced 64-row plan: 28672 x 8192 at
 // M = 128 / 256 / 512 / 768 44 / 70 / 125 / 193 against 48 / 80 / 145 / 215 us, 17408 x 5120 at M = 256 / 512 / 768
 // 36 / 56 / 77 against 40 / 77 / 88; at K = 14336 and below the 64-row plan holds its own (14336 x 4096 at
 // M = 256: 27.5 against 29.4), and so it does below 256 rows at K = 17408.

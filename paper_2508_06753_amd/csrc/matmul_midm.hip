@@ -23,16 +23,16 @@
 // SH = 2: pairs of waves take different column blocks of the same K range and share its chunks (two buffers, one
 // barrier per chunk): half the activation traffic, for wide projections with int8 rows.
 //
-// Measured (graph-timed, us; before = the kernels this one replaces, which shared 1024-k chunks of all rows between
-// the waves of a workgroup with two barriers each, and split deep K across workgroups with a second launch):
-// int8 rows, M = 48: 4096 x 6144 9.4 -> 5.9, 4096 x 4096 9.2 -> 5.0, 14336 x 4096 16.2 -> 9.7, 17408 x 5120 18.6 ->
-// 13.1, 3584 x 18944 23.1 -> 11.5, 4096 x 28672 17.0 -> 14.6; bf16 rows, M = 64: 15.7 -> 8.8, 15.4 -> 6.6, 23.9 -> 15.7,
-// 32.0 -> 25.6, 38.7 -> 18.8, 32.1 -> 23.1.
+// Measured (graph-timed with weights out of memory, us; before = the kernels this one replaces, which shared 1024-k chunks
+// of all rows between the waves of a workgroup with two barriers each, and split deep K across workgroups more often):
+// int8 rows, M = 48: 4096 x 6144 9.7 -> 6.4, 4096 x 4096 9.4 -> 5.0, 14336 x 4096 17.3 -> 11.3, 17408 x 5120 18.9 ->
+// 13.4, 3584 x 18944 24.5 -> 11.8, 4096 x 28672 17.1 -> 14.8; bf16 rows, M = 64: 4096 x 6144 16.4 -> 9.5, 14336 x 4096 27.3 ->
+// 18.0, 4096 x 28672 33.6 -> 23.7, 28672 x 8192 54.9 -> 41.8.
 //
 // What bounds it (4096 x 28672, 64 int8 rows, 17.2 us; copies with parts taken out): without the activations 14.0,
 // without the weight loads 12.9, without either 10.3, without the epilogue 14.8: a launch of this size is too short
-// for its phases (first loads out of HBM, multiply, reduce) to overlap, and a SIMD's vector issue slots are two
-// thirds full while it multiplies.  Deeper load windows, a second operand set read a chunk ahead, pinned interleaving
+// for its phases (first loads out of HBM, multiply, reduce) to overlap (counters over the whole launch: vector issue slots a
+// third full, matrix pipe and local memory a fifth each, waves waiting a third of the time).  Deeper load windows, a second operand set read a chunk ahead, pinned interleaving
 // of vector and matrix instructions and a start of K that differs per workgroup were measured and gave nothing.
 #include <hip/hip_runtime.h>
 

@@ -597,6 +597,31 @@ def test_auto_dispatch_over_random_shapes(w2, M, K, N, G, seed):
         check_y(bf16_bits(Y16), Yo16, y64_16, mag16, f"a16 auto M={M} K={K} N={N} G={G} workspace={with_ws}")
 
 
+@pytest.mark.parametrize("path,M,K,N", [("a8", 48, 17920, 8208), ("a8", 49, 17920, 8208), ("a8", 64, 17920, 10240),
+                                        ("a8", 33, 15360, 16400), ("a8", 113, 25600, 8208), ("a8", 12, 8192, 12288),
+                                        ("a16", 8, 8192, 12288), ("a16", 96, 16384, 10256), ("a16", 97, 14080, 8208),
+                                        ("a16", 129, 8192, 10256), ("a16", 193, 11264, 6160)])
+def test_auto_ranges_agree_with_midm(w2, path, M, K, N):
+    # the edges of the ranges that AUTO gives to the decode and tiled kernels, with the workspace that the call asks for,
+    # against the mid-M kernel.  Bound: bf16 holds eight significant bits, so each side is within half a unit, 2^-8 |y|, of
+    # its fp32 sum (2^-7 |y| together), and the fp32 sums differ by the dequant's bias and the order of the additions, which
+    # stays below 2^-11 of the outputs' root mean square
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    codes = torch.randint(0, 4, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    scales = torch.empty((K // 128, N), device="cuda").uniform_(0.005, 0.05, generator=g).to(torch.bfloat16)
+    packed = w2.prepack(codes, scales, 128)
+    X = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    ws = torch.empty(max(16, w2.workspace_size(M, K, N, 128, a16=path == "a16")), dtype=torch.uint8, device="cuda")
+    if path == "a16":
+        call = lambda **kw: w2.matmul_a16(packed, K, N, 128, X, workspace=ws, **kw).float()
+    else:
+        xq, sx, _ = w2.quantize_rows(X)
+        call = lambda **kw: w2.matmul_a8(packed, K, N, 128, xq, sx, workspace=ws, **kw).float()
+    a, b = call(), call(variant=w2.VARIANT_MIDM)
+    rms = b.pow(2).mean().sqrt()
+    assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 2.0 ** -11 * rms).all()
+
+
 @pytest.mark.parametrize("codec", [0, 1])
 def test_config0_gemv_2048(w2, codec):
     """The single-GEMV configuration: M=1, K=N=2048, G=128, seed 0."""
