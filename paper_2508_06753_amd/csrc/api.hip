@@ -291,12 +291,14 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
         // their tiles: 49 to 64 rows up to 640 blocks from K = 17920 (tiled / mid-M at M = 64: 20480 0.91 .. 0.96, 24576
         // 0.86 .. 0.90, 28672 0.92 .. 0.96; on 704 to 896 blocks 0.98 .. 1.29, at M = 48 0.95 .. 1.04), 33 to 64 up to 1280
         // (M = 40 / 64: K = 16384 0.89 .. 0.98, 18432 1.02 .. 1.07, 22528 0.76 .. 0.89, 26624 0.72 .. 0.86), 113 to 128 from K = 25600 (28672 at M = 128 0.78 .. 0.87; 24576 1.00 .. 1.22).
-        const bool two_parts = a.part_bytes >= (size_t)(2 * M * N) * sizeof(float);
-        const bool full_tiles = two_parts && !tn.midm_max_m && G == 128 &&
+        // (All the parts that the tiled kernels want have to fit: in fewer they leave CUs idle.)
+        const bool full_tiles = !tn.midm_max_m && G == 128 &&
                                 ((a.n_kt >= 70 && a.n_cb > 512 && a.n_cb <= 640 && M > 48 && M <= 64) ||
                                  (a.n_kt >= 60 && a.n_cb > 1024 && a.n_cb <= 1280 && M > 32 && M <= 64) ||
                                  (a.n_kt >= 100 && a.n_cb > 512 && a.n_cb < 1024 && M > 112 && M <= 128));
-        const bool midm_ok = M >= midm_min && M <= midm_max && !full_tiles && a8_midm_supports(a);
+        const size_t want = full_tiles ? a8_tiled_splitk_bytes(M, N, a.n_kt, G, tn) : 0;
+        const bool tiled_first = want > 0 && a.part_bytes >= want;
+        const bool midm_ok = M >= midm_min && M <= midm_max && !tiled_first && a8_midm_supports(a);
         // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
         // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
         const int64_t row_bytes = M * (K + 32);
@@ -586,7 +588,7 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
         const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
         // Upper end, against the tiled kernel of 128-row tiles (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096
         // x 28672 at M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  With room for
-        // two parts of a split K that kernel wins earlier, by the number of tiles P of the matrix (its time / the mid-M
+        // all the parts of a split K that it wants that kernel wins earlier, by the number of tiles P of the matrix (its time / the mid-M
         // kernel's): at M = 96 once P passes 40000 (25000 for 641 to 768 column blocks, 50000 up to 1023, 60000 above; never up
         // to 512): 14336 x 10240, P = 35840, 1.01; 17408 x 10240 0.96; 24576 x 10240 0.82; 8192 x 11264, P = 22528, 1.03; 11008
         // x 12288, P = 33024, 0.88; 16384 x 14336, P = 57344, 0.98; 14336 x 16384, P = 57344, 1.00; 24576 x 8192 1.04.  From 97
@@ -594,7 +596,6 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
         // fewer 26112 1.01, 34816 1.06, 36864 0.91.  Up to 192 its second row tile is half empty (24576 x 6144 at M = 160
         // 1.13); up to 256 past 17000 (P = 16512 at M = 240 0.99, 17920 0.91).
         const int64_t P = a.n_cb * a.n_kt;
-        const bool two_parts = a.part_bytes >= (size_t)(2 * M * N) * sizeof(float);
         const int64_t midm_max = tn.midm_max_m                        ? tn.midm_max_m
                                : a.n_cb >= 2560                       ? 64
                                : a.n_cb >= 1024 || P > 40000          ? 96
@@ -603,7 +604,8 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
                             : M <= 96  ? (a.n_cb <= 512 ? P : a.n_cb <= 640 ? 40000 : a.n_cb <= 768 ? 25000 : a.n_cb < 1024 ? 50000 : 60000)
                             : M <= 128 ? (a.n_cb <= 512 ? 35000 : 27000)
                             : M <= 192 ? 40000 : 17000;
-        const bool below_max = M <= midm_max && (tn.midm_max_m || !two_parts || P <= p_max);
+        const size_t want = M <= midm_max && P > p_max && !tn.midm_max_m ? a16_fold_splitk_bytes(M, N, a.n_kt, tn) : 0;
+        const bool below_max = M <= midm_max && !(want > 0 && a.part_bytes >= want);
         const bool gemv_rows = M < midm_min;
         if (gemv_rows && a16_gemv_supports(a)) {
             rc = launch_a16_gemv(a, (hipStream_t)stream);
