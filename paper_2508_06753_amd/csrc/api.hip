@@ -286,18 +286,11 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
         // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7; 28672 x 5120 at M = 240 50.2 against 54.5).
         const int midm_max = tn.midm_max_m ? tn.midm_max_m
                            : a.n_cb >= 2560 ? 48 : a.n_cb >= 1536 ? 112 : a.n_cb > 448 ? 160 : G == 128 && a.n_kt > 104 && a.n_cb > 256 ? 192 : 240;
-        // A little more than 512 (1024) column blocks, in groups of two (four), are a little more than one round of 256
-        // workgroups; on a very deep K the tiled kernels with K split across workgroups are then ahead where the rows fill
-        // their tiles: 49 to 64 rows up to 640 blocks from K = 17920 (tiled / mid-M at M = 64: 20480 0.91 .. 0.96, 24576
-        // 0.86 .. 0.90, 28672 0.92 .. 0.96; on 704 to 896 blocks 0.98 .. 1.29, at M = 48 0.95 .. 1.04), 33 to 64 up to 1280
-        // (M = 40 / 64: K = 16384 0.89 .. 0.98, 18432 1.02 .. 1.07, 22528 0.76 .. 0.89, 26624 0.72 .. 0.86), 113 to 128 from K = 25600 (28672 at M = 128 0.78 .. 0.87; 24576 1.00 .. 1.22).
-        // (All the parts that the tiled kernels want have to fit: in fewer they leave CUs idle.)
-        const bool full_tiles = !tn.midm_max_m && G == 128 &&
-                                ((a.n_kt >= 70 && a.n_cb > 512 && a.n_cb <= 640 && M > 48 && M <= 64) ||
-                                 (a.n_kt >= 60 && a.n_cb > 1024 && a.n_cb <= 1280 && M > 32 && M <= 64) ||
-                                 (a.n_kt >= 100 && a.n_cb > 512 && a.n_cb < 1024 && M > 112 && M <= 128));
-        const size_t want = full_tiles ? a8_tiled_splitk_bytes(M, N, a.n_kt, G, tn) : 0;
-        const bool tiled_first = want > 0 && a.part_bytes >= want;
+        // Below it, from 33 rows on, they are taken where their price (tile_plan.h) is under the mid-M kernel's (midm_plan.h)
+        // by more than that one errs: with less of a margin 28672 x 8192 at M = 100 takes 38.0 us instead of 35.2.
+        const int64_t cap = a.part && !acc_out ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
+        const bool tiled_first = M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m &&
+                                 a8_tiled_us(M, N, a.n_kt, G, cap, tn) < 0.86 * midm_us(0, M, a.n_cb, a.n_kt, epi.act == ACT_SILU_MUL, cap, tn);
         const bool midm_ok = M >= midm_min && M <= midm_max && !tiled_first && a8_midm_supports(a);
         // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
         // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
@@ -522,6 +515,12 @@ int w2_debug_group_acc_a8(const void* packed, int64_t K, int64_t N, int G, const
                      tune, stream);
 }
 
+// The tiled kernel instead of the mid-M kernel where both take the rows: by price, with a margin for the errors of the latter's.
+static bool a16_tiled_first(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tn)
+{
+    return a16_tiled_us(M, N, n_kt, cap, tn) < 0.93 * midm_us(1, M, n_cb, n_kt, gated, cap, tn);
+}
+
 static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, int G,
                       const uint16_t* X, int64_t ldx, int64_t M, uint16_t* Y, int64_t ldy,
                       void* workspace, size_t workspace_bytes, const w2_tuning_t* tune, void* stream,
@@ -586,26 +585,16 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
                             : a.n_kt > 16                                  ? 8
                             : G == 128 || a.n_cb < 1024                    ? 9 : 17;
         const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
-        // Upper end, against the tiled kernel of 128-row tiles (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096
-        // x 28672 at M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  With room for
-        // all the parts of a split K that it wants that kernel wins earlier, by the number of tiles P of the matrix (its time / the mid-M
-        // kernel's): at M = 96 once P passes 40000 (25000 for 641 to 768 column blocks, 50000 up to 1023, 60000 above; never up
-        // to 512): 14336 x 10240, P = 35840, 1.01; 17408 x 10240 0.96; 24576 x 10240 0.82; 8192 x 11264, P = 22528, 1.03; 11008
-        // x 12288, P = 33024, 0.88; 16384 x 14336, P = 57344, 0.98; 14336 x 16384, P = 57344, 1.00; 24576 x 8192 1.04.  From 97
-        // to 128, a tile full of rows, past 27000 (35000 up to 512 blocks): P = 27520 on 640 blocks 0.97, 35840 0.88; on 512 and
-        // fewer 26112 1.01, 34816 1.06, 36864 0.91.  Up to 192 its second row tile is half empty (24576 x 6144 at M = 160
-        // 1.13); up to 256 past 17000 (P = 16512 at M = 240 0.99, 17920 0.91).
-        const int64_t P = a.n_cb * a.n_kt;
-        const int64_t midm_max = tn.midm_max_m                        ? tn.midm_max_m
-                               : a.n_cb >= 2560                       ? 64
-                               : a.n_cb >= 1024 || P > 40000          ? 96
-                               : a.n_cb <= 448 && a.n_kt <= 56        ? 256 : 192;
-        const int64_t p_max = M <= 64  ? P
-                            : M <= 96  ? (a.n_cb <= 512 ? P : a.n_cb <= 640 ? 40000 : a.n_cb <= 768 ? 25000 : a.n_cb < 1024 ? 50000 : 60000)
-                            : M <= 128 ? (a.n_cb <= 512 ? 35000 : 27000)
-                            : M <= 192 ? 40000 : 17000;
-        const size_t want = M <= midm_max && P > p_max && !tn.midm_max_m ? a16_fold_splitk_bytes(M, N, a.n_kt, tn) : 0;
-        const bool below_max = M <= midm_max && !(want > 0 && a.part_bytes >= want);
+        // Upper end, against the tiled kernel (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096 x 28672 at
+        // M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  Below it, from 33 rows
+        // on, by their prices (tile_plan.h, midm_plan.h).
+        const int64_t midm_max = tn.midm_max_m                               ? tn.midm_max_m
+                               : a.n_cb >= 2560                              ? 64
+                               : a.n_cb >= 1024 || a.n_cb * a.n_kt > 40000   ? 96
+                               : a.n_cb <= 448 && a.n_kt <= 56               ? 256 : 192;
+        const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
+        const bool below_max = M <= midm_max && !(M > 32 && M >= midm_min && !tn.midm_max_m &&
+                                                  a16_tiled_first(M, N, a.n_cb, a.n_kt, epi.act == ACT_SILU_MUL, cap, tn));
         const bool gemv_rows = M < midm_min;
         if (gemv_rows && a16_gemv_supports(a)) {
             rc = launch_a16_gemv(a, (hipStream_t)stream);
@@ -666,7 +655,8 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
     const w2_tuning_t dflt = {};
     if (M == 0) *bytes = 0;
     else if (a16) {
-        const size_t tiled = M > 64 ? a16_fold_splitk_bytes(M, N, L.n_kt, dflt) : 0;
+        const bool want = M > 64 || (M > 32 && a16_tiled_first(M, N, L.n_cb, L.n_kt, false, 16, dflt));
+        const size_t tiled = want ? a16_fold_splitk_bytes(M, N, L.n_kt, dflt) : 0;
         const size_t midm = M >= 3 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = tiled > midm ? tiled : midm;
     }

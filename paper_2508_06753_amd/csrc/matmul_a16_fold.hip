@@ -18,7 +18,8 @@
 // construction the faster one for prefill: measured, it issues 2.3 vector
 // instructions per matrix instruction where the zero-point kernel issues 5.9.
 //
-// Workgroup: 128 rows x (32 columns per wave) x 64 k per stage; activations go
+// Workgroup: 128 rows (lower tiles of 64 to 112 where those waste less: tile_plan.h;
+// 4096 x 28672 at M = 300 95.7 -> 79.3 us) x (32 columns per wave) x 64 k per stage; activations go
 // through LDS (three or five buffers, rows de-interleaved [even k | odd k] per
 // 16-k block to match the order the codes come out of a dword, row stride
 // 160 B: conflict-free operand reads); weights go from global memory to
@@ -30,6 +31,7 @@
 
 #include <type_traits>
 
+#include "tile_plan.h"
 #include "w2_small_common.h"
 
 namespace w2 {
@@ -48,10 +50,11 @@ constexpr int A_STRIDE = BK * 2 + 32;              // 32 mod 64 bytes: conflict-
 constexpr int nbuf_of(int bn) { return bn >= 256 ? 5 : 3; }
 constexpr int E_STRIDE = WN * 2 + 16;              // epilogue: bytes per LDS row of a wave's result
 constexpr int waves_of(int bn) { return bn / WN; }
-constexpr int lds_bytes(int bn, int bm)
+constexpr int CP_ROWS = 128;                       // rows that a workgroup's threads stage (a lower tile's last row repeated)
+constexpr int A_BUF = CP_ROWS * A_STRIDE;
+constexpr int lds_bytes(int bn)
 {
-    return nbuf_of(bn) * bm * A_STRIDE > waves_of(bn) * bm * E_STRIDE ? nbuf_of(bn) * bm * A_STRIDE
-                                                                      : waves_of(bn) * bm * E_STRIDE;
+    return nbuf_of(bn) * A_BUF > waves_of(bn) * CP_ROWS * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * CP_ROWS * E_STRIDE;
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
@@ -103,16 +106,16 @@ struct WTile {
     uint32_t s[CJ][G == 128 ? 1 : 2];              // the lane's column: 2 (G=128) or 4 (G=64) bf16 group scales
 };
 
-// RI: 16-row tiles per wave (the workgroup's rows: BM = 16 RI)
+// RI: 16-row tiles per wave (the workgroup's rows: BM = 16 RI), 4 to 8
 template <int G, int BN, int RI>
-__global__ void __launch_bounds__(64 * waves_of(BN), (waves_of(BN) > 4 || RI > 8) ? 1 : 2)
+__global__ void __launch_bounds__(64 * waves_of(BN), waves_of(BN) > 4 ? 1 : 2)
 a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int splits)
 {
-    constexpr int BM = 16 * RI, A_BUF = BM * A_STRIDE;
+    constexpr int BM = 16 * RI;
     constexpr int WAVES = waves_of(BN), THREADS = 64 * WAVES;
     constexpr int GPT = TILE_K / G;
     constexpr int NBUF = nbuf_of(BN);
-    constexpr int NP = BM * 8 / THREADS;           // 16-byte activation pieces per thread and stage: 2 or 4
+    constexpr int NP = CP_ROWS * 8 / THREADS;           // 16-byte activation pieces per thread and stage: 2 or 4
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -152,7 +155,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int row = (tid >> 3) + p * (THREADS / 8);
-        int64_t m = m0 + row;
+        int64_t m = m0 + min(row, BM - 1);
         if (m >= a.M) m = a.M - 1;
         cp_lane[p] = (uint32_t)((m - m0) * a.ldx * 2) + (uint32_t)cp_seg * 16u;
         cp_dst[p] = row * A_STRIDE + (cp_seg >> 1) * 16 + (cp_seg & 1) * 8;
@@ -260,6 +263,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     prep_b(std::integral_constant<int, 0>{}, w0, 1, bA);
     int buf = 0;
 
+    constexpr int VPM = RI == 8 ? 2 : 3;                     // vector instructions per matrix instruction
     auto stage = [&](int64_t it, auto tc, const WTile<G>& wc, WTile<G>& wnx, const BSet& bc, BSet& bn) {
         constexpr int t = decltype(tc)::value;
         constexpr std::integral_constant<int, (t + 1) & 3> tn{};
@@ -296,12 +300,12 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
             for (int k = 0; k < RI; ++k) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
             }
 #pragma unroll
             for (int k = RI; k < RI * CJ; ++k) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
             }
         }
         buf = buf1;
@@ -325,15 +329,15 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
         // the end of the last stage freed the activation buffers; rows padded by 16 bytes, conflict-free both
         // ways), and leaves as 16-byte stores in 128-byte runs.
         constexpr int P_STRIDE = WN * 4 + 16;
-        static_assert(WAVES * 64 * P_STRIDE <= lds_bytes(BN, BM), "partial-result staging fits the activation buffers");
+        static_assert(WAVES * 64 * P_STRIDE <= lds_bytes(BN), "partial-result staging fits the activation buffers");
         float* dst = a.part + (int64_t)blockIdx.y * a.M * a.N;
         int8_t* pbase = smem + wn * (64 * P_STRIDE);
         const int prow = lane >> 3, pcol = (lane & 7) * 4;   // eight lanes per row piece
         const int64_t n = n0 + wn * WN + pcol;
 #pragma unroll
-        for (int h = 0; h < RI / 4; ++h) {
+        for (int h = 0; h < (RI + 3) / 4; ++h) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4 && h * 4 + i < RI; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -345,7 +349,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
                 const int row = p * 8 + prow;
                 const int64_t m = m0 + h * 64 + row;
                 const float4 v = *reinterpret_cast<const float4*>(pbase + row * P_STRIDE + pcol * 4);
-                if (m < a.M && n < a.N) *reinterpret_cast<float4*>(dst + m * a.N + n) = v;   // N % 8 == 0: all 4 or none
+                if (h * 64 + row < BM && m < a.M && n < a.N) *reinterpret_cast<float4*>(dst + m * a.N + n) = v;   // N % 8 == 0: all 4 or none
             }
         }
         return;
@@ -353,7 +357,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
 
     // The wave's 128 x 32 result goes through LDS (its own region; the barrier at the end of the last
     // stage freed the activation buffers) and leaves as 16-byte stores, four lanes per 64-byte row piece.
-    int8_t* ebase = smem + wn * (BM * E_STRIDE);
+    int8_t* ebase = smem + wn * (CP_ROWS * E_STRIDE);
     uint16_t* eb = reinterpret_cast<uint16_t*>(ebase);
     // Fused epilogue (Sec. II-D: bias and activation applied while the outputs are in registers).  The
     // gated form combines the wave's two column blocks, an even (gate) and an odd (up) one, into one.
@@ -393,11 +397,11 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     const int rpp = 64 / lpr;                                // rows per pass
     const int64_t ncol = (gated ? (n0 + wn * WN) / 2 : n0 + wn * WN) + (lane % lpr) * 8;   // first of this lane's 8 columns
     const int64_t n_out = gated ? a.N / 2 : a.N;
-    for (int p = 0; p < BM / rpp; ++p) {
+    for (int p = 0; p * rpp < BM; ++p) {
         const int row = p * rpp + lane / lpr;
         const int64_t m = m0 + row;
         const uint4 v = *reinterpret_cast<const uint4*>(ebase + row * E_STRIDE + (lane % lpr) * 16);
-        if (m < a.M && ncol < n_out) *reinterpret_cast<uint4*>(a.Y + m * a.ldy + ncol) = v;   // N % 8 == 0: all 8 or none
+        if (row < BM && m < a.M && ncol < n_out) *reinterpret_cast<uint4*>(a.Y + m * a.ldy + ncol) = v;   // N % 8 == 0: all 8 or none
     }
 }
 
@@ -414,7 +418,7 @@ static int launch_fold_bn(const A16Args& a_in, int splits, hipStream_t stream)
     const int tiles_n = (int)((a.N + BN - 1) / BN);
     const int group_m = a.tune.tiled_group_m ? a.tune.tiled_group_m : 8;
     const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n), (unsigned)(splits < 2 ? 1 : splits)), block(64 * waves_of(BN));
-    constexpr int lds = lds_bytes(BN, BM);
+    constexpr int lds = lds_bytes(BN);
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(a16_fold_tiled_kernel<G, BN, RI>), lds,
                                     "w2_matmul_a16[scaled16 tiled]"))
         return rc;
@@ -425,45 +429,15 @@ static int launch_fold_bn(const A16Args& a_in, int splits, hipStream_t stream)
     return launch_splitk_reduce(a.part, splits, a.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
-// Columns per workgroup and K ranges across workgroups.  With room for partial results: 256-column workgroups
-// (eight waves, one per CU) and as many K ranges (up to 8, at least two 256-k tiles each, at most 64 MiB of
-// partial results) as bring the grid up to one workgroup per CU -- floor(256 / tiles), never more than one
-// round.  From sweeps over 4096 x 4096, 4096 x 6144, 5120 x 7168, 8192 x 8192, 14336 x 4096, 4096 x 28672 and
-// 28672 x 8192 at M = 65..512 that rule is within 5 % of the best (columns, ranges) everywhere and up to 17 %
-// ahead of the older one (128 columns when 256 leave half the chip idle, about 1.5 workgroups per CU): 4096 x
-// 6144 at M = 256 32.1 -> 26.8 us, 8192 x 8192 at M = 512 76.7 -> 67.7, 14336 x 4096 at M = 512 70.2 -> 62.1,
-// 4096 x 28672 at M = 65 40.6 -> 34.7.  Without room: 128 columns when 256 would leave half the chip idle.
-struct FoldPlan { int bn, splits; };
-
-static FoldPlan fold_plan(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+// Forced 128-column workgroups keep 128 rows (tuning and tests).
+static tiles::Shape fold_plan(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
 {
-    FoldPlan p;
-    const int64_t tiles_m = (M + 127) / 128;
-    const int64_t t256 = tiles_m * ((N + 255) / 256);
-    const int forced = tune.splitk;                          // tuning and tests: 1 = never, n = n parts if they fit
-    p.bn = tune.tiled_bn == 128 || tune.tiled_bn == 256 ? tune.tiled_bn : 0;
-    if (forced > 0) {
-        p.splits = (int)max((int64_t)1, min((int64_t)forced, min(cap, n_kt)));
-        if (!p.bn) p.bn = t256 <= 128 && p.splits < 2 ? 128 : 256;
-        return p;
-    }
-    int64_t s = 256 / max(t256, (int64_t)1);
-    s = min(s, (int64_t)8);
-    s = min(s, n_kt / 2);
-    s = min(s, ((int64_t)64 << 20) / (M * N * (int64_t)sizeof(float)));
-    s = min(s, cap);
-    if (p.bn == 128) {                                       // forced narrow workgroups: two fit a CU
-        const int64_t t128 = tiles_m * ((N + 127) / 128);
-        s = min(s, max((int64_t)1, 512 / max(t128, (int64_t)1)));
-    }
-    if (s < 2) {
-        p.splits = 1;
-        if (!p.bn) p.bn = t256 <= 128 ? 128 : 256;
-        return p;
-    }
-    p.splits = (int)s;
-    if (!p.bn) p.bn = 256;
-    return p;
+    return tiles::pick(tiles::A16, M, N, n_kt, cap, tune.tiled_bn == 128 ? 8 : 0, tune.splitk);
+}
+
+double a16_tiled_us(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+{
+    return fold_plan(M, N, n_kt, cap, tune).us;
 }
 
 size_t a16_fold_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, const w2_tuning_t& tune)
@@ -475,9 +449,21 @@ size_t a16_fold_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, const w2_tuning
 int launch_a16_fold_tiled(const A16Args& a, hipStream_t stream)
 {
     const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const FoldPlan p = fold_plan(a.M, a.N, a.n_kt, cap, a.tune);
-    if (p.bn == 256)
-        return a.G == 128 ? launch_fold_bn<128, 256, 8>(a, p.splits, stream) : launch_fold_bn<64, 256, 8>(a, p.splits, stream);
+    const tiles::Shape p = fold_plan(a.M, a.N, a.n_kt, cap, a.tune);
+    if (a.tune.tiled_bn != 128) {
+        switch (p.ri * 128 + a.G) {
+        case 4 * 128 + 64: return launch_fold_bn<64, 256, 4>(a, p.splits, stream);
+        case 5 * 128 + 64: return launch_fold_bn<64, 256, 5>(a, p.splits, stream);
+        case 6 * 128 + 64: return launch_fold_bn<64, 256, 6>(a, p.splits, stream);
+        case 7 * 128 + 64: return launch_fold_bn<64, 256, 7>(a, p.splits, stream);
+        case 8 * 128 + 64: return launch_fold_bn<64, 256, 8>(a, p.splits, stream);
+        case 4 * 128 + 128: return launch_fold_bn<128, 256, 4>(a, p.splits, stream);
+        case 5 * 128 + 128: return launch_fold_bn<128, 256, 5>(a, p.splits, stream);
+        case 6 * 128 + 128: return launch_fold_bn<128, 256, 6>(a, p.splits, stream);
+        case 7 * 128 + 128: return launch_fold_bn<128, 256, 7>(a, p.splits, stream);
+        default: return launch_fold_bn<128, 256, 8>(a, p.splits, stream);
+        }
+    }
     return a.G == 128 ? launch_fold_bn<128, 128, 8>(a, p.splits, stream) : launch_fold_bn<64, 128, 8>(a, p.splits, stream);
 }
 

@@ -36,6 +36,7 @@
 
 #include <type_traits>
 
+#include "tile_plan.h"
 #include "w2_internal.h"
 
 #if defined(__HIP_DEVICE_COMPILE__) && defined(__FAST_MATH__)
@@ -520,100 +521,49 @@ static int tiled_bn(int64_t M, int64_t N, const w2_tuning_t& tune)
     return bn;
 }
 
-// How a problem's K is cut: `splits` ranges across workgroups (partial results in the workspace, summed
-// by a second launch) times `kw` ranges inside a workgroup (128-column workgroups only).
-struct TiledPlan { int bn, splits, kw; };
-
-static TiledPlan tiled_plan(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+// Fewer than 400 tiles of 64 x 256: from a few dozen to a few hundred workgroups against 256 CUs, so K is cut both across and
+// inside workgroups of 128 or 64 columns, by price (tile_plan.h).  More tiles: K is split only to fill the chip (splitk_plan).
+static tiles::Shape64 tiled_plan(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
 {
-    TiledPlan p;
-    p.bn = tiled_bn(M, N, tune);
-    const int64_t tiles_m = (M + tiled::BM - 1) / tiled::BM;
-    const int forced_s = tune.splitk;                        // tuning and tests: 1 = never, n = n parts if they fit
-    if (p.bn == 256) {
-        // many output tiles: split only to fill the chip (splitk_plan)
-        const int64_t wgs_n = tiles_m * ((N + 255) / 256);
-        if (forced_s > 0) p.splits = (int)min((int64_t)forced_s, min(max(cap, (int64_t)1), n_kt));
-        else p.splits = splitk_plan(wgs_n, n_kt, tune.splitk_min_tiles ? tune.splitk_min_tiles : 12, M, N, cap);
-        p.kw = 1;
-        return p;
-    }
-    // Fewer than 400 tiles of 64 x 256: from a few dozen to a few hundred workgroups against 256 CUs, so K is
-    // cut both ways.  Every (splits, kw) that divides the tiles evenly is priced with a model fitted to sweeps
-    // over 28672 x 8192, 14336 x 4096, 17408 x 5120, 4096 x 28672, 8192 x 8192, 4096 x 4096, 4096 x 6144,
-    // 5120 x 7168 and 2048 x 2048 at M = 32..768:
-    //   loop  = the work of the busiest CU at 1600 TOP/s: it gets ceil(workgroups / 256) workgroups (a CU holds
-    //           one of 16 waves, two of 8, four of 4 at a time; more run in rounds, +10 %); with fewer than 8
-    //           waves on the CU it runs at 0.55 of that rate (measured: 8 and 16 waves per CU run a stage in the
-    //           same time); fewer workgroups than CUs cost another 15 % (the busy CUs queue more stages each);
-    //   parts = 6 us for the second launch and both kernels' ends + the partial results written and read once
-    //           at 3 TB/s.
-    // 64-column workgroups (two waves per group, four groups) are priced too where they still fit the chip in
-    // one round and K is not split across workgroups, at 30 % more per unit of work (every workgroup stages
-    // the whole 64-row panel of activations for half the columns; fitted: 13.4 / 20.8 / 54.2 us at 6.3 / 10.7 /
-    // 37.6 us of work): 4096 x 6144 at M = 65..128 13.1 against 15.5 us, 8192 x 8192 19.3 against 21.4, 4096 x
-    // 4096 at M = 256 13.3 against 15.7.  In more than one round, or with K split on top, they lost everywhere
-    // (14336 x 4096 at M = 384: 62 against 38 us).
-    const double work_us = 2.0 * (double)(tiles_m * tiled::BM) * (double)N * (double)(n_kt * TILE_K) / 1600e6;
-    const int64_t room = max(cap, (int64_t)1);
-    int64_t s_lo = 1, s_hi = min(min((int64_t)16, room), max((int64_t)1, ((int64_t)16 << 20) / (M * N * (int64_t)sizeof(float))));
-    if (forced_s > 0) s_lo = s_hi = min((int64_t)forced_s, min(room, n_kt));
-    const int forced_kw = tune.tiled_kw;
-    double best = 1e30;
-    p.splits = (int)s_lo;
-    p.kw = 1;
-    auto price = [&](int bn, int kw, int64_t sp) {
-        const int64_t wgs = tiles_m * ((N + bn - 1) / bn) * sp;
-        const int64_t per_cu = (wgs + 255) / 256;                        // workgroups on the busiest CU
-        const int64_t at_once = min(per_cu, (int64_t)(kw == 4 ? 1 : kw == 2 ? 2 : 4));
-        const double waves = (double)(at_once * (bn / 32) * kw);
-        const double rate = waves >= 8.0 ? 1.0 : 0.55;
-        double loop = (double)per_cu * work_us * 256.0 / (double)wgs / rate;
-        if (wgs < 256) loop /= 0.85;
-        if (per_cu > at_once) loop *= 1.1;
-        if (bn == 64) loop *= 1.3;
-        const double parts = sp > 1 ? 6.0 + 2.0 * (double)sp * (double)M * (double)N * 4.0 / 3e6 : 0.0;
-        return loop + parts;
-    };
-    bool found = false;
-    for (int kw = 4; kw >= 1; kw >>= 1) {
-        if (forced_kw && kw > forced_kw) continue;           // (a forced kw that does not divide the tiles falls back to the next smaller)
-        for (int64_t sp = s_lo; sp <= s_hi && sp <= n_kt; ++sp) {
-            if (kw > 1 && n_kt % (kw * sp) != 0) continue;
-            if (forced_s <= 0 && sp > 1 && n_kt / (sp * kw) < 2) continue;
-            const double t = price(p.bn, kw, sp);
-            found = true;
-            if (t < best) { best = t; p.splits = (int)sp; p.kw = kw; }
-        }
-        if (forced_kw && found) break;
-    }
-    // (an unsplit launch carries about 4 us of first loads and epilogue that the split launches' 6 us include;
-    // the narrow workgroups one more; and they must win by 10 %: the model is that good and no better)
-    if (tune.tiled_bn == 0 && forced_s <= 1 && (forced_kw == 0 || forced_kw == 4) && n_kt % 4 == 0 &&
-        tiles_m * ((N + 63) / 64) <= 256 && price(64, 4, 1) + 5.0 < 0.9 * (best + (p.splits > 1 ? 0.0 : 4.0))) {
-        p.bn = 64;
-        p.splits = 1;
-        p.kw = 4;
-    }
-    return p;
+    if (tiled_bn(M, N, tune) != 256) return tiles::pick64(G, M, N, n_kt, cap, tune.tiled_bn, tune.tiled_kw, tune.splitk);
+    const int64_t wgs = (M + tiled::BM - 1) / tiled::BM * ((N + 255) / 256);
+    const int splits = tune.splitk > 0 ? (int)min((int64_t)tune.splitk, min(max(cap, (int64_t)1), n_kt))
+                                       : splitk_plan(wgs, n_kt, tune.splitk_min_tiles ? tune.splitk_min_tiles : 12, M, N, cap);
+    return {256, 1, splits, tiles::price64_wide(G, M, N, n_kt, splits)};
 }
 
-// Deep K with room for partial results: the 128-row kernel with its own K ranges (half the up-convert work per
-// matrix instruction) instead of 64-row tiles, from 113 rows, which fill its tile.  Measured against the priced 64-row plan: 28672 x 8192 at
-// M = 128 / 256 / 512 / 768 44 / 70 / 125 / 193 against 48 / 80 / 145 / 215 us, 17408 x 5120 at M = 256 / 512 / 768
-// 36 / 56 / 77 against 40 / 77 / 88; at K = 14336 and below the 64-row plan holds its own (14336 x 4096 at
-// M = 256: 27.5 against 29.4), and so it does below 256 rows at K = 17408.
-static int deep128_splits(int64_t M, int64_t N, int64_t n_kt, int64_t G, int64_t cap, const w2_tuning_t& tune)
+// The kernel for a problem of many rows: 64-row tiles as planned above, or the taller tiles of matmul_a8_tiled128.hip, by
+// price.
+struct A8Tiles {
+    bool tall;
+    int ri, splits;                                          // (tall)
+    double us;
+};
+
+static A8Tiles a8_tiles(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
 {
-    if (tune.tiled_bm || G != 128 || !((n_kt >= 100 && M > 112) || (n_kt >= 64 && M >= 256))) return 1;
-    const int s = a8_tiled128_splits(M, N, n_kt, cap, tune);
-    const int64_t t256 = ((M + 127) / 128) * ((N + 255) / 256);
-    return s >= 2 && t256 * s >= 192 ? s : 1;
+    const tiles::Kind kind = G == 128 ? tiles::A8_G128 : tiles::A8_G64;
+    // tuning and tests: forced 128-row tiles; forced shapes that only the 64-row kernel has
+    if (tune.tiled_bm == 128) {
+        const tiles::Shape t = tiles::pick(kind, M, N, n_kt, cap, 8, tune.splitk);
+        return {true, 8, t.splits, t.us};
+    }
+    const tiles::Shape64 p = tiled_plan(M, N, n_kt, G, cap, tune);
+    if (tune.tiled_bm == 64 || tune.tiled_bn == 64 || tune.tiled_bn == 128 || tune.tiled_kw || tune.tiled_wd) return {false, 0, p.splits, p.us};
+    const tiles::Shape t = tiles::pick(kind, M, N, n_kt, cap, 0, tune.splitk);
+    // (256-column workgroups: the margins that leave the fewest of 380 measured problems slower than in these tiles)
+    const bool tall = t.us < p.us * (p.bn < 256 ? 1.0 : G == 128 ? 0.985 : 0.965);
+    return tall ? A8Tiles{true, t.ri, t.splits, t.us} : A8Tiles{false, 0, p.splits, p.us};
+}
+
+double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
+{
+    return a8_tiles(M, N, n_kt, G, cap, tune).us;
 }
 
 size_t a8_tiled_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, int G, const w2_tuning_t& tune)
 {
-    const int s = max(tiled_plan(M, N, n_kt, 16, tune).splits, deep128_splits(M, N, n_kt, G, 16, tune));
+    const int s = a8_tiles(M, N, n_kt, G, 16, tune).splits;
     return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
 }
 
@@ -621,7 +571,7 @@ template <int G, bool DBG>
 static int launch_tiled_bn(const A8Args& a, hipStream_t stream)
 {
     const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    TiledPlan p = tiled_plan(a.M, a.N, a.n_kt, cap, a.tune);
+    tiles::Shape64 p = tiled_plan(a.M, a.N, a.n_kt, G, cap, a.tune);
     if (DBG) { p.splits = 1; p.kw = 1; }
     const int splits = p.splits;
     if constexpr (!DBG) {
@@ -641,33 +591,9 @@ static int launch_tiled_bn(const A8Args& a, hipStream_t stream)
 
 int launch_a8_tiled(const A8Args& a, hipStream_t stream)
 {
-    // 128-row tiles (half the up-convert work per matrix instruction) where the problem has the rows for
-    // them and K is not split across workgroups
-    {
-        const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-        const int splits = a.acc_out ? 1 : tiled_plan(a.M, a.N, a.n_kt, cap, a.tune).splits;
-        // 128-row tiles run one workgroup per CU, so a last round of workgroups that fills less than half the
-        // chip costs a whole round (64-row workgroups share a CU in pairs and speed up when alone); with 224
-        // tiles and more and a last round at least half full they win from M = 128 on (8192 x 57344 at M = 128:
-        // 71 against 84 us; 4096 x 28672 at M = 384, 1.3 rounds: 66 against 57)
-        const int64_t t128 = (a.M + 127) / 128 * ((a.N + 255) / 256);
-        const bool fill_ok = t128 >= 768 || t128 % 256 == 0 || t128 % 256 >= 128;
-        // Groups of 64 (twice the dequant fmas, so less to gain per matrix instruction): where the rounds come out
-        // nearly whole and the rows fill their tiles (4096 x 28672 at M = 256 / 512 / 2048, 0.9 / 1.8 / 7 rounds: 43.5 /
-        // 82 / 293 us in 64-row tiles against 41.3 / 78 / 280; 28672 x 8192 at M = 768 / 1024, 0.75 / 1 rounds: 288 /
-        // 283 against 240 / 256; but at M = 1000, 3.5 rounds of 4096 x 28672, 148 against 155)
-        const int64_t tail = t128 % 256;
-        const bool rows_full = a.M * 20 >= (a.M + 127) / 128 * 128 * 17;
-        const bool whole64 = t128 <= 256 ? t128 >= 144 : (t128 >= 1792 || tail == 0 || tail >= 159) && rows_full;
-        const bool want128 = a.tune.tiled_bm ? a.tune.tiled_bm == 128
-                           : a.G == 64       ? a.M >= 128 && whole64
-                                             : a.M >= 1024 || (a.M >= 128 && t128 >= 224 && fill_ok);
-        const int s_deep = a.acc_out ? 1 : deep128_splits(a.M, a.N, a.n_kt, a.G, cap, a.tune);
-        // forced 128-row tiles: that kernel's own rule for K ranges (or the forced count)
-        if (a.tune.tiled_bm == 128) return launch_a8_tiled128(a, a8_tiled128_splits(a.M, a.N, a.n_kt, cap, a.tune), stream);
-        if (s_deep >= 2) return launch_a8_tiled128(a, s_deep, stream);
-        if (want128 && splits < 2) return launch_a8_tiled128(a, 1, stream);
-    }
+    const int64_t cap = a.part && !a.acc_out ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
+    const A8Tiles t = a8_tiles(a.M, a.N, a.n_kt, a.G, cap, a.tune);
+    if (t.tall) return launch_a8_tiled128(a, t.ri, t.splits, stream);
     if (a.G == 128)
         return a.acc_out ? launch_tiled_bn<128, true>(a, stream) : launch_tiled_bn<128, false>(a, stream);
     return a.acc_out ? launch_tiled_bn<64, true>(a, stream) : launch_tiled_bn<64, false>(a, stream);

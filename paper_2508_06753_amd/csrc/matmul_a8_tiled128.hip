@@ -1,4 +1,4 @@
-// w2a8 for prefill, 128-row tiles: the compute-bound regime (Sec. III-C, GEMM
+// w2a8 for prefill, tiles of 64 to 128 rows: the compute-bound regime (Sec. III-C, GEMM
 // results) on the int8 matrix cores.  Measured on MI355X, what limits this
 // method there is vector-instruction issue: a SIMD issues one vector
 // instruction, matrix ones included, about every four clocks, and per matrix
@@ -8,8 +8,12 @@
 // operand.  The 64-row kernel (RI = 4) runs at 5.2 vector instructions per
 // matrix instruction; this one halves the up-convert share with 128-row wave
 // tiles (RI = 8 x CJ = 2 column blocks of v_mfma_i32_16x16x64_i8) and spreads
-// the remaining vector work evenly under the matrix instructions:
-//   - workgroup 128 rows x 256 columns (eight waves of 128 x 32, one workgroup
+// the remaining vector work evenly under the matrix instructions.  Lower tiles
+// (RI = 4 .. 7) cost a tile 3.9 + RI parts of 12 instead of all twelve (K loop, G = 128)
+// and are taken where 128 rows leave rows past M or a last round of workgroups
+// mostly empty (tile_plan.h; 4096 x 28672 at M = 130 33.5 -> 26.1 us, 28672 x
+// 8192 with groups of 64 at M = 242 to 277 30 to 45 % less):
+//   - workgroup 16 RI rows x 256 columns (eight waves of 16 RI x 32, one workgroup
 //     per CU) or 128 x 128 (four waves, two per CU); a stage is 128 k = one
 //     group of G = 128, 32 matrix instructions per wave;
 //   - activations go through LDS (row stride 160 B: conflict-free operand
@@ -54,12 +58,12 @@ namespace w2 {
 
 namespace t128 {
 
-constexpr int RI = 8;                              // 16-row tiles per wave
 constexpr int CJ = 2;                              // 16-column blocks per wave
-constexpr int BM = 16 * RI, BK = 128;
+constexpr int BK = 128;
+constexpr int CP_ROWS = 128;                       // rows that a workgroup's threads stage (a lower tile's last row repeated)
 constexpr int WN = 16 * CJ;
 constexpr int A_STRIDE = BK + 32;                  // 32 mod 64 bytes: conflict-free A-operand reads
-constexpr int A_BUF = BM * A_STRIDE;
+constexpr int A_BUF = CP_ROWS * A_STRIDE;
 // LDS buffers: 3 with a barrier after every stage; 5 with a barrier after every other stage (eight-wave
 // workgroups, one per CU: the waves of a workgroup may then drift a stage apart inside a pair)
 constexpr int nbuf_of(int bn) { return bn >= 256 ? 5 : 3; }
@@ -67,10 +71,10 @@ constexpr int E_STRIDE = WN * 2 + 16;              // epilogue: bytes per LDS ro
 constexpr int BIAS = 1 << 21;                      // > 64 * 127 * 2 * 128 = 2 080 768
 constexpr float BIAS_F = 0x1p-128f;                // BIAS read as a float: 2^21 * 2^-149
 constexpr int waves_of(int bn) { return bn / WN; }
-constexpr int SX_BYTES = BM * 4;                   // the tile's activation scales, parked for the epilogue
+constexpr int SX_BYTES = CP_ROWS * 4;                   // the tile's activation scales, parked for the epilogue
 constexpr int lds_bytes(int bn)
 {
-    return nbuf_of(bn) * A_BUF > waves_of(bn) * BM * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * BM * E_STRIDE;
+    return nbuf_of(bn) * A_BUF > waves_of(bn) * CP_ROWS * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * CP_ROWS * E_STRIDE;
 }
 
 __device__ __forceinline__ v4i upconvert4(uint32_t w)
@@ -93,13 +97,14 @@ struct WTile {
 // c_rem ranges), one grid slice each; a range is entered by moving the base pointers, its fp32 results go to the
 // workspace and a second launch sums them (Sec. II-D, K-splitting for the smaller shapes).  An instantiation of
 // its own: the unsplit kernel is compiled exactly as before.
-template <int G, bool DBG, int BN, bool SPLIT = false>
+template <int G, bool DBG, int BN, bool SPLIT = false, int RI = 8>
 __global__ void __launch_bounds__(64 * waves_of(BN), BN >= 256 ? 1 : 2)
 a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, int c_rem)
 {
+    constexpr int BM = 16 * RI;
     constexpr int WAVES = waves_of(BN), THREADS = 64 * WAVES;
     constexpr int GPT = TILE_K / G;
-    constexpr int CPT = THREADS / BM;              // threads per activation row: 4 or 2
+    constexpr int CPT = THREADS / CP_ROWS;              // threads per activation row: 4 or 2
     constexpr int NV = BK / CPT / 16;              // 16-byte pieces per thread and stage: 2 or 4
     constexpr bool TWO_SETS = NV <= 2;             // two register sets: a load has two stages to land
     constexpr int NBUF = nbuf_of(BN);
@@ -152,7 +157,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     // global -> LDS copy: CPT threads per row, NV 16-byte pieces each; rows past M repeat the last row.
     // Lane offsets stay below 128 * K <= 2^31.
     const int cp_row = tid / CPT, cp_seg = tid % CPT;
-    int64_t cp_m = m0 + cp_row;
+    int64_t cp_m = m0 + min(cp_row, BM - 1);
     if (cp_m >= a.M) cp_m = a.M - 1;
     const char* cp_base = reinterpret_cast<const char*>(a.xq) + m0 * a.K + kt0 * TILE_K;  // uniform
     // piece v of a thread is the row's 16-byte piece v * CPT + cp_seg: the CPT threads of a row store CPT
@@ -220,7 +225,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     // the tile's activation scales, fetched now (unconditionally) and parked in LDS for the epilogue: loaded
     // there they would cost every workgroup a memory round trip with nothing to hide it
     float* sx_lds = reinterpret_cast<float*>(smem + lds_bytes(BN));
-    const float sx_mine = DBG ? 0.f : a.sx[min(m0 + (tid & (BM - 1)), a.M - 1)];
+    const float sx_mine = DBG ? 0.f : a.sx[min(m0 + (tid & (CP_ROWS - 1)), a.M - 1)];
 
     // prologue: stages 0 and 1 go to LDS; the registers then hold stage 2 (and 3)
     WTile<G> w0, w1;
@@ -239,15 +244,16 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         store_a(1, t1a, t1b, t1c, t1d);
         if constexpr (WR == 3) store_a(2, t2a, t2b, t2c, t2d);
     }
-    if (tid < BM) sx_lds[tid] = sx_mine;
+    if (tid < CP_ROWS) sx_lds[tid] = sx_mine;
     __syncthreads();
 
     const int8_t* a_base = smem + l16 * A_STRIDE + q * 16;
 
     // y += as_float(acc) * (sw * 2^64) for rows [i0, i0 + 4) of column block j
+    constexpr int H0 = RI / 2;                               // row tiles of the first half
     auto dequant_half = [&](int j, int i0, float swS, int64_t g) {
 #pragma unroll
-        for (int i = i0; i < i0 + RI / 2; ++i) {
+        for (int i = i0; i < (i0 ? RI : H0); ++i) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 if constexpr (DBG) {
@@ -327,12 +333,14 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         // region the scheduler pulled the fmas up to right behind the matrix instruction that produces their
         // operand, and every such pair stalls the wave until the matrix pipe has written the result (measured:
         // 2070 TOP/s; 4290 with the same fmas reading other registers).
-        auto interleave = [&](bool with_lds) {               // per matrix instruction: [one LDS read] three (five) vector instructions
+        auto interleave = [&](bool with_lds, int rows) {     // per matrix instruction: [one LDS read] its share of the vector instructions
 #pragma unroll
             for (int k = 0; k < RI; ++k) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (with_lds) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, G == 128 ? 3 : 5, 0);
+                if (rows == H0) __builtin_amdgcn_sched_group_barrier(0x002, (7 + 4 * H0 + RI - 1) / RI, 0);
+                else if (rows == RI) __builtin_amdgcn_sched_group_barrier(0x002, (7 + 4 * RI + RI - 1) / RI, 0);
+                else __builtin_amdgcn_sched_group_barrier(0x002, (7 + 4 * (RI - H0) + RI - 1) / RI, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -346,17 +354,17 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 #pragma unroll
             for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b00, biasv, 0, 0, 0);
             dequant_set(1, 1, pend_sw, pend_g);              // column 1's second group of the previous stage
-            interleave(true);
+            interleave(true, RI);
             const v4i b01 = upconvert4(dword_of(wc, 1, h, 0));
 #pragma unroll
             for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b10, biasv, 0, 0, 0);
             dequant_set(0, 0, sw0, 2 * g);
-            interleave(false);
+            interleave(false, RI);
             const v4i b11 = upconvert4(dword_of(wc, 1, h, 1));
 #pragma unroll
             for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b01, biasv, 0, 0, 0);
             dequant_set(1, 0, sw01, 2 * g + 1);
-            interleave(false);
+            interleave(false, RI);
 #pragma unroll
             for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
             b_next = upconvert4(dword_of(wn_tile, 0, h ^ 1, 0));
@@ -365,7 +373,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             dequant_set(0, 1, sw1, 2 * g);
             pend_sw = DBG ? 1.0f : sw11;
             pend_g = 2 * g + 1;
-            interleave(true);
+            interleave(true, RI);
             buf = buf1;
             if constexpr (NBUF == 3 || h == 1) __syncthreads();
             return;
@@ -377,31 +385,31 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b00, biasv, 0, 0, 0);
         dequant_half(1, 0, pend_sw, pend_g);
-        interleave(true);
+        interleave(true, H0);
         // block B
         const v4i b01 = upconvert4(dword_of(wc, 1, h, 0));
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b10, acc[i][0], 0, 0, 0);
-        dequant_half(1, RI / 2, pend_sw, pend_g);
+        dequant_half(1, H0, pend_sw, pend_g);
         ssum[1] += pend_sw;
-        interleave(false);
+        interleave(false, RI - H0);
         // block C
         const v4i b11 = upconvert4(dword_of(wc, 1, h, 1));
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b01, biasv, 0, 0, 0);
         dequant_half(0, 0, sw0, g);
-        interleave(false);
+        interleave(false, H0);
         // block D
 #pragma unroll
         for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
         b_next = upconvert4(dword_of(wn_tile, 0, h ^ 1, 0));
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b11, acc[i][1], 0, 0, 0);
-        dequant_half(0, RI / 2, sw0, g);
+        dequant_half(0, H0, sw0, g);
         ssum[0] += sw0;
         pend_sw = DBG ? 1.0f : sw1;
         pend_g = g;
-        interleave(true);
+        interleave(true, RI - H0);
         buf = buf1;
         if constexpr (NBUF == 3 || h == 1) __syncthreads();
     };
@@ -433,7 +441,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         dequant_set(1, 1, pend_sw, pend_g);
     } else {
         dequant_half(1, 0, pend_sw, pend_g);
-        dequant_half(1, RI / 2, pend_sw, pend_g);
+        dequant_half(1, H0, pend_sw, pend_g);
         ssum[1] += pend_sw;
     }
     if constexpr (DBG) return;
@@ -441,7 +449,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     // y_true = (y - BIAS*2^-149 * ssum) * 2^(149-64) * 2^-6 * sx.  The wave's 128 x 32 result goes through
     // LDS (its own region; the barrier at the end of the last stage freed the activation buffers) and
     // leaves as 16-byte stores.
-    int8_t* ebase = smem + wn * (BM * E_STRIDE);
+    int8_t* ebase = smem + wn * (CP_ROWS * E_STRIDE);
     uint16_t* eb = reinterpret_cast<uint16_t*>(ebase);
     const bool gated = a.epi.act == ACT_SILU_MUL;
     float bias[CJ];
@@ -468,9 +476,9 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         const int prow = lane >> 3, pcol = (lane & 7) * 4;   // eight lanes per row piece
         const int64_t n = n0 + wn * WN + pcol;
 #pragma unroll
-        for (int h = 0; h < RI / 4; ++h) {
+        for (int h = 0; h < (RI + 3) / 4; ++h) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < 4 && h * 4 + i < RI; ++i) {
                 const float4 s4 = *reinterpret_cast<const float4*>(sx_lds + (h * 4 + i) * 16 + 4 * q);
                 const float sr[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
@@ -485,7 +493,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
                 const int row = p * 8 + prow;
                 const int64_t m = m0 + h * 64 + row;
                 const float4 v = *reinterpret_cast<const float4*>(pbase + row * P_STRIDE + pcol * 4);
-                if (m < a.M && n < a.N) *reinterpret_cast<float4*>(dst + m * a.N + n) = v;   // N % 8 == 0: all 4 or none
+                if (h * 64 + row < BM && m < a.M && n < a.N) *reinterpret_cast<float4*>(dst + m * a.N + n) = v;   // N % 8 == 0: all 4 or none
             }
         }
         return;
@@ -522,18 +530,18 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     const int rpp = 64 / lpr;                                // rows per pass
     const int64_t ncol = (gated ? (n0 + wn * WN) / 2 : n0 + wn * WN) + (lane % lpr) * 8;   // first of this lane's 8 columns
     const int64_t n_out = gated ? a.N / 2 : a.N;
-    for (int p = 0; p < BM / rpp; ++p) {
+    for (int p = 0; p * rpp < BM; ++p) {
         const int row = p * rpp + lane / lpr;
         const int64_t m = m0 + row;
         const uint4 v = *reinterpret_cast<const uint4*>(ebase + row * E_STRIDE + (lane % lpr) * 16);
-        if (m < a.M && ncol < n_out) *reinterpret_cast<uint4*>(a.Y + m * a.ldy + ncol) = v;   // N % 8 == 0: all 8 or none
+        if (row < BM && m < a.M && ncol < n_out) *reinterpret_cast<uint4*>(a.Y + m * a.ldy + ncol) = v;   // N % 8 == 0: all 8 or none
     }
 }
 
-template <int G, bool DBG, int BN, bool SPLIT = false>
+template <int G, bool DBG, int BN, bool SPLIT = false, int RI = 8>
 static int launch(const A8Args& a, int splits, hipStream_t stream)
 {
-    constexpr int WAVES = waves_of(BN);
+    constexpr int WAVES = waves_of(BN), BM = 16 * RI;
     const int tiles_m = (int)((a.M + BM - 1) / BM);
     const int tiles_n = (int)((a.N + BN - 1) / BN);
     // Row tiles per band: the 32 workgroups resident on an XCD cover group_m row tiles x 32 / group_m column
@@ -541,7 +549,7 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
     // moves the least through the XCD's L2 (measured as fast as 8 at M = 2048, 2 % faster at M = 4096).
     const int group_m = a.tune.tiled_group_m ? a.tune.tiled_group_m : 4;
     constexpr int lds = lds_bytes(BN) + SX_BYTES;
-    auto kern = a8_tiled128_kernel<G, DBG, BN, SPLIT>;
+    auto kern = a8_tiled128_kernel<G, DBG, BN, SPLIT, RI>;
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, "w2_matmul_a8[tiled 128]")) return rc;
     const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n), (unsigned)(SPLIT ? splits : 1)), block(64 * WAVES);
     hipLaunchKernelGGL(kern, grid, block, lds, stream, a, tiles_m, tiles_n, group_m, (int)(a.n_kt / (SPLIT ? splits : 1)),
@@ -554,33 +562,44 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
 }  // namespace t128
 
 
-// K ranges across workgroups for the 128-row kernel: with room for partial results, 256-column workgroups
-// (one per CU) times floor(256 / tiles) ranges -- one round, never more -- up to 8, at least two 256-k tiles
-// each, at most 64 MiB of partial results (the rule that came out of the w2a16 kernel's sweeps, which has
-// the same tiling).
-int a8_tiled128_splits(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
-{
-    if (tune.splitk > 0) return (int)max((int64_t)1, min((int64_t)tune.splitk, min(cap, n_kt)));
-    const int64_t t256 = ((M + 127) / 128) * ((N + 255) / 256);
-    int64_t s = 256 / max(t256, (int64_t)1);
-    s = min(s, (int64_t)8);
-    s = min(s, n_kt / 2);
-    s = min(s, ((int64_t)64 << 20) / (M * N * (int64_t)sizeof(float)));
-    s = min(s, cap);
-    return s < 2 ? 1 : (int)s;
-}
-
-// splits: K ranges across workgroups (1 = none); the caller decides (a8_tiled128_splits is the rule).
-int launch_a8_tiled128(const A8Args& a, int splits, hipStream_t stream)
+// ri: row tiles per wave (256-column workgroups; the test-only export and forced 128-column ones have eight); splits: K
+// ranges across workgroups (1 = none).  The caller decides (tile_plan.h has the rule).
+int launch_a8_tiled128(const A8Args& a, int ri, int splits, hipStream_t stream)
 {
     const int64_t wgs256 = ((a.M + 127) / 128) * ((a.N + 255) / 256);
     const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    if (a.acc_out || splits > cap || splits > a.n_kt || a.G != 128) splits = 1;
+    if (a.acc_out || splits > cap || splits > a.n_kt) splits = 1;
+    if (splits >= 2 && a.tune.tiled_bn == 128 && a.G == 128) return t128::launch<128, false, 128, true>(a, splits, stream);
     if (splits >= 2) {
-        if (a.tune.tiled_bn == 128) return t128::launch<128, false, 128, true>(a, splits, stream);
-        return t128::launch<128, false, 256, true>(a, splits, stream);
+        switch (ri * 128 + a.G) {
+        case 4 * 128 + 64: return t128::launch<64, false, 256, true, 4>(a, splits, stream);
+        case 5 * 128 + 64: return t128::launch<64, false, 256, true, 5>(a, splits, stream);
+        case 6 * 128 + 64: return t128::launch<64, false, 256, true, 6>(a, splits, stream);
+        case 7 * 128 + 64: return t128::launch<64, false, 256, true, 7>(a, splits, stream);
+        case 8 * 128 + 64: return t128::launch<64, false, 256, true>(a, splits, stream);
+        case 4 * 128 + 128: return t128::launch<128, false, 256, true, 4>(a, splits, stream);
+        case 5 * 128 + 128: return t128::launch<128, false, 256, true, 5>(a, splits, stream);
+        case 6 * 128 + 128: return t128::launch<128, false, 256, true, 6>(a, splits, stream);
+        case 7 * 128 + 128: return t128::launch<128, false, 256, true, 7>(a, splits, stream);
+        default: return t128::launch<128, false, 256, true>(a, splits, stream);
+        }
     }
-    const int bn = a.tune.tiled_bn == 128 || a.tune.tiled_bn == 256 ? a.tune.tiled_bn : wgs256 <= 128 ? 128 : 256;
+    // (128 columns: forced ones only)
+    const int bn = a.tune.tiled_bn == 128 || a.tune.tiled_bn == 256 ? a.tune.tiled_bn : a.tune.tiled_bm == 128 && wgs256 <= 128 ? 128 : 256;
+    if (!a.acc_out && bn == 256) {
+        switch (ri * 128 + a.G) {
+        case 4 * 128 + 64: return t128::launch<64, false, 256, false, 4>(a, 1, stream);
+        case 5 * 128 + 64: return t128::launch<64, false, 256, false, 5>(a, 1, stream);
+        case 6 * 128 + 64: return t128::launch<64, false, 256, false, 6>(a, 1, stream);
+        case 7 * 128 + 64: return t128::launch<64, false, 256, false, 7>(a, 1, stream);
+        case 8 * 128 + 64: return t128::launch<64, false, 256>(a, 1, stream);
+        case 4 * 128 + 128: return t128::launch<128, false, 256, false, 4>(a, 1, stream);
+        case 5 * 128 + 128: return t128::launch<128, false, 256, false, 5>(a, 1, stream);
+        case 6 * 128 + 128: return t128::launch<128, false, 256, false, 6>(a, 1, stream);
+        case 7 * 128 + 128: return t128::launch<128, false, 256, false, 7>(a, 1, stream);
+        default: return t128::launch<128, false, 256>(a, 1, stream);
+        }
+    }
     if (a.G == 64) {
         if (a.acc_out) return bn == 128 ? t128::launch<64, true, 128>(a, 1, stream) : t128::launch<64, true, 256>(a, 1, stream);
         return bn == 128 ? t128::launch<64, false, 128>(a, 1, stream) : t128::launch<64, false, 256>(a, 1, stream);

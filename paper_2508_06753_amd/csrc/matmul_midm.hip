@@ -546,6 +546,13 @@ size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt)
     return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
 }
 
+double midm_us(int a16, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tune)
+{
+    double us = 0.0;
+    midm::plan(a16, M, n_cb, n_kt, gated, cap, tune, &us);
+    return us;
+}
+
 int launch_a8_midm(const A8Args& a, hipStream_t stream)
 {
     const midm::Head h = {(const char*)a.xq, (const char*)a.codes, (const char*)a.scales, (uint32_t)a.K, (int)a.M, (int)a.n_cb, (int)a.n_kt};

@@ -74,8 +74,9 @@ constexpr int64_t ROW_BYTES_FROM_L2 = 172000000;
 // fitted on 36 shapes from 8192 x 1024 to 28672 x 10240, int8 and bf16 rows), and it has to win by more than the model errs.
 constexpr double PARTS_US[2] = {1.0, 2.0}, PARTS_US_PER_VALUE[2] = {3e-6, 2e-6}, PARTS_MARGIN = 1.04;
 
-// `cap`: fp32 copies of the output that the workspace holds.
-inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune)
+// `cap`: fp32 copies of the output that the workspace holds.  us: where the price goes, if wanted.
+inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune,
+                 double* us = nullptr)
 {
     const double* c = COEF[xt];
     const int M = (int)M64, n_cb = (int)n_cb64, n_kt = (int)n_kt64;
@@ -139,6 +140,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);
             }
     }
+    if (us) *us = best_price;
     return best;
 }
 

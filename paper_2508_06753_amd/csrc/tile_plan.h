@@ -1,0 +1,149 @@
+// Launch shapes of the tiled kernels: host code only, no HIP, so that a test can compile it by itself.
+//
+// First, tile height and K ranges of the two kernels of 256-column workgroups (w2a8: matmul_a8_tiled128.hip, w2a16:
+// matmul_a16_fold.hip).
+//
+// A workgroup (eight waves, one per CU) multiplies 16 ri rows, ri = 4 to 8, by 256 columns over one of `splits` near-equal
+// ranges of K.  A taller tile shares an up-converted weight between more matrix instructions, but the workgroups run in
+// rounds of 256 and a last round costs almost as much as a full one, and rows past M are multiplied like the others: 4096 x
+// 28672 at M = 130 takes 33.5 us in two row tiles of 128 and 26.1 in two of 80; at M = 1000 130 us in 3.5 rounds of 128 rows
+// and 121 in 3.94 rounds of 112.  So every (ri, splits) is priced and the cheapest wins.  The prices are linear in what a
+// launch does, coefficients (us) fitted to graph-timed launches of every (ri, splits) on 280 (int8 rows, groups of 128), 100
+// (groups of 64) and 392 (bf16 rows) problems, K 1024 to 28672, N 1024 to 57344, 40 to 4096 rows: they are 3.2, 2.4 and 3.2 %
+// off in the root mean square, and the (ri, splits) that they choose are 0.2, 0.1 and 0.3 % slower than the fastest measured.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace w2 {
+
+namespace tiles {
+
+enum Kind { A8_G128, A8_G64, A16 };
+
+struct Shape {
+    int ri, splits;
+    double us;                                               // the price
+};
+
+constexpr int MAX_SPLITS = 8;
+constexpr int64_t MAX_PART_BYTES = (int64_t)64 << 20;        // most bytes of partial results
+
+struct Coef {
+    double launch, wg,                  // fixed, and per workgroup / 256
+           round, round_ri,             // first loads and epilogue, per round
+           tile, tile_ri, tile_ri_wg,   // per 256 k and round; per workgroup / 256 (a full chip holds lower clocks)
+           parts, part_value;           // the second launch, and per value of a partial result, written and read
+};
+constexpr Coef COEF[3] = {
+    {2.957, 2.057, 0.0, 0.3544, 0.5388, 0.1307, 0.01674, 4.368, 0.7115e-6},
+    {3.102, 2.146, 0.0, 0.3454, 0.5539, 0.1836, 0.01042, 4.137, 0.6599e-6},
+    {2.500, 1.610, 1.146, 0.3411, 1.297, 0.1271, 0.07422, 3.773, 0.7268e-6}};
+
+inline double price(Kind kind, int64_t M, int64_t N, int64_t n_kt, int ri, int splits)
+{
+    const Coef& c = COEF[kind];
+    const int64_t wgs = (M + 16 * ri - 1) / (16 * ri) * ((N + 255) / 256) * splits;
+    const double rounds = (double)((wgs + 255) / 256), fill = (double)wgs / 256.0, nk = (double)((n_kt + splits - 1) / splits);
+    double t = c.launch + c.wg * fill + rounds * (c.round + c.round_ri * ri) +
+               nk * (rounds * (c.tile + c.tile_ri * ri) + fill * c.tile_ri_wg * ri);
+    if (splits > 1) t += c.parts + c.part_value * (double)M * (double)N * splits;
+    return t;
+}
+
+// `cap`: fp32 copies of the output that the caller's workspace holds.  forced_ri, forced_splits: 0, or the only ones
+// considered (splits: as many of them as fit).
+inline Shape pick(Kind kind, int64_t M, int64_t N, int64_t n_kt, int64_t cap, int forced_ri = 0, int forced_splits = 0)
+{
+    Shape best = {8, 1, 1e30};
+    int64_t most = std::min(std::min(n_kt / 2, cap), std::min((int64_t)MAX_SPLITS, MAX_PART_BYTES / (M * N * 4)));
+    int64_t least = 1;
+    if (forced_splits > 0) least = most = std::max((int64_t)1, std::min((int64_t)forced_splits, std::min(cap, n_kt)));
+    for (int ri = forced_ri ? forced_ri : 4; ri <= (forced_ri ? forced_ri : 8); ++ri) {
+        const int64_t wgs = (M + 16 * ri - 1) / (16 * ri) * ((N + 255) / 256);
+        for (int64_t s = least; s == least || s <= most; ++s) {
+            if (s > 1 && s > least && wgs * s > 768) break;  // (parts of a grid that is several rounds anyway never paid)
+            const double t = price(kind, M, N, n_kt, ri, (int)s);
+            if (t < best.us) best = {ri, (int)s, t};
+        }
+    }
+    return best;
+}
+
+// ---- the 64-row kernel of w2a8 (matmul_a8_tiled.hip)
+
+// bn columns per workgroup, `kw` K ranges inside a workgroup (of bn / 32 waves each) times `splits` across workgroups.
+struct Shape64 {
+    int bn, kw, splits;
+    double us;
+};
+
+// 256-column workgroups (two per CU): linear in the workgroups of the busiest CU and the rounds, 83 and 78 launches (groups of
+// 128 and 64), 2.6 and 2.5 % off in the root mean square.
+inline double price64_wide(int G, int64_t M, int64_t N, int64_t n_kt, int splits)
+{
+    const int64_t wgs = (M + 63) / 64 * ((N + 255) / 256) * splits;
+    const double per_cu = (double)((wgs + 255) / 256), rounds = (double)((wgs + 511) / 512), fill = (double)wgs / 256.0;
+    const double nk = (double)((n_kt + splits - 1) / splits);
+    return G == 128 ? 5.121 + 1.922 * fill + nk * (0.6839 * per_cu + 0.2249 * rounds + 0.1988 * fill)
+                    : 4.816 + 1.459 * fill + 0.4825 * rounds + nk * (0.7930 * per_cu + 0.2442 * rounds + 0.2361 * fill);
+}
+
+// Narrow workgroups; a CU holds one of four K ranges, two of two, four of one.  Fitted to every (bn, kw, splits) on 130
+// problems for each group size that leave fewer than 400 workgroups of 256 columns: 4.2 and 3.8 % off; the choices are 0.7 and
+// 0.2 % slower than the fastest measured (3.4 and 7.8 % with prices from the work of the busiest CU alone).
+struct Coef64 {
+    double launch, wg, round,                                // fixed, per workgroup / 256, per round
+           tile_round, tile_cu, tile_wg;                     // per 256 k of a range: and round, busiest CU's workgroup, workgroup / 256
+};
+constexpr Coef64 COEF64[2][4] = {                            // 128 columns with 1, 2, 4 ranges; 64 columns
+    {{3.683, 0.8661, 0.0, 0.8142, 0.1763, 0.0448}, {4.361, 1.641, 0.3831, 0.3615, 0.9383, 0.0696},
+     {2.363, 0.7873, 3.827, 2.193, 0.0, 0.2682}, {5.479, 0.0, 0.0, 1.674, 0.0, 0.4263}},
+    {{3.351, 1.172, 0.0, 1.317, 0.3121, 0.0963}, {4.812, 1.785, 0.0, 0.2825, 1.190, 0.0},
+     {3.533, 1.848, 2.648, 3.240, 0.0, 0.3995}, {5.510, 0.0, 0.0, 1.933, 0.0, 0.3805}}};
+constexpr double PARTS64[2][2] = {{2.249, 1.767e-6}, {2.231, 1.726e-6}};   // the second launch; per value of a partial result
+
+inline double price64(int G, int64_t M, int64_t N, int64_t n_kt, int bn, int kw, int splits)
+{
+    const Coef64& c = COEF64[G == 128 ? 0 : 1][bn == 64 ? 3 : kw >> 1];
+    const int64_t wgs = (M + 63) / 64 * ((N + bn - 1) / bn) * splits;
+    const int64_t at_once = 256 * (4 / kw);
+    const double rounds = (double)((wgs + at_once - 1) / at_once), per_cu = (double)((wgs + 255) / 256), fill = (double)wgs / 256.0;
+    const double nk = (double)((n_kt + splits * kw - 1) / (splits * kw));
+    double t = c.launch + c.wg * fill + c.round * rounds + nk * (c.tile_round * rounds + c.tile_cu * per_cu + c.tile_wg * fill);
+    if (splits > 1) t += PARTS64[G == 128 ? 0 : 1][0] + PARTS64[G == 128 ? 0 : 1][1] * (double)M * (double)N * splits;
+    return t;
+}
+
+// The cheapest narrow launch that divides the tiles evenly.  forced_*: 0, or the only value considered (kw: or the next smaller
+// one that divides the tiles).  64 columns: four ranges, one round, K not split across workgroups (on top of those they lost
+// everywhere: 14336 x 4096 at M = 384 62 against 38 us).
+inline Shape64 pick64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, int forced_bn = 0, int forced_kw = 0, int forced_splits = 0)
+{
+    const int bn = forced_bn == 64 ? 64 : 128;
+    const int64_t room = std::max(cap, (int64_t)1), wgs = (M + 63) / 64 * ((N + bn - 1) / bn);
+    int64_t least = 1, most = std::min(std::min((int64_t)16, room), std::max((int64_t)1, ((int64_t)16 << 20) / (M * N * 4)));
+    if (forced_splits > 0) least = most = std::min((int64_t)forced_splits, std::min(room, n_kt));
+    Shape64 best = {bn, 1, (int)least, 1e30};
+    for (int kw = 4; kw >= 1; kw >>= 1) {
+        if (forced_kw && kw > forced_kw) continue;
+        for (int64_t s = least; s <= most && s <= n_kt; ++s) {
+            if (kw > 1 && n_kt % (kw * s) != 0) continue;
+            if (s > 1 && forced_splits <= 0 && (n_kt / (s * kw) < 2 || wgs * s * kw > 1600)) break;
+            const double t = price64(G, M, N, n_kt, bn, kw, (int)s);
+            if (t < best.us) best = {bn, kw, (int)s, t};
+        }
+        if (forced_kw && best.us < 1e30) break;
+    }
+    if (!forced_bn && forced_splits <= 1 && (forced_kw == 0 || forced_kw == 4) && n_kt % 4 == 0 && (M + 63) / 64 * ((N + 63) / 64) <= 256) {
+        const double t = price64(G, M, N, n_kt, 64, 4, 1);
+        if (t < best.us) best = {64, 4, 1, t};
+    }
+    return best;
+}
+
+}  // namespace tiles
+
+}  // namespace w2

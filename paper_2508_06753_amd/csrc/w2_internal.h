@@ -82,8 +82,11 @@ int launch_a8_smallm(const A8Args& a, hipStream_t stream);
 bool a8_midm_supports(const A8Args& a);
 int launch_a8_midm(const A8Args& a, hipStream_t stream);
 int launch_a8_tiled(const A8Args& a, hipStream_t stream);
-int launch_a8_tiled128(const A8Args& a, int splits, hipStream_t stream);
-int a8_tiled128_splits(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune);
+int launch_a8_tiled128(const A8Args& a, int ri, int splits, hipStream_t stream);
+// What the kernels that AUTO chooses between are expected to take (us), with room for `cap` fp32 copies of the output.
+double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune);
+double a16_tiled_us(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune);
+double midm_us(int a16, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tune);
 
 // The decode kernel (M <= 32; rows quantised in the kernel: M <= 4): xt 0 = int8 rows (a.xq / a.sx), 1 = fp32 rows,
 // 2 = bf16 rows quantised in the kernel.
