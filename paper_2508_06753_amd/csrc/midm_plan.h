@@ -27,39 +27,135 @@ constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
 // K is split across (parts).
 struct Plan { int rt, cj, ks, sh, sp; };
 
-// Waves of each instantiation that a SIMD's registers hold (int8, bf16 rows; [rt - 1][cj: 1, 2, 4]).
-constexpr int SIMD_WAVES[2][4][3] = {{{6, 5, 4}, {4, 3, 2}, {4, 3, 2}, {3, 2, 2}},
-                                     {{6, 5, 4}, {4, 3, 2}, {3, 3, 2}, {4, 2, 2}}};
+constexpr int MAX_CJ = 5;
+// Waves of each instantiation that a SIMD's registers hold (int8, bf16 rows; [rt - 1][cj - 1]).
+constexpr int SIMD_WAVES[2][4][MAX_CJ] = {{{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {4, 3, 2, 2, 2}, {3, 2, 2, 2, 1}},
+                                          {{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {3, 3, 2, 2, 2}, {4, 2, 2, 2, 1}}};
 
-// The shapes of a workgroup: K ranges x waves that share one, and how many such workgroups a CU holds.
-constexpr int FORMS[4][2] = {{16, 1}, {8, 1}, {4, 1}, {2, 2}};
+// The shapes of a workgroup: K ranges x waves that share one.
+constexpr int N_FORMS = 5;
+constexpr int FORMS[N_FORMS][2] = {{16, 1}, {8, 1}, {4, 1}, {2, 2}, {4, 2}};
+constexpr int FORM_LOG[N_FORMS] = {4, 3, 2, 1, 2};           // FORMS[f][0] == 1 << FORM_LOG[f]
 constexpr int resident_of(int xt, int rt, int cj, int ks, int sh)
 {
     const int by_lds = 160 * 1024 / (ks * range_lds(rt, cj, sh) + rt * 64);
-    const int by_regs = 4 * SIMD_WAVES[xt][rt - 1][cj >> 1] / (ks * sh);
+    const int by_regs = 4 * SIMD_WAVES[xt][rt - 1][cj - 1] / (ks * sh);
     const int r = by_lds < by_regs ? by_lds : by_regs;
     return r > 1 ? r : 1;
 }
 struct Resident {
-    int8_t n[2][4][3][4];
+    int8_t n[2][4][MAX_CJ][N_FORMS];                         // workgroups that a CU holds
     constexpr Resident() : n{}
     {
         for (int xt = 0; xt < 2; ++xt)
             for (int rt = 1; rt <= 4; ++rt)
-                for (int cj = 1; cj <= 4; cj *= 2)
-                    for (int f = 0; f < 4; ++f) n[xt][rt - 1][cj >> 1][f] = (int8_t)resident_of(xt, rt, cj, FORMS[f][0], FORMS[f][1]);
+                for (int cj = 1; cj <= MAX_CJ; ++cj)
+                    for (int f = 0; f < N_FORMS; ++f) n[xt][rt - 1][cj - 1][f] = (int8_t)resident_of(xt, rt, cj, FORMS[f][0], FORMS[f][1]);
     }
 };
 constexpr Resident RESIDENT;
 
-// Every candidate shape is priced with a linear model and the cheapest wins.  The terms are what the busiest CU has to
-// do (nb workgroups, in rounds of as many as it holds at a time), the coefficients (us) a least-squares fit to 4400
-// graph-timed launches: 20 projection shapes from 2048 x 2048 and 28672 x 1024 to 8192 x 57344, 4 to 192 rows.  On 70
-// further shapes (K 2048 to 28672, N 1024 to 28672, 3 to 240 rows) its choices are on average 2.7 % (int8 rows) and
-// 0.9 % (bf16 rows) slower than the fastest shape measured.
-constexpr double COEF[2][13] = {
+// Which shapes are built and offered.  Three and five column blocks per wave are there for the balance of wide grids, below.
+constexpr bool built(int xt, int rt, int cj, int f)
+{
+    if (cj == 1) return rt == 1 && f <= 2;
+    if (f == 0) return rt == 1 && cj == 2;
+    if (cj == 5 && rt == 4) return false;                    // more registers than there are
+    if (f == 3) return cj == 3 || (xt == 0 && cj != 5);
+    if (f == 4) return cj == 3 || cj == 5;
+    return true;
+}
+
+// Every candidate shape is priced and the cheapest wins.  The price is linear in what the busiest CU has to do (in rounds of
+// as many workgroups as it holds at a time); the coefficients (us) are least-squares fits to graph-timed launches.
+//
+// Up to 512 column blocks one set for all forms: 4400 launches, 20 projections, 4 to 192 rows; on 70 further shapes (K 2048 to
+// 28672, 3 to 240 rows) its choices are 2.7 % (int8 rows) and 0.9 % (bf16 rows) slower than the fastest measured.
+constexpr int NARROW_BLOCKS = 512;
+constexpr double NARROW[2][13] = {
     {1.525, 0.1987e-2, 0.6254e-2, 1.419e-2, 1.127e-4, 0.3743e-4, 0.8993e-2, 0.4517e-1, 0.3403e-1, 0.6996, 0.6068e-1, 0.7275e-1, 0.3929e-3},
     {1.677, 1.494e-2, 0.3030e-2, 3.895e-2, 0.9297e-4, 0.9087e-4, 0.7657e-2, 0.0, 0.5634e-1, 0.4702, 0.9276e-1, 1.174e-1, 0.1319e-3}};
+
+// Above, a set for every (column blocks per wave, form): 19000 launches, 33 projections from 1024 x 9728 to 23040 x 16736 and
+// 8192 x 57344, 8 to 256 rows; on those the chosen shapes are 1.4 and 0.9 % slow (worst 15 %), where one set for all forms chose
+// 3.5 and 2.5 % slow (worst 38 %), and their prices 4 % off in the root mean square.  (On narrower grids it is no better than the one set, and on
+// 54 of 264 problems that neither was fitted to 2 to 25 % slower.)
+struct Coef {
+    double launch,
+           tile, tile_rt, wg_rt,        // per workgroup of the busiest CU: a tile of its K range, times row tiles; reduce and store
+           stream, stream_band,         // per tile of the projection: from memory, and once per band out of the L2s
+           round_tile, round_tile_rt, round, round_rt,       // per round: latency of a tile; start and end of a wave
+           range_tile,                  // per tile of a K range
+           rows_mb;                     // per MB of rows that all workgroups together read
+};
+constexpr Coef COEF[2][MAX_CJ][N_FORMS] = {                  // int8, bf16 rows; cj 1 to 5; forms
+    {
+     {{2.431, 0, 0, 1.048, 0.0001273, 2.015e-06, 0.3426, 0, 0, 0, 0.3202, 0.0242},
+      {2.163, 0, 0.09833, 0.2592, 0.000117, 3.393e-05, 0, 0, 0.1782, 0, 0.3913, 0.02309},
+      {1.598, 0, 0, 0.1994, 0.0001609, 6.715e-05, 0, 0, 0, 0, 0.1526, 0.02484},
+      {},
+      {}},
+     {{2.664, 0, 0, 1.128, 0.0001125, 1.338e-05, 0.4408, 0, 0, 0, 0.4218, 0.02653},
+      {2.085, 0, 0.1529, 0.4011, 9.513e-05, 5.021e-05, 0, 0, 0, 0, 0.2687, 0.02794},
+      {1.781, 0, 0.03083, 0.1981, 0.0001224, 3.459e-05, 0, 0.04539, 0.1191, 0, 0.2562, 0.0317},
+      {2.197, 0.1084, 0.02598, 0.2066, 9.056e-05, 0, 0, 0.08755, 0, 0.1804, 0.1111, 0.02454},
+      {}},
+     {{},
+      {1.894, 0.02003, 0.2264, 0.4611, 9.165e-05, 3.522e-05, 0, 0, 0.4704, 0.03959, 0.2737, 0.02961},
+      {2.053, 0.07646, 0.05088, 0.2303, 0.0001018, 2.088e-05, 0, 0.05488, 0.2526, 0.08886, 0.1662, 0.03273},
+      {2.132, 0.1999, 0.001542, 0.363, 7.641e-05, 0, 0.02526, 0.1406, 0.3148, 0.1909, 0.1545, 0.02994},
+      {1.865, 0.3416, 0.04713, 0.5481, 5.089e-05, 3.261e-05, 0, 0.1352, 0.3251, 0.1703, 0.3333, 0.02748}},
+     {{},
+      {1.657, 0, 0.1718, 0.4612, 0.0001061, 4.125e-05, 0.1183, 0.05242, 0.5533, 0, 0.2812, 0.03284},
+      {2.106, 0.0858, 0.05403, 0.2751, 9.8e-05, 3.066e-05, 0, 0.06871, 0.1138, 0.1826, 0.2346, 0.03084},
+      {2.625, 0.1489, 0.04238, 0.4777, 8.78e-05, 0, 0, 0.1018, 0, 0.2283, 0.316, 0.03639},
+      {}},
+     {{},
+      {2.486, 0, 0.2194, 0.8893, 7.169e-05, 4.504e-05, 0.3758, 0, 0.09598, 0, 0.1051, 0.03307},
+      {2.979, 0.2958, 0.08543, 0.3727, 7.825e-05, 1.922e-06, 0.1439, 0.01192, 0, 0.167, 0.08797, 0.03184},
+      {},
+      {2.774, 0.8062, 0.2497, 1.225, 8.42e-05, 0, 0, 0, 0, 0, 0.248, 0.02686}},
+    },
+    {
+     {{2.415, 0.1537, 0, 0.8938, 0.000125, 0.0001161, 0, 0, 0, 0, 0.9699, 0.02509},
+      {2.07, 0, 0, 0.275, 0.0001237, 0.0001512, 0, 0, 0, 0, 0.7189, 0.02172},
+      {1.524, 0.005756, 0, 0.2092, 0.0001979, 0.0001296, 0, 0, 0, 0, 0.2151, 0.01965},
+      {},
+      {}},
+     {{2.353, 0, 0, 0.9682, 9.553e-05, 0.0001533, 0.09447, 0, 0, 0, 1.576, 0.02023},
+      {2.235, 0, 0, 0, 9.657e-05, 0.000128, 0, 0.2732, 0.1739, 0.2768, 0.5055, 0.02159},
+      {1.987, 0, 0.06387, 0.1528, 0.0001231, 8.57e-05, 0, 0.1168, 0.04058, 0, 0.3335, 0.0241},
+      {},
+      {}},
+     {{},
+      {2.124, 0.01793, 0.2754, 0.3611, 8.289e-05, 0.0001082, 0, 0.1328, 0.3913, 0, 0.3668, 0.02087},
+      {2.319, 0.04381, 0.1128, 0.2272, 0.0001005, 8.079e-05, 0.06799, 0.07761, 0.02371, 0.01999, 0.3068, 0.02387},
+      {2.767, 0.4085, 0.02473, 0.416, 6.769e-05, 0, 0, 0.1281, 0, 0.0613, 0.4312, 0.03212},
+      {2.436, 0.7357, 0.3551, 0.5488, 5.968e-05, 7.868e-06, 0, 0, 0.08837, 0, 0.4526, 0.02128}},
+     {{},
+      {1.648, 0, 0.3189, 0.2526, 8.117e-05, 0.000116, 0.1001, 0.08021, 0.9146, 0, 0.5014, 0.02632},
+      {2.123, 0.1475, 0.1689, 0.1968, 7.354e-05, 6.388e-05, 0.1357, 0.01849, 0.2683, 0.1653, 0.4311, 0.02372},
+      {},
+      {}},
+     {{},
+      {1.821, 0.6328, 0.445, 0, 6.619e-05, 0.0001025, 0, 0, 1.664, 0.4319, 0, 0.0224},
+      {3.174, 0.3759, 0.2008, 0.3178, 6.152e-05, 4.659e-05, 0.2204, 0, 0, 0.1713, 0.2458, 0.02338},
+      {},
+      {3.012, 2.04, 0.3912, 1.104, 5.608e-05, 0, 0, 0, 0, 0, 0.199, 0.02283}},
+    }};
+
+// Three or five column blocks per wave: on more than 512 blocks, where no CU then has more of them to do than with any even
+// number (fewer, where waves share a range): 5120 x 34816, 2176 blocks, takes 15.2 us with 16 int8 rows in 544 workgroups of four
+// blocks, 12 on the busiest CU, and 13.5 in 726 of three, 9 on it; with 48 bf16 rows 32.9 and 27.4 (2 x 5 blocks); 8192 x 20480
+// with 32 int8 rows 17.2 and 14.3.  Over 23 projections of 9216 to 57344 columns the fastest shapes gain 3 % (int8 rows) and 6 %
+// (bf16 rows) by it.
+inline int busiest(int n_cb, int width, int bands) { return (((n_cb + width - 1) / width * bands + 255) >> 8) * width; }
+inline bool odd_balances(int n_cb, int cj, int sh, int bands)
+{
+    if (n_cb <= NARROW_BLOCKS || bands > 4) return false;
+    const int odd = busiest(n_cb, cj * sh, bands), even = std::min(busiest(n_cb, 2 * sh, bands), busiest(n_cb, 4 * sh, bands));
+    return sh == 1 ? odd <= even : odd < even;
+}
 
 // Int8 rows: what all workgroups together read of the rows comes out of the L2s at about 12 MB a microsecond; on a deep K
 // that is what a launch of narrow workgroups waits for, and the linear terms have no such limit.  Above 172 MB shapes of one
@@ -78,7 +174,6 @@ constexpr double PARTS_US[2] = {1.0, 2.0}, PARTS_US_PER_VALUE[2] = {3e-6, 2e-6},
 inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune,
                  double* us = nullptr)
 {
-    const double* c = COEF[xt];
     const int M = (int)M64, n_cb = (int)n_cb64, n_kt = (int)n_kt64;
     const double tiles = (double)n_cb * n_kt;
     const double part_us = PARTS_US_PER_VALUE[xt] * 16 * M * (double)n_cb;
@@ -87,42 +182,57 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
     Plan best = {1, 2, 1, 1, 1};
     double best_price = 1e30;
     // (this runs on every call of up to 256 rows: no division but by powers of two, where it can be had)
-    auto price = [&](const Plan& p, int bands, int groups, int T, int resident) {
-        const int wgs = groups * bands * p.sp, waves = p.ks * p.sh;
-        const int nb = (wgs + 255) >> 8;
+    const bool narrow = n_cb <= NARROW_BLOCKS;
+    const double row_mb = (double)M * n_kt * (xt == 0 ? 256e-6 : 512e-6);
+    auto price = [&](const Plan& p, int f, int bands, int groups, int T, int resident) {
+        const int nb = (groups * bands * p.sp + 255) >> 8;
         const int rounds = nb <= resident ? 1 : (nb + resident - 1) / resident;
-        const int rc = p.rt * p.cj;
-        double t = c[0]
-                 + (double)(nb * waves) * T * (c[1] * p.cj               // up-converts
-                                               + c[2] * rc)             // matrix instructions and dequant
-                 + c[3] * ((double)(nb * p.ks) * T * p.rt)               // activations through the L1
-                 + tiles * (c[4] + c[5] * bands)                         // the weight stream; ... once per band out of L2
-                 + c[6] * (nb * waves * rc)                              // reduce and store
-                 + (double)rounds * T * (c[7] + c[8] * rc)               // latency per tile, multiply,
-                 + rounds * (c[9] + c[10] * rc)                          // start and end of a wave
-                 + c[11] * T
-                 + c[12] * wgs;                                          // workgroups to launch
+        double t;
+        if (narrow) {
+            const double* c = NARROW[xt];
+            const int waves = p.ks * p.sh, rc = p.rt * p.cj;
+            t = c[0]
+              + (double)(nb * waves) * T * (c[1] * p.cj                  // up-converts
+                                          + c[2] * rc)                  // matrix instructions and dequant
+              + c[3] * ((double)(nb * p.ks) * T * p.rt)                  // activations through the L1
+              + tiles * (c[4] + c[5] * bands)                            // the weight stream; ... once per band out of L2
+              + c[6] * (nb * waves * rc)                                 // reduce and store
+              + (double)rounds * T * (c[7] + c[8] * rc)                  // latency per tile, multiply,
+              + rounds * (c[9] + c[10] * rc)                             // start and end of a wave
+              + c[11] * T
+              + c[12] * (groups * bands * p.sp);                         // workgroups to launch
+        } else {
+            const Coef& c = COEF[xt][p.cj - 1][f];
+            t = c.launch + nb * (T * (c.tile + c.tile_rt * p.rt) + c.wg_rt * p.rt) + tiles * (c.stream + c.stream_band * bands) +
+                rounds * (T * (c.round_tile + c.round_tile_rt * p.rt) + c.round + c.round_rt * p.rt) + c.range_tile * T +
+                c.rows_mb * row_mb * groups;
+        }
         if (p.sp > 1) t = PARTS_MARGIN * (t + PARTS_US[xt] + part_us * p.sp);
         return t;
     };
     const int row_tiles = std::min((M + 15) / 16, 4);
-    for (int rt = 1; rt <= row_tiles; ++rt) {
+    // (wide grids, one row tile per wave: up to four bands; beyond, every band streams and up-converts the weights again)
+    for (int rt = M > 64 && !narrow ? 2 : 1; rt <= row_tiles; ++rt) {
         const int bands = (M + 16 * rt - 1) / (16 * rt);
-        for (int lj = rt == 1 ? 0 : 1; lj <= 2; ++lj)
-            for (int f = max_waves(rt, 1 << lj) == 16 ? 0 : 1; f < (xt == 0 ? 4 : 3); ++f) {
-                const int cj = 1 << lj, sh = FORMS[f][1], lw = lj + (sh - 1);       // 1 << lw column blocks per workgroup
-                if (gated && lw == 0) continue;                          // a workgroup pairs gate and up blocks
-                if (cbw && 1 << lw != cbw) continue;
-                const int groups = (n_cb + (1 << lw) - 1) >> lw;
-                if (xt == 0 && lw <= 1 && !cbw && (int64_t)groups * M * n_kt * 256 > ROW_BYTES_FROM_L2) continue;
-                const int resident = RESIDENT.n[xt][rt - 1][cj >> 1][f];
+        for (int cj = rt == 1 ? 1 : 2; cj <= MAX_CJ; ++cj)
+            for (int f = 0; f < N_FORMS; ++f) {
+                if (!built(xt, rt, cj, f)) continue;
+                const int sh = FORMS[f][1], width = cj * sh;             // column blocks per workgroup
+                const bool odd = cj == 3 || cj == 5;
+                if (odd && !odd_balances(n_cb, cj, sh, bands)) continue;
+                if (gated && (width & 1)) continue;                      // a workgroup pairs gate and up blocks
+                if (cbw && width != cbw) continue;
+                const int groups = (n_cb + width - 1) / width;
+                if (xt == 0 && width <= 2 && !cbw && (int64_t)groups * M * n_kt * 256 > ROW_BYTES_FROM_L2) continue;
+                const int resident = RESIDENT.n[xt][rt - 1][cj - 1][f];
                 auto offer = [&](int ks, int sp, int T, int res) {
                     const Plan p = {rt, cj, ks, sh, sp};
-                    const double t = price(p, bands, groups, T, res);
+                    const double t = price(p, f, bands, groups, T, res);
                     if (t < best_price) { best = p; best_price = t; }
                 };
-                const int lk = 4 - f;                                    // FORMS[f][0] == 1 << lk
+                const int lk = FORM_LOG[f];
                 if (forced > 1) {
+                    if (odd) continue;
                     const int ks = std::max(1, std::min(1 << lk, n_kt / forced));
                     offer(ks, forced, (n_kt + ks * forced - 1) / (ks * forced), resident);
                     continue;
@@ -134,7 +244,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 // numbers of parts were hardly ever faster by more than 3 %.  From K = 8192 on, with int8 rows from 20480 (17408 x
                 // 1024 at M = 5 7.1 us in parts, 5.6 in one piece).
                 const int wgs = groups * bands;
-                if (cap < 2 || n_kt < (xt == 0 ? 80 : 32) || lw == 0 || f == 0 || tune.splitk == 1) continue;
+                if (cap < 2 || n_kt < (xt == 0 ? 80 : 32) || cj == 1 || odd || f == 0 || tune.splitk == 1) continue;
                 const int at_once = wgs <= 128 ? 256 : xt == 1 && wgs <= 256 && resident >= 2 ? 512 : 0;
                 const int sp = (int)std::min<int64_t>(std::min(at_once / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
                 if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);

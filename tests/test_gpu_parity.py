@@ -945,6 +945,33 @@ def test_a16_fused_epilogues(w2, K, N, G, with_bias, act):
             check_epilogue(bf16_bits(Y), y64, mag, bias, act, f"a16 epilogue {name} M={M} K={K} N={N} G={G} act={act}")
 
 
+# rows int8 0 / bf16 1, M, K, N, gated: three and five column blocks per wave (the launch shapes are pinned on the CPU), a wave
+# each or in pairs that share a K range; 1 to 4 row tiles, a last tile of one row, a last block of eight columns, a last
+# workgroup with one block, K ranges of one and of several tiles, idle ranges
+WIDE_MIDM = [(0, 64, 1024, 8776, 0), (0, 16, 2048, 22432, 1), (0, 96, 768, 11560, 0), (0, 48, 768, 21928, 0),
+             (0, 96, 2048, 10912, 1), (1, 32, 1280, 17928, 0), (1, 16, 2048, 8760, 0), (1, 32, 1024, 23200, 1),
+             (1, 31, 2048, 16392, 0), (1, 96, 1536, 8264, 0), (1, 96, 1536, 19360, 1), (1, 64, 1280, 18336, 1), (0, 64, 4096, 8200, 0),
+             (1, 64, 768, 18952, 0)]
+
+
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("xt,M,K,N,gated", WIDE_MIDM)
+def test_midm_odd_widths(w2, xt, M, K, N, gated, G):
+    codes, scales, X = synth.make_problem(M, K, N, G, 0, M + K + N)
+    packed = w2.prepack(dev(codes), dev(scales), G, 0)
+    act = w2.ACT_SILU_MUL if gated else w2.ACT_NONE
+    if xt == 0:
+        oq, osx, _ = oracle.quantize_rows(X, G)
+        _, y64 = oracle.matmul_a8(codes, scales, G, 0, oq, osx)
+        mag = oracle.a8_term_magnitude(codes, scales, G, 0, oq, osx)
+        Y = w2.matmul_a8_epi(packed, K, N, G, dev(oq), dev(osx), act=act, variant=w2.VARIANT_MIDM)
+    else:
+        Xb = synth.f32_to_bf16_bits(X)
+        _, y64, mag = oracle.matmul_a16(codes, scales, G, 0, Xb)
+        Y = w2.matmul_a16_epi(packed, K, N, G, dev(Xb).view(torch.bfloat16), act=act, variant=w2.VARIANT_MIDM)
+    check_epilogue(bf16_bits(Y), y64, mag, None, act, f"xt={xt} M={M} K={K} N={N} G={G} act={act}")
+
+
 def test_epilogue_argument_errors(w2):
     K, N, G = 256, 48, 128                                   # N % 32 != 0
     codes, scales, X = synth.make_problem(1, K, N, G, 0, 0)

@@ -90,3 +90,33 @@ def test_k_across_workgroups(plans):
             assert cap >= 2 and K >= (20480 if xt == 0 else 8192) and wgs * sp <= (256 if xt == 0 or wgs <= 128 else 512)
             assert ks * sp <= K // 512
     assert split > 50
+
+
+def test_odd_widths(plans):
+    # three or five column blocks per wave: only above 512 blocks, where the busiest CU then has no more blocks to do than with
+    # two or four; in pairs (an even number per workgroup) for the gated epilogue; never with K split across workgroups
+    def busiest(blocks, width, bands):
+        return -(-(-(-blocks // width) * bands) // 256) * width
+
+    problems = [(xt, M, K, N, g, 0, cap, 0) for xt in (0, 1) for K in (768, 1280, 2048, 5120) for N in range(7968, 36000, 544)
+                for M in (3, 16, 31, 33, 49, 64, 96, 240) for g in (0, 1) for cap in (0, 16)]
+    odd = set()
+    for (xt, M, K, N, g, _, _, _), (rt, cj, ks, sh, sp) in zip(problems, plans(problems)):
+        if cj not in (3, 5):
+            continue
+        blocks, bands = -(-N // 16), -(-M // (16 * rt))
+        assert blocks > 512 and sp == 1 and bands <= 4 and not (g and sh == 1) and not (rt == 4 and cj == 5)
+        assert ks * sh <= 8 and ks * max(rt * 2048 * sh, sh * rt * 16 * (cj * 16 + 4) * 4) + rt * 64 <= 160 * 1024
+        assert busiest(blocks, cj * sh, bands) <= min(busiest(blocks, 2 * sh, bands), busiest(blocks, 4 * sh, bands))
+        odd.add((xt, cj, sh))
+    assert odd >= {(0, 3, 1), (0, 3, 2), (1, 3, 1), (1, 3, 2), (1, 5, 1), (1, 5, 2)}
+    # the sizes that the GPU tests run
+    for p, want in (((0, 64, 1024, 8776, 0, 0), (1, 3, 4, 1)), ((0, 16, 2048, 22432, 1, 0), (1, 3, 4, 2)),
+                    ((0, 96, 768, 11560, 0, 0), (2, 3, 3, 1)), ((0, 48, 768, 21928, 0, 0), (3, 3, 3, 1)),
+                    ((0, 96, 2048, 10912, 1, 0), (3, 3, 4, 2)), ((1, 32, 1280, 17928, 0, 0), (1, 3, 4, 1)),
+                    ((1, 16, 2048, 8760, 0, 0), (1, 3, 8, 1)), ((1, 32, 1024, 23200, 1, 0), (2, 3, 4, 2)),
+                    ((1, 31, 2048, 16392, 0, 0), (2, 5, 8, 1)), ((1, 96, 1536, 8264, 0, 0), (3, 5, 6, 1)),
+                    ((1, 96, 1536, 19360, 1, 0), (3, 5, 4, 2)), ((1, 64, 1280, 18336, 1, 0), (4, 3, 2, 2)), ((0, 64, 4096, 8200, 0, 0), (2, 5, 8, 1)),
+                    ((1, 64, 768, 18952, 0, 0), (4, 3, 3, 1))):
+        (got,) = plans([p])
+        assert got == want + (1,), (p, got)
