@@ -58,7 +58,7 @@ constexpr Resident RESIDENT;
 // Which shapes are built and offered.  Three and five column blocks per wave are there for the balance of wide grids, below.
 constexpr bool built(int xt, int rt, int cj, int f)
 {
-    if (cj == 1) return rt == 1 && f <= 2;
+    if (cj == 1) return rt == 1 && (f <= 2 || (f == 3 && xt == 0));
     if (f == 0) return rt == 1 && cj == 2;
     if (cj == 5 && rt == 4) return false;                    // more registers than there are
     if (f == 3) return cj == 3 || (xt == 0 && cj != 5);
@@ -220,6 +220,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 const int sh = FORMS[f][1], width = cj * sh;             // column blocks per workgroup
                 const bool odd = cj == 3 || cj == 5;
                 if (odd && !odd_balances(n_cb, cj, sh, bands)) continue;
+                if (!narrow && cj == 1 && sh == 2) continue;             // (not fitted there: four blocks per workgroup and more win)
                 if (gated && (width & 1)) continue;                      // a workgroup pairs gate and up blocks
                 if (cbw && width != cbw) continue;
                 const int groups = (n_cb + width - 1) / width;

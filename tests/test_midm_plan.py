@@ -120,3 +120,9 @@ def test_odd_widths(plans):
                     ((1, 64, 768, 18952, 0, 0), (4, 3, 3, 1))):
         (got,) = plans([p])
         assert got == want + (1,), (p, got)
+
+
+def test_pairs_of_one_block(plans):
+    # int8 rows: two waves of one column block each on one K range, on narrow grids of short launches
+    for M, K, N in ((57, 1536, 4672), (77, 2560, 3360), (210, 1024, 1600), (169, 2560, 1632)):
+        assert plans([(0, M, K, N, int(N % 32 == 0), 0)]) == [(1, 1, 2, 2, 1)]
