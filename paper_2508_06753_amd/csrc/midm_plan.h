@@ -78,8 +78,7 @@ constexpr double NARROW[2][13] = {
 
 // Above, a set for every (column blocks per wave, form): 19000 launches, 33 projections from 1024 x 9728 to 23040 x 16736 and
 // 8192 x 57344, 8 to 256 rows; on those the chosen shapes are 1.4 and 0.9 % slow (worst 15 %), where one set for all forms chose
-// 3.5 and 2.5 % slow (worst 38 %), and their prices 4 % off in the root mean square.  (On narrower grids it is no better than the one set, and on
-// 54 of 264 problems that neither was fitted to 2 to 25 % slower.)
+// 3.5 and 2.5 % slow (worst 38 %), and their prices 4 % off in the root mean square.
 struct Coef {
     double launch,
            tile, tile_rt, wg_rt,        // per workgroup of the busiest CU: a tile of its K range, times row tiles; reduce and store
