@@ -76,7 +76,7 @@ constexpr double NARROW[2][13] = {
     {1.525, 0.1987e-2, 0.6254e-2, 1.419e-2, 1.127e-4, 0.3743e-4, 0.8993e-2, 0.4517e-1, 0.3403e-1, 0.6996, 0.6068e-1, 0.7275e-1, 0.3929e-3},
     {1.677, 1.494e-2, 0.3030e-2, 3.895e-2, 0.9297e-4, 0.9087e-4, 0.7657e-2, 0.0, 0.5634e-1, 0.4702, 0.9276e-1, 1.174e-1, 0.1319e-3}};
 
-// Above, a set for every (column blocks per wave, form): 19000 launches, 33 projections from 1024 x 9728 to 23040 x 16736 and
+// Above, a set for every (column blocks per wave, form): 16000 launches, 33 projections from 1024 x 9728 to 23040 x 16736 and
 // 8192 x 57344, 8 to 256 rows; on those the chosen shapes are 1.4 and 0.9 % slow (worst 15 %), where one set for all forms chose
 // 3.5 and 2.5 % slow (worst 38 %), and their prices 4 % off in the root mean square.
 struct Coef {
