@@ -6,6 +6,7 @@
 // order and rounds to bf16 once.
 #include <hip/hip_runtime.h>
 
+#include "tile_plan.h"
 #include "w2_internal.h"
 
 namespace w2 {
@@ -20,7 +21,7 @@ int splitk_plan(int64_t wgs, int64_t n_kt, int64_t min_tiles, int64_t M, int64_t
     int64_t s = (384 + wgs - 1) / wgs;
     s = min(s, n_kt / min_tiles);
     s = min(s, (int64_t)16);
-    s = min(s, max_bytes / (M * N * (int64_t)sizeof(float)));
+    s = min(s, tiles::copies(max_bytes, M, N));
     s = min(s, cap);
     return s < 2 ? 1 : (int)s;
 }

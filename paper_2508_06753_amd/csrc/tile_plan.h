@@ -31,6 +31,9 @@ struct Shape {
 constexpr int MAX_SPLITS = 8;
 constexpr int64_t MAX_PART_BYTES = (int64_t)64 << 20;        // most bytes of partial results
 
+// fp32 copies of the output in so many bytes (no product that a row count without limit could overflow to zero)
+inline int64_t copies(int64_t bytes, int64_t M, int64_t N) { return bytes / 4 / M / N; }
+
 struct Coef {
     double launch, wg,                  // fixed, and per workgroup / 256
            round, round_ri,             // first loads and epilogue, per round
@@ -58,7 +61,7 @@ inline double price(Kind kind, int64_t M, int64_t N, int64_t n_kt, int ri, int s
 inline Shape pick(Kind kind, int64_t M, int64_t N, int64_t n_kt, int64_t cap, int forced_ri = 0, int forced_splits = 0)
 {
     Shape best = {8, 1, 1e30};
-    int64_t most = std::min(std::min(n_kt / 2, cap), std::min((int64_t)MAX_SPLITS, MAX_PART_BYTES / (M * N * 4)));
+    int64_t most = std::min(std::min(n_kt / 2, cap), std::min((int64_t)MAX_SPLITS, copies(MAX_PART_BYTES, M, N)));
     int64_t least = 1;
     if (forced_splits > 0) least = most = std::max((int64_t)1, std::min((int64_t)forced_splits, std::min(cap, n_kt)));
     for (int ri = forced_ri ? forced_ri : 4; ri <= (forced_ri ? forced_ri : 8); ++ri) {
@@ -124,7 +127,7 @@ inline Shape64 pick64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, in
 {
     const int bn = forced_bn == 64 ? 64 : 128;
     const int64_t room = std::max(cap, (int64_t)1), wgs = (M + 63) / 64 * ((N + bn - 1) / bn);
-    int64_t least = 1, most = std::min(std::min((int64_t)16, room), std::max((int64_t)1, ((int64_t)16 << 20) / (M * N * 4)));
+    int64_t least = 1, most = std::min(std::min((int64_t)16, room), std::max((int64_t)1, copies((int64_t)16 << 20, M, N)));
     if (forced_splits > 0) least = most = std::min((int64_t)forced_splits, std::min(room, n_kt));
     Shape64 best = {bn, 1, (int)least, 1e30};
     for (int kw = 4; kw >= 1; kw >>= 1) {

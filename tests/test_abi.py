@@ -4,6 +4,8 @@ import ctypes
 import os
 import re
 
+import pytest
+
 from paper_2508_06753_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -53,6 +55,15 @@ def test_sizes_and_shape_rules_on_host():
     assert lib.w2_packed_size(256, 64, 128, None) == binding.ERR_INVALID_ARG
     assert lib.w2_status_string(0) == b"ok"
     assert lib.w2_status_string(binding.ERR_MISALIGNED) == b"misaligned pointer or stride"
+
+
+@pytest.mark.parametrize("a16", [False, True])
+def test_workspace_size_takes_any_row_count(a16):
+    # row counts whose product with N overflows 64 bits (to zero, for the powers of two): an answer, not a trap
+    for M in [1 << b for b in range(24, 63)] + [3 << 48, (1 << 50) + 1, (1 << 63) - 1]:
+        for K, N in ((256, 8), (4096, 4096), (28672, 4096), (4096, 28672), (2048, 1 << 24)):
+            for G in (64, 128):
+                assert binding.workspace_size(M, K, N, G, a16=a16) >= 0
 
 
 def test_null_and_misaligned_arguments_rejected_before_launch():
