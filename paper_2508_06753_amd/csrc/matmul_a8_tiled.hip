@@ -36,7 +36,6 @@
 
 #include <type_traits>
 
-#include "tile_plan.h"
 #include "w2_internal.h"
 
 #if defined(__HIP_DEVICE_COMPILE__) && defined(__FAST_MATH__)
@@ -512,67 +511,20 @@ static int launch_tiled(const A8Args& a_in, int splits, hipStream_t stream)
     return launch_splitk_reduce(a.part, splits, a.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
-// 256 columns per workgroup unless that leaves the chip's 512 workgroup slots clearly underfilled
-static int tiled_bn(int64_t M, int64_t N, const w2_tuning_t& tune)
-{
-    const int64_t wgs256 = ((M + tiled::BM - 1) / tiled::BM) * ((N + 255) / 256);
-    int bn = tune.tiled_bn;
-    if (bn != 64 && bn != 128 && bn != 256) bn = wgs256 < 400 ? 128 : 256;
-    return bn;
-}
-
-// Fewer than 400 tiles of 64 x 256: from a few dozen to a few hundred workgroups against 256 CUs, so K is cut both across and
-// inside workgroups of 128 or 64 columns, by price (tile_plan.h).  More tiles: K is split only to fill the chip (splitk_plan).
-static tiles::Shape64 tiled_plan(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
-{
-    if (tiled_bn(M, N, tune) != 256) return tiles::pick64(G, M, N, n_kt, cap, tune.tiled_bn, tune.tiled_kw, tune.splitk);
-    const int64_t wgs = (M + tiled::BM - 1) / tiled::BM * ((N + 255) / 256);
-    const int splits = tune.splitk > 0 ? (int)min((int64_t)tune.splitk, min(max(cap, (int64_t)1), n_kt))
-                                       : splitk_plan(wgs, n_kt, tune.splitk_min_tiles ? tune.splitk_min_tiles : 12, M, N, cap);
-    return {256, 1, splits, tiles::price64_wide(G, M, N, n_kt, splits)};
-}
-
-// The kernel for a problem of many rows: 64-row tiles as planned above, or the taller tiles of matmul_a8_tiled128.hip, by
-// price.
-struct A8Tiles {
-    bool tall;
-    int ri, splits;                                          // (tall)
-    double us;
-};
-
-static A8Tiles a8_tiles(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
-{
-    const tiles::Kind kind = G == 128 ? tiles::A8_G128 : tiles::A8_G64;
-    // tuning and tests: forced 128-row tiles; forced shapes that only the 64-row kernel has
-    if (tune.tiled_bm == 128) {
-        const tiles::Shape t = tiles::pick(kind, M, N, n_kt, cap, 8, tune.splitk);
-        return {true, 8, t.splits, t.us};
-    }
-    const tiles::Shape64 p = tiled_plan(M, N, n_kt, G, cap, tune);
-    if (tune.tiled_bm == 64 || tune.tiled_bn == 64 || tune.tiled_bn == 128 || tune.tiled_kw || tune.tiled_wd) return {false, 0, p.splits, p.us};
-    const tiles::Shape t = tiles::pick(kind, M, N, n_kt, cap, 0, tune.splitk);
-    // (256-column workgroups: the margins that leave the fewest of 380 measured problems slower than in these tiles)
-    const bool tall = t.us < p.us * (p.bn < 256 ? 1.0 : G == 128 ? 0.985 : 0.965);
-    return tall ? A8Tiles{true, t.ri, t.splits, t.us} : A8Tiles{false, 0, p.splits, p.us};
-}
-
 double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
 {
-    return a8_tiles(M, N, n_kt, G, cap, tune).us;
+    return tiles::a8_shape(G, M, N, n_kt, cap, tune).us;
 }
 
 size_t a8_tiled_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, int G, const w2_tuning_t& tune)
 {
-    const int s = a8_tiles(M, N, n_kt, G, 16, tune).splits;
+    const int s = tiles::a8_shape(G, M, N, n_kt, 16, tune).splits;
     return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
 }
 
 template <int G, bool DBG>
-static int launch_tiled_bn(const A8Args& a, hipStream_t stream)
+static int launch_tiled_bn(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
 {
-    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    tiles::Shape64 p = tiled_plan(a.M, a.N, a.n_kt, G, cap, a.tune);
-    if (DBG) { p.splits = 1; p.kw = 1; }
     const int splits = p.splits;
     if constexpr (!DBG) {
         if (a.tune.tiled_wd == 8) {
@@ -592,11 +544,11 @@ static int launch_tiled_bn(const A8Args& a, hipStream_t stream)
 int launch_a8_tiled(const A8Args& a, hipStream_t stream)
 {
     const int64_t cap = a.part && !a.acc_out ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const A8Tiles t = a8_tiles(a.M, a.N, a.n_kt, a.G, cap, a.tune);
-    if (t.tall) return launch_a8_tiled128(a, t.ri, t.splits, stream);
+    const tiles::A8Shape p = tiles::a8_shape(a.G, a.M, a.N, a.n_kt, cap, a.tune);
+    if (p.ri) return launch_a8_tiled128(a, p, stream);
     if (a.G == 128)
-        return a.acc_out ? launch_tiled_bn<128, true>(a, stream) : launch_tiled_bn<128, false>(a, stream);
-    return a.acc_out ? launch_tiled_bn<64, true>(a, stream) : launch_tiled_bn<64, false>(a, stream);
+        return a.acc_out ? launch_tiled_bn<128, true>(a, p, stream) : launch_tiled_bn<128, false>(a, p, stream);
+    return a.acc_out ? launch_tiled_bn<64, true>(a, p, stream) : launch_tiled_bn<64, false>(a, p, stream);
 }
 
 }  // namespace w2

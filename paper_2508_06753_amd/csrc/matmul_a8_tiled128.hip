@@ -562,50 +562,43 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
 }  // namespace t128
 
 
-// ri: row tiles per wave (256-column workgroups; the test-only export and forced 128-column ones have eight); splits: K
-// ranges across workgroups (1 = none).  The caller decides (tile_plan.h has the rule).
-int launch_a8_tiled128(const A8Args& a, int ri, int splits, hipStream_t stream)
+// The test-only export and 128-column workgroups have eight row tiles per wave.
+int launch_a8_tiled128(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
 {
-    const int64_t wgs256 = ((a.M + 127) / 128) * ((a.N + 255) / 256);
-    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    if (a.acc_out || splits > cap || splits > a.n_kt) splits = 1;
-    if (splits >= 2 && a.tune.tiled_bn == 128 && a.G == 128) return t128::launch<128, false, 128, true>(a, splits, stream);
-    if (splits >= 2) {
-        switch (ri * 128 + a.G) {
-        case 4 * 128 + 64: return t128::launch<64, false, 256, true, 4>(a, splits, stream);
-        case 5 * 128 + 64: return t128::launch<64, false, 256, true, 5>(a, splits, stream);
-        case 6 * 128 + 64: return t128::launch<64, false, 256, true, 6>(a, splits, stream);
-        case 7 * 128 + 64: return t128::launch<64, false, 256, true, 7>(a, splits, stream);
-        case 8 * 128 + 64: return t128::launch<64, false, 256, true>(a, splits, stream);
-        case 4 * 128 + 128: return t128::launch<128, false, 256, true, 4>(a, splits, stream);
-        case 5 * 128 + 128: return t128::launch<128, false, 256, true, 5>(a, splits, stream);
-        case 6 * 128 + 128: return t128::launch<128, false, 256, true, 6>(a, splits, stream);
-        case 7 * 128 + 128: return t128::launch<128, false, 256, true, 7>(a, splits, stream);
-        default: return t128::launch<128, false, 256, true>(a, splits, stream);
+    if (a.acc_out) {
+        if (a.G == 64) return p.bn == 128 ? t128::launch<64, true, 128>(a, 1, stream) : t128::launch<64, true, 256>(a, 1, stream);
+        return p.bn == 128 ? t128::launch<128, true, 128>(a, 1, stream) : t128::launch<128, true, 256>(a, 1, stream);
+    }
+    if (p.bn == 128) {
+        if (a.G == 64) return t128::launch<64, false, 128>(a, 1, stream);
+        return p.splits >= 2 ? t128::launch<128, false, 128, true>(a, p.splits, stream) : t128::launch<128, false, 128>(a, 1, stream);
+    }
+    if (p.splits >= 2) {
+        switch (p.ri * 128 + a.G) {
+        case 4 * 128 + 64: return t128::launch<64, false, 256, true, 4>(a, p.splits, stream);
+        case 5 * 128 + 64: return t128::launch<64, false, 256, true, 5>(a, p.splits, stream);
+        case 6 * 128 + 64: return t128::launch<64, false, 256, true, 6>(a, p.splits, stream);
+        case 7 * 128 + 64: return t128::launch<64, false, 256, true, 7>(a, p.splits, stream);
+        case 8 * 128 + 64: return t128::launch<64, false, 256, true>(a, p.splits, stream);
+        case 4 * 128 + 128: return t128::launch<128, false, 256, true, 4>(a, p.splits, stream);
+        case 5 * 128 + 128: return t128::launch<128, false, 256, true, 5>(a, p.splits, stream);
+        case 6 * 128 + 128: return t128::launch<128, false, 256, true, 6>(a, p.splits, stream);
+        case 7 * 128 + 128: return t128::launch<128, false, 256, true, 7>(a, p.splits, stream);
+        default: return t128::launch<128, false, 256, true>(a, p.splits, stream);
         }
     }
-    // (128 columns: forced ones only)
-    const int bn = a.tune.tiled_bn == 128 || a.tune.tiled_bn == 256 ? a.tune.tiled_bn : a.tune.tiled_bm == 128 && wgs256 <= 128 ? 128 : 256;
-    if (!a.acc_out && bn == 256) {
-        switch (ri * 128 + a.G) {
-        case 4 * 128 + 64: return t128::launch<64, false, 256, false, 4>(a, 1, stream);
-        case 5 * 128 + 64: return t128::launch<64, false, 256, false, 5>(a, 1, stream);
-        case 6 * 128 + 64: return t128::launch<64, false, 256, false, 6>(a, 1, stream);
-        case 7 * 128 + 64: return t128::launch<64, false, 256, false, 7>(a, 1, stream);
-        case 8 * 128 + 64: return t128::launch<64, false, 256>(a, 1, stream);
-        case 4 * 128 + 128: return t128::launch<128, false, 256, false, 4>(a, 1, stream);
-        case 5 * 128 + 128: return t128::launch<128, false, 256, false, 5>(a, 1, stream);
-        case 6 * 128 + 128: return t128::launch<128, false, 256, false, 6>(a, 1, stream);
-        case 7 * 128 + 128: return t128::launch<128, false, 256, false, 7>(a, 1, stream);
-        default: return t128::launch<128, false, 256>(a, 1, stream);
-        }
+    switch (p.ri * 128 + a.G) {
+    case 4 * 128 + 64: return t128::launch<64, false, 256, false, 4>(a, 1, stream);
+    case 5 * 128 + 64: return t128::launch<64, false, 256, false, 5>(a, 1, stream);
+    case 6 * 128 + 64: return t128::launch<64, false, 256, false, 6>(a, 1, stream);
+    case 7 * 128 + 64: return t128::launch<64, false, 256, false, 7>(a, 1, stream);
+    case 8 * 128 + 64: return t128::launch<64, false, 256>(a, 1, stream);
+    case 4 * 128 + 128: return t128::launch<128, false, 256, false, 4>(a, 1, stream);
+    case 5 * 128 + 128: return t128::launch<128, false, 256, false, 5>(a, 1, stream);
+    case 6 * 128 + 128: return t128::launch<128, false, 256, false, 6>(a, 1, stream);
+    case 7 * 128 + 128: return t128::launch<128, false, 256, false, 7>(a, 1, stream);
+    default: return t128::launch<128, false, 256>(a, 1, stream);
     }
-    if (a.G == 64) {
-        if (a.acc_out) return bn == 128 ? t128::launch<64, true, 128>(a, 1, stream) : t128::launch<64, true, 256>(a, 1, stream);
-        return bn == 128 ? t128::launch<64, false, 128>(a, 1, stream) : t128::launch<64, false, 256>(a, 1, stream);
-    }
-    if (a.acc_out) return bn == 128 ? t128::launch<128, true, 128>(a, 1, stream) : t128::launch<128, true, 256>(a, 1, stream);
-    return bn == 128 ? t128::launch<128, false, 128>(a, 1, stream) : t128::launch<128, false, 256>(a, 1, stream);
 }
 
 }  // namespace w2

@@ -2,29 +2,13 @@
 // K for the smaller GEMM shapes): when a problem has too few output tiles to
 // fill the chip, each tile's K range is cut into `splits` parts computed by
 // different workgroups, which leave fp32 partial results in a workspace; this
-// file holds the plan and the second launch that sums the parts in a fixed
-// order and rounds to bf16 once.
+// file holds the second launch, which sums the parts in a fixed order and
+// rounds to bf16 once (the plans: tile_plan.h, midm_plan.h).
 #include <hip/hip_runtime.h>
 
-#include "tile_plan.h"
 #include "w2_internal.h"
 
 namespace w2 {
-
-int splitk_plan(int64_t wgs, int64_t n_kt, int64_t min_tiles, int64_t M, int64_t N, int64_t cap, int64_t max_bytes)
-{
-    // enough parts for about 1.5 workgroups per CU; a part spans at least min_tiles 256-k tiles (below
-    // that the partial results and the second launch cost more than the idle CUs); at most 16 parts
-    // and at most max_bytes (16 MiB unless the caller says otherwise) of partial results (the second launch
-    // reads them all)
-    if (wgs >= 192 || cap < 2) return 1;
-    int64_t s = (384 + wgs - 1) / wgs;
-    s = min(s, n_kt / min_tiles);
-    s = min(s, (int64_t)16);
-    s = min(s, tiles::copies(max_bytes, M, N));
-    s = min(s, cap);
-    return s < 2 ? 1 : (int)s;
-}
 
 // Sum over the parts of eight adjacent columns, part 0 first.  All SMAX loads are issued before the
 // first addition (a loop with a run-time trip count would wait for each part's round trip in turn);

@@ -17,6 +17,8 @@
 
 #include <algorithm>
 
+#include "../../include/w2mm.h"
+
 namespace w2 {
 
 namespace tiles {
@@ -145,6 +147,65 @@ inline Shape64 pick64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, in
         if (t < best.us) best = {64, 4, 1, t};
     }
     return best;
+}
+
+// 256 columns per workgroup: K split across workgroups only to fill the chip, in enough parts for about 1.5 workgroups per
+// CU.  A part spans at least min_tiles 256-k tiles (below that the partial results and the second launch cost more than the
+// idle CUs); at most 16 parts and 16 MiB of partial results (the second launch reads them all).
+inline int splits64_wide(int64_t wgs, int64_t n_kt, int64_t min_tiles, int64_t M, int64_t N, int64_t cap)
+{
+    if (wgs >= 192 || cap < 2) return 1;
+    int64_t s = (384 + wgs - 1) / wgs;
+    s = std::min(std::min(s, n_kt / min_tiles), std::min((int64_t)16, cap));
+    s = std::min(s, copies((int64_t)16 << 20, M, N));
+    return s < 2 ? 1 : (int)s;
+}
+
+// 256 columns per workgroup unless that leaves the chip's 512 workgroup slots clearly underfilled.  Fewer than 400 tiles of
+// 64 x 256: from a few dozen to a few hundred workgroups against 256 CUs, so K is cut both across and inside workgroups of
+// 128 or 64 columns, by price.
+inline Shape64 shape64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+{
+    const int64_t wgs = (M + 63) / 64 * ((N + 255) / 256);
+    const int bn = tune.tiled_bn;
+    if (bn == 64 || bn == 128 || (bn != 256 && wgs < 400)) return pick64(G, M, N, n_kt, cap, bn, tune.tiled_kw, tune.splitk);
+    const int splits = tune.splitk > 0 ? (int)std::min((int64_t)tune.splitk, std::min(std::max(cap, (int64_t)1), n_kt))
+                                       : splits64_wide(wgs, n_kt, tune.splitk_min_tiles ? tune.splitk_min_tiles : 12, M, N, cap);
+    return {256, 1, splits, price64_wide(G, M, N, n_kt, splits)};
+}
+
+// ---- w2a8: which of its two kernels, and its launch shape
+
+struct A8Shape {
+    int ri;                                                  // 16-row tiles per wave of the tall kernel (4 to 8); 0: the 64-row kernel
+    int bn, kw, splits;                                      // columns per workgroup, K ranges inside and across workgroups
+    double us;                                               // the price
+};
+
+inline A8Shape a8_shape(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+{
+    const Kind kind = G == 128 ? A8_G128 : A8_G64;
+    if (tune.tiled_bm == 128) {                              // forced 128-row tiles (tuning and tests)
+        const Shape t = pick(kind, M, N, n_kt, cap, 8, tune.splitk);
+        const bool few = (M + 127) / 128 * ((N + 255) / 256) <= 128;
+        const int bn = tune.tiled_bn == 128 || tune.tiled_bn == 256 ? tune.tiled_bn : few && t.splits < 2 ? 128 : 256;
+        // (128 columns and groups of 64: no instantiation that splits K)
+        return {8, bn, 1, bn == 128 && G == 64 ? 1 : t.splits, t.us};
+    }
+    const Shape64 p = shape64(G, M, N, n_kt, cap, tune);
+    const A8Shape low = {0, p.bn, p.kw, p.splits, p.us};
+    // forced shapes that only the 64-row kernel has
+    if (tune.tiled_bm == 64 || tune.tiled_bn == 64 || tune.tiled_bn == 128 || tune.tiled_kw || tune.tiled_wd) return low;
+    const Shape t = pick(kind, M, N, n_kt, cap, 0, tune.splitk);
+    // (256-column workgroups: the margins that leave the fewest of 380 measured problems slower than in these tiles)
+    const bool tall = t.us < p.us * (p.bn < 256 ? 1.0 : G == 128 ? 0.985 : 0.965);
+    return tall ? A8Shape{t.ri, 256, 1, t.splits, t.us} : low;
+}
+
+// ---- w2a16: the scale-folded kernel; forced 128-column workgroups keep 128 rows (tuning and tests)
+inline Shape a16_shape(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+{
+    return pick(A16, M, N, n_kt, cap, tune.tiled_bn == 128 ? 8 : 0, tune.splitk);
 }
 
 }  // namespace tiles

@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include "../../include/w2mm.h"
+#include "tile_plan.h"
 #include "w2_layout.h"
 
 namespace w2 {
@@ -82,7 +83,7 @@ int launch_a8_smallm(const A8Args& a, hipStream_t stream);
 bool a8_midm_supports(const A8Args& a);
 int launch_a8_midm(const A8Args& a, hipStream_t stream);
 int launch_a8_tiled(const A8Args& a, hipStream_t stream);
-int launch_a8_tiled128(const A8Args& a, int ri, int splits, hipStream_t stream);
+int launch_a8_tiled128(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream);
 // What the kernels that AUTO chooses between are expected to take (us), with room for `cap` fp32 copies of the output.
 double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune);
 double a16_tiled_us(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune);
@@ -119,12 +120,6 @@ int launch_a16_gemv(const A16Args& a, hipStream_t stream);
 bool a16_midm_supports(const A16Args& a);
 int launch_a16_midm(const A16Args& a, hipStream_t stream);
 
-// Split-K across workgroups for shapes whose output tiles are too few to fill the chip (Sec. II-D,
-// K-splitting for smaller GEMM shapes).  splitk_plan: number of K ranges for `wgs` output tiles of a
-// kernel whose K loop has `n_kt` 256-k tiles (a part spans at least `min_tiles` of them), given room
-// for `cap` fp32 copies of the M x N output.
-int splitk_plan(int64_t wgs, int64_t n_kt, int64_t min_tiles, int64_t M, int64_t N, int64_t cap,
-                int64_t max_bytes = (int64_t)16 << 20);
 // Bytes of workspace with which the tiled kernels would split K for this problem (0: they would not).
 size_t a8_tiled_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, int G, const w2_tuning_t& tune);
 size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt);

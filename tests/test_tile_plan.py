@@ -22,7 +22,14 @@ int main()
     int kind, f1, f2, f3;
     long long M, N, n_kt, cap;
     while (scanf(" %%c %%d %%lld %%lld %%lld %%lld %%d %%d %%d", &what, &kind, &M, &N, &n_kt, &cap, &f1, &f2, &f3) == 9) {
-        if (what == 't') {
+        if (what == 'a') {                                   // the whole choice for w2a8: kind is G, the forced tiled_bm, tiled_bn, splitk
+            w2_tuning_t tune = {};
+            tune.tiled_bm = f1;
+            tune.tiled_bn = f2;
+            tune.splitk = f3;
+            const A8Shape s = a8_shape(kind, M, N, n_kt, cap, tune);
+            printf("%%d %%d %%d %%.9g\n", 16 * s.ri, s.bn, s.splits, s.us);
+        } else if (what == 't') {
             const Shape s = pick((Kind)kind, M, N, n_kt, cap, f1, f2);
             printf("%%d %%d 0 %%.9g\n", s.ri, s.splits, s.us);
         } else {
@@ -97,6 +104,18 @@ def test_narrow_64_row_tiles(plans):
             assert k == 4 and s == 1 and -(-M // 64) * -(-N // 64) <= 256
 
 
+def test_forced_tiles(plans):
+    # a forced width and height are what runs, whatever the price says of K ranges; parts only as far as there is room
+    ask = [("a", G, M, N, K // 256, cap, bm, bn, forced) for G in (64, 128) for K, N in SHAPES for M in ROWS for cap in (0, 1, 3, 16)
+           for bm, bn, forced in ((128, 128, 0), (128, 128, 3), (128, 256, 0), (128, 256, 16), (128, 0, 0), (64, 64, 0), (64, 128, 0), (64, 256, 0),
+                                  (64, 0, 0), (0, 64, 0), (0, 128, 2))]
+    for (_, G, _, _, n_kt, cap, bm, bn, forced), (rows, width, splits, _) in zip(ask, plans(ask)):
+        assert rows == (128 if bm == 128 else 0)                             # (0: the 64-row kernel)
+        assert width == bn if bn else width in ((128, 256) if bm == 128 else (64, 128, 256))
+        assert 1 <= splits <= max(1, min(cap, n_kt))
+        assert splits == 1 or not (bm == 128 and width == 128 and G == 64)    # (not built)
+
+
 def test_heights_are_the_librarys_choice(plans):
     ask = [("t", KINDS[p, G], M, N, K // 256, 16, 0, 0, 0) for p, G, K, N, M, _, _ in HEIGHTS]
     for case, (ri, splits, _, us) in zip(HEIGHTS, plans(ask)):
@@ -142,3 +161,24 @@ def test_tile_heights(path, G, K, N, M, ri, split, gated):
         check_epilogue(np.ascontiguousarray(bf16_bits(Y)[:, ocols]), y64, mag, None, act, what)
     else:
         check_y(np.ascontiguousarray(bf16_bits(Y)[:, cols]), Yo, y64, mag, what)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(129, 4608, 288), (256, 1024, 1056)])
+def test_forced_width_groups_of_64_with_a_workspace(M, K, N):
+    # 128-row tiles of 128 columns, groups of 64: K is never cut into ranges there, so that room for partial results
+    # changes nothing, bit for bit
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_06753_amd import binding as w2
+    from test_gpu_parity import bf16_bits, check_y, dev
+    codes, scales, X = synth.make_problem(M, K, N, 64, 0, seed=M + K + N)
+    packed = w2.prepack(dev(codes), dev(scales), 64, 0)
+    xq, sx, _ = w2.quantize_rows(dev(X), 64)
+    ws = torch.empty(8 * M * N * 4, dtype=torch.uint8, device="cuda")
+    tune = {"tiled_bm": 128, "tiled_bn": 128}
+    Y, Z = (bf16_bits(w2.matmul_a8(packed, K, N, 64, xq, sx, variant=w2.VARIANT_TILED, workspace=w, tune=tune)) for w in (ws, None))
+    assert np.array_equal(Y, Z)
+    oq, osx, _ = oracle.quantize_rows(X, 64)
+    Yo, y64 = oracle.matmul_a8(codes, scales, 64, 0, oq, osx)
+    check_y(Y, Yo, y64, oracle.a8_term_magnitude(codes, scales, 64, 0, oq, osx), f"128 x 128 tiles M={M} K={K} N={N} G=64")
