@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "../../include/w2mm.h"
+#include "auto_plan.h"
 #include "w2_internal.h"
 
 namespace w2 {
@@ -261,63 +262,23 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
     a.part_bytes = workspace ? workspace_bytes : 0;
     a.epi = epi;
     a.tune = tn;
-    int fallback = W2_VARIANT_SMALLM;                        // where the decode kernel cannot hold the rows
-    if (variant == W2_VARIANT_AUTO) {
-        // Few rows: the decode kernel, which reads the weights once and keeps whole rows in local memory (the MFMA
-        // form is at least as fast as dot4 from M = 1 on).  Then the mid-M kernel, then the tiled ones.
-        // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
-        // before against the mid-M kernel): at M = 9 in general (4096 x 6144 5.3 against 5.2 at M = 16; 4096 x 28672 at
-        // M = 8 / 9 9.2 / 10.1 against 9.6 / 9.7; 8192 x 10240 8.8 / 11.7 against 8.8 / 8.9).  At M = 5 where the decode
-        // kernel has few workgroups and two pieces of a row per thread (decode / mid-M at M = 5 and 8, 192 to 512 column
-        // blocks: K = 4096 0.91 .. 1.05, but 1.20 on 320 blocks; K = 5120 1.08 .. 1.24, 6144 1.03 .. 1.20, 7168 0.91 .. 1.10,
-        // 8192 0.93 .. 1.01), on a deep K of few columns (17408 x 1024 1.19, x 2048 0.98), and below where it cannot hold the
-        // rows in one round of workgroups (17408 x 5120 1.35, x 4096 0.94).  At 13 on 16384 columns and more with groups of
-        // 64 (5120 x 34816 at M = 12 / 16 15.2 / 21.4 against 16.1 / 17.2).  At 17 where K near 8192 keeps its whole grid
-        // busy in one round, 768 to 1024 column blocks (K = 8192 at M = 9 .. 16 0.91 .. 0.97, 7168 1.00 .. 1.05).
-        const int dot4_max = tn.dot4_max_m;
-        const bool wide = a.n_cb >= 1024;
-        const int midm_from = a.n_kt > 28 && a.n_kt <= 32 && a.n_cb >= 768 && a.n_cb <= 1024 ? 17
-                            : wide                                                           ? (G == 128 ? 9 : 13)
-                            : (a.n_kt > 64 && a.n_cb < 128) || (a.n_kt > 16 && a.n_kt <= 26 && a.n_cb <= 512) ? 5 : 9;
-        const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
-        // Upper end, against the tiled kernels with a workspace: they win earlier the more columns there are to fill
-        // the chip with (2048 x 57344 at M = 48 / 64 16.6 / 17.4 us against 15.3 / 18.5; 4096 x 28672 at M = 96 / 128
-        // 24.3 / 25.2 against 20.4 / 24.9; 8192 x 10240 at M = 160 / 192 24.8 / 25.1 against 24.3 / 26.0; 5120 x 7168
-        // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7; 28672 x 5120 at M = 240 50.2 against 54.5).
-        const int midm_max = tn.midm_max_m ? tn.midm_max_m
-                           : a.n_cb >= 2560 ? 48 : a.n_cb >= 1536 ? 112 : a.n_cb > 448 ? 160 : G == 128 && a.n_kt > 104 && a.n_cb > 256 ? 192 : 240;
-        // Below it, from 33 rows on, they are taken where their price (tile_plan.h) is under the mid-M kernel's (midm_plan.h)
-        // by more than that one errs: with less of a margin 28672 x 8192 at M = 100 takes 38.0 us instead of 35.2.
-        const int64_t cap = a.part && !acc_out ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
-        const bool tiled_first = M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m &&
-                                 a8_tiled_us(M, N, a.n_kt, G, cap, tn) < 0.86 * midm_us(0, M, a.n_cb, a.n_kt, epi.act == ACT_SILU_MUL, cap, tn);
-        const bool midm_ok = M >= midm_min && M <= midm_max && !tiled_first && a8_midm_supports(a);
-        // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
-        // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
-        const int64_t row_bytes = M * (K + 32);
-        int gcbw = 4;                                        // (the decode kernel's rule for five rows and more)
-        while (gcbw > 1 && (a.n_cb / gcbw < 192 || (a.n_kt + 8 / gcbw - 1) / (8 / gcbw) > 16)) gcbw >>= 1;
-        const int64_t gemv_wgs = (a.n_cb + gcbw - 1) / gcbw;
-        const bool one_round = row_bytes <= 72 * 1024 || gemv_wgs <= 256 || a.n_kt <= 32;
-        const int gemv_max = tn.gemv_max_m ? tn.gemv_max_m : one_round ? midm_from - 1 : 4;
-        fallback = midm_ok || (!tn.midm_min_m && M >= 4 && M < midm_min && M <= midm_max) ? W2_VARIANT_MIDM
-                 : a8_smallm_supports(a)                                 ? W2_VARIANT_SMALLM
-                                                                         : W2_VARIANT_TILED;
-        variant = M <= dot4_max && a8_dot4_supports(a) ? W2_VARIANT_DOT4
-                : M <= gemv_max && a8_gemv_supports(M) ? W2_VARIANT_GEMV
-                                                       : fallback;
-    }
+    const int64_t cap = a.part && !acc_out ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
+    const route::Problem pb = {M, K, N, a.n_cb, a.n_kt, G, epi.act == ACT_SILU_MUL, cap};
+    route::A8 r = {};
     hipStream_t s = (hipStream_t)stream;
-    switch (variant) {
-    case W2_VARIANT_GEMV: {
-        if (!a8_gemv_supports(M)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: GEMV needs M <= 32", fn);
-        rc = launch_a8_gemv(a, xq, 0, K, s);
-        // rows too long for one workgroup: the kernels that stage them in chunks
-        if (rc != W2_ERR_UNSUPPORTED_SHAPE || tn.variant == W2_VARIANT_GEMV) return rc;
-        if (fallback == W2_VARIANT_MIDM) return launch_a8_midm(a, s);
-        if (fallback == W2_VARIANT_TILED) return launch_a8_tiled(a, s);
-        return launch_a8_smallm(a, s);
+    if (variant == W2_VARIANT_AUTO) {
+        r = route::a8(pb, tn);
+        variant = r.variant;
+        if (variant == W2_VARIANT_GEMV) {
+            rc = launch_a8_gemv(a, xq, 0, K, s);
+            if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;
+            variant = r.fallback;                            // rows too long for one workgroup: the kernels that stage them in chunks
+        }
     }
+    switch (variant) {
+    case W2_VARIANT_GEMV:
+        if (!a8_gemv_supports(M)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: GEMV needs M <= 32", fn);
+        return launch_a8_gemv(a, xq, 0, K, s);
     case W2_VARIANT_DOT4:
         if (!a8_dot4_supports(a)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: DOT4 needs M <= 4", fn);
         return launch_a8_dot4(a, s);
@@ -326,9 +287,9 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
         return launch_a8_smallm(a, s);
     case W2_VARIANT_MIDM:
         if (!a8_midm_supports(a)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: MIDM needs M <= 256", fn);
-        return launch_a8_midm(a, s);
+        return launch_a8_midm(a, r.has_midm ? r.midm : route::midm_shape(0, pb, tn), s);
     default:
-        return launch_a8_tiled(a, s);
+        return launch_a8_tiled(a, r.has_tiled ? r.tiled : route::a8_tiled_shape(pb, tn), s);
     }
 }
 
@@ -515,12 +476,6 @@ int w2_debug_group_acc_a8(const void* packed, int64_t K, int64_t N, int G, const
                      tune, stream);
 }
 
-// The tiled kernel instead of the mid-M kernel where both take the rows: by price, with a margin for the errors of the latter's.
-static bool a16_tiled_first(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tn)
-{
-    return a16_tiled_us(M, N, n_kt, cap, tn) < 0.93 * midm_us(1, M, n_cb, n_kt, gated, cap, tn);
-}
-
 static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, int G,
                       const uint16_t* X, int64_t ldx, int64_t M, uint16_t* Y, int64_t ldy,
                       void* workspace, size_t workspace_bytes, const w2_tuning_t* tune, void* stream,
@@ -561,63 +516,39 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
     a.epi = epi;
     a.tune = tn;
     a.fold = variant == W2_VARIANT_SCALED16;
-    if (variant == W2_VARIANT_GEMV) return launch_a16_gemv(a, (hipStream_t)stream);
+    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
+    const route::Problem pb = {M, K, N, a.n_cb, a.n_kt, G, epi.act == ACT_SILU_MUL, cap};
+    hipStream_t s = (hipStream_t)stream;
+    if (variant == W2_VARIANT_GEMV) return launch_a16_gemv(a, s);
     if (variant == W2_VARIANT_SCALED16) {
         // the scale-folded construction: the small-M kernel with it, or the kernels built on it
         if (!a16_smallm_supports(a))
-            return M <= 64 ? launch_a16_midm(a, (hipStream_t)stream) : launch_a16_fold_tiled(a, (hipStream_t)stream);
+            return M <= 64 ? launch_a16_midm(a, route::midm_shape(1, pb, tn), s) : launch_a16_fold_tiled(a, route::a16_tiled_shape(pb, tn), s);
         variant = W2_VARIANT_SMALLM;
     }
     if (variant == W2_VARIANT_AUTO) {
-        // Few rows: the decode kernel wherever a workgroup can hold them, else the small-M kernel (both with the
-        // zero-point construction); then the mid-M kernel; above, 128-row tiles.  Both of the latter fold the scale
-        // into the weights: fewest vector instructions per matrix instruction.
-        // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
-        // before against the mid-M kernel): at M = 3 for rows too long for a workgroup (17408 x 5120 16.5 against
-        // 13.2), at M = 5 where K passes 4096 (5120 x 5120 8.2 against 5.8, 14336 x 4096 10.7 against 8.8, 8192 x 10240
-        // 15.5 against 12.7) but for 768 to 1024 column blocks up to K = 8192, whose grid fills one round (decode / mid-M
-        // at M = 5 and 8 0.85 .. 0.98; K = 9216 1.41 .. 1.53), at 8 on wide projections of K = 5120 (5120 x 34816 at M =
-        // 6 / 8 19.1 / 24.3 against 20.4), and at 9 up to K = 4096 (4096 x 6144 at M = 8 / 9 5.9 / 7.1 against 5.7; 4096 x 28672 12.0 / 13.3
-        // against 13.1), with groups of 64 and 16384 columns at 17 (at M = 16 / 24 13.9 / 22.0 against 14.7 / 17.6).
-        const int midm_from = a.n_kt > 64                                  ? 3
-                            : a.n_kt > 20 && a.n_kt <= 32 && a.n_cb >= 768 && a.n_cb <= 1024 ? 9
-                            : a.n_kt > 20 || (a.n_kt > 16 && a.n_cb < 640) ? 5
-                            : a.n_kt > 16                                  ? 8
-                            : G == 128 || a.n_cb < 1024                    ? 9 : 17;
-        const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
-        // Upper end, against the tiled kernel (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096 x 28672 at
-        // M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  Below it, from 33 rows
-        // on, by their prices (tile_plan.h, midm_plan.h).
-        const int64_t midm_max = tn.midm_max_m                               ? tn.midm_max_m
-                               : a.n_cb >= 2560                              ? 64
-                               : a.n_cb >= 1024 || a.n_cb * a.n_kt > 40000   ? 96
-                               : a.n_cb <= 448 && a.n_kt <= 56               ? 256 : 192;
-        const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)M * N * sizeof(float))) : 0;
-        const bool below_max = M <= midm_max && !(M > 32 && M >= midm_min && !tn.midm_max_m &&
-                                                  a16_tiled_first(M, N, a.n_cb, a.n_kt, epi.act == ACT_SILU_MUL, cap, tn));
-        const bool gemv_rows = M < midm_min;
-        if (gemv_rows && a16_gemv_supports(a)) {
-            rc = launch_a16_gemv(a, (hipStream_t)stream);
+        const route::A16 r = route::a16(pb, tn);
+        if (r.gemv_first && a16_gemv_supports(a)) {
+            rc = launch_a16_gemv(a, s);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
         }
-        // (from three rows on the mid-M kernel, not the small-M one, also takes what the decode kernel turns down)
-        if ((M >= midm_min || (!tn.midm_min_m && M >= 3)) && below_max && a16_midm_supports(a)) return launch_a16_midm(a, (hipStream_t)stream);
-        if (!gemv_rows && a16_gemv_supports(a)) {            // (only where tuning fields leave rows to neither of the two)
-            rc = launch_a16_gemv(a, (hipStream_t)stream);
+        if (r.to_midm) return launch_a16_midm(a, r.has_midm ? r.midm : route::midm_shape(1, pb, tn), s);
+        if (!r.gemv_first && a16_gemv_supports(a)) {         // (only where tuning fields leave rows to neither of the two)
+            rc = launch_a16_gemv(a, s);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;
         }
-        if (!a16_smallm_supports(a)) return launch_a16_fold_tiled(a, (hipStream_t)stream);
+        if (!a16_smallm_supports(a)) return launch_a16_fold_tiled(a, r.has_tiled ? r.tiled : route::a16_tiled_shape(pb, tn), s);
         variant = W2_VARIANT_SMALLM;
     }
     if (variant == W2_VARIANT_MIDM) {
         if (!a16_midm_supports(a)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: MIDM needs M <= 256", fn);
-        return launch_a16_midm(a, (hipStream_t)stream);
+        return launch_a16_midm(a, route::midm_shape(1, pb, tn), s);
     }
     if (variant == W2_VARIANT_SMALLM) {
         if (!a16_smallm_supports(a)) return fail(W2_ERR_UNSUPPORTED_SHAPE, "%s: SMALLM needs M <= 16", fn);
-        return launch_a16_smallm(a, (hipStream_t)stream);
+        return launch_a16_smallm(a, s);
     }
-    return launch_a16_tiled(a, (hipStream_t)stream);
+    return launch_a16_tiled(a, s);
 }
 
 int w2_matmul_a16_ex(const void* packed, int64_t K, int64_t N, int G, const uint16_t* X,
@@ -643,6 +574,9 @@ int w2_matmul_a16(const void* packed, int64_t K, int64_t N, int G, const uint16_
     return w2_matmul_a16_ex(packed, K, N, G, X, ldx, M, Y, ldy, workspace, workspace_bytes, nullptr, stream);
 }
 
+// fp32 partial results of K cut into so many ranges across workgroups
+static size_t part_bytes(int splits, int64_t M, int64_t N) { return splits < 2 ? 0 : (size_t)splits * M * N * sizeof(float); }
+
 int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* bytes)
 {
     if (!bytes) return fail(W2_ERR_INVALID_ARG, "w2_workspace_size: bytes is NULL");
@@ -653,16 +587,18 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
     const bool single = M <= 2 && M * K * 4 <= 64 * 1024;
     const Layout L = make_layout(K, N, G);
     const w2_tuning_t dflt = {};
+    const route::Problem pb = {M, K, N, L.n_cb, L.n_kt, G, false, 16};
     if (M == 0) *bytes = 0;
     else if (a16) {
-        const bool want = M > 64 || (M > 32 && a16_tiled_first(M, N, L.n_cb, L.n_kt, false, 16, dflt));
-        const size_t tiled = want ? a16_fold_splitk_bytes(M, N, L.n_kt, dflt) : 0;
+        route::A16 r = {};
+        const bool first = M > 32 && M <= 64 && route::a16_tiled_first(pb, dflt, &r);
+        const size_t tiled = M > 64 || first ? part_bytes(route::a16_tiled_shape(pb, dflt).splits, M, N) : 0;
         const size_t midm = M >= 3 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = tiled > midm ? tiled : midm;
     }
     else {
         // split-K partial results of the tiled kernels; what was reported for the mid-M range is reported still
-        const size_t tiled = M > 32 ? a8_tiled_splitk_bytes(M, N, L.n_kt, G, dflt) : 0;
+        const size_t tiled = M > 32 ? part_bytes(route::a8_tiled_shape(pb, dflt).splits, M, N) : 0;
         const size_t midm = M >= 4 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = (single ? 0 : fused_workspace_bytes(M, K)) + (tiled > midm ? tiled : midm);
     }

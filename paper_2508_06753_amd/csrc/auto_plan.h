@@ -1,0 +1,163 @@
+// AUTO: which kernel a call goes to, and the launch shape of the kernels that have several.  Host code only, no HIP, so that a
+// test can compile it by itself.  What is priced for the choice is launched as priced: a shape is found once per call.
+#pragma once
+#include <stdint.h>
+
+#include "midm_plan.h"
+#include "tile_plan.h"
+
+namespace w2 {
+
+namespace route {
+
+// Most rows of each kernel.
+constexpr int64_t DOT4_ROWS = 4, SMALL_ROWS = 16, GEMV_ROWS = 32, MIDM_ROWS = 256;
+
+// The tiled kernels before the mid-M kernel where both take the rows (int8, bf16 rows): where their price (tile_plan.h) is
+// under its price (midm_plan.h) by more than the latter errs; with less of a margin 28672 x 8192 at M = 100 takes 38.0 us
+// instead of 35.2.
+constexpr double TILED_MARGIN[2] = {0.86, 0.93};
+
+struct Problem {
+    int64_t M, K, N;
+    int64_t n_cb, n_kt;                                      // column blocks, 256-k tiles
+    int G;
+    bool gated;
+    int64_t cap;                                             // fp32 copies of the output that the workspace holds
+};
+
+inline midm::Plan midm_shape(int a16, const Problem& p, const w2_tuning_t& tn, double* us = nullptr)
+{
+    return midm::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.cap, tn, us);
+}
+
+// ---- w2a8
+
+struct A8 {
+    int variant;
+    int fallback;                                            // where the decode kernel turns the rows down
+    bool has_midm, has_tiled;                                // shapes found on the way
+    midm::Plan midm;
+    tiles::A8Shape tiled;
+};
+
+inline tiles::A8Shape a8_tiled_shape(const Problem& p, const w2_tuning_t& tn) { return tiles::a8_shape(p.G, p.M, p.N, p.n_kt, p.cap, tn); }
+
+inline A8 a8(const Problem& p, const w2_tuning_t& tn)
+{
+    const int64_t M = p.M;
+    A8 r = {};
+    // Few rows: the decode kernel, which reads the weights once and keeps whole rows in local memory (the MFMA
+    // form is at least as fast as dot4 from M = 1 on).  Then the mid-M kernel, then the tiled ones.
+    // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
+    // before against the mid-M kernel): at M = 9 in general (4096 x 6144 5.3 against 5.2 at M = 16; 4096 x 28672 at
+    // M = 8 / 9 9.2 / 10.1 against 9.6 / 9.7; 8192 x 10240 8.8 / 11.7 against 8.8 / 8.9).  At M = 5 where the decode
+    // kernel has few workgroups and two pieces of a row per thread (decode / mid-M at M = 5 and 8, 192 to 512 column
+    // blocks: K = 4096 0.91 .. 1.05, but 1.20 on 320 blocks; K = 5120 1.08 .. 1.24, 6144 1.03 .. 1.20, 7168 0.91 .. 1.10,
+    // 8192 0.93 .. 1.01), on a deep K of few columns (17408 x 1024 1.19, x 2048 0.98), and below where it cannot hold the
+    // rows in one round of workgroups (17408 x 5120 1.35, x 4096 0.94).  At 13 on 16384 columns and more with groups of
+    // 64 (5120 x 34816 at M = 12 / 16 15.2 / 21.4 against 16.1 / 17.2).  At 17 where K near 8192 keeps its whole grid
+    // busy in one round, 768 to 1024 column blocks (K = 8192 at M = 9 .. 16 0.91 .. 0.97, 7168 1.00 .. 1.05).
+    const bool wide = p.n_cb >= 1024;
+    const int midm_from = p.n_kt > 28 && p.n_kt <= 32 && p.n_cb >= 768 && p.n_cb <= 1024 ? 17
+                        : wide                                                           ? (p.G == 128 ? 9 : 13)
+                        : (p.n_kt > 64 && p.n_cb < 128) || (p.n_kt > 16 && p.n_kt <= 26 && p.n_cb <= 512) ? 5 : 9;
+    const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
+    // Upper end, against the tiled kernels with a workspace: they win earlier the more columns there are to fill
+    // the chip with (2048 x 57344 at M = 48 / 64 16.6 / 17.4 us against 15.3 / 18.5; 4096 x 28672 at M = 96 / 128
+    // 24.3 / 25.2 against 20.4 / 24.9; 8192 x 10240 at M = 160 / 192 24.8 / 25.1 against 24.3 / 26.0; 5120 x 7168
+    // at M = 192 / 256 17.4 / 17.5 against 14.1 / 17.7; 28672 x 5120 at M = 240 50.2 against 54.5).
+    const int midm_max = tn.midm_max_m ? tn.midm_max_m
+                       : p.n_cb >= 2560 ? 48 : p.n_cb >= 1536 ? 112 : p.n_cb > 448 ? 160 : p.G == 128 && p.n_kt > 104 && p.n_cb > 256 ? 192 : 240;
+    // Below it, from 33 rows on, by price.
+    bool tiled_first = false;
+    if (M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m) {
+        double us;
+        r.midm = midm_shape(0, p, tn, &us);
+        r.has_midm = true;
+        us *= TILED_MARGIN[0];
+        if (us > tiles::LEAST_US[p.G == 128 ? tiles::A8_G128 : tiles::A8_G64]) {
+            r.tiled = a8_tiled_shape(p, tn);
+            r.has_tiled = true;
+            tiled_first = r.tiled.us < us;
+        }
+    }
+    const bool midm_ok = M >= midm_min && M <= midm_max && !tiled_first && M <= MIDM_ROWS;
+    // Rows of more than 72 KiB leave the decode kernel one workgroup per CU: then the grid must fit the chip in one
+    // round (or K be moderate), else the mid-M kernel from M = 5 on there too.
+    const int64_t row_bytes = M * (p.K + 32);
+    int gcbw = 4;                                            // (the decode kernel's rule for five rows and more)
+    while (gcbw > 1 && (p.n_cb / gcbw < 192 || (p.n_kt + 8 / gcbw - 1) / (8 / gcbw) > 16)) gcbw >>= 1;
+    const int64_t gemv_wgs = (p.n_cb + gcbw - 1) / gcbw;
+    const bool one_round = row_bytes <= 72 * 1024 || gemv_wgs <= 256 || p.n_kt <= 32;
+    const int gemv_max = tn.gemv_max_m ? tn.gemv_max_m : one_round ? midm_from - 1 : 4;
+    r.fallback = midm_ok || (!tn.midm_min_m && M >= 4 && M < midm_min && M <= midm_max) ? W2_VARIANT_MIDM
+               : M <= SMALL_ROWS                                                        ? W2_VARIANT_SMALLM
+                                                                                        : W2_VARIANT_TILED;
+    r.variant = M <= tn.dot4_max_m && M <= DOT4_ROWS ? W2_VARIANT_DOT4
+              : M <= gemv_max && M <= GEMV_ROWS      ? W2_VARIANT_GEMV
+                                                     : r.fallback;
+    return r;
+}
+
+// ---- w2a16
+
+struct A16 {
+    bool gemv_first;                                         // the decode kernel, where a workgroup can hold the rows
+    bool to_midm;                                            // then the mid-M kernel, else the small-M or the tiled one
+    bool has_midm, has_tiled;
+    midm::Plan midm;
+    tiles::Shape tiled;
+};
+
+inline tiles::Shape a16_tiled_shape(const Problem& p, const w2_tuning_t& tn) { return tiles::a16_shape(p.M, p.N, p.n_kt, p.cap, tn); }
+
+inline bool a16_tiled_first(const Problem& p, const w2_tuning_t& tn, A16* r)
+{
+    double us;
+    r->midm = midm_shape(1, p, tn, &us);
+    r->has_midm = true;
+    us *= TILED_MARGIN[1];
+    if (us <= tiles::LEAST_US[tiles::A16]) return false;
+    r->tiled = a16_tiled_shape(p, tn);
+    r->has_tiled = true;
+    return r->tiled.us < us;
+}
+
+inline A16 a16(const Problem& p, const w2_tuning_t& tn)
+{
+    const int64_t M = p.M;
+    A16 r = {};
+    // Few rows: the decode kernel wherever a workgroup can hold them, else the small-M kernel (both with the
+    // zero-point construction); then the mid-M kernel; above, 128-row tiles.  Both of the latter fold the scale
+    // into the weights: fewest vector instructions per matrix instruction.
+    // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
+    // before against the mid-M kernel): at M = 3 for rows too long for a workgroup (17408 x 5120 16.5 against
+    // 13.2), at M = 5 where K passes 4096 (5120 x 5120 8.2 against 5.8, 14336 x 4096 10.7 against 8.8, 8192 x 10240
+    // 15.5 against 12.7) but for 768 to 1024 column blocks up to K = 8192, whose grid fills one round (decode / mid-M
+    // at M = 5 and 8 0.85 .. 0.98; K = 9216 1.41 .. 1.53), at 8 on wide projections of K = 5120 (5120 x 34816 at M =
+    // 6 / 8 19.1 / 24.3 against 20.4), and at 9 up to K = 4096 (4096 x 6144 at M = 8 / 9 5.9 / 7.1 against 5.7; 4096 x 28672 12.0 / 13.3
+    // against 13.1), with groups of 64 and 16384 columns at 17 (at M = 16 / 24 13.9 / 22.0 against 14.7 / 17.6).
+    const int midm_from = p.n_kt > 64                                  ? 3
+                        : p.n_kt > 20 && p.n_kt <= 32 && p.n_cb >= 768 && p.n_cb <= 1024 ? 9
+                        : p.n_kt > 20 || (p.n_kt > 16 && p.n_cb < 640) ? 5
+                        : p.n_kt > 16                                  ? 8
+                        : p.G == 128 || p.n_cb < 1024                  ? 9 : 17;
+    const int midm_min = tn.midm_min_m ? tn.midm_min_m : midm_from;
+    // Upper end, against the tiled kernel (8192 x 57344 at M = 64 / 96 95 / 101 us against 77 / 114; 4096 x 28672 at
+    // M = 96 / 128 36.4 / 39.1 against 33.9 / 40.7; 4096 x 4096 at M = 256 22.9 against 12.3).  Below it, from 33 rows
+    // on, by their prices (tile_plan.h, midm_plan.h).
+    const int64_t midm_max = tn.midm_max_m                               ? tn.midm_max_m
+                           : p.n_cb >= 2560                              ? 64
+                           : p.n_cb >= 1024 || p.n_cb * p.n_kt > 40000   ? 96
+                           : p.n_cb <= 448 && p.n_kt <= 56               ? 256 : 192;
+    const bool tiled_first = M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m && a16_tiled_first(p, tn, &r);
+    r.gemv_first = M < midm_min;
+    // (from three rows on the mid-M kernel, not the small-M one, also takes what the decode kernel turns down)
+    r.to_midm = (M >= midm_min || (!tn.midm_min_m && M >= 3)) && M <= midm_max && !tiled_first && M <= MIDM_ROWS;
+    return r;
+}
+
+}  // namespace route
+
+}  // namespace w2

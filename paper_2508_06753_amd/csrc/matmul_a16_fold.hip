@@ -428,21 +428,8 @@ static int launch_fold_bn(const A16Args& a_in, int splits, hipStream_t stream)
     return launch_splitk_reduce(a.part, splits, a.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
-double a16_tiled_us(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune)
+int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, hipStream_t stream)
 {
-    return tiles::a16_shape(M, N, n_kt, cap, tune).us;
-}
-
-size_t a16_fold_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, const w2_tuning_t& tune)
-{
-    const int s = tiles::a16_shape(M, N, n_kt, 16, tune).splits;
-    return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
-}
-
-int launch_a16_fold_tiled(const A16Args& a, hipStream_t stream)
-{
-    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const tiles::Shape p = tiles::a16_shape(a.M, a.N, a.n_kt, cap, a.tune);
     if (a.tune.tiled_bn != 128) {
         switch (p.ri * 128 + a.G) {
         case 4 * 128 + 64: return launch_fold_bn<64, 256, 4>(a, p.splits, stream);

@@ -511,17 +511,6 @@ static int launch_tiled(const A8Args& a_in, int splits, hipStream_t stream)
     return launch_splitk_reduce(a.part, splits, a.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
-double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune)
-{
-    return tiles::a8_shape(G, M, N, n_kt, cap, tune).us;
-}
-
-size_t a8_tiled_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, int G, const w2_tuning_t& tune)
-{
-    const int s = tiles::a8_shape(G, M, N, n_kt, 16, tune).splits;
-    return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
-}
-
 template <int G, bool DBG>
 static int launch_tiled_bn(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
 {
@@ -541,10 +530,8 @@ static int launch_tiled_bn(const A8Args& a, const tiles::A8Shape& p, hipStream_t
     return p.bn == 128 ? launch_tiled<G, DBG, 128>(a, splits, stream) : launch_tiled<G, DBG, 256>(a, splits, stream);
 }
 
-int launch_a8_tiled(const A8Args& a, hipStream_t stream)
+int launch_a8_tiled(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
 {
-    const int64_t cap = a.part && !a.acc_out ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const tiles::A8Shape p = tiles::a8_shape(a.G, a.M, a.N, a.n_kt, cap, a.tune);
     if (p.ri) return launch_a8_tiled128(a, p, stream);
     if (a.G == 128)
         return a.acc_out ? launch_tiled_bn<128, true>(a, p, stream) : launch_tiled_bn<128, false>(a, p, stream);

@@ -552,10 +552,10 @@ static int launch_g(const Head& h, const Args& a, const Plan& p, hipStream_t str
 
 }  // namespace midm
 
-constexpr int64_t MIDM_MAX_ROWS = 256;                       // beyond that the tiled kernels' reuse of the weights wins everywhere
+// (beyond 256 rows the tiled kernels' reuse of the weights wins everywhere)
 
-bool a8_midm_supports(const A8Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
-bool a16_midm_supports(const A16Args& a) { return a.M >= 1 && a.M <= MIDM_MAX_ROWS; }
+bool a8_midm_supports(const A8Args& a) { return a.M >= 1 && a.M <= 256; }
+bool a16_midm_supports(const A16Args& a) { return a.M >= 1 && a.M <= 256; }
 
 // What w2_workspace_size adds for this range on a deep K (K > 13312): fp32 copies of the output, 2..16 of them, as many
 // parts as about 64 workgroups across the columns need for one workgroup per CU.
@@ -569,28 +569,17 @@ size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt)
     return s < 2 ? 0 : (size_t)s * M * N * sizeof(float);
 }
 
-double midm_us(int a16, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tune)
-{
-    double us = 0.0;
-    midm::plan(a16, M, n_cb, n_kt, gated, cap, tune, &us);
-    return us;
-}
-
-int launch_a8_midm(const A8Args& a, hipStream_t stream)
+int launch_a8_midm(const A8Args& a, const midm::Plan& p, hipStream_t stream)
 {
     const midm::Head h = {(const char*)a.xq, (const char*)a.codes, (const char*)a.scales, (uint32_t)a.K, (int)a.M, (int)a.n_cb, (int)a.n_kt};
     const midm::Args k = {a.sx, a.Y, a.acc_out, a.acc_out ? nullptr : a.part, a.N, a.ldy, a.epi};
-    const int64_t cap = k.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const midm::Plan p = midm::plan(0, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, cap, a.tune);
     return a.G == 128 ? midm::launch_g<0, 128>(h, k, p, stream) : midm::launch_g<0, 64>(h, k, p, stream);
 }
 
-int launch_a16_midm(const A16Args& a, hipStream_t stream)
+int launch_a16_midm(const A16Args& a, const midm::Plan& p, hipStream_t stream)
 {
     const midm::Head h = {(const char*)a.X, (const char*)a.codes, (const char*)a.scales, (uint32_t)(a.ldx * 2), (int)a.M, (int)a.n_cb, (int)a.n_kt};
     const midm::Args k = {nullptr, a.Y, nullptr, a.part, a.N, a.ldy, a.epi};
-    const int64_t cap = a.part ? (int64_t)(a.part_bytes / ((size_t)a.M * a.N * sizeof(float))) : 0;
-    const midm::Plan p = midm::plan(1, a.M, a.n_cb, a.n_kt, a.epi.act == ACT_SILU_MUL, cap, a.tune);
     return a.G == 128 ? midm::launch_g<1, 128>(h, k, p, stream) : midm::launch_g<1, 64>(h, k, p, stream);
 }
 

@@ -66,6 +66,21 @@ constexpr bool built(int xt, int rt, int cj, int f)
     return true;
 }
 
+struct Offered {
+    int8_t n[2][2][4][MAX_CJ], f[2][2][4][MAX_CJ][N_FORMS];  // [activations][gated][rt - 1][cj - 1]: how many forms, and which
+    constexpr Offered() : n{}, f{}
+    {
+        for (int xt = 0; xt < 2; ++xt)
+            for (int gated = 0; gated < 2; ++gated)          // (the gated epilogue: a workgroup pairs gate and up blocks)
+                for (int rt = 1; rt <= 4; ++rt)
+                    for (int cj = 1; cj <= MAX_CJ; ++cj)
+                        for (int k = 0; k < N_FORMS; ++k)
+                            if (built(xt, rt, cj, k) && !(gated && (cj * FORMS[k][1]) & 1))
+                                f[xt][gated][rt - 1][cj - 1][n[xt][gated][rt - 1][cj - 1]++] = (int8_t)k;
+    }
+};
+constexpr Offered OFFERED;
+
 // Every candidate shape is priced and the cheapest wins.  The price is linear in what the busiest CU has to do (in rounds of
 // as many workgroups as it holds at a time); the coefficients (us) are least-squares fits to graph-timed launches.
 //
@@ -148,11 +163,12 @@ constexpr Coef COEF[2][MAX_CJ][N_FORMS] = {                  // int8, bf16 rows;
 // blocks, 12 on the busiest CU, and 13.5 in 726 of three, 9 on it; with 48 bf16 rows 32.9 and 27.4 (2 x 5 blocks); 8192 x 20480
 // with 32 int8 rows 17.2 and 14.3.  Over 23 projections of 9216 to 57344 columns the fastest shapes gain 3 % (int8 rows) and 6 %
 // (bf16 rows) by it.
-inline int busiest(int n_cb, int width, int bands) { return (((n_cb + width - 1) / width * bands + 255) >> 8) * width; }
-inline bool odd_balances(int n_cb, int cj, int sh, int bands)
+// `groups`: workgroups across the columns, by their width in column blocks.
+inline int busiest(const int* groups, int width, int bands) { return ((groups[width] * bands + 255) >> 8) * width; }
+inline bool odd_balances(const int* groups, int cj, int sh, int bands)
 {
-    if (n_cb <= NARROW_BLOCKS || bands > 4) return false;
-    const int odd = busiest(n_cb, cj * sh, bands), even = std::min(busiest(n_cb, 2 * sh, bands), busiest(n_cb, 4 * sh, bands));
+    if (bands > 4) return false;
+    const int odd = busiest(groups, cj * sh, bands), even = std::min(busiest(groups, 2 * sh, bands), busiest(groups, 4 * sh, bands));
     return sh == 1 ? odd <= even : odd < even;
 }
 
@@ -209,20 +225,22 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
         if (p.sp > 1) t = PARTS_MARGIN * (t + PARTS_US[xt] + part_us * p.sp);
         return t;
     };
+    int group_count[2 * MAX_CJ + 1];
+    for (int w : {1, 2, 3, 4, 5, 6, 8, 10}) group_count[w] = (n_cb + w - 1) / w;
     const int row_tiles = std::min((M + 15) / 16, 4);
     // (wide grids, one row tile per wave: up to four bands; beyond, every band streams and up-converts the weights again)
     for (int rt = M > 64 && !narrow ? 2 : 1; rt <= row_tiles; ++rt) {
         const int bands = (M + 16 * rt - 1) / (16 * rt);
-        for (int cj = rt == 1 ? 1 : 2; cj <= MAX_CJ; ++cj)
-            for (int f = 0; f < N_FORMS; ++f) {
-                if (!built(xt, rt, cj, f)) continue;
-                const int sh = FORMS[f][1], width = cj * sh;             // column blocks per workgroup
-                const bool odd = cj == 3 || cj == 5;
-                if (odd && !odd_balances(n_cb, cj, sh, bands)) continue;
+        for (int cj = rt == 1 ? 1 : 2; cj <= MAX_CJ; ++cj) {
+            const bool odd = cj == 3 || cj == 5;
+            if (odd && narrow) continue;
+            const int8_t n_forms = OFFERED.n[xt][gated][rt - 1][cj - 1], *forms = OFFERED.f[xt][gated][rt - 1][cj - 1];
+            for (int i = 0; i < n_forms; ++i) {
+                const int f = forms[i], sh = FORMS[f][1], width = cj * sh;   // column blocks per workgroup
+                if (odd && !odd_balances(group_count, cj, sh, bands)) continue;
                 if (!narrow && cj == 1 && sh == 2) continue;             // (not fitted there: four blocks per workgroup and more win)
-                if (gated && (width & 1)) continue;                      // a workgroup pairs gate and up blocks
                 if (cbw && width != cbw) continue;
-                const int groups = (n_cb + width - 1) / width;
+                const int groups = group_count[width];
                 if (xt == 0 && width <= 2 && !cbw && (int64_t)groups * M * n_kt * 256 > ROW_BYTES_FROM_L2) continue;
                 const int resident = RESIDENT.n[xt][rt - 1][cj - 1][f];
                 auto offer = [&](int ks, int sp, int T, int res) {
@@ -249,6 +267,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 const int sp = (int)std::min<int64_t>(std::min(at_once / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
                 if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);
             }
+        }
     }
     if (us) *us = best_price;
     return best;

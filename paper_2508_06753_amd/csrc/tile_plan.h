@@ -47,14 +47,13 @@ constexpr Coef COEF[3] = {
     {3.102, 2.146, 0.0, 0.3454, 0.5539, 0.1836, 0.01042, 4.137, 0.6599e-6},
     {2.500, 1.610, 1.146, 0.3411, 1.297, 0.1271, 0.07422, 3.773, 0.7268e-6}};
 
-inline double price(Kind kind, int64_t M, int64_t N, int64_t n_kt, int ri, int splits)
+// wgs: workgroups, nk: 256-k tiles of the longest range
+inline double price(const Coef& c, int64_t wgs, int64_t nk, int ri, int splits, double values)
 {
-    const Coef& c = COEF[kind];
-    const int64_t wgs = (M + 16 * ri - 1) / (16 * ri) * ((N + 255) / 256) * splits;
-    const double rounds = (double)((wgs + 255) / 256), fill = (double)wgs / 256.0, nk = (double)((n_kt + splits - 1) / splits);
+    const double rounds = (double)((wgs + 255) >> 8), fill = (double)wgs / 256.0;
     double t = c.launch + c.wg * fill + rounds * (c.round + c.round_ri * ri) +
-               nk * (rounds * (c.tile + c.tile_ri * ri) + fill * c.tile_ri_wg * ri);
-    if (splits > 1) t += c.parts + c.part_value * (double)M * (double)N * splits;
+               (double)nk * (rounds * (c.tile + c.tile_ri * ri) + fill * c.tile_ri_wg * ri);
+    if (splits > 1) t += c.parts + c.part_value * values * splits;
     return t;
 }
 
@@ -66,11 +65,14 @@ inline Shape pick(Kind kind, int64_t M, int64_t N, int64_t n_kt, int64_t cap, in
     int64_t most = std::min(std::min(n_kt / 2, cap), std::min((int64_t)MAX_SPLITS, copies(MAX_PART_BYTES, M, N)));
     int64_t least = 1;
     if (forced_splits > 0) least = most = std::max((int64_t)1, std::min((int64_t)forced_splits, std::min(cap, n_kt)));
+    const double values = (double)M * (double)N;
+    int64_t nk[17];                                          // (no more divisions than there have to be: this runs on every call)
+    for (int64_t s = least; s == least || s <= most; ++s) nk[s] = (n_kt + s - 1) / s;
     for (int ri = forced_ri ? forced_ri : 4; ri <= (forced_ri ? forced_ri : 8); ++ri) {
         const int64_t wgs = (M + 16 * ri - 1) / (16 * ri) * ((N + 255) / 256);
         for (int64_t s = least; s == least || s <= most; ++s) {
             if (s > 1 && s > least && wgs * s > 768) break;  // (parts of a grid that is several rounds anyway never paid)
-            const double t = price(kind, M, N, n_kt, ri, (int)s);
+            const double t = price(COEF[kind], wgs * s, nk[s], ri, (int)s, values);
             if (t < best.us) best = {ri, (int)s, t};
         }
     }
@@ -110,15 +112,13 @@ constexpr Coef64 COEF64[2][4] = {                            // 128 columns with
      {3.533, 1.848, 2.648, 3.240, 0.0, 0.3995}, {5.510, 0.0, 0.0, 1.933, 0.0, 0.3805}}};
 constexpr double PARTS64[2][2] = {{2.249, 1.767e-6}, {2.231, 1.726e-6}};   // the second launch; per value of a partial result
 
-inline double price64(int G, int64_t M, int64_t N, int64_t n_kt, int bn, int kw, int splits)
+inline double price64(int G, int64_t wgs, int64_t nk, int bn, int kw, int splits, double values)
 {
     const Coef64& c = COEF64[G == 128 ? 0 : 1][bn == 64 ? 3 : kw >> 1];
-    const int64_t wgs = (M + 63) / 64 * ((N + bn - 1) / bn) * splits;
-    const int64_t at_once = 256 * (4 / kw);
-    const double rounds = (double)((wgs + at_once - 1) / at_once), per_cu = (double)((wgs + 255) / 256), fill = (double)wgs / 256.0;
-    const double nk = (double)((n_kt + splits * kw - 1) / (splits * kw));
-    double t = c.launch + c.wg * fill + c.round * rounds + nk * (c.tile_round * rounds + c.tile_cu * per_cu + c.tile_wg * fill);
-    if (splits > 1) t += PARTS64[G == 128 ? 0 : 1][0] + PARTS64[G == 128 ? 0 : 1][1] * (double)M * (double)N * splits;
+    const int at_once = kw == 4 ? 8 : kw == 2 ? 9 : 10;      // log2 of the workgroups that run at a time
+    const double rounds = (double)((wgs + (1 << at_once) - 1) >> at_once), per_cu = (double)((wgs + 255) >> 8), fill = (double)wgs / 256.0;
+    double t = c.launch + c.wg * fill + c.round * rounds + (double)nk * (c.tile_round * rounds + c.tile_cu * per_cu + c.tile_wg * fill);
+    if (splits > 1) t += PARTS64[G == 128 ? 0 : 1][0] + PARTS64[G == 128 ? 0 : 1][1] * values * splits;
     return t;
 }
 
@@ -131,19 +131,23 @@ inline Shape64 pick64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, in
     const int64_t room = std::max(cap, (int64_t)1), wgs = (M + 63) / 64 * ((N + bn - 1) / bn);
     int64_t least = 1, most = std::min(std::min((int64_t)16, room), std::max((int64_t)1, copies((int64_t)16 << 20, M, N)));
     if (forced_splits > 0) least = most = std::min((int64_t)forced_splits, std::min(room, n_kt));
+    const double values = (double)M * (double)N;
+    const int tiles = (int)n_kt;                             // (32-bit divisions: this runs on every call)
     Shape64 best = {bn, 1, (int)least, 1e30};
     for (int kw = 4; kw >= 1; kw >>= 1) {
         if (forced_kw && kw > forced_kw) continue;
         for (int64_t s = least; s <= most && s <= n_kt; ++s) {
-            if (kw > 1 && n_kt % (kw * s) != 0) continue;
-            if (s > 1 && forced_splits <= 0 && (n_kt / (s * kw) < 2 || wgs * s * kw > 1600)) break;
-            const double t = price64(G, M, N, n_kt, bn, kw, (int)s);
+            const int ranges = kw * (int)s;
+            if (s > 1 && forced_splits <= 0 && (tiles < 2 * ranges || wgs * ranges > 1600)) break;
+            const int nk = (tiles + ranges - 1) / ranges;
+            if (kw > 1 && nk * ranges != tiles) continue;
+            const double t = price64(G, wgs * s, nk, bn, kw, (int)s, values);
             if (t < best.us) best = {bn, kw, (int)s, t};
         }
         if (forced_kw && best.us < 1e30) break;
     }
     if (!forced_bn && forced_splits <= 1 && (forced_kw == 0 || forced_kw == 4) && n_kt % 4 == 0 && (M + 63) / 64 * ((N + 63) / 64) <= 256) {
-        const double t = price64(G, M, N, n_kt, 64, 4, 1);
+        const double t = price64(G, (M + 63) / 64 * ((N + 63) / 64), n_kt / 4, 64, 4, 1, values);
         if (t < best.us) best = {64, 4, 1, t};
     }
     return best;
@@ -173,6 +177,18 @@ inline Shape64 shape64(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, c
                                        : splits64_wide(wgs, n_kt, tune.splitk_min_tiles ? tune.splitk_min_tiles : 12, M, N, cap);
     return {256, 1, splits, price64_wide(G, M, N, n_kt, splits)};
 }
+
+// No launch of them is priced below: one 256-k tile in one workgroup.
+constexpr double least(const Coef& c) { return c.launch + c.round + 4 * c.round_ri + c.tile + 4 * c.tile_ri; }
+constexpr double least(const Coef64& c) { return c.launch + c.round + c.tile_round + c.tile_cu; }
+constexpr double least_us(Kind kind)
+{
+    double t = least(COEF[kind]);
+    if (kind != A16)
+        for (const Coef64& c : COEF64[kind == A8_G128 ? 0 : 1]) t = least(c) < t ? least(c) : t;
+    return t;
+}
+constexpr double LEAST_US[3] = {least_us(A8_G128), least_us(A8_G64), least_us(A16)};
 
 // ---- w2a8: which of its two kernels, and its launch shape
 

@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include "../../include/w2mm.h"
+#include "midm_plan.h"
 #include "tile_plan.h"
 #include "w2_layout.h"
 
@@ -81,13 +82,10 @@ int launch_a8_dot4(const A8Args& a, hipStream_t stream);
 bool a8_smallm_supports(const A8Args& a);
 int launch_a8_smallm(const A8Args& a, hipStream_t stream);
 bool a8_midm_supports(const A8Args& a);
-int launch_a8_midm(const A8Args& a, hipStream_t stream);
-int launch_a8_tiled(const A8Args& a, hipStream_t stream);
+// (launch shapes: midm_plan.h, tile_plan.h)
+int launch_a8_midm(const A8Args& a, const midm::Plan& p, hipStream_t stream);
+int launch_a8_tiled(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream);
 int launch_a8_tiled128(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream);
-// What the kernels that AUTO chooses between are expected to take (us), with room for `cap` fp32 copies of the output.
-double a8_tiled_us(int64_t M, int64_t N, int64_t n_kt, int G, int64_t cap, const w2_tuning_t& tune);
-double a16_tiled_us(int64_t M, int64_t N, int64_t n_kt, int64_t cap, const w2_tuning_t& tune);
-double midm_us(int a16, int64_t M, int64_t n_cb, int64_t n_kt, bool gated, int64_t cap, const w2_tuning_t& tune);
 
 // The decode kernel (M <= 32; rows quantised in the kernel: M <= 4): xt 0 = int8 rows (a.xq / a.sx), 1 = fp32 rows,
 // 2 = bf16 rows quantised in the kernel.
@@ -113,17 +111,14 @@ struct A16Args {
 bool a16_smallm_supports(const A16Args& a);
 int launch_a16_smallm(const A16Args& a, hipStream_t stream);
 int launch_a16_tiled(const A16Args& a, hipStream_t stream);
-int launch_a16_fold_tiled(const A16Args& a, hipStream_t stream);
+int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, hipStream_t stream);
 // w2a16 through the decode kernel (bf16 rows as they are, M <= 4, rows that fit one workgroup)
 bool a16_gemv_supports(const A16Args& a);
 int launch_a16_gemv(const A16Args& a, hipStream_t stream);
 bool a16_midm_supports(const A16Args& a);
-int launch_a16_midm(const A16Args& a, hipStream_t stream);
+int launch_a16_midm(const A16Args& a, const midm::Plan& p, hipStream_t stream);
 
-// Bytes of workspace with which the tiled kernels would split K for this problem (0: they would not).
-size_t a8_tiled_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, int G, const w2_tuning_t& tune);
 size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt);
-size_t a16_fold_splitk_bytes(int64_t M, int64_t N, int64_t n_kt, const w2_tuning_t& tune);
 // Y[m][n] = bf16(sum_s part[s][m][n]), a fixed order of summation
 int launch_splitk_reduce(const float* part, int splits, int64_t M, int64_t N, uint16_t* Y, int64_t ldy,
                          const Epilogue& epi, hipStream_t stream);
