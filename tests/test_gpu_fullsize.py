@@ -144,21 +144,22 @@ def test_70b_prefill_down(w2):
     check_a16(w2, 256, K, N, 128, 0, seed=4, ncols=64)
 
 
+@pytest.mark.parametrize("bm,rows", [(64, 80), (128, 144)])
 @pytest.mark.parametrize("name", ["gate_up", "down"])
-def test_70b_prefill_tiled_kernel_accumulators(w2, name):
-    """The int32 group accumulators of the PREFILL kernel at the full K of the 70B-class shapes (8192 and
+def test_70b_prefill_tiled_kernel_accumulators(w2, name, bm, rows):
+    """The int32 group accumulators of the two PREFILL kernels at the full K of the 70B-class shapes (8192 and
     28672: 64 and 224 groups, the long pipelines and every periodic bias settlement), bit for bit, on a
-    band of rows that spans two row tiles with a ragged second one.  The kernel family is forced: AUTO
-    would send so few rows to the mid-M kernel."""
+    band of rows that spans two row tiles with a ragged second one.  The kernel and its tile
+    height are forced: AUTO would send so few rows to the mid-M kernel."""
     K, N = synth.SHAPES_70B[name]
-    G, rows = 128, 80
+    G = 128
     codes, scales, packed = weights(w2, K, N, G, 0, 4)
     X = synth.make_activations(rows, K, seed=4321)
     xq, _, _ = w2.quantize_rows(dev(X), G)
     oq, _, _ = oracle.quantize_rows(X, G, want_gsum=False)
     assert np.array_equal(xq.cpu().numpy(), oq)
     cols = sample_cols(N, 192, 17)
-    acc = w2.debug_group_acc_a8(packed, K, N, G, xq, variant=w2.VARIANT_TILED)        # [rows][K/G][N] on the device
+    acc = w2.debug_group_acc_a8(packed, K, N, G, xq, variant=w2.VARIANT_TILED, tune={"tiled_bm": bm})   # [rows][K/G][N] on the device
     got = acc[:, :, torch.from_numpy(cols).cuda()].cpu().numpy()
     del acc
     oacc = oracle.group_acc(np.ascontiguousarray(codes[:, cols]), G, 0, oq)

@@ -375,8 +375,31 @@ def test_a8_midm_long_k_and_limits(w2):
 @pytest.mark.parametrize("K,N", [(256, 16), (1024, 272), (512, 1032)])
 @pytest.mark.parametrize("M", [1, 17, 127, 128, 200])
 def test_a8_tiled(w2, M, K, N, G, bn):
-    # the three workgroup widths (two, four and eight waves); ragged M, N; one to four stages of K
-    run_a8_case(w2, M, K, N, G, (M + K) % 2, w2.VARIANT_TILED, seed=M + K + N + G, tune={"tiled_bn": bn})
+    # 64-row tiles in the three workgroup widths (two, four and eight waves; the height is forced too, or eight waves may run
+    # the other kernel); ragged M, N; one to four stages of K
+    run_a8_case(w2, M, K, N, G, (M + K) % 2, w2.VARIANT_TILED, seed=M + K + N + G, tune={"tiled_bm": 64, "tiled_bn": bn})
+
+
+@pytest.mark.parametrize("act", [0, 2])
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("splitk", [1, 2, 3])
+@pytest.mark.parametrize("M,K,N", [(1, 768, 32), (65, 1024, 544), (129, 2304, 288), (64, 4608, 64)])
+def test_a8_tiled_256_columns_split_k(w2, M, K, N, splitk, G, act):
+    # 64-row tiles of 256 columns, whole and with K in equal and unequal ranges across workgroups (one tile per range, three
+    # and nine tiles in two, eighteen in three), plain and gated; a last row tile of one row, a last column tile of one pair
+    codes, scales, X = synth.make_problem(M, K, N, G, 0, M + K + N + G)
+    packed = w2.prepack(dev(codes), dev(scales), G, 0)
+    oq, osx, _ = oracle.quantize_rows(X, G)
+    Yo, y64 = oracle.matmul_a8(codes, scales, G, 0, oq, osx)
+    mag = oracle.a8_term_magnitude(codes, scales, G, 0, oq, osx)
+    ws = torch.empty(splitk * M * N * 4, dtype=torch.uint8, device="cuda")
+    Y = w2.matmul_a8_epi(packed, K, N, G, dev(oq), dev(osx), act=act, variant=w2.VARIANT_TILED, workspace=ws,
+                         tune={"tiled_bm": 64, "tiled_bn": 256, "splitk": splitk})
+    what = f"a8 64 x 256 tiles split-K {splitk} M={M} K={K} N={N} G={G} act={act}"
+    if act == 0:
+        check_y(bf16_bits(Y), Yo, y64, mag, what)
+    else:
+        check_epilogue(bf16_bits(Y), y64, mag, None, act, what)
 
 
 @pytest.mark.parametrize("bn", [64, 128])
