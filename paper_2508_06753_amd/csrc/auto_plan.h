@@ -28,7 +28,7 @@ struct Problem {
 
 inline midm::Plan midm_shape(int a16, const Problem& p, const w2_tuning_t& tn, double* us = nullptr)
 {
-    return midm::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.cap, tn, us);
+    return midm::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.cap, tn, us, p.G);
 }
 
 // ---- w2a8

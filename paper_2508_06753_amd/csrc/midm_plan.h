@@ -28,29 +28,45 @@ constexpr int max_waves(int rt, int cj) { return rt == 1 && cj <= 2 ? 16 : 8; }
 struct Plan { int rt, cj, ks, sh, sp; };
 
 constexpr int MAX_CJ = 5;
-// Waves of each instantiation that a SIMD's registers hold (int8, bf16 rows; [rt - 1][cj - 1]).
-constexpr int SIMD_WAVES[2][4][MAX_CJ] = {{{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {4, 3, 2, 2, 2}, {3, 2, 2, 2, 1}},
-                                          {{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {3, 3, 2, 2, 2}, {4, 2, 2, 2, 1}}};
+// Waves that a SIMD's registers hold at least ([kind of rows and groups][rt - 1][cj - 1]), over the instantiations that take the
+// whole of K; pairs of waves, the exact dequant and two row tiles x 2 blocks with groups of 64 mostly hold one more, which the
+// prices were fitted without.  A workgroup fewer than claimed costs a round: groups of 64 claimed five at one row tile x 2 blocks,
+// and 1280 x 12896 took 8.3 us with 18 bf16 rows; with four 6.1 (22784 x 13184 at M = 8, claimed to hold parts in one round, 34.7
+// -> 29.2).
+enum Kind { INT8, BF16, BF16_G64, N_KINDS };                 // (int8 rows: both group sizes alike)
+inline Kind kind_of(int xt, int G) { return xt == 0 ? INT8 : G == 64 ? BF16_G64 : BF16; }
+constexpr int SIMD_WAVES[N_KINDS][4][MAX_CJ] = {{{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {4, 3, 2, 2, 2}, {3, 2, 2, 2, 1}},
+                                                {{6, 5, 4, 4, 3}, {4, 3, 3, 2, 2}, {3, 3, 2, 2, 2}, {4, 2, 2, 2, 1}},
+                                                {{6, 4, 4, 4, 3}, {4, 3, 3, 2, 2}, {3, 3, 2, 2, 2}, {4, 2, 2, 2, 1}}};
+// The same where K is split across workgroups: two instantiations that store parts take more registers than the whole ones.
+constexpr int simd_waves(int kind, int rt, int cj, bool parts)
+{
+    if (parts && kind != INT8 && rt == 1 && cj == 2) return 4;
+    if (parts && kind == BF16_G64 && rt == 1 && cj == 4) return 3;
+    return SIMD_WAVES[kind][rt - 1][cj - 1];
+}
 
 // The shapes of a workgroup: K ranges x waves that share one.
 constexpr int N_FORMS = 5;
 constexpr int FORMS[N_FORMS][2] = {{16, 1}, {8, 1}, {4, 1}, {2, 2}, {4, 2}};
 constexpr int FORM_LOG[N_FORMS] = {4, 3, 2, 1, 2};           // FORMS[f][0] == 1 << FORM_LOG[f]
-constexpr int resident_of(int xt, int rt, int cj, int ks, int sh)
+constexpr int resident_of(int kind, int rt, int cj, int ks, int sh, bool parts)
 {
     const int by_lds = 160 * 1024 / (ks * range_lds(rt, cj, sh) + rt * 64);
-    const int by_regs = 4 * SIMD_WAVES[xt][rt - 1][cj - 1] / (ks * sh);
+    const int by_regs = 4 * simd_waves(kind, rt, cj, parts) / (ks * sh);
     const int r = by_lds < by_regs ? by_lds : by_regs;
     return r > 1 ? r : 1;
 }
 struct Resident {
-    int8_t n[2][4][MAX_CJ][N_FORMS];                         // workgroups that a CU holds
+    int8_t n[N_KINDS][2][4][MAX_CJ][N_FORMS];                // workgroups that a CU holds; [1]: that store parts
     constexpr Resident() : n{}
     {
-        for (int xt = 0; xt < 2; ++xt)
-            for (int rt = 1; rt <= 4; ++rt)
-                for (int cj = 1; cj <= MAX_CJ; ++cj)
-                    for (int f = 0; f < N_FORMS; ++f) n[xt][rt - 1][cj - 1][f] = (int8_t)resident_of(xt, rt, cj, FORMS[f][0], FORMS[f][1]);
+        for (int k = 0; k < N_KINDS; ++k)
+            for (int parts = 0; parts < 2; ++parts)
+                for (int rt = 1; rt <= 4; ++rt)
+                    for (int cj = 1; cj <= MAX_CJ; ++cj)
+                        for (int f = 0; f < N_FORMS; ++f)
+                            n[k][parts][rt - 1][cj - 1][f] = (int8_t)resident_of(k, rt, cj, FORMS[f][0], FORMS[f][1], parts);
     }
 };
 constexpr Resident RESIDENT;
@@ -187,7 +203,7 @@ constexpr double PARTS_US[2] = {1.0, 2.0}, PARTS_US_PER_VALUE[2] = {3e-6, 2e-6},
 
 // `cap`: fp32 copies of the output that the workspace holds.  us: where the price goes, if wanted.
 inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated, int64_t cap, const w2_tuning_t& tune,
-                 double* us = nullptr)
+                 double* us = nullptr, int G = 128)
 {
     const int M = (int)M64, n_cb = (int)n_cb64, n_kt = (int)n_kt64;
     const double tiles = (double)n_cb * n_kt;
@@ -198,6 +214,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
     double best_price = 1e30;
     // (this runs on every call of up to 256 rows: no division but by powers of two, where it can be had)
     const bool narrow = n_cb <= NARROW_BLOCKS;
+    const Kind kind = kind_of(xt, G);
     const double row_mb = (double)M * n_kt * (xt == 0 ? 256e-6 : 512e-6);
     auto price = [&](const Plan& p, int f, int bands, int groups, int T, int resident) {
         const int nb = (groups * bands * p.sp + 255) >> 8;
@@ -242,7 +259,7 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 if (cbw && width != cbw) continue;
                 const int groups = group_count[width];
                 if (xt == 0 && width <= 2 && !cbw && (int64_t)groups * M * n_kt * 256 > ROW_BYTES_FROM_L2) continue;
-                const int resident = RESIDENT.n[xt][rt - 1][cj - 1][f];
+                const int resident = RESIDENT.n[kind][0][rt - 1][cj - 1][f], resident_parts = RESIDENT.n[kind][1][rt - 1][cj - 1][f];
                 auto offer = [&](int ks, int sp, int T, int res) {
                     const Plan p = {rt, cj, ks, sh, sp};
                     const double t = price(p, f, bands, groups, T, res);
@@ -252,20 +269,20 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
                 if (forced > 1) {
                     if (odd) continue;
                     const int ks = std::max(1, std::min(1 << lk, n_kt / forced));
-                    offer(ks, forced, (n_kt + ks * forced - 1) / (ks * forced), resident);
+                    offer(ks, forced, (n_kt + ks * forced - 1) / (ks * forced), resident_parts);
                     continue;
                 }
                 if (n_kt >= 1 << lk) offer(1 << lk, 1, (n_kt + (1 << lk) - 1) >> lk, resident);
-                else offer(n_kt, 1, 1, resident_of(xt, rt, cj, n_kt, sh));
+                else offer(n_kt, 1, 1, resident_of(kind, rt, cj, n_kt, sh, false));
                 // Across workgroups: grids that leave half the chip idle, in as many parts as still run at once, one per CU, and
                 // with bf16 rows (whose workgroups take longer) grids of one round in two per CU, where two fit; other
                 // numbers of parts were hardly ever faster by more than 3 %.  From K = 8192 on, with int8 rows from 20480 (17408 x
                 // 1024 at M = 5 7.1 us in parts, 5.6 in one piece).
                 const int wgs = groups * bands;
                 if (cap < 2 || n_kt < (xt == 0 ? 80 : 32) || cj == 1 || odd || f == 0 || tune.splitk == 1) continue;
-                const int at_once = wgs <= 128 ? 256 : xt == 1 && wgs <= 256 && resident >= 2 ? 512 : 0;
+                const int at_once = wgs <= 128 ? 256 : xt == 1 && wgs <= 256 && resident_parts >= 2 ? 512 : 0;
                 const int sp = (int)std::min<int64_t>(std::min(at_once / wgs, n_kt >> (lk + 1)), std::min<int64_t>(8, cap));
-                if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident);
+                if (sp >= 2) offer(1 << lk, sp, (n_kt + (sp << lk) - 1) / (sp << lk), resident_parts);
             }
         }
     }

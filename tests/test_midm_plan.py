@@ -1,6 +1,8 @@
 """The mid-M kernel's launch shapes, on the host: csrc/midm_plan.h compiled by itself."""
 import os
+import re
 import shutil
+import struct
 import subprocess
 
 import pytest
@@ -11,13 +13,17 @@ PROGRAM = r"""
 #include <stdio.h>
 int main()
 {
-    int xt, gated, cbw, splitk;
+    int xt, gated, cbw, splitk, G;
     long long M, n_cb, n_kt, cap;
-    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d", &xt, &M, &n_cb, &n_kt, &gated, &cbw, &cap, &splitk) == 8) {
+    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d %%d", &xt, &M, &n_cb, &n_kt, &gated, &cbw, &cap, &splitk, &G) == 9) {
+        if (M == 0) {                                        // (rows that no call has: the registers' table; gated: with parts)
+            printf("%%d\n", w2::midm::simd_waves(w2::midm::kind_of(xt, G), (int)n_cb, (int)n_kt, gated != 0));
+            continue;
+        }
         w2_tuning_t tune = {};
         tune.midm_cbw = cbw;
         tune.splitk = splitk;
-        const w2::midm::Plan p = w2::midm::plan(xt, M, n_cb, n_kt, gated != 0, cap, tune);
+        const w2::midm::Plan p = w2::midm::plan(xt, M, n_cb, n_kt, gated != 0, cap, tune, nullptr, G);
         printf("%%d %%d %%d %%d %%d\n", p.rt, p.cj, p.ks, p.sh, p.sp);
     }
 }
@@ -33,9 +39,9 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
 
     def ask(problems):
-        """problems: (rows int8 0 / bf16 1, M, K, N, gated, midm_cbw[, copies of the output that fit, splitk])
+        """problems: (rows int8 0 / bf16 1, M, K, N, gated, midm_cbw[, copies of the output that fit, splitk[, G]])
         -> (rt, cj, ks, sh, sp) each"""
-        text = "".join("{} {} {} {} {} {} {} {}\n".format(xt, M, (N + 15) // 16, K // 256, g, cbw, *(more or (0, 0)))
+        text = "".join("{} {} {} {} {} {} {} {} {}\n".format(xt, M, (N + 15) // 16, K // 256, g, cbw, *(more + [0, 0, 128][len(more):]))
                        for xt, M, K, N, g, cbw, *more in problems)
         out = subprocess.run([str(d / "p")], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, l.split())) for l in out.splitlines()]
@@ -126,3 +132,41 @@ def test_pairs_of_one_block(plans):
     # int8 rows: two waves of one column block each on one K range, on narrow grids of short launches
     for M, K, N in ((57, 1536, 4672), (77, 2560, 3360), (210, 1024, 1600), (169, 2560, 1632)):
         assert plans([(0, M, K, N, int(N % 32 == 0), 0)]) == [(1, 1, 2, 2, 1)]
+
+
+def test_groups_of_64_take_more_registers(plans):
+    # bf16 rows, groups of 64: one row tile x 2 blocks holds four waves a SIMD where groups of 128 hold five, and parts of one
+    # row tile x 4 blocks three: no second round that the price does not know of, no parts that do not run at once
+    assert plans([(1, 18, 1280, 12896, 0, 0, 16, 0, G) for G in (128, 64)]) == [(1, 2, 5, 1, 1), (2, 2, 5, 1, 1)]
+    for M, K, N in ((7, 27648, 12896), (8, 22784, 13184), (3, 26624, 14240)):
+        assert [p[4] for p in plans([(1, M, K, N, 0, 0, 16, 0, G) for G in (128, 64)])] == [2, 1]
+
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+def test_simd_waves_are_those_of_the_built_kernels(plans, tmp_path):
+    # the planner's table against the registers of what was compiled
+    lib = os.path.join(ROOT, "paper_2508_06753_amd", "libw2mm.so")
+    if not (os.path.exists(lib) and os.path.exists(READELF)):
+        pytest.skip("no built library or no llvm-readelf")
+    data, magic, regs, at = open(lib, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}, -1
+    while (at := data.find(magic, at + 1)) >= 0:             # (one bundle per source file)
+        (n,), p = struct.unpack_from("<Q", data, at + len(magic)), at + len(magic) + 8
+        if n > 8:
+            continue                                         # (the text itself, in a string)
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", data, p)
+            name, p = data[p + 24:p + 24 + idlen], p + 24 + idlen
+            if b"gfx950" in name and b"midm_kernel" in (code := data[at + off:at + off + size]):
+                (tmp_path / "code").write_bytes(code)
+                notes = subprocess.run([READELF, "--notes", str(tmp_path / "code")], capture_output=True, text=True).stdout
+                for m in re.finditer(r"\.name:\s+\S*midm_kernelILi(\d)ELi(\d+)ELi(\d)ELi(\d)ELi(\d)ELb(\d)ELi(\d)E.*?\.vgpr_count:\s+(\d+)",
+                                     notes, re.S):
+                    regs[tuple(map(int, m.groups()[:7]))] = int(m[8])
+    assert len(regs) > 200
+    # (xt, G, rt, cj, waves to a range, exact dequant, 0 whole / 1 parts / 2 the test-only export)
+    keys = [k for k in regs if k[6] < 2]
+    for k, (table,) in zip(keys, plans([(k[0], 0, 256 * k[3], 16 * k[2], k[6], 0, 0, 0, k[1]) for k in keys])):
+        waves = min(8, 512 // (-(-regs[k] // 8) * 8))
+        assert waves - 2 <= table <= waves, (k, regs[k])     # (pairs of one block with the exact dequant: six of eight)
