@@ -254,6 +254,10 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
             const int8_t n_forms = OFFERED.n[xt][gated][rt - 1][cj - 1], *forms = OFFERED.f[xt][gated][rt - 1][cj - 1];
             for (int i = 0; i < n_forms; ++i) {
                 const int f = forms[i], sh = FORMS[f][1], width = cj * sh;   // column blocks per workgroup
+                // (K = 1280 in five waves: one SIMD of four has two of them, which the price, fitted to eight, does not know.  Over
+                // 49 problems what was chosen with them was 11 % slower than the fastest shape, without them 4 %; 1280 x 9280 with 72
+                // bf16 rows 11.8 -> 9.0 us.  Six and seven waves are right within 4 and 2 %.)
+                if (!narrow && f == 1 && n_kt == 5 && !forced) continue;
                 if (odd && !odd_balances(group_count, cj, sh, bands)) continue;
                 if (!narrow && cj == 1 && sh == 2) continue;             // (not fitted there: four blocks per workgroup and more win)
                 if (cbw && width != cbw) continue;

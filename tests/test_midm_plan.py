@@ -137,9 +137,17 @@ def test_pairs_of_one_block(plans):
 def test_groups_of_64_take_more_registers(plans):
     # bf16 rows, groups of 64: one row tile x 2 blocks holds four waves a SIMD where groups of 128 hold five, and parts of one
     # row tile x 4 blocks three: no second round that the price does not know of, no parts that do not run at once
-    assert plans([(1, 18, 1280, 12896, 0, 0, 16, 0, G) for G in (128, 64)]) == [(1, 2, 5, 1, 1), (2, 2, 5, 1, 1)]
+    assert plans([(1, 28, 2560, 6784, 0, 0, 16, 0, G) for G in (128, 64)]) == [(1, 2, 10, 1, 1), (2, 2, 4, 1, 1)]
     for M, K, N in ((7, 27648, 12896), (8, 22784, 13184), (3, 26624, 14240)):
         assert [p[4] for p in plans([(1, M, K, N, 0, 0, 16, 0, G) for G in (128, 64)])] == [2, 1]
+
+
+def test_no_five_waves_on_wide_grids(plans):
+    # (two of them on one SIMD; up to 512 column blocks they are priced for what they are)
+    problems = [(xt, M, 1280, N, g, 0, 16, 0, G) for xt in (0, 1) for M in (3, 9, 17, 40, 72, 113, 240) for N in range(8224, 57344, 1120)
+                for g in (0, 1) for G in (64, 128)]
+    assert all(p[2] != 5 for p in plans(problems))
+    assert any(p[2] == 5 for p in plans([(1, M, 1280, 4096, 0, 0) for M in (9, 17, 40)]))
 
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
