@@ -13,10 +13,16 @@ namespace route {
 // Most rows of each kernel.
 constexpr int64_t DOT4_ROWS = 4, SMALL_ROWS = 16, GEMV_ROWS = 32, MIDM_ROWS = 256;
 
-// The tiled kernels before the mid-M kernel where both take the rows (int8, bf16 rows): where their price (tile_plan.h) is
-// under its price (midm_plan.h) by more than the latter errs; with less of a margin 28672 x 8192 at M = 100 takes 38.0 us
-// instead of 35.2.
-constexpr double TILED_MARGIN[2] = {0.86, 0.93};
+// The tiled kernels before the mid-M kernel where both take the rows: where their price (tile_plan.h) is under this share of its
+// price (midm_plan.h).  By activations and by the shape that the mid-M kernel would run: eight K ranges and more to a workgroup are
+// priced 3 to 9 % high on the deep K where the two meet, four and fewer are not.  Loss against the faster of the two, graph-timed on
+// 1850 random problems of 33 to 250 rows around the line (K from 1024, N from 1024 up), in per cent by share:
+//   int8 rows, fewer than eight ranges  0.86 3.9, 0.94 1.6, 1.0 1.0, 1.05 1.0     eight  0.84 0.54, 0.88 0.45, 0.94 0.6, 1.0 1.7
+//   bf16 rows, fewer than eight ranges  0.93 1.5, 0.96 0.8, 1.0 0.3, 1.05 0.5     eight  0.90 1.8, 0.94 0.7, 0.96 0.6, 1.0 0.7
+// With one share of 0.86 for all int8 and 0.93 for all bf16 rows 26880 x 9664 at M = 127 took 55 us instead of 47, 13312 x 6688
+// with bf16 rows and groups of 64 at M = 226 57 instead of 51; 220 further problems whose kernel changed are 7 % faster.
+constexpr double TILED_SHARE[2][2] = {{1.0, 0.88}, {1.0, 0.94}};
+inline double tiled_share(int a16, const midm::Plan& p) { return TILED_SHARE[a16][p.ks >= 8]; }
 
 struct Problem {
     int64_t M, K, N;
@@ -75,7 +81,7 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
         double us;
         r.midm = midm_shape(0, p, tn, &us);
         r.has_midm = true;
-        us *= TILED_MARGIN[0];
+        us *= tiled_share(0, r.midm);
         if (us > tiles::LEAST_US[p.G == 128 ? tiles::A8_G128 : tiles::A8_G64]) {
             r.tiled = a8_tiled_shape(p, tn);
             r.has_tiled = true;
@@ -117,7 +123,7 @@ inline bool a16_tiled_first(const Problem& p, const w2_tuning_t& tn, A16* r)
     double us;
     r->midm = midm_shape(1, p, tn, &us);
     r->has_midm = true;
-    us *= TILED_MARGIN[1];
+    us *= tiled_share(1, r->midm);
     if (us <= tiles::LEAST_US[tiles::A16]) return false;
     r->tiled = a16_tiled_shape(p, tn);
     r->has_tiled = true;
