@@ -623,12 +623,13 @@ def test_auto_dispatch_over_random_shapes(w2, M, K, N, G, seed):
 @pytest.mark.parametrize("path,M,K,N", [("a8", 48, 17920, 8208), ("a8", 49, 17920, 8208), ("a8", 64, 17920, 10240),
                                         ("a8", 33, 15360, 16400), ("a8", 113, 25600, 8208), ("a8", 12, 8192, 12288),
                                         ("a16", 8, 8192, 12288), ("a16", 96, 16384, 10256), ("a16", 97, 14080, 8208),
-                                        ("a16", 129, 8192, 10256), ("a16", 193, 11264, 6160)])
+                                        ("a16", 129, 8192, 10256), ("a16", 193, 11264, 6160), ("a8", 127, 26880, 9664),
+                                        ("a8", 103, 24832, 6976), ("a16", 128, 24576, 6144), ("a16", 100, 28672, 4096)])
 def test_auto_ranges_agree_with_midm(w2, path, M, K, N):
-    # the edges of the ranges that AUTO gives to the decode and tiled kernels, with the workspace that the call asks for,
-    # against the mid-M kernel.  Bound: bf16 holds eight significant bits, so each side is within half a unit, 2^-8 |y|, of
-    # its fp32 sum (2^-7 |y| together), and the fp32 sums differ by the dequant's bias and the order of the additions, which
-    # stays below 2^-11 of the outputs' root mean square
+    # both sides of the lines between the decode, mid-M and tiled kernels, with the workspace that the call asks for: the mid-M
+    # kernel against the other one that takes the rows, and AUTO as one of the two.  Bound: bf16 holds eight significant bits, so
+    # each side is within half a unit, 2^-8 |y|, of its fp32 sum (2^-7 |y| together), and the fp32 sums differ by the dequant's
+    # bias and the order of the additions, which stays below 2^-11 of the outputs' root mean square
     g = torch.Generator(device="cuda").manual_seed(M + K + N)
     codes = torch.randint(0, 4, (K, N), dtype=torch.uint8, device="cuda", generator=g)
     scales = torch.empty((K // 128, N), device="cuda").uniform_(0.005, 0.05, generator=g).to(torch.bfloat16)
@@ -640,9 +641,12 @@ def test_auto_ranges_agree_with_midm(w2, path, M, K, N):
     else:
         xq, sx, _ = w2.quantize_rows(X)
         call = lambda **kw: w2.matmul_a8(packed, K, N, 128, xq, sx, workspace=ws, **kw).float()
-    a, b = call(), call(variant=w2.VARIANT_MIDM)
-    rms = b.pow(2).mean().sqrt()
-    assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 2.0 ** -11 * rms).all()
+    auto, midm = call(), call(variant=w2.VARIANT_MIDM)
+    other = call(tune={"midm_max_m": 1}) if M > 32 else call(variant=w2.VARIANT_GEMV)
+    rms = midm.pow(2).mean().sqrt()
+    assert ((other - midm).abs() <= 2.0 ** -7 * midm.abs() + 2.0 ** -11 * rms).all()
+    assert M <= 32 or not torch.equal(other, midm)           # (or it is the same kernel twice; up to 32 rows sums are exact)
+    assert torch.equal(auto, other) or torch.equal(auto, midm)
 
 
 @pytest.mark.parametrize("codec", [0, 1])
@@ -993,6 +997,49 @@ def test_midm_odd_widths(w2, xt, M, K, N, gated, G):
         _, y64, mag = oracle.matmul_a16(codes, scales, G, 0, Xb)
         Y = w2.matmul_a16_epi(packed, K, N, G, dev(Xb).view(torch.bfloat16), act=act, variant=w2.VARIANT_MIDM)
     check_epilogue(bf16_bits(Y), y64, mag, None, act, f"xt={xt} M={M} K={K} N={N} G={G} act={act}")
+
+
+# every form of three and five column blocks per wave that the planner gives, (rows int8 0 / bf16 1, M, K, N, gated): row tiles x
+# blocks, a wave or a pair to a K range, with the exact dequant (int8 rows up to 32) or not; the CPU test of the planner holds the
+# list complete
+MIDM_ODD_FORMS = [(0, 40, 1024, 12248, 0), (0, 1, 3584, 11984, 0), (0, 13, 2048, 24224, 1), (0, 1, 3840, 20080, 0), (0, 16, 10240, 40512, 1),
+                  (0, 97, 768, 8200, 0), (0, 17, 768, 32840, 0), (0, 97, 512, 16472, 0), (0, 17, 2816, 24480, 1), (0, 49, 3328, 9256, 0),
+                  (0, 17, 3072, 19816, 0), (0, 128, 12288, 10144, 1), (0, 17, 8192, 37088, 1), (0, 33, 1536, 10928, 0),
+                  (0, 33, 1792, 23968, 1), (0, 33, 2816, 16472, 0), (0, 33, 5120, 34784, 1), (0, 49, 6144, 12072, 0), (0, 49, 5120, 18592, 1),
+                  (1, 1, 3328, 11896, 0), (1, 13, 2048, 24224, 1), (1, 1, 5632, 20168, 0), (1, 17, 1792, 10224, 0), (1, 31, 1024, 23616, 1),
+                  (1, 24, 1792, 18320, 0), (1, 17, 2048, 40608, 1), (1, 33, 768, 10928, 0), (1, 40, 1024, 24416, 1), (1, 33, 1536, 16472, 0),
+                  (1, 40, 1024, 39456, 1), (1, 49, 1024, 11456, 0), (1, 49, 768, 23360, 1)]
+
+
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("xt,M,K,N,gated", MIDM_ODD_FORMS)
+def test_midm_odd_widths_every_form(w2, xt, M, K, N, gated, G):
+    # all columns are computed; the oracle has the first 12 and the last 12 pairs of column blocks (more than the widest workgroup)
+    # and 12 between, in whole pairs
+    rng = np.random.default_rng(M + K + N + G)
+    g = torch.Generator(device="cuda").manual_seed(M + K + N + G)
+    codes = torch.randint(0, 4, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    scales = torch.empty((K // G, N), device="cuda").uniform_(0.005, 0.05, generator=g).to(torch.bfloat16)
+    packed = w2.prepack(codes, scales, G)
+    pairs = np.unique(np.concatenate([np.arange(12), rng.choice(np.arange(12, N // 32 - 12), 12, replace=False), np.arange(N // 32 - 12, N // 32)]))
+    cols = (pairs[:, None] * 32 + np.arange(32)).reshape(-1)
+    if not gated:
+        cols = np.concatenate([cols, np.arange(N // 32 * 32, N)])
+    at = torch.from_numpy(cols).cuda()
+    cs, ss = codes[:, at].cpu().numpy(), scales[:, at].contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    X = synth.make_activations(M, K, seed=M + K)
+    act = w2.ACT_SILU_MUL if gated else w2.ACT_NONE
+    if xt == 0:
+        oq, osx, _ = oracle.quantize_rows(X, G)
+        _, y64 = oracle.matmul_a8(cs, ss, G, 0, oq, osx)
+        mag = oracle.a8_term_magnitude(cs, ss, G, 0, oq, osx)
+        Y = w2.matmul_a8_epi(packed, K, N, G, dev(oq), dev(osx), act=act, variant=w2.VARIANT_MIDM)
+    else:
+        Xb = synth.f32_to_bf16_bits(X)
+        _, y64, mag = oracle.matmul_a16(cs, ss, G, 0, Xb)
+        Y = w2.matmul_a16_epi(packed, K, N, G, dev(Xb).view(torch.bfloat16), act=act, variant=w2.VARIANT_MIDM)
+    out = (pairs[:, None] * 16 + np.arange(16)).reshape(-1) if gated else cols
+    check_epilogue(np.ascontiguousarray(bf16_bits(Y)[:, out]), y64, mag, None, act, f"xt={xt} M={M} K={K} N={N} G={G} act={act}")
 
 
 def test_epilogue_argument_errors(w2):

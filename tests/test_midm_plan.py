@@ -128,6 +128,23 @@ def test_odd_widths(plans):
         assert got == want + (1,), (p, got)
 
 
+def test_every_odd_form_is_run(plans):
+    # the GPU tests' list has every (rows, row tiles, blocks, waves to a range, exact dequant) of three and five blocks that the
+    # planner gives over a grid of sizes, in both group sizes
+    from test_gpu_parity import MIDM_ODD_FORMS
+
+    def forms(problems):
+        return {(p[0], rt, cj, sh, p[0] == 0 and p[1] <= 32) for p, (rt, cj, _, sh, _) in zip(problems, plans(problems)) if cj in (3, 5)}
+
+    grid = [(xt, M, K, N, g, 0, 0, 0, G) for xt in (0, 1) for M in (5, 9, 16, 17, 31, 33, 40, 49, 64, 96, 97, 128, 192)
+            for K in (512, 768, 1024, 2048, 3072, 5120, 8192, 10240, 14336) for N in range(8192, 57344, 416) for g in (0, 1) for G in (64, 128)]
+    run = [{(p, G): forms([p + (0, 0, 0, G)]) for p in MIDM_ODD_FORMS} for G in (64, 128)]
+    for r in run:
+        assert all(r.values())                               # each is what it is there for
+        have = set().union(*r.values())
+        assert len(have) == len(MIDM_ODD_FORMS) == 32 and have >= forms(grid)
+
+
 def test_pairs_of_one_block(plans):
     # int8 rows: two waves of one column block each on one K range, on narrow grids of short launches
     for M, K, N in ((57, 1536, 4672), (77, 2560, 3360), (210, 1024, 1600), (169, 2560, 1632)):
