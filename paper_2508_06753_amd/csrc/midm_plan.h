@@ -53,7 +53,12 @@ constexpr int FORM_LOG[N_FORMS] = {4, 3, 2, 1, 2};           // FORMS[f][0] == 1
 constexpr int resident_of(int kind, int rt, int cj, int ks, int sh, bool parts)
 {
     const int by_lds = 160 * 1024 / (ks * range_lds(rt, cj, sh) + rt * 64);
-    const int by_regs = 4 * simd_waves(kind, rt, cj, parts) / (ks * sh);
+    // A workgroup's waves go round the four SIMDs from the same one on, so of 5, 6, 9 or 10 waves it is the SIMD with the most that
+    // fills up: 10 waves of one row tile x 2 blocks run one workgroup to a CU, not two, 6 of three row tiles x 2 blocks too.  Priced as
+    // two 1536 x 8384 took 12.0 us with 71 bf16 rows, now 8.0 in another shape, 1280 x 6112 with 243 17.3 and 10.7, 2560 x 2112 with 79
+    // int8 rows 6.1 and 4.6; 300 random problems whose shape changes 14 % less.
+    const int waves = ks * sh, per_simd = simd_waves(kind, rt, cj, parts);
+    const int by_regs = waves <= 4 ? 4 * per_simd / waves : per_simd / ((waves + 3) / 4);
     const int r = by_lds < by_regs ? by_lds : by_regs;
     return r > 1 ? r : 1;
 }
@@ -254,10 +259,6 @@ inline Plan plan(int xt, int64_t M64, int64_t n_cb64, int64_t n_kt64, bool gated
             const int8_t n_forms = OFFERED.n[xt][gated][rt - 1][cj - 1], *forms = OFFERED.f[xt][gated][rt - 1][cj - 1];
             for (int i = 0; i < n_forms; ++i) {
                 const int f = forms[i], sh = FORMS[f][1], width = cj * sh;   // column blocks per workgroup
-                // (K = 1280 in five waves: one SIMD of four has two of them, which the price, fitted to eight, does not know.  Over
-                // 49 problems what was chosen with them was 11 % slower than the fastest shape, without them 4 %; 1280 x 9280 with 72
-                // bf16 rows 11.8 -> 9.0 us.  Six and seven waves are right within 4 and 2 %.)
-                if (!narrow && f == 1 && n_kt == 5 && !forced) continue;
                 if (odd && !odd_balances(group_count, cj, sh, bands)) continue;
                 if (!narrow && cj == 1 && sh == 2) continue;             // (not fitted there: four blocks per workgroup and more win)
                 if (cbw && width != cbw) continue;
