@@ -213,8 +213,11 @@ inline A8Shape a8_shape(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, 
     // forced shapes that only the 64-row kernel has
     if (tune.tiled_bm == 64 || tune.tiled_bn == 64 || tune.tiled_bn == 128 || tune.tiled_kw || tune.tiled_wd) return low;
     const Shape t = pick(kind, M, N, n_kt, cap, 0, tune.splitk);
-    // (256-column workgroups: the margins that leave the fewest of 380 measured problems slower than in these tiles)
-    const bool tall = t.us < p.us * (p.bn < 256 ? 1.0 : G == 128 ? 0.985 : 0.965);
+    // (256-column workgroups: the margins that leave the fewest of 380 measured problems slower than in these tiles.  Narrow ones
+    // with groups of 64: over 120 problems near the line a share of 1.0 loses 1.0 %, 0.95 0.3 %; 27648 x 5440 at M = 506 without a
+    // workspace 150 us in tall tiles, 137 in 64-row ones.  With groups of 128 1.0 is best: 0.2 %, 0.95 2.3 %.)
+    const double share = p.bn < 256 ? (G == 128 ? 1.0 : 0.95) : G == 128 ? 0.985 : 0.965;
+    const bool tall = t.us < p.us * share;
     return tall ? A8Shape{t.ri, 256, 1, t.splits, t.us} : low;
 }
 

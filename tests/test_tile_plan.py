@@ -116,6 +116,13 @@ def test_forced_tiles(plans):
         assert splits == 1 or not (bm == 128 and width == 128 and G == 64)    # (not built)
 
 
+def test_groups_of_64_on_narrow_grids(plans):
+    # 64-row tiles, measured 8 to 10 % faster than the tall ones whose price is 2 to 3 % lower; tall ones where the price is clear
+    low = [("a", 64, M, N, K // 256, 0, 0, 0, 0) for M, K, N in ((506, 27648, 5440), (1257, 26112, 1728), (597, 18432, 3584))]
+    tall = [("a", 64, 257, 1752, 32, 16, 0, 0, 0), ("a", 64, 321, 2744, 32, 16, 0, 0, 0)]
+    assert [r[0] for r in plans(low)] == [0] * 3 and all(r[0] for r in plans(tall))
+
+
 def test_heights_are_the_librarys_choice(plans):
     ask = [("t", KINDS[p, G], M, N, K // 256, 16, 0, 0, 0) for p, G, K, N, M, _, _ in HEIGHTS]
     for case, (ri, splits, _, us) in zip(HEIGHTS, plans(ask)):
