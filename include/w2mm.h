@@ -70,13 +70,13 @@ typedef enum {
  * AUTO picks by shape.  w2a8: GEMV up to M = 8 (M = 4 where the rows leave a workgroup little room or the
  * projection has few columns and K is around 5120 or 6144, or beyond 16384; M = 12 with G = 64 and N >= 16384;
  * M = 16 on some 12288 to 16384 columns of K near 8192), MIDM above it up to M = 240 (160 when N > 7168, 112
- * when N >= 24576, 48 when N >= 40960; less where a workspace lets the tiled kernels split a very deep K over
- * rows that fill their tiles), else TILED (64-row tiles; 128-row tiles from M = 1024, or from M = 128 where they
- * fill the chip).
+ * when N >= 24576, 48 when N >= 40960; from M = 33 on only where a price fitted to measurements is not clearly
+ * lower for the tiled kernels, with the K ranges that the workspace has room for), else TILED (tiles of 64 to 128
+ * rows, by price).
  * w2a16: GEMV up to M = 8 (M = 4 when K > 4096, 7 at K = 5120 with N >= 10240, 2 when K > 16384, with exceptions
  * on 12288 to 16384 columns; M = 16 with G = 64, K <= 4096 and N >= 16384) wherever the bf16 rows fit a workgroup's
  * local memory, else SMALLM; MIDM up to M = 192 (256 when N <= 7168 and K <= 14336, 96 when N >= 16384 or K*N >
- * 160 Mi, 64 when N >= 40960; with a workspace less on large K*N), else the SCALED16 tiled kernel.
+ * 160 Mi, 64 when N >= 40960; from M = 33 on by price, as for w2a8), else the SCALED16 tiled kernel.
  * GEMV: the decode kernel: whole rows in local memory, a wave streams a contiguous run of a column
  * block's tiles through a rolling register window into int8 MFMA (w2a8, M <= 32) or, with bf16 rows left as they
  * are and the zero-point weight construction, into bf16 MFMA (w2a16, M <= 16; W2_ERR_UNSUPPORTED_SHAPE when the
@@ -94,7 +94,7 @@ typedef enum {
  * matrix instruction as they are: no zero-point term, no dequant step, one
  * fp32 accumulator per output over the whole K.  M <= 16: the SMALLM kernel
  * with this construction (never picked by AUTO: the zero-point form is faster
- * there); M <= 64: the MIDM kernel; above: a 128-row tiled kernel of its own,
+ * there); M <= 64: the MIDM kernel; above: a tiled kernel of its own (64 to 128 rows),
  * AUTO's choice for prefill.  Needs bf16 scales with an exponent field below
  * 254 (-2 sw is made by raising the exponent by one); AUTO takes this construction
  * from M = 17 on. */

@@ -135,7 +135,7 @@ inline A16 a16(const Problem& p, const w2_tuning_t& tn)
     const int64_t M = p.M;
     A16 r = {};
     // Few rows: the decode kernel wherever a workgroup can hold them, else the small-M kernel (both with the
-    // zero-point construction); then the mid-M kernel; above, 128-row tiles.  Both of the latter fold the scale
+    // zero-point construction); then the mid-M kernel; above, tiles of 64 to 128 rows.  Both of the latter fold the scale
     // into the weights: fewest vector instructions per matrix instruction.
     // Where the mid-M kernel takes over (graph-timed, every launch with rows and weights of its own, us, what ran
     // before against the mid-M kernel): at M = 3 for rows too long for a workgroup (17408 x 5120 16.5 against
