@@ -22,7 +22,13 @@ constexpr int64_t DOT4_ROWS = 4, SMALL_ROWS = 16, GEMV_ROWS = 32, MIDM_ROWS = 25
 // With one share of 0.86 for all int8 and 0.93 for all bf16 rows 26880 x 9664 at M = 127 took 55 us instead of 47, 13312 x 6688
 // with bf16 rows and groups of 64 at M = 226 57 instead of 51; 220 further problems whose kernel changed are 7 % faster.
 constexpr double TILED_SHARE[2][2] = {{1.0, 0.88}, {1.0, 0.94}};
-inline double tiled_share(int a16, const midm::Plan& p) { return TILED_SHARE[a16][p.ks >= 8]; }
+// (The int8 ones further by the kernel, whose price runs a few per cent low for the 64-row one on wide grids.  Fewer than eight
+// ranges, loss by share: 64-row tiles 0.94 0.5, 1.0 1.0, taller ones 0.94 1.8, 1.0 1.0; 7680 x 33408 at M = 101 55 us against 51.)
+constexpr double LOW_TILES_SHARE = 0.94;
+inline double tiled_share(int a16, const midm::Plan& p, bool low_tiles)
+{
+    return low_tiles && p.ks < 8 ? LOW_TILES_SHARE : TILED_SHARE[a16][p.ks >= 8];
+}
 
 struct Problem {
     int64_t M, K, N;
@@ -81,11 +87,10 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
         double us;
         r.midm = midm_shape(0, p, tn, &us);
         r.has_midm = true;
-        us *= tiled_share(0, r.midm);
-        if (us > tiles::LEAST_US[p.G == 128 ? tiles::A8_G128 : tiles::A8_G64]) {
+        if (us * tiled_share(0, r.midm, false) > tiles::LEAST_US[p.G == 128 ? tiles::A8_G128 : tiles::A8_G64]) {
             r.tiled = a8_tiled_shape(p, tn);
             r.has_tiled = true;
-            tiled_first = r.tiled.us < us;
+            tiled_first = r.tiled.us < us * tiled_share(0, r.midm, r.tiled.ri == 0);
         }
     }
     const bool midm_ok = M >= midm_min && M <= midm_max && !tiled_first && M <= MIDM_ROWS;
@@ -123,7 +128,7 @@ inline bool a16_tiled_first(const Problem& p, const w2_tuning_t& tn, A16* r)
     double us;
     r->midm = midm_shape(1, p, tn, &us);
     r->has_midm = true;
-    us *= tiled_share(1, r->midm);
+    us *= tiled_share(1, r->midm, false);
     if (us <= tiles::LEAST_US[tiles::A16]) return false;
     r->tiled = a16_tiled_shape(p, tn);
     r->has_tiled = true;

@@ -21,11 +21,11 @@ int main()
         double us = 0, tiled_us;
         const midm::Plan m = M <= 256 ? route::midm_shape(a16, p, tn, &us) : midm::Plan{};
         int variant, fallback = 0;
-        bool as_planned;
+        bool as_planned, low = false;
         if (!a16) {
             const route::A8 r = route::a8(p, tn);
             const tiles::A8Shape t = route::a8_tiled_shape(p, tn);
-            variant = r.variant; fallback = r.fallback; tiled_us = t.us;
+            variant = r.variant; fallback = r.fallback; tiled_us = t.us; low = t.ri == 0;
             as_planned = (!r.has_midm || same(r.midm, m)) &&
                          (!r.has_tiled || (r.tiled.ri == t.ri && r.tiled.bn == t.bn && r.tiled.kw == t.kw && r.tiled.splits == t.splits));
         } else {
@@ -35,7 +35,7 @@ int main()
             fallback = r.to_midm ? W2_VARIANT_MIDM : W2_VARIANT_TILED; tiled_us = t.us;
             as_planned = (!r.has_midm || same(r.midm, m)) && (!r.has_tiled || (r.tiled.ri == t.ri && r.tiled.splits == t.splits));
         }
-        printf("%%d %%d %%d %%.9g %%.9g %%.9g\n", variant, fallback, (int)as_planned, us, tiled_us, route::tiled_share(a16, m));
+        printf("%%d %%d %%d %%.9g %%.9g %%.9g\n", variant, fallback, (int)as_planned, us, tiled_us, route::tiled_share(a16, m, low));
     }
 }
 """
@@ -92,10 +92,10 @@ def test_prices_decide_and_shapes_are_handed_on(routes):
 
 def test_sides_of_the_line(routes):
     # graph-timed on both kernels: tiled 6 to 14 % faster, where one share for all shapes kept the mid-M kernel; mid-M 1 to 5 %
-    # faster (eight K ranges, priced high); tiled with room for its K ranges only
+    # faster (eight K ranges, priced high), or 10 % (64-row tiles, priced low); tiled with room for its K ranges only
     tiled = [(0, 127, 26880, 9664, 128, 0, 16), (0, 121, 27648, 11648, 128, 0, 16), (0, 126, 25600, 10112, 128, 0, 16),
              (1, 226, 13312, 6688, 64, 0, 16), (1, 128, 24576, 6144, 128, 0, 16), (1, 225, 12800, 6912, 64, 0, 16)]
     midm = [(0, 103, 24832, 6976, 128, 0, 16), (0, 80, 29440, 8192, 128, 0, 16), (0, 77, 26624, 7360, 128, 0, 16),
-            (1, 100, 28672, 4096, 128, 0, 16)] + [p[:6] + (0,) for p in tiled]
+            (1, 100, 28672, 4096, 128, 0, 16), (0, 101, 7680, 33408, 128, 0, 16)] + [p[:6] + (0,) for p in tiled]
     assert [r[0] for r in routes(tiled)] == [TILED] * len(tiled)
     assert [r[0] for r in routes(midm)] == [MIDM] * len(midm)
