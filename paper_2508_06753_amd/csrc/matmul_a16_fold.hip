@@ -11,22 +11,31 @@
 // bytes in one and high bytes in the other.  A dword of the packed tile holds
 // 16 codes, four per byte; (w >> 2j) & 0x03030303 is four codes as four byte
 // selectors, two v_perm_b32 look the low and the high bytes up, two more
-// interleave them into [k even pair] and [k odd pair] registers: 23 vector
+// interleave them into pairs of adjacent k: 23 vector
 // instructions per 16 weights.  They are amortised over a 128-row wave tile
 // (RI = 8 row tiles x CJ = 2 column blocks of v_mfma_f32_16x16x32_bf16: 32
 // matrix instructions per 64-k stage and wave), which is what makes this
-// construction the faster one for prefill: measured, it issues 2.3 vector
+// construction the faster one for prefill: it issues 1.66 vector
 // instructions per matrix instruction where the zero-point kernel issues 5.9.
 //
 // Workgroup: 128 rows (lower tiles of 64 to 112 where those waste less: tile_plan.h;
 // 4096 x 28672 at M = 300 95.7 -> 79.3 us) x (32 columns per wave) x 64 k per stage; activations go
-// through LDS (three or five buffers, rows de-interleaved [even k | odd k] per
-// 16-k block to match the order the codes come out of a dword, row stride
-// 160 B: conflict-free operand reads); weights go from global memory to
+// to local memory by loads that write it directly, six stages ahead (eight
+// buffers; four with 128 columns), 16-byte pieces XORed by row so that operands are
+// read without bank conflicts; weights go from global memory to
 // registers, one 16-byte load per lane, column block and 256-k tile, a whole
 // tile ahead.  Each wave is software-pipelined on its own (next stage's weights
 // are up-converted and its first operands read under this stage's matrix
 // instructions).  Tried and slower: 256-row wave tiles at one wave per SIMD.
+//
+// What bounds it: the issue of vector instructions beside the matrix ones (every one per matrix instruction costs about
+// a tenth of the matrix rate; the matrix pipe alone reaches 1745 TFLOP/s on such operands) and the local memory, which
+// delivers a stage's operands in about the time that the matrix pipe takes.  So nothing but the up-convert is left on the
+// vector pipe: activations that went through registers were written with four permutations and two address sums per 16
+// bytes, and buffer indexes that were not constants cost two more sums a stage and 64-bit compares.  4096 x 28672 at M = 333,
+// groups of 128 (us, tiles of 128 / 112 / 96 / 80 / 64 rows): 97.6 / 93.7 / 91.2 / 118.5 / 110.6 with activations through
+// registers and 2.07 vector instructions per matrix instruction, 95.0 / 89.4 / 85.6 / 111.5 / 97.3 with direct loads (1.79),
+// 90.0 / 83.9 / 79.1 / 102.7 / 91.0 with constant buffer indexes and 32-bit stage numbers (1.66).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -43,14 +52,14 @@ namespace fold16 {
 constexpr int CJ = 2;                              // 16-column blocks per wave
 constexpr int BK = 64;
 constexpr int WN = 16 * CJ;
-constexpr int A_STRIDE = BK * 2 + 32;              // 32 mod 64 bytes: conflict-free A-operand reads
-// LDS buffers: 3 with a barrier after every stage; 5 with a barrier after every other stage (eight-wave
+constexpr int A_ROW = BK * 2;                      // bytes of a row in one stage: eight 16-byte pieces
+// LDS buffers: 4 with a barrier after every stage; 8 with a barrier after every other stage (eight-wave
 // workgroups, one per CU, where the LDS is there for it)
-constexpr int nbuf_of(int bn) { return bn >= 256 ? 5 : 3; }
+constexpr int nbuf_of(int bn) { return bn >= 256 ? 8 : 4; }
 constexpr int E_STRIDE = WN * 2 + 16;              // epilogue: bytes per LDS row of a wave's result
 constexpr int waves_of(int bn) { return bn / WN; }
-constexpr int CP_ROWS = 128;                       // rows that a workgroup's threads stage (a lower tile's last row repeated)
-constexpr int A_BUF = CP_ROWS * A_STRIDE;
+constexpr int CP_ROWS = 128;                       // most rows of a tile
+constexpr int A_BUF = CP_ROWS * A_ROW;
 constexpr int lds_bytes(int bn)
 {
     return nbuf_of(bn) * A_BUF > waves_of(bn) * CP_ROWS * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * CP_ROWS * E_STRIDE;
@@ -80,7 +89,8 @@ __device__ __forceinline__ Lut make_lut(uint32_t s)          // s: bf16 bit patt
     return l;
 }
 
-// 16 codes of one dword -> b0 (even k of the lane's 16-k block), b1 (odd k)
+// 16 codes of one dword -> b0 (k 8 .. 15 of the lane's 16-k block), b1 (k 0 .. 7): the upper half is multiplied first, so that
+// sums over the same K ranges can be told from the mid-M kernel's
 __device__ __forceinline__ void upconvert(uint32_t w, const Lut& l, v4i& b0, v4i& b1)
 {
 #pragma unroll
@@ -88,8 +98,9 @@ __device__ __forceinline__ void upconvert(uint32_t w, const Lut& l, v4i& b0, v4i
         const uint32_t t = (w >> (2 * j)) & 0x03030303u;     // the codes of k = 4j .. 4j+3 as byte selectors
         const uint32_t lo = __builtin_amdgcn_perm(0u, l.lo4, t);
         const uint32_t hi = __builtin_amdgcn_perm(0u, l.hi4, t);
-        b0[j] = (int)__builtin_amdgcn_perm(hi, lo, 0x06020400u);   // k = 4j, 4j+2
-        b1[j] = (int)__builtin_amdgcn_perm(hi, lo, 0x07030501u);   // k = 4j+1, 4j+3
+        v4i& b = j < 2 ? b1 : b0;
+        b[2 * (j & 1)] = (int)__builtin_amdgcn_perm(hi, lo, 0x05010400u);       // k = 4j, 4j+1
+        b[2 * (j & 1) + 1] = (int)__builtin_amdgcn_perm(hi, lo, 0x07030602u);   // k = 4j+2, 4j+3
     }
 }
 
@@ -111,10 +122,12 @@ __global__ void __launch_bounds__(64 * waves_of(BN), waves_of(BN) > 4 ? 1 : 2)
 a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int splits)
 {
     constexpr int BM = 16 * RI;
-    constexpr int WAVES = waves_of(BN), THREADS = 64 * WAVES;
+    constexpr int WAVES = waves_of(BN);
     constexpr int GPT = TILE_K / G;
     constexpr int NBUF = nbuf_of(BN);
-    constexpr int NP = CP_ROWS * 8 / THREADS;           // 16-byte activation pieces per thread and stage: 2 or 4
+    constexpr bool PAIR = BN >= 256;                    // a barrier after every other stage
+    constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
+    constexpr int NP = (2 * RI + WAVES - 1) / WAVES;    // KiBs of activations (eight rows) per wave and stage: 1, 2 or 4
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -145,20 +158,18 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     uint32_t w_lane = (uint32_t)lane * 16u;
     uint32_t s_lane = (uint32_t)l16 * (GPT * 2u);
 
-    // copy: eight threads per row, 16 B (eight k) each, NP rows per thread; rows past M repeat the
-    // last row.  Lane offsets stay below 128 * 2 * ldx <= 2^32 (ldx <= 2^24).
-    const int cp_seg = tid & 7;
-    const char* cp_base = reinterpret_cast<const char*>(a.X + m0 * a.ldx);               // uniform
-    uint32_t cp_lane[NP];
-    int cp_dst[NP];
+    // The activations go from global to local memory directly, a KiB (eight rows x 128 bytes) per instruction.  A row's
+    // 16-byte pieces stand there XORed by row mod 8 (operand reads without bank conflicts), k-step e's piece of lane
+    // quarter q, k 16q + 8 - 8e .. 16q + 15 - 8e, at slot (4e + q) ^ (row mod 8): the lanes fetch their pieces in that order.
+    // Rows past M or past the tile lie past the resource's end; lane offsets stay below 2^32 (ldx <= 2^24).
+    const int rows = (int)min((int64_t)BM, a.M - m0);
+    const uint32_t stride = (uint32_t)a.ldx * 2u;
+    const char* const xbase = reinterpret_cast<const char*>(a.X + m0 * a.ldx);
+    const uint32_t xbytes = (uint32_t)(rows - 1) * stride + (uint32_t)a.n_kt * (TILE_K * 2);
+    const int slot = (lane & 7) ^ (lane >> 3), piece = ((slot & 3) << 1) | (slot >> 2 ^ 1);
+    uint32_t xoff[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const int row = (tid >> 3) + p * (THREADS / 8);
-        int64_t m = m0 + min(row, BM - 1);
-        if (m >= a.M) m = a.M - 1;
-        cp_lane[p] = (uint32_t)((m - m0) * a.ldx * 2) + (uint32_t)cp_seg * 16u;
-        cp_dst[p] = row * A_STRIDE + (cp_seg >> 1) * 16 + (cp_seg & 1) * 8;
-    }
+    for (int p = 0; p < NP; ++p) xoff[p] = (uint32_t)((wn + WAVES * p) * 8 + (lane >> 3)) * stride + (uint32_t)piece * 16u;
 
     v4f acc[RI][CJ];
 #pragma unroll
@@ -167,40 +178,18 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
         for (int j = 0; j < CJ; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
 
     // this workgroup's K range (split-K: blockIdx.y of `splits` near-equal ranges of whole tiles)
-    const int64_t kt_b = a.n_kt * blockIdx.y / splits, kt_e = a.n_kt * (blockIdx.y + 1) / splits;
-    const int64_t st_b = kt_b * 4, n_st = kt_e * 4;          // stages of 64 k: [st_b, n_st)
-    // two register sets: a load has two stages to land before its data goes to LDS
-    // (four-wave workgroups copy twice as much per thread and keep one set: the registers do not allow two)
-    constexpr bool TWO_SETS = NP <= 2;
-    uint4 ar0[NP], ar1[TWO_SETS ? NP : 1];
-    auto load_a = [&](int64_t st, uint4 (&ar)[NP]) {
-        st = min(st, n_st - 1);
-        const char* p = cp_base + st * (BK * 2);             // uniform
+    const int kt_b = (int)(a.n_kt * blockIdx.y / splits), kt_e = (int)(a.n_kt * (blockIdx.y + 1) / splits);
+    const int st_b = kt_b * 4, n_st = kt_e * 4;              // stages of 64 k: [st_b, n_st)
+    // (past the range's end: nothing is read, but the instructions are there, for they are counted)
+    auto load_a = [&](int st, int buf) {
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(xbase, st < n_st ? xbytes : 0u);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            asm volatile("" : "+v"(cp_lane[i]));             // keeps "scalar base + 32-bit offset" addressing
-            ar[i] = *reinterpret_cast<const uint4*>(p + cp_lane[i]);
-        }
+        for (int p = 0; p < NP; ++p) load_to_lds(xr, smem + buf * A_BUF + (wn + WAVES * p) * 1024, xoff[p], (uint32_t)st * A_ROW);
     };
-    // eight k of a row: the even ones to the [even] half of the 16-k block's image, the odd ones 64 B on
-    auto store_a = [&](int buf, const uint4 (&ar)[NP]) {
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const uint32_t d[4] = {ar[i].x, ar[i].y, ar[i].z, ar[i].w};
-            uint2 ev, od;
-            ev.x = __builtin_amdgcn_perm(d[1], d[0], 0x05040100u);
-            ev.y = __builtin_amdgcn_perm(d[3], d[2], 0x05040100u);
-            od.x = __builtin_amdgcn_perm(d[1], d[0], 0x07060302u);
-            od.y = __builtin_amdgcn_perm(d[3], d[2], 0x07060302u);
-            int8_t* dst = smem + buf * A_BUF + cp_dst[i];
-            *reinterpret_cast<uint2*>(dst) = ev;
-            *reinterpret_cast<uint2*>(dst + 64) = od;
-        }
-    };
-    auto load_w = [&](int64_t kt, WTile<G>& r) {
+    auto load_w = [&](int kt, WTile<G>& r) {
         kt = min(kt, kt_e - 1);
-        const int64_t w_off = kt * 1024;
-        const int64_t s_off = kt * (TILE_N * GPT * 2);
+        const int64_t w_off = (int64_t)kt * 1024;
+        const int64_t s_off = (int64_t)kt * (TILE_N * GPT * 2);
         asm volatile("" : "+v"(w_lane), "+v"(s_lane));
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
@@ -217,18 +206,16 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
 
     WTile<G> w0, w1;
     load_w(kt_b, w0);
-    // stages 0 .. WR-1 go to LDS up front; the registers then hold stages WR and WR+1
-    constexpr int WR = NBUF == 3 ? 2 : 3;          // stage it writes the activations of stage it+WR
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int p = 0; p < WR; ++p) {
-        load_a(st_b + p, ar0);
-        store_a(p, ar0);
-    }
-    load_a(st_b + WR, ar0);
-    if constexpr (TWO_SETS) load_a(st_b + WR + 1, ar1);
-    __syncthreads();
+    for (int p = 0; p < AHEAD; ++p) load_a(st_b + p, p);
+    wait_loads<(PAIR ? AHEAD - 3 : AHEAD - 2) * NP>();       // stages 0, 1 (and 2) are there
+    bare_barrier();
 
-    const int8_t* a_base = smem + l16 * A_STRIDE + q * 16;
+    // (operands of k-step 0 and 1 in buffers 0 .. 3 and, beyond the reach of an instruction's offset, from 4 on)
+    const int a_e0 = l16 * A_ROW + (q ^ (l16 & 7)) * 16, a_e1 = l16 * A_ROW + ((4 + q) ^ (l16 & 7)) * 16;
+    int a_f0 = a_e0 + 4 * A_BUF, a_f1 = a_e1 + 4 * A_BUF;
+    asm volatile("" : "+v"(a_f0), "+v"(a_f1));
     Lut lut[CJ];
     struct BSet { v4i b0[CJ], b1[CJ]; };
 
@@ -245,41 +232,36 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     };
 
     // Software pipeline.  A wave enters stage `it` with the stage's weights up-converted (bc) and its
-    // even-k activation operands (a0) in registers.  Under the stage's 32 matrix instructions it
-    // reads the odd-k operands, up-converts the weights of stage it+1 (bn) and reads that stage's
-    // even-k operands, so every wave keeps the matrix pipe and the vector pipe busy at the same
+    // first activation operands (a0) in registers.  Under the stage's 32 matrix instructions it
+    // reads the second k-step's operands, up-converts the weights of stage it+1 (bn) and reads that stage's
+    // first ones, so every wave keeps the matrix pipe and the vector pipe busy at the same
     // time whatever the other waves of the workgroup, which the barriers keep in step, are doing.
-    // LDS, three buffers: stage it reads buffers it and it+1 and writes the activations of stage it+2
-    // (loaded from global memory two stages earlier) into the third; the barrier at the end of a stage
-    // orders both.  Five buffers: a barrier after every other stage only; the pair of stages (2S, 2S+1)
-    // reads stages 2S .. 2S+2 and writes stages 2S+3 and 2S+4, five different buffers, so waves of a
-    // workgroup may be a stage apart inside a pair.
+    // LDS: stage it reads buffers it and it+1.  Eight buffers: the pair of stages (2S, 2S+1) reads stages 2S .. 2S+2
+    // and asks for stages 2S+6 and 2S+7 in the buffers of the pair before, which the barrier ahead of the pair freed;
+    // that barrier follows every wave's wait for its loads up to stage 2S+2, two pairs old.  So waves of a workgroup
+    // may be a stage apart inside a pair.  Four buffers: the same with a barrier after every stage.
     v4i a0[RI];
 #pragma unroll
-    for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(a_base + i * 16 * A_STRIDE);
+    for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(smem + a_e0 + i * 16 * A_ROW);
     BSet bA, bB;
     prep_b(std::integral_constant<int, 0>{}, w0, 0, bA);
     prep_b(std::integral_constant<int, 0>{}, w0, 1, bA);
-    int buf = 0;
-
-    constexpr int VPM = RI == 8 ? 2 : 3;                     // vector instructions per matrix instruction
-    auto stage = [&](int64_t it, auto tc, const WTile<G>& wc, WTile<G>& wnx, const BSet& bc, BSet& bn) {
-        constexpr int t = decltype(tc)::value;
+    constexpr int VPM = RI >= 6 ? 2 : 3;                     // vector instructions per matrix instruction
+    // sc: stage of the loop below, 0 .. 7, and its buffer (mod NBUF)
+    auto stage = [&](int it, auto sc, const WTile<G>& wc, WTile<G>& wnx, const BSet& bc, BSet& bn) {
+        constexpr int t = decltype(sc)::value & 3, buf = decltype(sc)::value & (NBUF - 1);
         constexpr std::integral_constant<int, (t + 1) & 3> tn{};
         const WTile<G>& wn_tile = t == 3 ? wnx : wc;         // where stage it+1 finds its weights
-        const int buf1 = buf == NBUF - 1 ? 0 : buf + 1;
-        const int bufw = buf + WR >= NBUF ? buf + WR - NBUF : buf + WR;
-        if constexpr (TWO_SETS) store_a(bufw, (t & 1) ? ar1 : ar0);      // activations of stage it+WR
-        else store_a(bufw, ar0);
+        constexpr int buf1 = (buf + 1) & (NBUF - 1);
         if constexpr (t == 0) load_w((it >> 2) + 1, wnx);
-        if constexpr (TWO_SETS) load_a(it + WR + 2, (t & 1) ? ar1 : ar0);
-        else load_a(it + WR + 1, ar0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(it + AHEAD, (buf + AHEAD) & (NBUF - 1));
         __builtin_amdgcn_sched_barrier(0);                   // all loads are issued up here, unconditionally
-        const int8_t* ab = a_base + buf * A_BUF;
-        const int8_t* abn = a_base + buf1 * A_BUF;
+        const int8_t* const ab = smem + (buf < 4 ? a_e1 : a_f1) + (buf & 3) * A_BUF;
+        const int8_t* const abn = smem + (buf1 < 4 ? a_e0 : a_f0) + (buf1 & 3) * A_BUF;
         v4i a1[RI];
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_STRIDE + 64);
+        for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_ROW);
         prep_b(tn, wn_tile, 0, bn);
 #pragma unroll
         for (int j = 0; j < CJ; ++j)
@@ -287,7 +269,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
             for (int i = 0; i < RI; ++i) acc[i][j] = mfma_bf16(a0[i], bc.b0[j], acc[i][j]);
         prep_b(tn, wn_tile, 1, bn);
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
+        for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_ROW);
 #pragma unroll
         for (int j = 0; j < CJ; ++j)
 #pragma unroll
@@ -307,19 +289,25 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
                 __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
             }
         }
-        buf = buf1;
-        if constexpr (NBUF == 3 || (t & 1)) __syncthreads();
+        // before the next pair: stages up to its third have landed; what was asked for since, three more, and a tile's
+        // weights in its first stage, may be under way.  (Four buffers: the next two stages; one more.)
+        if constexpr (PAIR && (t & 1)) wait_loads<3 * NP + (t == 1 ? 2 * CJ : 0)>();
+        if constexpr (!PAIR) wait_loads<NP + (t == 0 ? 2 * CJ : 0)>();
+        if constexpr (!PAIR || (t & 1)) bare_barrier();
     };
-    auto tile = [&](int64_t kt, const WTile<G>& wc, WTile<G>& wnx) {
-        stage(kt * 4, std::integral_constant<int, 0>{}, wc, wnx, bA, bB);
-        stage(kt * 4 + 1, std::integral_constant<int, 1>{}, wc, wnx, bB, bA);
-        stage(kt * 4 + 2, std::integral_constant<int, 2>{}, wc, wnx, bA, bB);
-        stage(kt * 4 + 3, std::integral_constant<int, 3>{}, wc, wnx, bB, bA);
+    auto tile = [&](int kt, auto oc, const WTile<G>& wc, WTile<G>& wnx) {
+        constexpr int o = decltype(oc)::value;
+        stage(kt * 4, std::integral_constant<int, o>{}, wc, wnx, bA, bB);
+        stage(kt * 4 + 1, std::integral_constant<int, o + 1>{}, wc, wnx, bB, bA);
+        stage(kt * 4 + 2, std::integral_constant<int, o + 2>{}, wc, wnx, bA, bB);
+        stage(kt * 4 + 3, std::integral_constant<int, o + 3>{}, wc, wnx, bB, bA);
     };
-    for (int64_t kt = kt_b; kt < kt_e; kt += 2) {
-        tile(kt, w0, w1);
-        if (kt + 1 < kt_e) tile(kt + 1, w1, w0);             // uniform
+    for (int kt = kt_b; kt < kt_e; kt += 2) {
+        tile(kt, std::integral_constant<int, 0>{}, w0, w1);
+        if (kt + 1 < kt_e) tile(kt + 1, std::integral_constant<int, 4>{}, w1, w0);   // uniform
     }
+    wait_loads<0>();                                         // (stages past the end still store zeros)
+    __syncthreads();
 
     if (a.part) {
         // split-K: this range's fp32 partial results go to the workspace.  A lane holds single columns of

@@ -71,11 +71,6 @@ struct Head {
     int M, n_cb, n_kt;                                       // (and t_lo, t_rem: tiles per K range, one more for the first t_rem)
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-
 // The four weights of one (group, column), low bytes and high bytes, indexed by the raw code
 // (00 -> 0, 01 -> +sw, 10 -> -2 sw: sign flipped and exponent + 1, 11 -> -sw).
 struct Lut { uint32_t lo4, hi4; };

@@ -68,6 +68,45 @@ __device__ __forceinline__ void store_outputs(const Epilogue& e, uint16_t* __res
     }
 }
 
+// ---- global memory -> local memory without a stop in registers (the tiled kernels' activations)
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
+// One KiB per wave: lane i's 16 bytes go to dst + 16 i (dst the same in every lane), from byte `lane_off` of the resource,
+// moved on by `off`; a lane offset past the resource's end stores zeros and reads nothing.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, int8_t* dst, uint32_t lane_off, uint32_t off)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)lane_off, (int)off, 0, 0);
+#endif
+}
+
+// Waits until at most N of the wave's vector memory operations are outstanding (they complete in order).  Nothing tells the
+// compiler that a read of local memory needs such a load to have landed: the callers count what they issue.
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    static_assert(N >= 0 && N < 64, "six bits");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The workgroup's barrier alone: __syncthreads() also waits for every load to local memory that is still under way.  What a
+// wave read or wrote in local memory before it has to be complete by other means.
+__device__ __forceinline__ void bare_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // 16 two-bit fields -> four dwords of int8 lanes holding 64*q.
 __device__ __forceinline__ void upconvert(uint32_t w, int (&u)[4])
 {

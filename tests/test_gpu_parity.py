@@ -1070,6 +1070,27 @@ def run_a16_case(w2, M, K, N, G, codec, variant, seed, tune=None):
     check_y(bf16_bits(Y), Yo, y64, mag, f"a16 M={M} K={K} N={N} G={G} codec={codec} variant={variant}")
 
 
+@pytest.mark.parametrize("bn", [128, 256])
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("K", [256, 512, 768, 2304])
+@pytest.mark.parametrize("M", [17, 80, 113, 130])
+def test_a16_tiled_rows_straight_to_local_memory(w2, M, K, G, bn):
+    # fewer stages than are asked for ahead, odd and even numbers of 256-k tiles, whole K and a K range of one tile, rows of a
+    # tile that are missing, rows that lie in a wider matrix of NaNs (none of which may be read as part of a row)
+    N = 264
+    codes, scales, X = synth.make_problem(M, K, N, G, M % 2, M + K + G)
+    Xb = synth.f32_to_bf16_bits(X)
+    wide = torch.full((M + 1, K + 24), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:M, 8:K + 8] = dev(Xb).view(torch.bfloat16)
+    packed = w2.prepack(dev(codes), dev(scales), G, M % 2)
+    Yo, y64, mag = oracle.matmul_a16(codes, scales, G, M % 2, Xb)
+    ws = torch.empty(4 * M * N * 9, dtype=torch.uint8, device="cuda")
+    for splitk in (1, K // 256):
+        Y = w2.matmul_a16(packed, K, N, G, wide[:M, 8:K + 8], workspace=ws,
+                          tune={"tiled_bn": bn, "splitk": splitk, "midm_max_m": 1, "midm_min_m": 1})
+        check_y(bf16_bits(Y), Yo, y64, mag, f"a16 tiled M={M} K={K} G={G} bn={bn} splitk={splitk}")
+
+
 @pytest.mark.parametrize("G", [64, 128])
 @pytest.mark.parametrize("K,N", SMALL_SHAPES)
 @pytest.mark.parametrize("M", [1, 4, 7, 16])
