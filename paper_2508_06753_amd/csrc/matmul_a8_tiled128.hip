@@ -16,16 +16,21 @@
 //   - workgroup 16 RI rows x 256 columns (eight waves of 16 RI x 32, one workgroup
 //     per CU) or 128 x 128 (four waves, two per CU); a stage is 128 k = one
 //     group of G = 128, 32 matrix instructions per wave;
-//   - activations go through LDS (row stride 160 B: conflict-free operand
-//     reads).  Three buffers: stage s reads buffers s and s+1 and writes the rows
-//     of stage s+2, one barrier per stage.  Five buffers (eight-wave workgroups):
-//     the pair of stages (2S, 2S+1) reads stages 2S .. 2S+2 and writes stages
-//     2S+3 and 2S+4, five different buffers, one barrier per pair, so the waves
-//     of a workgroup may be a stage apart inside a pair.  Rows are loaded from
-//     global memory two stages before they go to LDS;
+//   - activations go from global to local memory directly, 16-byte pieces XORed by
+//     row (conflict-free operand reads), six stages ahead in eight buffers
+//     (eight-wave workgroups): the pair of stages (2S, 2S+1) reads stages 2S ..
+//     2S+2 and asks for stages 2S+6 and 2S+7 in the buffers of the pair before, one
+//     barrier per pair, so the waves of a workgroup may be a stage apart inside a
+//     pair.  Four buffers (128 columns): one barrier per stage;
 //   - the weights go from global memory to registers (the packed dword IS the
 //     matrix operand), one 16-byte load per lane, column block and 256-k tile,
 //     a tile ahead;
+//   - buffers and weight registers are constants of a loop of four 256-k tiles: 3.0 vector
+//     instructions per matrix instruction.  With activations through registers and
+//     buffers numbered at run time, 3.4: 8192 x 57344 at M = 2048 887 -> 824 us, 4096 x
+//     28672 at M = 1000 in tiles of 128 / 112 / 96 / 80 / 64 rows 135 / 128 / 146 / 149 /
+//     159 -> 127 / 119 / 129 / 137 / 135 us, with groups of 64 159 / 151 / 162 / 176 /
+//     182 -> 150 / 140 / 152 / 163 / 158;
 //   - every wave is software-pipelined on its own: under a stage's matrix
 //     instructions it reads the second k-step's operands and the next stage's
 //     first ones, up-converts one operand ahead, and dequantises a finished
@@ -60,13 +65,13 @@ namespace t128 {
 
 constexpr int CJ = 2;                              // 16-column blocks per wave
 constexpr int BK = 128;
-constexpr int CP_ROWS = 128;                       // rows that a workgroup's threads stage (a lower tile's last row repeated)
+constexpr int CP_ROWS = 128;                       // most rows of a tile
 constexpr int WN = 16 * CJ;
-constexpr int A_STRIDE = BK + 32;                  // 32 mod 64 bytes: conflict-free A-operand reads
-constexpr int A_BUF = CP_ROWS * A_STRIDE;
-// LDS buffers: 3 with a barrier after every stage; 5 with a barrier after every other stage (eight-wave
+constexpr int A_ROW = BK;                          // bytes of a row in one stage: eight 16-byte pieces
+constexpr int A_BUF = CP_ROWS * A_ROW;
+// LDS buffers: 4 with a barrier after every stage; 8 with a barrier after every other stage (eight-wave
 // workgroups, one per CU: the waves of a workgroup may then drift a stage apart inside a pair)
-constexpr int nbuf_of(int bn) { return bn >= 256 ? 5 : 3; }
+constexpr int nbuf_of(int bn) { return bn >= 256 ? 8 : 4; }
 constexpr int E_STRIDE = WN * 2 + 16;              // epilogue: bytes per LDS row of a wave's result
 constexpr int BIAS = 1 << 21;                      // > 64 * 127 * 2 * 128 = 2 080 768
 constexpr float BIAS_F = 0x1p-128f;                // BIAS read as a float: 2^21 * 2^-149
@@ -102,14 +107,12 @@ __global__ void __launch_bounds__(64 * waves_of(BN), BN >= 256 ? 1 : 2)
 a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, int c_rem)
 {
     constexpr int BM = 16 * RI;
-    constexpr int WAVES = waves_of(BN), THREADS = 64 * WAVES;
+    constexpr int WAVES = waves_of(BN);
     constexpr int GPT = TILE_K / G;
-    constexpr int CPT = THREADS / CP_ROWS;              // threads per activation row: 4 or 2
-    constexpr int NV = BK / CPT / 16;              // 16-byte pieces per thread and stage: 2 or 4
-    constexpr bool TWO_SETS = NV <= 2;             // two register sets: a load has two stages to land
     constexpr int NBUF = nbuf_of(BN);
-    constexpr int WR = NBUF == 3 ? 2 : 3;          // stage s writes the activations of stage s + WR
-    static_assert(NBUF == 3 || TWO_SETS, "five buffers go with two register sets");
+    constexpr bool PAIR = BN >= 256;               // a barrier after every other stage
+    constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
+    constexpr int NP = (2 * RI + WAVES - 1) / WAVES;    // KiBs of activations (eight rows) per wave and stage: 1, 2 or 4
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -141,31 +144,30 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     }
     uint32_t w_lane = (uint32_t)lane * 16u;
     uint32_t s_lane = (uint32_t)l16 * (GPT * 2u);
-    int64_t nkt = a.n_kt;                                    // tiles this workgroup multiplies
-    int64_t kt0 = 0;                                         // the first of them
+    int nkt = (int)a.n_kt;                                   // tiles this workgroup multiplies
+    int kt0 = 0;                                             // the first of them
     if constexpr (SPLIT) {
         const int z = (int)blockIdx.y;
-        kt0 = (int64_t)z * c_lo + min(z, c_rem);
+        kt0 = z * c_lo + min(z, c_rem);
         nkt = c_lo + (z < c_rem ? 1 : 0);
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
-            wb[j] += kt0 * 1024;
-            sb[j] += kt0 * (TILE_N * GPT * 2);
+            wb[j] += (int64_t)kt0 * 1024;
+            sb[j] += (int64_t)kt0 * (TILE_N * GPT * 2);
         }
     }
 
-    // global -> LDS copy: CPT threads per row, NV 16-byte pieces each; rows past M repeat the last row.
-    // Lane offsets stay below 128 * K <= 2^31.
-    const int cp_row = tid / CPT, cp_seg = tid % CPT;
-    int64_t cp_m = m0 + min(cp_row, BM - 1);
-    if (cp_m >= a.M) cp_m = a.M - 1;
-    const char* cp_base = reinterpret_cast<const char*>(a.xq) + m0 * a.K + kt0 * TILE_K;  // uniform
-    // piece v of a thread is the row's 16-byte piece v * CPT + cp_seg: the CPT threads of a row store CPT
-    // consecutive pieces per instruction, so eight lanes (two or four rows) never share an LDS bank
-    // (with NV consecutive pieces per thread a row's last piece fell on the next row's first bank)
-    uint32_t cp_lane = (uint32_t)((cp_m - m0) * a.K) + (uint32_t)cp_seg * 16u;
-    const int cp_dst = cp_row * A_STRIDE + cp_seg * 16;
-    constexpr int CP_STEP = CPT * 16;              // bytes between a thread's pieces
+    // The activations go from global to local memory directly, a KiB (eight rows x 128 bytes) per instruction.  A row's
+    // 16-byte pieces stand there XORed by row mod 8 (operand reads without bank conflicts): the lanes fetch them in that
+    // order.  Rows past M or past the tile lie past the resource's end; lane offsets stay below 128 * K <= 2^31.
+    const int rows = (int)min((int64_t)BM, a.M - m0);
+    const uint32_t stride = (uint32_t)a.K;
+    const int8_t* const xbase = a.xq + m0 * a.K + (int64_t)kt0 * TILE_K;
+    const uint32_t xbytes = (uint32_t)(rows - 1) * stride + (uint32_t)nkt * TILE_K;
+    uint32_t xoff[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+        xoff[p] = (uint32_t)((wn + WAVES * p) * 8 + (lane >> 3)) * stride + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
 
     v4i acc[RI][CJ];
     float y[RI][CJ][4];
@@ -180,34 +182,17 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             for (int r = 0; r < 4; ++r) y[i][j][r] = 0.0f;
         }
 
-    const int64_t n_st = nkt * 2;                            // stages of 128 k
-    // plain named registers (arrays and structs of them ended up in scratch memory)
-    uint4 p00, p01, p02 = make_uint4(0, 0, 0, 0), p03 = p02;         // set 0
-    uint4 p10 = p02, p11 = p02;                                      // set 1 (eight-wave workgroups)
-    auto load_a = [&](int64_t st, uint4& v0, uint4& v1, uint4& v2, uint4& v3) {
-        st = min(st, n_st - 1);                              // past the end: re-read the last stage (never used)
-        const char* p = cp_base + st * BK;                   // uniform
-        asm volatile("" : "+v"(cp_lane));                    // keeps "scalar base + 32-bit offset" addressing
-        v0 = *reinterpret_cast<const uint4*>(p + cp_lane);
-        v1 = *reinterpret_cast<const uint4*>(p + cp_lane + CP_STEP);
-        if constexpr (NV > 2) {
-            v2 = *reinterpret_cast<const uint4*>(p + cp_lane + 2 * CP_STEP);
-            v3 = *reinterpret_cast<const uint4*>(p + cp_lane + 3 * CP_STEP);
-        }
+    const int n_st = nkt * 2;                                // stages of 128 k
+    // (past the range's end: nothing is read, but the instructions are there, for they are counted)
+    auto load_a = [&](int st, int buf) {
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(xbase, st < n_st ? xbytes : 0u);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) load_to_lds(xr, smem + buf * A_BUF + (wn + WAVES * p) * 1024, xoff[p], (uint32_t)st * BK);
     };
-    auto store_a = [&](int buf, const uint4& v0, const uint4& v1, const uint4& v2, const uint4& v3) {
-        int8_t* dst = smem + buf * A_BUF + cp_dst;
-        *reinterpret_cast<uint4*>(dst) = v0;
-        *reinterpret_cast<uint4*>(dst + CP_STEP) = v1;
-        if constexpr (NV > 2) {
-            *reinterpret_cast<uint4*>(dst + 2 * CP_STEP) = v2;
-            *reinterpret_cast<uint4*>(dst + 3 * CP_STEP) = v3;
-        }
-    };
-    auto load_w = [&](int64_t kt, WTile<G>& r) {
+    auto load_w = [&](int kt, WTile<G>& r) {
         kt = min(kt, nkt - 1);
-        const int64_t w_off = kt * 1024;
-        const int64_t s_off = kt * (TILE_N * GPT * 2);
+        const int64_t w_off = (int64_t)kt * 1024;
+        const int64_t s_off = (int64_t)kt * (TILE_N * GPT * 2);
         asm volatile("" : "+v"(w_lane), "+v"(s_lane));
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
@@ -227,31 +212,24 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     float* sx_lds = reinterpret_cast<float*>(smem + lds_bytes(BN));
     const float sx_mine = DBG ? 0.f : a.sx[min(m0 + (tid & (CP_ROWS - 1)), a.M - 1)];
 
-    // prologue: stages 0 and 1 go to LDS; the registers then hold stage 2 (and 3)
     WTile<G> w0, w1;
     load_w(0, w0);
-    {
-        // every load of the prologue is issued before the first store waits: one memory round trip, not one
-        // per stage (nothing else runs on the CU meanwhile: a workgroup has it to itself)
-        const uint4 zero4 = make_uint4(0, 0, 0, 0);
-        uint4 t0a, t0b, t0c = zero4, t0d = zero4, t1a, t1b, t1c = zero4, t1d = zero4, t2a = zero4, t2b = zero4, t2c = zero4, t2d = zero4;
-        load_a(0, t0a, t0b, t0c, t0d);
-        load_a(1, t1a, t1b, t1c, t1d);
-        if constexpr (WR == 3) load_a(2, t2a, t2b, t2c, t2d);
-        load_a(WR, p00, p01, p02, p03);
-        if constexpr (TWO_SETS) load_a(WR + 1, p10, p11, p02, p03);
-        store_a(0, t0a, t0b, t0c, t0d);
-        store_a(1, t1a, t1b, t1c, t1d);
-        if constexpr (WR == 3) store_a(2, t2a, t2b, t2c, t2d);
-    }
-    if (tid < CP_ROWS) sx_lds[tid] = sx_mine;
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) load_a(p, p);
+    if (tid < CP_ROWS) sx_lds[tid] = sx_mine;                // (read after barriers that wait for local memory, in the epilogue)
+    wait_loads<(PAIR ? AHEAD - 3 : AHEAD - 2) * NP>();       // stages 0, 1 (and 2) are there
+    bare_barrier();
 
-    const int8_t* a_base = smem + l16 * A_STRIDE + q * 16;
+    // where a lane finds the operands of k-step 0 and 1 in buffers 0 .. 3 and, beyond the reach of an instruction's offset,
+    // from 4 on
+    const int a_e0 = l16 * A_ROW + (q ^ (l16 & 7)) * 16, a_e1 = l16 * A_ROW + ((4 + q) ^ (l16 & 7)) * 16;
+    int a_f0 = a_e0 + 4 * A_BUF, a_f1 = a_e1 + 4 * A_BUF;
+    asm volatile("" : "+v"(a_f0), "+v"(a_f1));
 
     // y += as_float(acc) * (sw * 2^64) for rows [i0, i0 + 4) of column block j
     constexpr int H0 = RI / 2;                               // row tiles of the first half
-    auto dequant_half = [&](int j, int i0, float swS, int64_t g) {
+    auto dequant_half = [&](int j, int i0, float swS, int g) {
 #pragma unroll
         for (int i = i0; i < (i0 ? RI : H0); ++i) {
 #pragma unroll
@@ -267,7 +245,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         }
     };
     // G = 64: the group in accumulator set `set`, all rows, into column block j
-    auto dequant_set = [&](int set, int j, float swS, int64_t g) {
+    auto dequant_set = [&](int set, int j, float swS, int g) {
 #pragma unroll
         for (int i = 0; i < RI; ++i) {
 #pragma unroll
@@ -296,11 +274,10 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 
     v4i a0[RI], a1[RI];
 #pragma unroll
-    for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(a_base + i * 16 * A_STRIDE);
+    for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(smem + a_e0 + i * 16 * A_ROW);
     v4i b_next = upconvert4(w0.w[0].x);                      // operand (k-step 0, column block 0) of the coming stage
     float pend_sw = 0.f;                                     // column block 1 of the previous stage: nothing yet
-    int64_t pend_g = -1;
-    int buf = 0;
+    int pend_g = -1;
 
     // One stage (G = 128: one group).  Order of the matrix instructions: column block 0, k-steps 0 and 1
     // (blocks A, B), then column block 1 (blocks C, D).  Vector work under them:
@@ -308,25 +285,26 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     //   B: up-convert (0,1), dequant the previous stage's column 1, rows 64..127
     //   C: up-convert (1,1), dequant this stage's column 0, rows 0..63
     //   D: next stage's first operands from LDS, up-convert its (0,0), dequant column 0, rows 64..127
-    auto stage = [&](int64_t it, auto hc, const WTile<G>& wc, WTile<G>& wnx) {
-        constexpr int h = decltype(hc)::value;
-        const int buf1 = buf == NBUF - 1 ? 0 : buf + 1;
-        const int bufw = buf + WR >= NBUF ? buf + WR - NBUF : buf + WR;
-        if constexpr (TWO_SETS && h == 1) {                  // activations of stage it+2
-            store_a(bufw, p10, p11, p02, p03);
-            load_a(it + WR + 2, p10, p11, p02, p03);
-        } else {
-            store_a(bufw, p00, p01, p02, p03);
-            load_a(it + WR + (TWO_SETS ? 2 : 1), p00, p01, p02, p03);
-        }
+    // sc: stage of the loop below, 0 .. 7, and its buffer (mod NBUF)
+    auto stage = [&](int it, auto sc, const WTile<G>& wc, WTile<G>& wnx) {
+        constexpr int h = decltype(sc)::value & 1, buf = decltype(sc)::value & (NBUF - 1), buf1 = (buf + 1) & (NBUF - 1);
         if constexpr (h == 0) load_w((it >> 1) + 1, wnx);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(it + AHEAD, (buf + AHEAD) & (NBUF - 1));
         __builtin_amdgcn_sched_barrier(0);                   // all loads are issued up here, unconditionally
-        const int8_t* ab = a_base + buf * A_BUF;
-        const int8_t* abn = a_base + buf1 * A_BUF;
+        const int8_t* const ab = smem + (buf < 4 ? a_e1 : a_f1) + (buf & 3) * A_BUF;
+        const int8_t* const abn = smem + (buf1 < 4 ? a_e0 : a_f0) + (buf1 & 3) * A_BUF;
         const WTile<G>& wn_tile = h == 1 ? wnx : wc;         // where the next stage finds its weights
         const float sw0 = scale_of(wc, 0, h, 0), sw1 = scale_of(wc, 1, h, 0);
-        const int64_t g = it;                                // group index = stage index (G = 128)
+        const int g = it;                                    // group index = stage index (G = 128)
 
+        // before the next pair: stages up to its third have landed; what was asked for since, three more and a tile's weights,
+        // may be under way.  (Four buffers: the next two stages; one more and, asked for in this stage, weights.)
+        auto end_of_stage = [&]() {
+            if constexpr (PAIR && h == 1) wait_loads<3 * NP + 2 * CJ>();
+            if constexpr (!PAIR) wait_loads<NP + (h == 0 ? 2 * CJ : 0)>();
+            if constexpr (!PAIR || h == 1) bare_barrier();
+        };
         const v4i b00 = b_next;
         // Each block is a scheduling region of its own (sched_barrier at its end): the vector work placed in a
         // block reads only accumulators finished at least one block (eight matrix instructions) earlier.  In one
@@ -349,7 +327,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             // acc[.][1]), which the next block folds in row by row, eight matrix instructions behind.
             const float sw01 = scale_of(wc, 0, h, 1), sw11 = scale_of(wc, 1, h, 1);
 #pragma unroll
-            for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_STRIDE + 64);
+            for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_ROW);
             const v4i b10 = upconvert4(dword_of(wc, 0, h, 1));
 #pragma unroll
             for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b00, biasv, 0, 0, 0);
@@ -366,7 +344,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             dequant_set(1, 0, sw01, 2 * g + 1);
             interleave(false, RI);
 #pragma unroll
-            for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
+            for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_ROW);
             b_next = upconvert4(dword_of(wn_tile, 0, h ^ 1, 0));
 #pragma unroll
             for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b11, biasv, 0, 0, 0);
@@ -374,13 +352,12 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             pend_sw = DBG ? 1.0f : sw11;
             pend_g = 2 * g + 1;
             interleave(true, RI);
-            buf = buf1;
-            if constexpr (NBUF == 3 || h == 1) __syncthreads();
+            end_of_stage();
             return;
         }
         // block A
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_STRIDE + 64);
+        for (int i = 0; i < RI; ++i) a1[i] = *reinterpret_cast<const v4i*>(ab + i * 16 * A_ROW);
         const v4i b10 = upconvert4(dword_of(wc, 0, h, 1));
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[i], b00, biasv, 0, 0, 0);
@@ -401,7 +378,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         interleave(false, H0);
         // block D
 #pragma unroll
-        for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_STRIDE);
+        for (int i = 0; i < RI; ++i) a0[i] = *reinterpret_cast<const v4i*>(abn + i * 16 * A_ROW);
         b_next = upconvert4(dword_of(wn_tile, 0, h ^ 1, 0));
 #pragma unroll
         for (int i = 0; i < RI; ++i) acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[i], b11, acc[i][1], 0, 0, 0);
@@ -410,18 +387,24 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         pend_sw = DBG ? 1.0f : sw1;
         pend_g = g;
         interleave(true, RI - H0);
-        buf = buf1;
-        if constexpr (NBUF == 3 || h == 1) __syncthreads();
+        end_of_stage();
     };
 
-    // one 256-k tile (two stages) per iteration; the next tile's weights arrive in w1 meanwhile and move
-    // to w0 at the end (every load and every register write is unconditional: registers written under a
-    // condition end up in scratch memory)
-    for (int64_t kt = 0; kt < nkt; ++kt) {
-        stage(kt * 2, std::integral_constant<int, 0>{}, w0, w1);
-        stage(kt * 2 + 1, std::integral_constant<int, 1>{}, w0, w1);
-        w0 = w1;
-        if ((kt & (G == 128 ? 7 : 3)) == (G == 128 ? 7 : 3)) {
+    auto tile = [&](int kt, auto oc, const WTile<G>& wc, WTile<G>& wnx) {
+        constexpr int o = decltype(oc)::value;
+        stage(kt * 2, std::integral_constant<int, o>{}, wc, wnx);
+        stage(kt * 2 + 1, std::integral_constant<int, o + 1>{}, wc, wnx);
+    };
+    // four 256-k tiles (eight stages) per turn, so that buffers and the two sets of weight registers are constants
+    for (int kt = 0; kt < nkt; kt += 4) {
+        tile(kt, std::integral_constant<int, 0>{}, w0, w1);
+        if (kt + 1 >= nkt) break;                            // uniform
+        tile(kt + 1, std::integral_constant<int, 2>{}, w1, w0);
+        if (kt + 2 >= nkt) break;
+        tile(kt + 2, std::integral_constant<int, 4>{}, w0, w1);
+        if (kt + 3 >= nkt) break;
+        tile(kt + 3, std::integral_constant<int, 6>{}, w1, w0);
+        if (G == 64 || (kt & 4)) {
             // take the accumulated bias term out every 16 groups, so that the running sums never carry
             // more than 16 groups of it (the rounding error stays near 2^-14 of the result, whatever K is)
 #pragma unroll
@@ -436,6 +419,8 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
             }
         }
     }
+    wait_loads<0>();                                         // (stages past the end still store zeros)
+    __syncthreads();
     // the very last stage's column block 1
     if constexpr (G == 64) {
         dequant_set(1, 1, pend_sw, pend_g);
@@ -447,7 +432,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     if constexpr (DBG) return;
 
     // y_true = (y - BIAS*2^-149 * ssum) * 2^(149-64) * 2^-6 * sx.  The wave's 128 x 32 result goes through
-    // LDS (its own region; the barrier at the end of the last stage freed the activation buffers) and
+    // LDS (its own region; the barrier above freed the activation buffers) and
     // leaves as 16-byte stores.
     int8_t* ebase = smem + wn * (CP_ROWS * E_STRIDE);
     uint16_t* eb = reinterpret_cast<uint16_t*>(ebase);

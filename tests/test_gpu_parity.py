@@ -510,6 +510,15 @@ def test_a8_128_row_tiles_groups_of_64(w2, M, K, N, bn):
     run_a8_case(w2, M, K, N, 64, M % 2, w2.VARIANT_TILED, seed=M + K + N, tune={"tiled_bm": 128, "tiled_bn": bn})
 
 
+@pytest.mark.parametrize("bn", [128, 256])
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("K", [512, 768, 1280, 2816, 3072])
+@pytest.mark.parametrize("M", [1, 120, 129])
+def test_a8_tall_tiles_loop_of_four_tiles(w2, M, K, G, bn):
+    # every remainder of the loop of four 256-k tiles, fewer stages than are asked for ahead, missing rows
+    run_a8_case(w2, M, K, 264, G, M % 2, w2.VARIANT_TILED, seed=M + K + G, tune={"tiled_bm": 128, "tiled_bn": bn, "splitk": 1})
+
+
 @pytest.mark.parametrize("M", [20, 100, 300])
 def test_a8_one_fma_dequant_keeps_denormals(w2, M):
     # the mid-M and prefill kernels read BIAS + 64*sum as an fp32 denormal and multiply by sw * 2^64: a build
