@@ -77,6 +77,9 @@ typedef enum {
  * on 12288 to 16384 columns; M = 16 with G = 64, K <= 4096 and N >= 16384) wherever the bf16 rows fit a workgroup's
  * local memory, else SMALLM; MIDM up to M = 192 (256 when N <= 7168 and K <= 14336, 96 when N >= 16384 or K*N >
  * 160 Mi, 64 when N >= 40960; from M = 33 on by price, as for w2a8), else the SCALED16 tiled kernel.
+ * From 17 to 144 rows, on 4096 columns and more and K from 768 to 20480, AUTO runs instead of MIDM and TILED a
+ * kernel that has no name here where its price is lower: MIDM's arithmetic in workgroups of up to sixteen column
+ * blocks that share their rows (not where midm_min_m, gemv_max_m or a field of the launch shape is set).
  * GEMV: the decode kernel: whole rows in local memory, a wave streams a contiguous run of a column
  * block's tiles through a rolling register window into int8 MFMA (w2a8, M <= 32) or, with bf16 rows left as they
  * are and the zero-point weight construction, into bf16 MFMA (w2a16, M <= 16; W2_ERR_UNSUPPORTED_SHAPE when the

@@ -12,9 +12,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libw2mm.so")
 SOURCES = ["api.hip", "prepack.hip", "quantize.hip", "matmul_a8_small.hip",
-           "matmul_midm.hip", "matmul_a8_tiled.hip", "matmul_a8_tiled128.hip", "matmul_a8_gemv.hip", "matmul_a16.hip", "matmul_a16_fold.hip",
+           "matmul_midm.hip", "matmul_shared.hip", "matmul_a8_tiled.hip", "matmul_a8_tiled128.hip", "matmul_a8_gemv.hip", "matmul_a16.hip", "matmul_a16_fold.hip",
            "comparators.hip", "splitk.hip"]
-HEADERS = ["w2_layout.h", "w2_internal.h", "w2_small_common.h", "midm_plan.h", "tile_plan.h", "auto_plan.h", os.path.join("..", "..", "include", "w2mm.h")]
+HEADERS = ["w2_layout.h", "w2_internal.h", "w2_small_common.h", "midm_common.h", "midm_plan.h", "shared_plan.h", "tile_plan.h", "auto_plan.h", os.path.join("..", "..", "include", "w2mm.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Wall", "-Wno-unused-function",
@@ -30,7 +30,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 _PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 # (also the row quantiser and the streaming-read probe the decode kernel is compared with: scalar parameters already)
 EXTRA_FLAGS = {"matmul_a8_gemv.hip": _PRELOAD, "quantize.hip": _PRELOAD, "api.hip": _PRELOAD,
-               "matmul_midm.hip": _PRELOAD}
+               "matmul_midm.hip": _PRELOAD, "matmul_shared.hip": _PRELOAD}
 
 
 def _newer(target, deps):

@@ -268,6 +268,7 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
     hipStream_t s = (hipStream_t)stream;
     if (variant == W2_VARIANT_AUTO) {
         r = route::a8(pb, tn);
+        if (r.to_shared && !acc_out) return launch_a8_shared(a, r.shared, s);
         variant = r.variant;
         if (variant == W2_VARIANT_GEMV) {
             rc = launch_a8_gemv(a, xq, 0, K, s);
@@ -532,6 +533,7 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
             rc = launch_a16_gemv(a, s);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
         }
+        if (r.to_shared) return launch_a16_shared(a, r.shared, s);
         if (r.to_midm) return launch_a16_midm(a, r.has_midm ? r.midm : route::midm_shape(1, pb, tn), s);
         if (!r.gemv_first && a16_gemv_supports(a)) {         // (only where tuning fields leave rows to neither of the two)
             rc = launch_a16_gemv(a, s);
@@ -591,7 +593,8 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
     if (M == 0) *bytes = 0;
     else if (a16) {
         route::A16 r = {};
-        const bool first = M > 32 && M <= 64 && route::a16_tiled_first(pb, dflt, &r);
+        double us;
+        const bool first = M > 32 && M <= 64 && route::a16_tiled_first(pb, dflt, &r, &us);
         const size_t tiled = M > 64 || first ? part_bytes(route::a16_tiled_shape(pb, dflt).splits, M, N) : 0;
         const size_t midm = M >= 3 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
         *bytes = tiled > midm ? tiled : midm;

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "midm_plan.h"
+#include "shared_plan.h"
 #include "tile_plan.h"
 
 namespace w2 {
@@ -30,6 +31,22 @@ inline double tiled_share(int a16, const midm::Plan& p, bool low_tiles)
     return low_tiles && p.ks < 8 ? LOW_TILES_SHARE : TILED_SHARE[a16][p.ks >= 8];
 }
 
+// The mid-M kernel that shares its rows (shared_plan.h) instead of what would run otherwise: where its price is under this share of
+// that kernel's.  By what would run and by rows; loss or gain against never taking it, graph-timed on 1130 random problems of 17 to
+// 150 rows (N from 4096, K from 768), time by share:
+//   mid-M kernel, fewer than eight K ranges   to 32 rows   int8 0.96 0.985, 1.0 0.978, 1.06 0.970 (6 of 88 slower by over 3 %; 1 at 1.0)
+//                                                          bf16 0.96 0.962, 0.98 0.953, 1.02 0.946 (4 of 77 slower; 1 at 0.98)
+//                                             above        int8 1.0 0.909, 1.06 0.882;  bf16 1.0 0.886, 1.02 0.878, 1.06 0.879
+//   eight K ranges                            to 32 rows   never below 1.000
+//                                             33 to 64     1.0 0.973 and 0.994, 1.04 0.969 and 1.003;  above  1.0 0.993 and 0.977, 1.04 0.983 and 0.968
+//   64-row tiles 1.04 0.982;  tall tiles 0.92 0.990, 1.0 0.992 (2 of 26 slower);  w2a16 0.88 0.977, 1.0 0.986 (12 of 71 slower; 5 at 0.88)
+constexpr double SHARED_SHARE_LOW = 1.04, SHARED_SHARE_TALL[2] = {0.92, 0.88};
+inline double shared_share(int a16, int64_t M, const midm::Plan& p)
+{
+    if (M <= 32) return p.ks >= 8 ? 0.0 : a16 ? 0.98 : 1.0;
+    return p.ks < 8 ? (a16 ? 1.02 : 1.06) : M <= 64 ? 1.0 : 1.04;
+}
+
 struct Problem {
     int64_t M, K, N;
     int64_t n_cb, n_kt;                                      // column blocks, 256-k tiles
@@ -43,10 +60,29 @@ inline midm::Plan midm_shape(int a16, const Problem& p, const w2_tuning_t& tn, d
     return midm::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.cap, tn, us, p.G);
 }
 
+// (not where the caller says which rows the decode or the mid-M kernel gets)
+inline bool shared_offered(const Problem& p, const w2_tuning_t& tn)
+{
+    return !tn.midm_min_m && !tn.gemv_max_m && !tn.midm_cbw && tn.splitk <= 1 && !tn.tiled_bm && !tn.tiled_bn && !tn.tiled_kw && !tn.tiled_wd &&
+           shared::offered(p.M, p.n_cb, p.n_kt);
+}
+
+inline bool shared_first(int a16, const Problem& p, double against, shared::Plan* shape)
+{
+    if (against <= 0) return false;
+    double us;
+    const shared::Plan s = shared::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.G, &us);
+    if (us >= against) return false;
+    *shape = s;
+    return true;
+}
+
 // ---- w2a8
 
 struct A8 {
-    int variant;
+    int variant;                                             // (of the kernels that can be asked for by name)
+    bool to_shared;                                          // the mid-M kernel that shares its rows runs instead
+    shared::Plan shared;
     int fallback;                                            // where the decode kernel turns the rows down
     bool has_midm, has_tiled;                                // shapes found on the way
     midm::Plan midm;
@@ -83,8 +119,9 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
                        : p.n_cb >= 2560 ? 48 : p.n_cb >= 1536 ? 112 : p.n_cb > 448 ? 160 : p.G == 128 && p.n_kt > 104 && p.n_cb > 256 ? 192 : 240;
     // Below it, from 33 rows on, by price.
     bool tiled_first = false;
+    double midm_us = 0;
     if (M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m) {
-        double us;
+        double& us = midm_us;
         r.midm = midm_shape(0, p, tn, &us);
         r.has_midm = true;
         if (us * tiled_share(0, r.midm, false) > tiles::LEAST_US[p.G == 128 ? tiles::A8_G128 : tiles::A8_G64]) {
@@ -108,6 +145,17 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
     r.variant = M <= tn.dot4_max_m && M <= DOT4_ROWS ? W2_VARIANT_DOT4
               : M <= gemv_max && M <= GEMV_ROWS      ? W2_VARIANT_GEMV
                                                      : r.fallback;
+    if ((r.variant == W2_VARIANT_MIDM || r.variant == W2_VARIANT_TILED) && shared_offered(p, tn)) {
+        double against;
+        if (r.variant == W2_VARIANT_MIDM) {
+            if (!r.has_midm) { r.midm = midm_shape(0, p, tn, &midm_us); r.has_midm = true; }
+            against = midm_us * shared_share(0, M, r.midm);
+        } else {
+            if (!r.has_tiled) { r.tiled = a8_tiled_shape(p, tn); r.has_tiled = true; }
+            against = r.tiled.us * (r.tiled.ri ? SHARED_SHARE_TALL[0] : SHARED_SHARE_LOW);
+        }
+        r.to_shared = shared_first(0, p, against, &r.shared);
+    }
     return r;
 }
 
@@ -115,6 +163,8 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
 
 struct A16 {
     bool gemv_first;                                         // the decode kernel, where a workgroup can hold the rows
+    bool to_shared;                                          // instead of the following two: the mid-M kernel that shares its rows
+    shared::Plan shared;
     bool to_midm;                                            // then the mid-M kernel, else the small-M or the tiled one
     bool has_midm, has_tiled;
     midm::Plan midm;
@@ -123,12 +173,11 @@ struct A16 {
 
 inline tiles::Shape a16_tiled_shape(const Problem& p, const w2_tuning_t& tn) { return tiles::a16_shape(p.M, p.N, p.n_kt, p.cap, tn); }
 
-inline bool a16_tiled_first(const Problem& p, const w2_tuning_t& tn, A16* r)
+inline bool a16_tiled_first(const Problem& p, const w2_tuning_t& tn, A16* r, double* midm_us)
 {
-    double us;
-    r->midm = midm_shape(1, p, tn, &us);
+    r->midm = midm_shape(1, p, tn, midm_us);
     r->has_midm = true;
-    us *= tiled_share(1, r->midm, false);
+    const double us = *midm_us * tiled_share(1, r->midm, false);
     if (us <= tiles::LEAST_US[tiles::A16]) return false;
     r->tiled = a16_tiled_shape(p, tn);
     r->has_tiled = true;
@@ -162,10 +211,22 @@ inline A16 a16(const Problem& p, const w2_tuning_t& tn)
                            : p.n_cb >= 2560                              ? 64
                            : p.n_cb >= 1024 || p.n_cb * p.n_kt > 40000   ? 96
                            : p.n_cb <= 448 && p.n_kt <= 56               ? 256 : 192;
-    const bool tiled_first = M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m && a16_tiled_first(p, tn, &r);
+    double midm_us = 0;
+    const bool tiled_first = M > 32 && M >= midm_min && M <= midm_max && !tn.midm_max_m && a16_tiled_first(p, tn, &r, &midm_us);
     r.gemv_first = M < midm_min;
     // (from three rows on the mid-M kernel, not the small-M one, also takes what the decode kernel turns down)
     r.to_midm = (M >= midm_min || (!tn.midm_min_m && M >= 3)) && M <= midm_max && !tiled_first && M <= MIDM_ROWS;
+    if (!r.gemv_first && (r.to_midm || M > SMALL_ROWS) && shared_offered(p, tn)) {
+        double against;
+        if (r.to_midm) {
+            if (!r.has_midm) { r.midm = midm_shape(1, p, tn, &midm_us); r.has_midm = true; }
+            against = midm_us * shared_share(1, M, r.midm);
+        } else {
+            if (!r.has_tiled) { r.tiled = a16_tiled_shape(p, tn); r.has_tiled = true; }
+            against = r.tiled.us * SHARED_SHARE_TALL[1];
+        }
+        r.to_shared = shared_first(1, p, against, &r.shared);
+    }
     return r;
 }
 

@@ -6,6 +6,7 @@
 
 #include "../../include/w2mm.h"
 #include "midm_plan.h"
+#include "shared_plan.h"
 #include "tile_plan.h"
 #include "w2_layout.h"
 
@@ -82,8 +83,9 @@ int launch_a8_dot4(const A8Args& a, hipStream_t stream);
 bool a8_smallm_supports(const A8Args& a);
 int launch_a8_smallm(const A8Args& a, hipStream_t stream);
 bool a8_midm_supports(const A8Args& a);
-// (launch shapes: midm_plan.h, tile_plan.h)
+// (launch shapes: midm_plan.h, shared_plan.h, tile_plan.h)
 int launch_a8_midm(const A8Args& a, const midm::Plan& p, hipStream_t stream);
+int launch_a8_shared(const A8Args& a, const shared::Plan& p, hipStream_t stream);
 int launch_a8_tiled(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream);
 int launch_a8_tiled128(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream);
 
@@ -117,6 +119,7 @@ bool a16_gemv_supports(const A16Args& a);
 int launch_a16_gemv(const A16Args& a, hipStream_t stream);
 bool a16_midm_supports(const A16Args& a);
 int launch_a16_midm(const A16Args& a, const midm::Plan& p, hipStream_t stream);
+int launch_a16_shared(const A16Args& a, const shared::Plan& p, hipStream_t stream);
 
 size_t midm_room_bytes(int64_t M, int64_t N, int64_t n_cb, int64_t n_kt);
 // Y[m][n] = bf16(sum_s part[s][m][n]), a fixed order of summation

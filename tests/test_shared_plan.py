@@ -1,0 +1,146 @@
+"""The mid-M kernel that shares its rows: csrc/shared_plan.h compiled by itself, and the kernel in every form that AUTO gives."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2508_06753_amd import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include "%s/paper_2508_06753_amd/csrc/auto_plan.h"
+#include <stdio.h>
+using namespace w2;
+int main()
+{
+    int a16, G, gated, limit;
+    long long M, K, N, cap;
+    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d", &a16, &M, &K, &N, &gated, &G, &cap, &limit) == 8) {
+        w2_tuning_t tn = {};
+        tn.midm_min_m = limit;
+        const route::Problem p = {M, K, N, (N + 15) / 16, K / 256, G, gated != 0, cap};
+        bool to;
+        shared::Plan s;
+        if (a16) { const route::A16 r = route::a16(p, tn); to = r.to_shared; s = r.shared; }
+        else { const route::A8 r = route::a8(p, tn); to = r.to_shared; s = r.shared; }
+        if (to) printf("1 %%d %%d %%d %%d %%d\n", s.rt, s.cj, s.sh, shared::k_ranges(a16, G, s.rt, s.cj, s.sh), shared::range_lds(s.rt, s.cj, s.sh));
+        else printf("0 0 0 0 0 0\n");
+    }
+}
+"""
+# one problem for every (rows int8 0 / bf16 1, row tiles, blocks per wave, waves across the columns, exact dequant) that AUTO gives:
+# (rows, M, K, N, gated, G), without a workspace
+SHARED_FORMS = [(0, 49, 768, 5992, 0, 128), (0, 24, 2560, 12208, 0, 128), (0, 65, 3072, 4912, 0, 128),
+                (0, 17, 4608, 12304, 0, 128), (0, 49, 768, 9016, 0, 128), (0, 28, 1280, 18616, 0, 64),
+                (0, 49, 768, 10272, 1, 128), (0, 17, 1280, 20488, 0, 128), (0, 65, 768, 8200, 0, 128),
+                (0, 17, 768, 24592, 0, 128), (0, 65, 768, 8224, 1, 128), (0, 32, 768, 24672, 1, 128),
+                (0, 65, 4096, 8672, 1, 128), (0, 20, 4608, 26080, 1, 128), (0, 97, 768, 8224, 1, 128),
+                (0, 20, 1280, 32776, 0, 128), (0, 32, 768, 48328, 0, 128), (0, 65, 768, 16408, 0, 128),
+                (0, 17, 768, 49168, 0, 128), (0, 65, 768, 20488, 0, 128), (0, 33, 768, 5464, 0, 128),
+                (0, 33, 768, 10936, 0, 64), (0, 33, 768, 13144, 0, 128), (0, 33, 768, 16408, 0, 64),
+                (0, 33, 768, 16416, 1, 128), (0, 65, 768, 12304, 0, 64), (0, 65, 768, 12320, 1, 128),
+                (0, 33, 4608, 24608, 1, 64), (0, 33, 768, 32776, 0, 128), (0, 36, 1024, 46024, 0, 64),
+                (0, 65, 768, 24592, 0, 128), (0, 65, 768, 28696, 0, 64), (0, 49, 1792, 7456, 0, 128),
+                (0, 49, 768, 10288, 0, 64), (0, 49, 768, 12320, 1, 128), (0, 97, 768, 8200, 0, 64),
+                (0, 49, 768, 16416, 1, 128), (0, 97, 768, 12304, 0, 64), (0, 97, 768, 14344, 0, 128),
+                (0, 49, 3072, 24608, 1, 64), (0, 97, 768, 16408, 0, 128), (0, 97, 768, 20488, 0, 64),
+                (0, 97, 768, 20488, 0, 128), (0, 97, 768, 28696, 0, 64), (1, 33, 2560, 4096, 0, 128),
+                (1, 49, 1280, 5128, 0, 64), (1, 17, 2560, 15488, 1, 128), (1, 17, 1280, 17320, 0, 64),
+                (1, 17, 1280, 21016, 0, 128), (1, 17, 1280, 24592, 0, 64), (1, 17, 1280, 24608, 1, 128),
+                (1, 24, 3584, 30424, 0, 128), (1, 17, 768, 40072, 0, 128), (1, 24, 1024, 40984, 0, 128),
+                (1, 17, 1024, 49168, 0, 128), (1, 33, 2560, 5464, 0, 64), (1, 33, 768, 10936, 0, 128),
+                (1, 33, 768, 16240, 0, 64), (1, 33, 768, 16408, 0, 128), (1, 33, 768, 21688, 0, 64),
+                (1, 33, 768, 26152, 0, 128), (1, 65, 1280, 12320, 1, 64), (1, 33, 5120, 24640, 1, 128),
+                (1, 33, 768, 32800, 1, 64), (1, 33, 768, 40984, 0, 128), (1, 33, 768, 50992, 0, 64),
+                (1, 65, 768, 31744, 0, 128), (1, 49, 2560, 4128, 1, 64), (1, 49, 768, 9160, 0, 128),
+                (1, 49, 768, 14008, 0, 64), (1, 97, 768, 8200, 0, 128), (1, 49, 768, 16416, 1, 64),
+                (1, 97, 768, 12304, 0, 128), (1, 97, 768, 12320, 1, 64), (1, 97, 4096, 12320, 1, 128),
+                (1, 97, 768, 16408, 0, 64), (1, 97, 768, 20488, 0, 128), (1, 97, 1536, 24592, 0, 64),
+                (1, 97, 2560, 28696, 0, 128)]
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("shared_plan")
+    (d / "p.cpp").write_text(PROGRAM % ROOT)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
+
+    def ask(problems, cap=0, midm_min_m=0):
+        """-> (taken, rt, cj, sh, K ranges, bytes of local memory of one) each"""
+        text = "".join("{} {} {} {} {} {} {} {}\n".format(*p, cap, midm_min_m) for p in problems)
+        out = subprocess.run([str(d / "p")], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, l.split())) for l in out.splitlines()]
+
+    return ask
+
+
+GRID = [(xt, M, K, N, g, G) for xt in (0, 1) for M in (1, 8, 9, 16, 17, 32, 33, 48, 49, 64, 65, 100, 144, 145, 300)
+        for K in (512, 768, 1280, 2048, 4096, 5120, 8192, 12288, 20480, 20736) for N in list(range(2048, 57344, 1312)) + [4080, 4096, 28672]
+        for g in (0, 1) if not (g and N % 32) for G in (64, 128)]
+
+
+def test_shapes_fit_the_kernel(routes):
+    taken = 0
+    for cap in (0, 8):
+        for (xt, M, K, N, g, G), (to, rt, cj, sh, ks, lds) in zip(GRID, routes(GRID, cap)):
+            assert not to or (17 <= M <= 144 and N > 4080 and 768 <= K <= 20480)
+            if to:
+                taken += 1
+                assert 2 <= rt <= min(4, -(-M // 16)) and cj in (1, 2) and 2 <= sh <= 8 and not (g and cj * sh % 2)
+                assert 1 <= ks <= 8 and ks * sh <= 16 and ks * lds + rt * 64 <= 160 * 1024
+                # room for every load of every wave in four buffers, and for the waves' partial results
+                assert lds >= 4 * -(-2 * rt // sh) * sh * 1024 and lds >= sh * rt * 16 * (cj * 16 + 4) * 4
+    assert taken > 2000
+    assert not any(r[0] for r in routes(GRID, 0, 5))                         # (where the caller says which rows the mid-M kernel gets)
+
+
+def test_every_form_is_run(routes):
+    def forms(problems):
+        return {(p[0],) + r[1:4] + (p[0] == 0 and p[1] <= 32,) for p, r in zip(problems, routes(problems)) if r[0]}
+
+    assert all(r[0] for r in routes(SHARED_FORMS)) and forms(SHARED_FORMS) >= forms(GRID)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("xt,M,K,N,gated,G", SHARED_FORMS)
+def test_every_form(xt, M, K, N, gated, G):
+    # all columns are computed; the oracle has the first 8 and the last 8 pairs of column blocks (a widest workgroup) and 8 between,
+    # in whole pairs; bf16 rows lie in a wider matrix of NaNs, none of which may be read as part of a row
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_06753_amd import binding as w2
+    from test_gpu_parity import bf16_bits, check_epilogue, dev
+    rng = np.random.default_rng(M + K + N)
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    codes = torch.randint(0, 4, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    scales = torch.empty((K // G, N), device="cuda").uniform_(0.005, 0.05, generator=g).to(torch.bfloat16)
+    packed = w2.prepack(codes, scales, G)
+    pairs = np.unique(np.concatenate([np.arange(8), rng.choice(np.arange(8, N // 32 - 8), 8, replace=False), np.arange(N // 32 - 8, N // 32)]))
+    cols = (pairs[:, None] * 32 + np.arange(32)).reshape(-1)
+    if not gated:
+        cols = np.concatenate([cols, np.arange(N // 32 * 32, N)])
+    at = torch.from_numpy(cols).cuda()
+    cs, ss = codes[:, at].cpu().numpy(), scales[:, at].contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    X = synth.make_activations(M, K, seed=M + K)
+    act = w2.ACT_SILU_MUL if gated else w2.ACT_NONE
+    if xt == 0:
+        oq, osx, _ = oracle.quantize_rows(X, G)
+        _, y64 = oracle.matmul_a8(cs, ss, G, 0, oq, osx)
+        mag = oracle.a8_term_magnitude(cs, ss, G, 0, oq, osx)
+        call = lambda: w2.matmul_a8_epi(packed, K, N, G, dev(oq), dev(osx), act=act)
+    else:
+        Xb = synth.f32_to_bf16_bits(X)
+        wide = torch.full((M + 1, K + 24), float("nan"), dtype=torch.bfloat16, device="cuda")
+        wide[:M, 8:K + 8] = dev(Xb).view(torch.bfloat16)
+        _, y64, mag = oracle.matmul_a16(cs, ss, G, 0, Xb)
+        call = lambda: w2.matmul_a16_epi(packed, K, N, G, wide[:M, 8:K + 8], act=act)
+    Y = call()
+    assert torch.equal(Y.view(torch.int16), call().view(torch.int16)), "not deterministic"
+    out = (pairs[:, None] * 16 + np.arange(16)).reshape(-1) if gated else cols
+    check_epilogue(np.ascontiguousarray(bf16_bits(Y)[:, out]), y64, mag, None, act, f"xt={xt} M={M} K={K} N={N} G={G} act={act}")
