@@ -268,7 +268,8 @@ static int a8_common(const char* fn, const void* packed, int64_t K, int64_t N, i
     hipStream_t s = (hipStream_t)stream;
     if (variant == W2_VARIANT_AUTO) {
         r = route::a8(pb, tn);
-        if (r.to_shared && !acc_out) return launch_a8_shared(a, r.shared, s);
+        if (r.instead.to_shared && !acc_out) return launch_a8_shared(a, r.instead.shared, s);
+        if (r.instead.to_slim && !acc_out) return launch_a8_tiled128(a, {r.instead.slim.ri, 128, 1, r.instead.slim.splits, r.instead.slim.us}, s);
         variant = r.variant;
         if (variant == W2_VARIANT_GEMV) {
             rc = launch_a8_gemv(a, xq, 0, K, s);
@@ -524,7 +525,7 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
     if (variant == W2_VARIANT_SCALED16) {
         // the scale-folded construction: the small-M kernel with it, or the kernels built on it
         if (!a16_smallm_supports(a))
-            return M <= 64 ? launch_a16_midm(a, route::midm_shape(1, pb, tn), s) : launch_a16_fold_tiled(a, route::a16_tiled_shape(pb, tn), s);
+            return M <= 64 ? launch_a16_midm(a, route::midm_shape(1, pb, tn), s) : launch_a16_fold_tiled(a, route::a16_tiled_shape(pb, tn), tn.tiled_bn == 128, s);
         variant = W2_VARIANT_SMALLM;
     }
     if (variant == W2_VARIANT_AUTO) {
@@ -533,13 +534,14 @@ static int a16_common(const char* fn, const void* packed, int64_t K, int64_t N, 
             rc = launch_a16_gemv(a, s);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;   // (a shape it turns down after all goes on to the other kernels)
         }
-        if (r.to_shared) return launch_a16_shared(a, r.shared, s);
+        if (r.instead.to_shared) return launch_a16_shared(a, r.instead.shared, s);
+        if (r.instead.to_slim) return launch_a16_fold_tiled(a, r.instead.slim, true, s);
         if (r.to_midm) return launch_a16_midm(a, r.has_midm ? r.midm : route::midm_shape(1, pb, tn), s);
         if (!r.gemv_first && a16_gemv_supports(a)) {         // (only where tuning fields leave rows to neither of the two)
             rc = launch_a16_gemv(a, s);
             if (rc != W2_ERR_UNSUPPORTED_SHAPE) return rc;
         }
-        if (!a16_smallm_supports(a)) return launch_a16_fold_tiled(a, r.has_tiled ? r.tiled : route::a16_tiled_shape(pb, tn), s);
+        if (!a16_smallm_supports(a)) return launch_a16_fold_tiled(a, r.has_tiled ? r.tiled : route::a16_tiled_shape(pb, tn), tn.tiled_bn == 128, s);
         variant = W2_VARIANT_SMALLM;
     }
     if (variant == W2_VARIANT_MIDM) {

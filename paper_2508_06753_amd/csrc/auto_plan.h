@@ -47,6 +47,16 @@ inline double shared_share(int a16, int64_t M, const midm::Plan& p)
     return p.ks < 8 ? (a16 ? 1.02 : 1.06) : M <= 64 ? 1.0 : 1.04;
 }
 
+// The tiled kernels' 128-column workgroups (tiles::slim), from 33 rows on: where their price is under this share of that of the tiled
+// shape that would run.  Graph-timed on random problems of 34 to 4096 rows, time by share against never taking them: 64-row tiles 0.92
+// 0.928, 1.0 0.903 (2 of 135 slower by over 3 %), 1.06 0.901 (8); tall tiles of 256 columns, groups of 128 0.88 0.989 (7 of 157
+// slower), 0.92 0.985 (15); groups of 64 0.90 0.973 (3 of 180), 0.94 0.971 (11); w2a16 0.90 0.966 (4 of 356), 0.94 0.965 (22).  Of
+// 420 further problems near the lines, time by the quotient of the prices: groups of 128 0.88 to 0.90 0.942, to 0.92 0.983, to 0.94 0.987, to 0.96
+// 1.008; groups of 64 0.90 to 0.92 0.981, to 0.94 0.983 (none slower by over 3 %), to 0.96 0.999; w2a16 0.90 to 0.92 0.985, to 0.94 1.010.
+// Where rows would be shared instead, 0.98.  Not offered where the mid-M kernel would run: 0.996 of its time over 414 problems.
+constexpr double SLIM_SHARE = 0.98, SLIM_SHARE_LOW = 1.0, SLIM_SHARE_TALL[3] = {0.90, 0.94, 0.90};
+constexpr int64_t SLIM_LEAST_ROWS = 33;
+
 struct Problem {
     int64_t M, K, N;
     int64_t n_cb, n_kt;                                      // column blocks, 256-k tiles
@@ -60,29 +70,38 @@ inline midm::Plan midm_shape(int a16, const Problem& p, const w2_tuning_t& tn, d
     return midm::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.cap, tn, us, p.G);
 }
 
-// (not where the caller says which rows the decode or the mid-M kernel gets)
-inline bool shared_offered(const Problem& p, const w2_tuning_t& tn)
-{
-    return !tn.midm_min_m && !tn.gemv_max_m && !tn.midm_cbw && tn.splitk <= 1 && !tn.tiled_bm && !tn.tiled_bn && !tn.tiled_kw && !tn.tiled_wd &&
-           shared::offered(p.M, p.n_cb, p.n_kt);
-}
+// What takes the place of the kernel that would run, if anything does.
+struct Instead {
+    bool to_shared, to_slim;
+    shared::Plan shared;
+    tiles::Shape slim;
+};
 
-inline bool shared_first(int a16, const Problem& p, double against, shared::Plan* shape)
+// `us`: price of the kernel that would run; the shares of it.  (Not where the caller says which rows the decode or the mid-M kernel
+// gets, or what a launch shape is to be.)
+inline Instead instead(int a16, const Problem& p, const w2_tuning_t& tn, double us, double shared_share, double slim_share)
 {
-    if (against <= 0) return false;
-    double us;
-    const shared::Plan s = shared::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.G, &us);
-    if (us >= against) return false;
-    *shape = s;
-    return true;
+    Instead r = {};
+    if (tn.midm_min_m || tn.gemv_max_m || tn.midm_cbw || tn.splitk || tn.tiled_bm || tn.tiled_bn || tn.tiled_kw || tn.tiled_wd) return r;
+    if (shared_share > 0 && shared::offered(p.M, p.n_cb, p.n_kt)) {
+        double price;
+        r.shared = shared::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.G, &price);
+        r.to_shared = price < us * shared_share;
+        if (r.to_shared) { us = price; slim_share = slim_share > 0 ? SLIM_SHARE : 0; }
+    }
+    if (p.M >= SLIM_LEAST_ROWS && slim_share > 0) {
+        r.slim = tiles::slim(a16 ? tiles::A16 : p.G == 128 ? tiles::A8_G128 : tiles::A8_G64, p.M, p.N, p.n_kt, p.cap);
+        r.to_slim = r.slim.us < us * slim_share;
+        if (r.to_slim) r.to_shared = false;
+    }
+    return r;
 }
 
 // ---- w2a8
 
 struct A8 {
     int variant;                                             // (of the kernels that can be asked for by name)
-    bool to_shared;                                          // the mid-M kernel that shares its rows runs instead
-    shared::Plan shared;
+    Instead instead;                                         // of it
     int fallback;                                            // where the decode kernel turns the rows down
     bool has_midm, has_tiled;                                // shapes found on the way
     midm::Plan midm;
@@ -145,16 +164,12 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
     r.variant = M <= tn.dot4_max_m && M <= DOT4_ROWS ? W2_VARIANT_DOT4
               : M <= gemv_max && M <= GEMV_ROWS      ? W2_VARIANT_GEMV
                                                      : r.fallback;
-    if ((r.variant == W2_VARIANT_MIDM || r.variant == W2_VARIANT_TILED) && shared_offered(p, tn)) {
-        double against;
-        if (r.variant == W2_VARIANT_MIDM) {
-            if (!r.has_midm) { r.midm = midm_shape(0, p, tn, &midm_us); r.has_midm = true; }
-            against = midm_us * shared_share(0, M, r.midm);
-        } else {
-            if (!r.has_tiled) { r.tiled = a8_tiled_shape(p, tn); r.has_tiled = true; }
-            against = r.tiled.us * (r.tiled.ri ? SHARED_SHARE_TALL[0] : SHARED_SHARE_LOW);
-        }
-        r.to_shared = shared_first(0, p, against, &r.shared);
+    if (r.variant == W2_VARIANT_MIDM && M >= shared::LEAST_ROWS) {
+        if (!r.has_midm) { r.midm = midm_shape(0, p, tn, &midm_us); r.has_midm = true; }
+        r.instead = instead(0, p, tn, midm_us, shared_share(0, M, r.midm), 0);
+    } else if (r.variant == W2_VARIANT_TILED) {
+        if (!r.has_tiled) { r.tiled = a8_tiled_shape(p, tn); r.has_tiled = true; }
+        r.instead = instead(0, p, tn, r.tiled.us, r.tiled.ri ? SHARED_SHARE_TALL[0] : SHARED_SHARE_LOW, r.tiled.ri ? SLIM_SHARE_TALL[p.G == 64] : SLIM_SHARE_LOW);
     }
     return r;
 }
@@ -163,8 +178,7 @@ inline A8 a8(const Problem& p, const w2_tuning_t& tn)
 
 struct A16 {
     bool gemv_first;                                         // the decode kernel, where a workgroup can hold the rows
-    bool to_shared;                                          // instead of the following two: the mid-M kernel that shares its rows
-    shared::Plan shared;
+    Instead instead;                                         // of the mid-M or the tiled kernel
     bool to_midm;                                            // then the mid-M kernel, else the small-M or the tiled one
     bool has_midm, has_tiled;
     midm::Plan midm;
@@ -216,16 +230,12 @@ inline A16 a16(const Problem& p, const w2_tuning_t& tn)
     r.gemv_first = M < midm_min;
     // (from three rows on the mid-M kernel, not the small-M one, also takes what the decode kernel turns down)
     r.to_midm = (M >= midm_min || (!tn.midm_min_m && M >= 3)) && M <= midm_max && !tiled_first && M <= MIDM_ROWS;
-    if (!r.gemv_first && (r.to_midm || M > SMALL_ROWS) && shared_offered(p, tn)) {
-        double against;
-        if (r.to_midm) {
-            if (!r.has_midm) { r.midm = midm_shape(1, p, tn, &midm_us); r.has_midm = true; }
-            against = midm_us * shared_share(1, M, r.midm);
-        } else {
-            if (!r.has_tiled) { r.tiled = a16_tiled_shape(p, tn); r.has_tiled = true; }
-            against = r.tiled.us * SHARED_SHARE_TALL[1];
-        }
-        r.to_shared = shared_first(1, p, against, &r.shared);
+    if (!r.gemv_first && r.to_midm && M >= shared::LEAST_ROWS) {
+        if (!r.has_midm) { r.midm = midm_shape(1, p, tn, &midm_us); r.has_midm = true; }
+        r.instead = instead(1, p, tn, midm_us, shared_share(1, M, r.midm), 0);
+    } else if (!r.gemv_first && !r.to_midm && M > SMALL_ROWS) {
+        if (!r.has_tiled) { r.tiled = a16_tiled_shape(p, tn); r.has_tiled = true; }
+        r.instead = instead(1, p, tn, r.tiled.us, SHARED_SHARE_TALL[1], SLIM_SHARE_TALL[2]);
     }
     return r;
 }

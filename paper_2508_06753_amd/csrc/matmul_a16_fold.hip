@@ -19,7 +19,8 @@
 // instructions per matrix instruction where the zero-point kernel issues 5.9.
 //
 // Workgroup: 128 rows (lower tiles of 64 to 112 where those waste less: tile_plan.h;
-// 4096 x 28672 at M = 300 95.7 -> 79.3 us) x (32 columns per wave) x 64 k per stage; activations go
+// 4096 x 28672 at M = 300 95.7 -> 79.3 us) x (32 columns per wave: 256, or 128 in two workgroups per CU, three
+// of 64 and 80 rows, where that is priced lower) x 64 k per stage; activations go
 // to local memory by loads that write it directly, six stages ahead (eight
 // buffers; four with 128 columns), 16-byte pieces XORed by row so that operands are
 // read without bank conflicts; weights go from global memory to
@@ -38,6 +39,7 @@
 // 90.0 / 83.9 / 79.1 / 102.7 / 91.0 with constant buffer indexes and 32-bit stage numbers (1.66).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "w2_small_common.h"
@@ -58,12 +60,16 @@ constexpr int A_ROW = BK * 2;                      // bytes of a row in one stag
 constexpr int nbuf_of(int bn) { return bn >= 256 ? 8 : 4; }
 constexpr int E_STRIDE = WN * 2 + 16;              // epilogue: bytes per LDS row of a wave's result
 constexpr int waves_of(int bn) { return bn / WN; }
-constexpr int CP_ROWS = 128;                       // most rows of a tile
-constexpr int A_BUF = CP_ROWS * A_ROW;
-constexpr int lds_bytes(int bn)
+constexpr int P_STRIDE = WN * 4 + 16;              // partial results: bytes per LDS row
+// KiBs of activations (eight rows) per wave and stage, and a stage of them
+constexpr int loads(int bn, int ri) { return (2 * ri + waves_of(bn) - 1) / waves_of(bn); }
+constexpr int a_buf(int bn, int ri) { return loads(bn, ri) * waves_of(bn) * 1024; }
+constexpr int lds_bytes(int bn, int ri)
 {
-    return nbuf_of(bn) * A_BUF > waves_of(bn) * CP_ROWS * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * CP_ROWS * E_STRIDE;
+    return std::max(std::max(nbuf_of(bn) * a_buf(bn, ri), waves_of(bn) * 16 * ri * E_STRIDE), waves_of(bn) * 64 * P_STRIDE);
 }
+// waves per SIMD that the registers are held to: one eight-wave workgroup to a CU, three of four waves (80 rows and less), two
+constexpr int simd_waves(int bn, int ri) { return bn >= 256 || ri > 5 ? 2 : 3; }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 {
@@ -118,7 +124,7 @@ struct WTile {
 
 // RI: 16-row tiles per wave (the workgroup's rows: BM = 16 RI), 4 to 8
 template <int G, int BN, int RI>
-__global__ void __launch_bounds__(64 * waves_of(BN), waves_of(BN) > 4 ? 1 : 2)
+__global__ void __launch_bounds__(64 * waves_of(BN), simd_waves(BN, RI))
 a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int splits)
 {
     constexpr int BM = 16 * RI;
@@ -127,7 +133,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     constexpr int NBUF = nbuf_of(BN);
     constexpr bool PAIR = BN >= 256;                    // a barrier after every other stage
     constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
-    constexpr int NP = (2 * RI + WAVES - 1) / WAVES;    // KiBs of activations (eight rows) per wave and stage: 1, 2 or 4
+    constexpr int NP = loads(BN, RI), A_BUF = a_buf(BN, RI);
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -315,8 +321,6 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
         // launch); the wave's tile goes through LDS, 64 rows at a time (a region of its own: the barrier at
         // the end of the last stage freed the activation buffers; rows padded by 16 bytes, conflict-free both
         // ways), and leaves as 16-byte stores in 128-byte runs.
-        constexpr int P_STRIDE = WN * 4 + 16;
-        static_assert(WAVES * 64 * P_STRIDE <= lds_bytes(BN), "partial-result staging fits the activation buffers");
         float* dst = a.part + (int64_t)blockIdx.y * a.M * a.N;
         int8_t* pbase = smem + wn * (64 * P_STRIDE);
         const int prow = lane >> 3, pcol = (lane & 7) * 4;   // eight lanes per row piece
@@ -344,7 +348,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
 
     // The wave's 128 x 32 result goes through LDS (its own region; the barrier at the end of the last
     // stage freed the activation buffers) and leaves as 16-byte stores, four lanes per 64-byte row piece.
-    int8_t* ebase = smem + wn * (CP_ROWS * E_STRIDE);
+    int8_t* ebase = smem + wn * (BM * E_STRIDE);
     uint16_t* eb = reinterpret_cast<uint16_t*>(ebase);
     // Fused epilogue (Sec. II-D: bias and activation applied while the outputs are in registers).  The
     // gated form combines the wave's two column blocks, an even (gate) and an odd (up) one, into one.
@@ -405,7 +409,7 @@ static int launch_fold_bn(const A16Args& a_in, int splits, hipStream_t stream)
     const int tiles_n = (int)((a.N + BN - 1) / BN);
     const int group_m = a.tune.tiled_group_m ? a.tune.tiled_group_m : 8;
     const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n), (unsigned)(splits < 2 ? 1 : splits)), block(64 * waves_of(BN));
-    constexpr int lds = lds_bytes(BN);
+    constexpr int lds = lds_bytes(BN, RI);
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(a16_fold_tiled_kernel<G, BN, RI>), lds,
                                     "w2_matmul_a16[scaled16 tiled]"))
         return rc;
@@ -416,23 +420,22 @@ static int launch_fold_bn(const A16Args& a_in, int splits, hipStream_t stream)
     return launch_splitk_reduce(a.part, splits, a.M, a.N, a.Y, a.ldy, a.epi, stream);
 }
 
-int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, hipStream_t stream)
+template <int G, int BN>
+static int launch_fold_ri(const A16Args& a, const tiles::Shape& p, hipStream_t stream)
 {
-    if (a.tune.tiled_bn != 128) {
-        switch (p.ri * 128 + a.G) {
-        case 4 * 128 + 64: return launch_fold_bn<64, 256, 4>(a, p.splits, stream);
-        case 5 * 128 + 64: return launch_fold_bn<64, 256, 5>(a, p.splits, stream);
-        case 6 * 128 + 64: return launch_fold_bn<64, 256, 6>(a, p.splits, stream);
-        case 7 * 128 + 64: return launch_fold_bn<64, 256, 7>(a, p.splits, stream);
-        case 8 * 128 + 64: return launch_fold_bn<64, 256, 8>(a, p.splits, stream);
-        case 4 * 128 + 128: return launch_fold_bn<128, 256, 4>(a, p.splits, stream);
-        case 5 * 128 + 128: return launch_fold_bn<128, 256, 5>(a, p.splits, stream);
-        case 6 * 128 + 128: return launch_fold_bn<128, 256, 6>(a, p.splits, stream);
-        case 7 * 128 + 128: return launch_fold_bn<128, 256, 7>(a, p.splits, stream);
-        default: return launch_fold_bn<128, 256, 8>(a, p.splits, stream);
-        }
+    switch (p.ri) {
+    case 4: return launch_fold_bn<G, BN, 4>(a, p.splits, stream);
+    case 5: return launch_fold_bn<G, BN, 5>(a, p.splits, stream);
+    case 6: return launch_fold_bn<G, BN, 6>(a, p.splits, stream);
+    case 7: return launch_fold_bn<G, BN, 7>(a, p.splits, stream);
+    default: return launch_fold_bn<G, BN, 8>(a, p.splits, stream);
     }
-    return a.G == 128 ? launch_fold_bn<128, 128, 8>(a, p.splits, stream) : launch_fold_bn<64, 128, 8>(a, p.splits, stream);
+}
+
+int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, bool slim, hipStream_t stream)
+{
+    if (slim) return a.G == 128 ? launch_fold_ri<128, 128>(a, p, stream) : launch_fold_ri<64, 128>(a, p, stream);
+    return a.G == 128 ? launch_fold_ri<128, 256>(a, p, stream) : launch_fold_ri<64, 256>(a, p, stream);
 }
 
 }  // namespace w2

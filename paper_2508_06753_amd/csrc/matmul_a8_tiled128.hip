@@ -14,8 +14,11 @@
 // mostly empty (tile_plan.h; 4096 x 28672 at M = 130 33.5 -> 26.1 us, 28672 x
 // 8192 with groups of 64 at M = 242 to 277 30 to 45 % less):
 //   - workgroup 16 RI rows x 256 columns (eight waves of 16 RI x 32, one workgroup
-//     per CU) or 128 x 128 (four waves, two per CU); a stage is 128 k = one
-//     group of G = 128, 32 matrix instructions per wave;
+//     per CU) or x 128 (four waves, two workgroups per CU, three of RI = 4 and 5:
+//     their loads, barriers and stores lie under one another's multiplication, which
+//     grids of few rounds want; 4096 x 28672 gated at M = 1000, groups of 64, 142 ->
+//     131 us, and tile_plan.h); a stage is 128 k = one group of G = 128, 32 matrix
+//     instructions per wave;
 //   - activations go from global to local memory directly, 16-byte pieces XORed by
 //     row (conflict-free operand reads), six stages ahead in eight buffers
 //     (eight-wave workgroups): the pair of stages (2S, 2S+1) reads stages 2S ..
@@ -51,6 +54,7 @@
 //     which costs the near-zero outputs their accuracy.)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "w2_small_common.h"
@@ -68,7 +72,6 @@ constexpr int BK = 128;
 constexpr int CP_ROWS = 128;                       // most rows of a tile
 constexpr int WN = 16 * CJ;
 constexpr int A_ROW = BK;                          // bytes of a row in one stage: eight 16-byte pieces
-constexpr int A_BUF = CP_ROWS * A_ROW;
 // LDS buffers: 4 with a barrier after every stage; 8 with a barrier after every other stage (eight-wave
 // workgroups, one per CU: the waves of a workgroup may then drift a stage apart inside a pair)
 constexpr int nbuf_of(int bn) { return bn >= 256 ? 8 : 4; }
@@ -77,10 +80,16 @@ constexpr int BIAS = 1 << 21;                      // > 64 * 127 * 2 * 128 = 2 0
 constexpr float BIAS_F = 0x1p-128f;                // BIAS read as a float: 2^21 * 2^-149
 constexpr int waves_of(int bn) { return bn / WN; }
 constexpr int SX_BYTES = CP_ROWS * 4;                   // the tile's activation scales, parked for the epilogue
-constexpr int lds_bytes(int bn)
+constexpr int P_STRIDE = WN * 4 + 16;              // partial results: bytes per LDS row
+// KiBs of activations (eight rows) per wave and stage, and a stage of them
+constexpr int loads(int bn, int ri) { return (2 * ri + waves_of(bn) - 1) / waves_of(bn); }
+constexpr int a_buf(int bn, int ri) { return loads(bn, ri) * waves_of(bn) * 1024; }
+constexpr int lds_bytes(int bn, int ri)
 {
-    return nbuf_of(bn) * A_BUF > waves_of(bn) * CP_ROWS * E_STRIDE ? nbuf_of(bn) * A_BUF : waves_of(bn) * CP_ROWS * E_STRIDE;
+    return std::max(std::max(nbuf_of(bn) * a_buf(bn, ri), waves_of(bn) * 16 * ri * E_STRIDE), waves_of(bn) * 64 * P_STRIDE);
 }
+// waves per SIMD that the registers are held to: one eight-wave workgroup to a CU, three of four waves (80 rows and less), two
+constexpr int simd_waves(int bn, int ri) { return bn >= 256 || ri > 5 ? 2 : 3; }
 
 __device__ __forceinline__ v4i upconvert4(uint32_t w)
 {
@@ -103,7 +112,7 @@ struct WTile {
 // workspace and a second launch sums them (Sec. II-D, K-splitting for the smaller shapes).  An instantiation of
 // its own: the unsplit kernel is compiled exactly as before.
 template <int G, bool DBG, int BN, bool SPLIT = false, int RI = 8>
-__global__ void __launch_bounds__(64 * waves_of(BN), BN >= 256 ? 1 : 2)
+__global__ void __launch_bounds__(64 * waves_of(BN), simd_waves(BN, DBG ? 8 : RI))
 a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, int c_rem)
 {
     constexpr int BM = 16 * RI;
@@ -112,7 +121,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     constexpr int NBUF = nbuf_of(BN);
     constexpr bool PAIR = BN >= 256;               // a barrier after every other stage
     constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
-    constexpr int NP = (2 * RI + WAVES - 1) / WAVES;    // KiBs of activations (eight rows) per wave and stage: 1, 2 or 4
+    constexpr int NP = loads(BN, RI), A_BUF = a_buf(BN, RI);
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -209,7 +218,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 
     // the tile's activation scales, fetched now (unconditionally) and parked in LDS for the epilogue: loaded
     // there they would cost every workgroup a memory round trip with nothing to hide it
-    float* sx_lds = reinterpret_cast<float*>(smem + lds_bytes(BN));
+    float* sx_lds = reinterpret_cast<float*>(smem + lds_bytes(BN, RI));
     const float sx_mine = DBG ? 0.f : a.sx[min(m0 + (tid & (CP_ROWS - 1)), a.M - 1)];
 
     WTile<G> w0, w1;
@@ -434,7 +443,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     // y_true = (y - BIAS*2^-149 * ssum) * 2^(149-64) * 2^-6 * sx.  The wave's 128 x 32 result goes through
     // LDS (its own region; the barrier above freed the activation buffers) and
     // leaves as 16-byte stores.
-    int8_t* ebase = smem + wn * (CP_ROWS * E_STRIDE);
+    int8_t* ebase = smem + wn * (BM * E_STRIDE);
     uint16_t* eb = reinterpret_cast<uint16_t*>(ebase);
     const bool gated = a.epi.act == ACT_SILU_MUL;
     float bias[CJ];
@@ -454,8 +463,6 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         // this range's results, dequantised, as fp32 rows of the workspace: the wave's 128 x 32 tile goes
         // through LDS 64 rows at a time (rows padded by 16 bytes: conflict-free both ways; the wave reads
         // back only what it wrote) and leaves as 16-byte stores in 128-byte runs
-        constexpr int P_STRIDE = WN * 4 + 16;
-        static_assert(waves_of(BN) * 64 * P_STRIDE <= lds_bytes(BN), "partial-result staging fits the activation buffers");
         float* dst = a.part + (int64_t)blockIdx.y * a.M * a.N;
         int8_t* pbase = smem + wn * (64 * P_STRIDE);
         const int prow = lane >> 3, pcol = (lane & 7) * 4;   // eight lanes per row piece
@@ -533,7 +540,7 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
     // tiles and fetch group_m MiB of activations and 16 / group_m MiB of weights per round at K = 8192: 4
     // moves the least through the XCD's L2 (measured as fast as 8 at M = 2048, 2 % faster at M = 4096).
     const int group_m = a.tune.tiled_group_m ? a.tune.tiled_group_m : 4;
-    constexpr int lds = lds_bytes(BN) + SX_BYTES;
+    constexpr int lds = lds_bytes(BN, RI) + SX_BYTES;
     auto kern = a8_tiled128_kernel<G, DBG, BN, SPLIT, RI>;
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, "w2_matmul_a8[tiled 128]")) return rc;
     const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n), (unsigned)(SPLIT ? splits : 1)), block(64 * WAVES);
@@ -547,43 +554,30 @@ static int launch(const A8Args& a, int splits, hipStream_t stream)
 }  // namespace t128
 
 
-// The test-only export and 128-column workgroups have eight row tiles per wave.
+template <int G, int BN, bool SPLIT>
+static int launch_ri(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
+{
+    switch (p.ri) {
+    case 4: return t128::launch<G, false, BN, SPLIT, 4>(a, p.splits, stream);
+    case 5: return t128::launch<G, false, BN, SPLIT, 5>(a, p.splits, stream);
+    case 6: return t128::launch<G, false, BN, SPLIT, 6>(a, p.splits, stream);
+    case 7: return t128::launch<G, false, BN, SPLIT, 7>(a, p.splits, stream);
+    default: return t128::launch<G, false, BN, SPLIT>(a, p.splits, stream);
+    }
+}
+
+template <int G>
+static int launch_g(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
+{
+    if (a.acc_out)                                           // (the test-only export has eight row tiles per wave)
+        return p.bn == 128 ? t128::launch<G, true, 128>(a, 1, stream) : t128::launch<G, true, 256>(a, 1, stream);
+    if (p.bn == 128) return p.splits >= 2 ? launch_ri<G, 128, true>(a, p, stream) : launch_ri<G, 128, false>(a, p, stream);
+    return p.splits >= 2 ? launch_ri<G, 256, true>(a, p, stream) : launch_ri<G, 256, false>(a, p, stream);
+}
+
 int launch_a8_tiled128(const A8Args& a, const tiles::A8Shape& p, hipStream_t stream)
 {
-    if (a.acc_out) {
-        if (a.G == 64) return p.bn == 128 ? t128::launch<64, true, 128>(a, 1, stream) : t128::launch<64, true, 256>(a, 1, stream);
-        return p.bn == 128 ? t128::launch<128, true, 128>(a, 1, stream) : t128::launch<128, true, 256>(a, 1, stream);
-    }
-    if (p.bn == 128) {
-        if (a.G == 64) return t128::launch<64, false, 128>(a, 1, stream);
-        return p.splits >= 2 ? t128::launch<128, false, 128, true>(a, p.splits, stream) : t128::launch<128, false, 128>(a, 1, stream);
-    }
-    if (p.splits >= 2) {
-        switch (p.ri * 128 + a.G) {
-        case 4 * 128 + 64: return t128::launch<64, false, 256, true, 4>(a, p.splits, stream);
-        case 5 * 128 + 64: return t128::launch<64, false, 256, true, 5>(a, p.splits, stream);
-        case 6 * 128 + 64: return t128::launch<64, false, 256, true, 6>(a, p.splits, stream);
-        case 7 * 128 + 64: return t128::launch<64, false, 256, true, 7>(a, p.splits, stream);
-        case 8 * 128 + 64: return t128::launch<64, false, 256, true>(a, p.splits, stream);
-        case 4 * 128 + 128: return t128::launch<128, false, 256, true, 4>(a, p.splits, stream);
-        case 5 * 128 + 128: return t128::launch<128, false, 256, true, 5>(a, p.splits, stream);
-        case 6 * 128 + 128: return t128::launch<128, false, 256, true, 6>(a, p.splits, stream);
-        case 7 * 128 + 128: return t128::launch<128, false, 256, true, 7>(a, p.splits, stream);
-        default: return t128::launch<128, false, 256, true>(a, p.splits, stream);
-        }
-    }
-    switch (p.ri * 128 + a.G) {
-    case 4 * 128 + 64: return t128::launch<64, false, 256, false, 4>(a, 1, stream);
-    case 5 * 128 + 64: return t128::launch<64, false, 256, false, 5>(a, 1, stream);
-    case 6 * 128 + 64: return t128::launch<64, false, 256, false, 6>(a, 1, stream);
-    case 7 * 128 + 64: return t128::launch<64, false, 256, false, 7>(a, 1, stream);
-    case 8 * 128 + 64: return t128::launch<64, false, 256>(a, 1, stream);
-    case 4 * 128 + 128: return t128::launch<128, false, 256, false, 4>(a, 1, stream);
-    case 5 * 128 + 128: return t128::launch<128, false, 256, false, 5>(a, 1, stream);
-    case 6 * 128 + 128: return t128::launch<128, false, 256, false, 6>(a, 1, stream);
-    case 7 * 128 + 128: return t128::launch<128, false, 256, false, 7>(a, 1, stream);
-    default: return t128::launch<128, false, 256>(a, 1, stream);
-    }
+    return a.G == 128 ? launch_g<128>(a, p, stream) : launch_g<64>(a, p, stream);
 }
 
 }  // namespace w2

@@ -79,6 +79,57 @@ inline Shape pick(Kind kind, int64_t M, int64_t N, int64_t n_kt, int64_t cap, in
     return best;
 }
 
+// ---- the same two kernels in workgroups of 128 columns: four waves, two workgroups to a CU, three of 64 and 80 rows.  Rounds are
+// shorter, and the first loads and the store of one workgroup lie under the other's multiplication, but the activations are read by
+// twice as many workgroups.  The fastest shape of 256 and of 128 columns (us): int8 rows, 4096 x 28672 gated at M = 1000 120 and 112,
+// groups of 64 142 and 131; 8192 x 10240 at M = 2048 163 and 154; 8192 x 57344 gated at M = 2048 831 and 858; bf16 rows, 190 and 193,
+// 263 and 273, 1408 and 1450.
+
+constexpr unsigned slim_at_once(int ri) { return ri <= 5 ? 768 : 512; }
+
+struct SlimCoef {
+    double launch, wg,                                       // fixed, and per workgroup / 256
+           tile, tile_ri,                                    // per 256 k and round; times row tiles
+           tile_cu, tile_cu_ri,                              // per 256 k and workgroup of the busiest CU
+           tile_wg, tile_wg_ri,                              // per 256 k and workgroup / 256 (a full chip holds lower clocks)
+           parts, part_value;                                // the second launch, and per value of a partial result
+};
+// Fits to 13000 graph-timed launches (64 and 80 rows, 96 and more) on 1410 problems (K 1024 to 28672, N 1024 to 57344, 34 to 4096
+// rows): 4.8 to 5.5 % off in the root mean square near the fastest; the shapes chosen are 0.6 to 0.8 % slower than the fastest measured.
+constexpr SlimCoef SLIM_COEF[3][2] = {
+    {{4.11, 1.042, 0.102, 0.04307, 0, 0.07706, 0, 0.01219, 2.851, 8.438e-07},
+     {4.417, 1.773, 0, 0.04697, 0, 0.06986, 0.04931, 0.006411, 3.066, 6.93e-07}},
+    {{4.486, 0.9412, 0.0173, 0.06897, 0.005868, 0.0973, 0, 0.01047, 2.793, 7.089e-07},
+     {4.773, 1.671, 0, 0.06723, 0, 0.08206, 0, 0.0118, 2.903, 6.478e-07}},
+    {{4.221, 0.9432, 0.2825, 0.04993, 0.02383, 0.1266, 0, 0.0438, 3.094, 6.252e-07},
+     {5.203, 1.171, 0.03201, 0.0749, 0, 0.1009, 0, 0.05355, 2.704, 6.753e-07}}};
+
+// The cheapest; parts as `pick` has them, and no grids of more than six workgroups to a CU in parts.
+inline Shape slim(Kind kind, int64_t M, int64_t N, int64_t n_kt, int64_t cap)
+{
+    Shape best = {8, 1, 1e30};
+    const int most = (int)std::min(std::min(n_kt / 2, cap), std::min((int64_t)MAX_SPLITS, copies(MAX_PART_BYTES, M, N)));
+    int nk[MAX_SPLITS + 1];                                  // (this runs on every call: 32-bit divisions)
+    nk[1] = (int)n_kt;
+    for (int s = 2; s <= most; ++s) nk[s] = ((int)n_kt + s - 1) / s;
+    const double values = (double)M * (double)N;
+    const int64_t cols = (N + 127) / 128, row_tiles = (M + 15) / 16;
+    for (int ri = 4; ri <= 8; ++ri) {
+        const SlimCoef& c = SLIM_COEF[kind][ri > 5];
+        const unsigned tiles = (unsigned)std::min((row_tiles + ri - 1) / ri * cols, (int64_t)1 << 30);
+        for (int s = 1; s <= std::max(most, 1); ++s) {
+            const unsigned wgs = tiles * s;
+            if (s > 1 && (tiles > 1536 || wgs > 1536)) break;
+            const double rounds = (wgs + slim_at_once(ri) - 1) / slim_at_once(ri), per_cu = (wgs + 255) >> 8, fill = wgs / 256.0;
+            double t = c.launch + c.wg * fill +
+                       nk[s] * (rounds * (c.tile + c.tile_ri * ri) + per_cu * (c.tile_cu + c.tile_cu_ri * ri) + fill * (c.tile_wg + c.tile_wg_ri * ri));
+            if (s > 1) t += c.parts + c.part_value * values * s;
+            if (t < best.us) best = {ri, s, t};
+        }
+    }
+    return best;
+}
+
 // ---- the 64-row kernel of w2a8 (matmul_a8_tiled.hip)
 
 // bn columns per workgroup, `kw` K ranges inside a workgroup (of bn / 32 waves each) times `splits` across workgroups.

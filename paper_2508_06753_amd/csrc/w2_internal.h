@@ -113,7 +113,8 @@ struct A16Args {
 bool a16_smallm_supports(const A16Args& a);
 int launch_a16_smallm(const A16Args& a, hipStream_t stream);
 int launch_a16_tiled(const A16Args& a, hipStream_t stream);
-int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, hipStream_t stream);
+// slim: workgroups of 128 columns, else 256
+int launch_a16_fold_tiled(const A16Args& a, const tiles::Shape& p, bool slim, hipStream_t stream);
 // w2a16 through the decode kernel (bf16 rows as they are, M <= 4, rows that fit one workgroup)
 bool a16_gemv_supports(const A16Args& a);
 int launch_a16_gemv(const A16Args& a, hipStream_t stream);
