@@ -37,14 +37,14 @@ inline double tiled_share(int a16, const midm::Plan& p, bool low_tiles)
 //   mid-M kernel, fewer than eight K ranges   to 32 rows   int8 0.96 0.985, 1.0 0.978, 1.06 0.970 (6 of 88 slower by over 3 %; 1 at 1.0)
 //                                                          bf16 0.96 0.962, 0.98 0.953, 1.02 0.946 (4 of 77 slower; 1 at 0.98)
 //                                             above        int8 1.0 0.909, 1.06 0.882;  bf16 1.0 0.886, 1.02 0.878, 1.06 0.879
-//   eight K ranges                            to 32 rows   never below 1.000
-//                                             33 to 64     1.0 0.973 and 0.994, 1.04 0.969 and 1.003;  above  1.0 0.993 and 0.977, 1.04 0.983 and 0.968
+//   eight K ranges: not offered.  Thirty of 2000 further problems, timed through these calls against never taking it: 33 to 64 rows
+//                   1.0 1.012 (12544 x 15488 gated bf16 M = 46 29.6 -> 32.2 us), above 1.04 0.997 (18688 x 7168 int8 M = 73 21.8 -> 23.5)
 //   64-row tiles 1.04 0.982;  tall tiles 0.92 0.990, 1.0 0.992 (2 of 26 slower);  w2a16 0.88 0.977, 1.0 0.986 (12 of 71 slower; 5 at 0.88)
 constexpr double SHARED_SHARE_LOW = 1.04, SHARED_SHARE_TALL[2] = {0.92, 0.88};
 inline double shared_share(int a16, int64_t M, const midm::Plan& p)
 {
-    if (M <= 32) return p.ks >= 8 ? 0.0 : a16 ? 0.98 : 1.0;
-    return p.ks < 8 ? (a16 ? 1.02 : 1.06) : M <= 64 ? 1.0 : 1.04;
+    if (p.ks >= 8) return 0.0;
+    return M <= 32 ? (a16 ? 0.98 : 1.0) : a16 ? 1.02 : 1.06;
 }
 
 // The tiled kernels' 128-column workgroups (tiles::slim), from 33 rows on: where their price is under this share of that of the tiled
