@@ -171,7 +171,8 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     const int rows = (int)min((int64_t)BM, a.M - m0);
     const uint32_t stride = (uint32_t)a.ldx * 2u;
     const char* const xbase = reinterpret_cast<const char*>(a.X + m0 * a.ldx);
-    const uint32_t xbytes = (uint32_t)(rows - 1) * stride + (uint32_t)a.n_kt * (TILE_K * 2);
+    // (128 rows of K = ldx = 2^24 are 2^32 bytes, one more than the resource counts; the last byte is no lane's offset)
+    const uint32_t xbytes = (uint32_t)min((int64_t)(rows - 1) * stride + a.n_kt * (TILE_K * 2), (int64_t)0xffffffff);
     const int slot = (lane & 7) ^ (lane >> 3), piece = ((slot & 3) << 1) | (slot >> 2 ^ 1);
     uint32_t xoff[NP];
 #pragma unroll

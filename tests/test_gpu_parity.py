@@ -1100,6 +1100,24 @@ def test_a16_tiled_rows_straight_to_local_memory(w2, M, K, G, bn):
         check_y(bf16_bits(Y), Yo, y64, mag, f"a16 tiled M={M} K={K} G={G} bn={bn} splitk={splitk}")
 
 
+def test_a16_tall_tiles_longest_rows(w2):
+    # 128 rows of the longest K are 2^32 bytes: no 32-bit count of them may come out as none.  Two ones in each row, one of them near
+    # its end, so that an output is the sum of two weights: bf16 of it is within 2^-8
+    M, K, N, G = 128, 1 << 24, 8, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    codes = torch.randint(0, 4, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    scales = torch.empty((K // G, N), device="cuda").uniform_(0.005, 0.05, generator=g).to(torch.bfloat16)
+    packed = w2.prepack(codes, scales, G)
+    X = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda")
+    rows = torch.arange(M, device="cuda")
+    want = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    for ks in (rows * 131101, K - 1 - rows):
+        X[rows, ks] = 1.0
+        want += (codes[ks].double() - 2) * scales[ks // G].double()
+    Y = w2.matmul_a16(packed, K, N, G, X, variant=w2.VARIANT_SCALED16, tune={"tiled_bn": 128})
+    assert ((Y.double() - want).abs() <= 2.0 ** -8 * want.abs()).all() and Y.count_nonzero() > M * N // 2
+
+
 @pytest.mark.parametrize("G", [64, 128])
 @pytest.mark.parametrize("K,N", SMALL_SHAPES)
 @pytest.mark.parametrize("M", [1, 4, 7, 16])
