@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libw2mm.so")
 SOURCES = ["api.hip", "prepack.hip", "quantize.hip", "matmul_a8_small.hip",
            "matmul_midm.hip", "matmul_shared.hip", "matmul_a8_tiled.hip", "matmul_a8_tiled128.hip", "matmul_a8_gemv.hip", "matmul_a16.hip", "matmul_a16_fold.hip",
            "comparators.hip", "splitk.hip"]
-HEADERS = ["w2_layout.h", "w2_internal.h", "w2_small_common.h", "midm_common.h", "midm_plan.h", "shared_plan.h", "tile_plan.h", "auto_plan.h", os.path.join("..", "..", "include", "w2mm.h")]
+HEADERS = ["w2_layout.h", "w2_internal.h", "w2_small_common.h", "midm_common.h", "midm_plan.h", "shared_plan.h", "tile_plan.h", "tall_waits.h", "auto_plan.h", os.path.join("..", "..", "include", "w2mm.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Wall", "-Wno-unused-function",

@@ -42,6 +42,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "tall_waits.h"
 #include "w2_small_common.h"
 
 namespace w2 {
@@ -132,7 +133,8 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     constexpr int GPT = TILE_K / G;
     constexpr int NBUF = nbuf_of(BN);
     constexpr bool PAIR = BN >= 256;                    // a barrier after every other stage
-    constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
+    constexpr int AHEAD = tall::ahead(PAIR);            // stage it asks for the activations of stage it + AHEAD
+    static_assert(AHEAD == (PAIR ? NBUF - 2 : NBUF - 1), "into the buffers that the barrier before freed");
     constexpr int NP = loads(BN, RI), A_BUF = a_buf(BN, RI);
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
@@ -216,7 +218,7 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < AHEAD; ++p) load_a(st_b + p, p);
-    wait_loads<(PAIR ? AHEAD - 3 : AHEAD - 2) * NP>();       // stages 0, 1 (and 2) are there
+    wait_loads<tall::at_start(PAIR, NP)>();       // stages 0, 1 (and 2) are there
     bare_barrier();
 
     // (operands of k-step 0 and 1 in buffers 0 .. 3 and, beyond the reach of an instruction's offset, from 4 on)
@@ -298,9 +300,10 @@ a16_fold_tiled_kernel(A16Args a, int tiles_m, int tiles_n, int group_m, int spli
         }
         // before the next pair: stages up to its third have landed; what was asked for since, three more, and a tile's
         // weights in its first stage, may be under way.  (Four buffers: the next two stages; one more.)
-        if constexpr (PAIR && (t & 1)) wait_loads<3 * NP + (t == 1 ? 2 * CJ : 0)>();
-        if constexpr (!PAIR) wait_loads<NP + (t == 0 ? 2 * CJ : 0)>();
-        if constexpr (!PAIR || (t & 1)) bare_barrier();
+        if constexpr (!PAIR || (t & 1)) {
+            wait_loads<tall::behind(PAIR, t, NP, tall::weights(false, CJ))>();
+            bare_barrier();
+        }
     };
     auto tile = [&](int kt, auto oc, const WTile<G>& wc, WTile<G>& wnx) {
         constexpr int o = decltype(oc)::value;

@@ -57,6 +57,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "tall_waits.h"
 #include "w2_small_common.h"
 
 #if defined(__HIP_DEVICE_COMPILE__) && defined(__FAST_MATH__)
@@ -120,7 +121,8 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
     constexpr int GPT = TILE_K / G;
     constexpr int NBUF = nbuf_of(BN);
     constexpr bool PAIR = BN >= 256;               // a barrier after every other stage
-    constexpr int AHEAD = PAIR ? NBUF - 2 : NBUF - 1;   // stage it asks for the activations of stage it + AHEAD
+    constexpr int AHEAD = tall::ahead(PAIR);       // stage it asks for the activations of stage it + AHEAD
+    static_assert(AHEAD == (PAIR ? NBUF - 2 : NBUF - 1), "into the buffers that the barrier before freed");
     constexpr int NP = loads(BN, RI), A_BUF = a_buf(BN, RI);
     extern __shared__ __align__(16) int8_t smem[];
     const int tid = threadIdx.x;
@@ -227,7 +229,7 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
 #pragma unroll
     for (int p = 0; p < AHEAD; ++p) load_a(p, p);
     if (tid < CP_ROWS) sx_lds[tid] = sx_mine;                // (read after barriers that wait for local memory, in the epilogue)
-    wait_loads<(PAIR ? AHEAD - 3 : AHEAD - 2) * NP>();       // stages 0, 1 (and 2) are there
+    wait_loads<tall::at_start(PAIR, NP)>();       // stages 0, 1 (and 2) are there
     bare_barrier();
 
     // where a lane finds the operands of k-step 0 and 1 in buffers 0 .. 3 and, beyond the reach of an instruction's offset,
@@ -310,9 +312,10 @@ a8_tiled128_kernel(A8Args a, int tiles_m, int tiles_n, int group_m, int c_lo, in
         // before the next pair: stages up to its third have landed; what was asked for since, three more and a tile's weights,
         // may be under way.  (Four buffers: the next two stages; one more and, asked for in this stage, weights.)
         auto end_of_stage = [&]() {
-            if constexpr (PAIR && h == 1) wait_loads<3 * NP + 2 * CJ>();
-            if constexpr (!PAIR) wait_loads<NP + (h == 0 ? 2 * CJ : 0)>();
-            if constexpr (!PAIR || h == 1) bare_barrier();
+            if constexpr (!PAIR || h == 1) {
+                wait_loads<tall::behind(PAIR, h, NP, tall::weights(DBG, CJ))>();
+                bare_barrier();
+            }
         };
         const v4i b00 = b_next;
         // Each block is a scheduling region of its own (sched_barrier at its end): the vector work placed in a
