@@ -79,8 +79,9 @@ typedef enum {
  * 160 Mi, 64 when N >= 40960; from M = 33 on by price, as for w2a8), else the SCALED16 tiled kernel.
  * From 17 to 144 rows, on 4096 columns and more and K from 768 to 20480, AUTO runs instead of MIDM and TILED a
  * kernel that has no name here where its price is lower: MIDM's arithmetic in workgroups of up to sixteen column
- * blocks that share their rows (not where midm_min_m, gemv_max_m or a field of the launch shape is set).  The tiled
- * kernels it runs in workgroups of 256 columns or, by price, of 128 (the latter likewise).
+ * blocks that share their rows.  The tiled kernels it runs in workgroups of 256 columns or, by price, of 128.  (Neither
+ * where midm_min_m, midm_max_m, gemv_max_m, midm_cbw, splitk, splitk_min_tiles, tiled_bm, tiled_bn, tiled_kw or
+ * tiled_wd is set.)
  * GEMV: the decode kernel: whole rows in local memory, a wave streams a contiguous run of a column
  * block's tiles through a rolling register window into int8 MFMA (w2a8, M <= 32) or, with bf16 rows left as they
  * are and the zero-point weight construction, into bf16 MFMA (w2a16, M <= 16; W2_ERR_UNSUPPORTED_SHAPE when the

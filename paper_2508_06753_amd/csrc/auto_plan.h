@@ -82,7 +82,9 @@ struct Instead {
 inline Instead instead(int a16, const Problem& p, const w2_tuning_t& tn, double us, double shared_share, double slim_share)
 {
     Instead r = {};
-    if (tn.midm_min_m || tn.gemv_max_m || tn.midm_cbw || tn.splitk || tn.tiled_bm || tn.tiled_bn || tn.tiled_kw || tn.tiled_wd) return r;
+    if (tn.midm_min_m || tn.midm_max_m || tn.gemv_max_m || tn.midm_cbw || tn.splitk || tn.splitk_min_tiles || tn.tiled_bm || tn.tiled_bn ||
+        tn.tiled_kw || tn.tiled_wd)
+        return r;
     if (shared_share > 0 && shared::offered(p.M, p.n_cb, p.n_kt)) {
         double price;
         r.shared = shared::plan(a16, p.M, p.n_cb, p.n_kt, p.gated, p.G, &price);

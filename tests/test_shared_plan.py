@@ -19,11 +19,13 @@ PROGRAM = r"""
 using namespace w2;
 int main()
 {
-    int a16, G, gated, limit;
+    int a16, G, gated, field, value;
     long long M, K, N, cap;
-    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d", &a16, &M, &K, &N, &gated, &G, &cap, &limit) == 8) {
+    while (scanf("%%d %%lld %%lld %%lld %%d %%d %%lld %%d %%d", &a16, &M, &K, &N, &gated, &G, &cap, &field, &value) == 9) {
         w2_tuning_t tn = {};
-        tn.midm_min_m = limit;
+        int* const fields[] = {&tn.midm_min_m, &tn.midm_max_m, &tn.gemv_max_m, &tn.midm_cbw, &tn.splitk, &tn.splitk_min_tiles,
+                               &tn.tiled_bm, &tn.tiled_bn, &tn.tiled_kw, &tn.tiled_wd};
+        *fields[field] = value;
         const route::Problem p = {M, K, N, (N + 15) / 16, K / 256, G, gated != 0, cap};
         const route::Instead r = a16 ? route::a16(p, tn).instead : route::a8(p, tn).instead;
         const shared::Plan s = r.shared;
@@ -88,9 +90,9 @@ def routes(tmp_path_factory):
     (d / "p.cpp").write_text(PROGRAM % ROOT)
     subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
 
-    def ask(problems, cap=0, midm_min_m=0):
+    def ask(problems, cap=0, field=0, value=0):
         """-> (1, rt, cj, sh, K ranges, bytes of local memory of one): rows shared; (2, row tiles, parts of K, ...): 128 columns; (0, ...)"""
-        text = "".join("{} {} {} {} {} {} {} {}\n".format(*p, cap, midm_min_m) for p in problems)
+        text = "".join("{} {} {} {} {} {} {} {} {}\n".format(*p, cap, field, value) for p in problems)
         out = subprocess.run([str(d / "p")], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, l.split())) for l in out.splitlines()]
 
@@ -117,7 +119,25 @@ def test_shapes_fit_the_kernel(routes):
                 # room for every load of every wave in four buffers, and for the waves' partial results
                 assert lds >= 4 * -(-2 * rt // sh) * sh * 1024 and lds >= sh * rt * 16 * (cj * 16 + 4) * 4
     assert taken > 2000 and slim > 2000
-    assert not any(r[0] for r in routes(GRID, 0, 5))                         # (where the caller says which rows the mid-M kernel gets)
+
+
+# a field of w2_tuning_t and a value of it: midm_min_m, midm_max_m, gemv_max_m, midm_cbw, splitk, splitk_min_tiles, tiled_bm, tiled_bn,
+# tiled_kw, tiled_wd
+@pytest.mark.parametrize("field,value", [(0, 5), (1, 1), (1, 16), (1, 256), (2, 8), (3, 4), (4, 2), (5, 1024), (6, 64), (7, 256), (8, 2), (9, 8)])
+def test_not_where_the_caller_says(routes, field, value):
+    # which rows the mid-M or the decode kernel gets, what a launch shape is to be, how many tiles a part of K has
+    assert not any(r[0] for cap in (0, 16) for r in routes(GRID[::7], cap, field, value))
+
+
+def test_sides_of_autos_lines(routes):
+    # of the problems that the mid-M kernel and another one are compared on, which AUTO gives to a third
+    from paper_2508_06753_amd import binding as w2
+    from test_gpu_parity import AUTO_SIDES, AUTO_SIDES_SHARED
+    for path, M, K, N in AUTO_SIDES:
+        p = [(int(path == "a16"), M, K, N, 0, 128)]
+        cap = w2.workspace_size(M, K, N, 128, a16=path == "a16") // (4 * M * N)
+        assert routes(p, cap)[0][0] == ((path, M, K, N) in AUTO_SIDES_SHARED)
+        assert routes(p, cap, 1, 1)[0][0] == 0                               # (the "other" side, midm_max_m = 1: the plain tiled kernel)
 
 
 def test_every_form_is_run(routes):
