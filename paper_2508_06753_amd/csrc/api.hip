@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/w2mm.h"
@@ -592,6 +593,9 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
     const Layout L = make_layout(K, N, G);
     const w2_tuning_t dflt = {};
     const route::Problem pb = {M, K, N, L.n_cb, L.n_kt, G, false, 16};
+    // (each kernel's parts, whichever of them runs in the end)
+    const size_t slim = M >= route::SLIM_LEAST_ROWS && tiles::copies(tiles::MAX_PART_BYTES, M, N) >= 2
+                            ? part_bytes(route::slim_parts(a16 != 0, pb, dflt), M, N) : 0;
     if (M == 0) *bytes = 0;
     else if (a16) {
         route::A16 r = {};
@@ -599,13 +603,13 @@ int w2_workspace_size(int64_t M, int64_t K, int64_t N, int G, int a16, size_t* b
         const bool first = M > 32 && M <= 64 && route::a16_tiled_first(pb, dflt, &r, &us);
         const size_t tiled = M > 64 || first ? part_bytes(route::a16_tiled_shape(pb, dflt).splits, M, N) : 0;
         const size_t midm = M >= 3 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
-        *bytes = tiled > midm ? tiled : midm;
+        *bytes = std::max(slim, std::max(tiled, midm));
     }
     else {
         // split-K partial results of the tiled kernels; what was reported for the mid-M range is reported still
         const size_t tiled = M > 32 ? part_bytes(route::a8_tiled_shape(pb, dflt).splits, M, N) : 0;
         const size_t midm = M >= 4 && M <= 128 ? midm_room_bytes(M, N, L.n_cb, L.n_kt) : 0;
-        *bytes = (single ? 0 : fused_workspace_bytes(M, K)) + (tiled > midm ? tiled : midm);
+        *bytes = (single ? 0 : fused_workspace_bytes(M, K)) + std::max(slim, std::max(tiled, midm));
     }
     return W2_OK;
 }

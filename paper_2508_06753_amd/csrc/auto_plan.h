@@ -242,6 +242,19 @@ inline A16 a16(const Problem& p, const w2_tuning_t& tn)
     return r;
 }
 
+// Most parts that AUTO cuts K into across 128-column workgroups, given the room, with any epilogue (the gated one changes what the
+// other kernels cost): what a workspace has to hold for that choice.
+inline int slim_parts(int a16, Problem p, const w2_tuning_t& tn)
+{
+    int parts = 1;
+    for (int gated = 0; gated <= (p.N % 32 == 0); ++gated) {
+        p.gated = gated != 0;
+        const Instead r = a16 ? route::a16(p, tn).instead : route::a8(p, tn).instead;
+        if (r.to_slim && r.slim.splits > parts) parts = r.slim.splits;
+    }
+    return parts;
+}
+
 }  // namespace route
 
 }  // namespace w2

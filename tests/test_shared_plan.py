@@ -91,8 +91,10 @@ def routes(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
 
     def ask(problems, cap=0, field=0, value=0):
-        """-> (1, rt, cj, sh, K ranges, bytes of local memory of one): rows shared; (2, row tiles, parts of K, ...): 128 columns; (0, ...)"""
-        text = "".join("{} {} {} {} {} {} {} {} {}\n".format(*p, cap, field, value) for p in problems)
+        """cap: copies of the output that the workspace holds, for all or each
+        -> (1, rt, cj, sh, K ranges, bytes of local memory of one): rows shared; (2, row tiles, parts of K, ...): 128 columns; (0, ...)"""
+        caps = cap if isinstance(cap, list) else [cap] * len(problems)
+        text = "".join("{} {} {} {} {} {} {} {} {}\n".format(*p, c, field, value) for p, c in zip(problems, caps))
         out = subprocess.run([str(d / "p")], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, l.split())) for l in out.splitlines()]
 
@@ -127,6 +129,22 @@ def test_shapes_fit_the_kernel(routes):
 def test_not_where_the_caller_says(routes, field, value):
     # which rows the mid-M or the decode kernel gets, what a launch shape is to be, how many tiles a part of K has
     assert not any(r[0] for cap in (0, 16) for r in routes(GRID[::7], cap, field, value))
+
+
+def test_the_workspace_asked_for_holds_the_parts(routes):
+    # whatever AUTO cuts into parts over 128-column workgroups where there is room, it does in the room that w2_workspace_size reports
+    # (behind the int8 rows and their scales)
+    from paper_2508_06753_amd import binding as w2
+    problems = [(xt, M, K, N, g, G) for xt in (0, 1) for M in (33, 46, 62, 96, 132, 255, 310, 392, 669, 851, 1300) for K in (256, 2816, 6656, 8960, 16384, 24832)
+                for N in (1024, 1576, 2056, 3488, 3808, 6240, 11104, 23872, 49248) for g in (0, 1) if not (g and N % 32) for G in (64, 128)]
+    quant = lambda M, K: ((M * K + 15) // 16 * 16 + 4 * M + 255) // 256 * 256
+    room = [(w2.workspace_size(M, K, N, G, a16=bool(xt)) - (0 if xt else quant(M, K))) // (4 * M * N) for xt, M, K, N, _, G in problems]
+    parts = 0
+    for p, there, reported in zip(problems, routes(problems, 16), routes(problems, room)):
+        if there[0] == 2:
+            assert there == reported, p
+            parts += there[2] > 1
+    assert parts > 200
 
 
 def test_sides_of_autos_lines(routes):
