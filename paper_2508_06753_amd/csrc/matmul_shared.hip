@@ -35,15 +35,6 @@ using shared::Plan;
 using shared::built;
 using shared::range_lds;
 
-// Tiles whose weights were asked for between a chunk's loads and its use: at the end of every chunk CH - 1 of a tile.  h: the chunk's
-// place in its tile.
-constexpr int tiles_since(int h, int ch)
-{
-    int n = 0;
-    for (int e = 1; e < BUFS; ++e) n += (h - e + BUFS * ch) % ch == ch - 1;
-    return n;
-}
-
 // XT 0: int8 rows (w2a8), 1: bf16 rows (w2a16).  EX (int8 rows): every group's sum is converted exactly before it is scaled.
 template <int XT, int G, int RT, int CJ, int SH, bool EX>
 __global__ void __launch_bounds__(64 * SH * k_ranges(XT, G, RT, CJ, SH), (SH * k_ranges(XT, G, RT, CJ, SH) + 3) / 4)
@@ -193,14 +184,13 @@ shared_kernel(const char* __restrict__ X, const char* __restrict__ codes, const 
         }
     };
     v4i f0[RT], f1[RT];                                      // matrix operands of the chunk's two k-steps
-    // Chunk c was asked for BUFS - 1 chunks ago, ahead of that chunk's arithmetic; since then BUFS - 2 chunks and, after a tile's last
-    // chunk, weights were.  Behind the barrier every wave's part of the chunk is there, and nobody reads the chunk before any
-    // more: its matrix instructions have been issued, so its operands have been read.
+    // Behind the barrier every wave's part of the chunk is there, and nobody reads the chunk before any more: its matrix
+    // instructions have been issued, so its operands have been read.
     auto wait_chunk = [&](int h) {
-        if (h == 0) wait_loads<(BUFS - 2) * NJ + tiles_since(0, CH) * 2 * CJ>();
-        else if (h == 1) wait_loads<(BUFS - 2) * NJ + tiles_since(1, CH) * 2 * CJ>();
-        else if (h == 2) wait_loads<(BUFS - 2) * NJ + tiles_since(2, CH) * 2 * CJ>();
-        else wait_loads<(BUFS - 2) * NJ + tiles_since(3, CH) * 2 * CJ>();
+        if (h == 0) wait_loads<under_way(0, CH, NJ, CJ)>();
+        else if (h == 1) wait_loads<under_way(1, CH, NJ, CJ)>();
+        else if (h == 2) wait_loads<under_way(2, CH, NJ, CJ)>();
+        else wait_loads<under_way(3, CH, NJ, CJ)>();
     };
     auto turn_chunk = [&](int c, int buf, int h) {
         wait_chunk(h);

@@ -34,6 +34,16 @@ constexpr int k_ranges(int xt, int G, int rt, int cj, int sh)
     return std::min(waves / sh, (LDS - rt * 64) / range_lds(rt, cj, sh));
 }
 
+// Loads that may still be under way when a chunk is used, h its place among the ch chunks of a 256-k tile, nj a wave's loads per
+// chunk.  It was asked for BUFS - 1 chunks ago, ahead of that chunk's arithmetic; since then BUFS - 2 chunks were and, behind a tile's
+// last chunk, the weights and scales of another tile, one load of each per column block.
+constexpr int under_way(int h, int ch, int nj, int cj)
+{
+    int tiles = 0;
+    for (int e = 1; e < BUFS; ++e) tiles += (h - e + BUFS * ch) % ch == ch - 1;
+    return (BUFS - 2) * nj + tiles * 2 * cj;
+}
+
 // The shapes that are built: column blocks per wave x waves across the columns, a width of every number of blocks that came out fastest
 // on some grid (nine, eleven and thirteen never by more than a per cent).
 constexpr int N_SHAPES = 12;

@@ -1,5 +1,5 @@
 """The kernels that count their loads to local memory: what a barrier lets through has landed.  The order in which a wave issues its
-loads, walked with the kernels' own counts (csrc/tall_waits.h, compiled by itself); vector memory operations complete in order."""
+loads, walked with the kernels' own counts (csrc/tall_waits.h and csrc/shared_plan.h, compiled by themselves); vector memory operations complete in order."""
 import os
 import shutil
 import subprocess
@@ -8,6 +8,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
+#include "%s/paper_2508_06753_amd/csrc/shared_plan.h"
 #include "%s/paper_2508_06753_amd/csrc/tall_waits.h"
 #include <stdio.h>
 using namespace w2;
@@ -19,6 +20,11 @@ int main()
             for (int t = 0; t < 4; ++t) printf(" %%d %%d", tall::behind(pair, t, np, 0), tall::behind(pair, t, np, 1));
             printf("\n");
         }
+    for (int ch : {2, 4})
+        for (int rt = 2; rt <= 4; ++rt)
+            for (const auto& s : shared::SHAPES)
+                for (int h = 0; h < ch; ++h)
+                    printf("%%d %%d %%d %%d %%d %%d\n", ch, shared::BUFS, shared::loads(rt, s[1]), s[0], h, shared::under_way(h, ch, shared::loads(rt, s[1]), s[0]));
 }
 """
 
@@ -28,10 +34,14 @@ def counts(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("no g++")
     d = tmp_path_factory.mktemp("load_waits")
-    (d / "p.cpp").write_text(PROGRAM % ROOT)
+    (d / "p.cpp").write_text(PROGRAM % (ROOT, ROOT))
     subprocess.run(["g++", "-O1", "-std=c++17", "-o", str(d / "p"), str(d / "p.cpp")], check=True)
-    lines = iter(subprocess.run([str(d / "p")], capture_output=True, text=True, check=True).stdout.splitlines())
-    return {(pair, np_): tuple(map(int, next(lines).split())) for pair in (0, 1) for np_ in (1, 2, 3, 4)}
+    lines = [tuple(map(int, l.split())) for l in subprocess.run([str(d / "p")], capture_output=True, text=True, check=True).stdout.splitlines()]
+    counts = {(pair, np_): lines[4 * pair + np_ - 1] for pair in (0, 1) for np_ in (1, 2, 3, 4)}
+    counts["shared"] = {}
+    for ch, bufs, nj, cj, h, n in lines[8:]:
+        counts["shared"].setdefault((ch, bufs, nj, cj), {})[h] = n
+    return counts
 
 
 class Wave:
@@ -79,3 +89,26 @@ def test_tall_tiles(counts, pair, np_):
         assert all(tall(counts, pair, np_, per_tile, export, n) for n in range(5))
         # (the walk sees a count that is too high)
         assert not tall(counts, pair, np_, per_tile, product, 2) and not tall(counts, pair, np_, per_tile, product + 1, 4)
+
+
+def shared(bufs, ch, nj, cj, counts, tiles=12):
+    w, ok = Wave(), True
+    for c in range(bufs - 1):
+        w.load(c, nj)
+    for i in range(2):                                       # two tiles of weights in flight
+        w.load("weights", 2 * cj)
+    for c in range(tiles * ch):
+        w.wait(counts[c % ch])
+        ok &= w.has(c)
+        w.load(c + bufs - 1, nj)
+        if c % ch == ch - 1:
+            w.load("weights", 2 * cj)
+    return ok
+
+
+def test_shared_rows(counts):
+    for (ch, bufs, nj, cj), n in counts["shared"].items():
+        assert max(n.values()) < 64                          # (what a wait can count)
+        assert shared(bufs, ch, nj, cj, n)
+        assert not any(shared(bufs, ch, nj, cj, {**n, h: n[h] + 1}) for h in n)
+    assert len(counts["shared"]) == 12
