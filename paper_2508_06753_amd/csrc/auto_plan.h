@@ -53,7 +53,8 @@ inline double shared_share(int a16, int64_t M, const midm::Plan& p)
 // slower), 0.92 0.985 (15); groups of 64 0.90 0.973 (3 of 180), 0.94 0.971 (11); w2a16 0.90 0.966 (4 of 356), 0.94 0.965 (22).  Of
 // 420 further problems near the lines, time by the quotient of the prices: groups of 128 0.88 to 0.90 0.942, to 0.92 0.983, to 0.94 0.987, to 0.96
 // 1.008; groups of 64 0.90 to 0.92 0.981, to 0.94 0.983 (none slower by over 3 %), to 0.96 0.999; w2a16 0.90 to 0.92 0.985, to 0.94 1.010.
-// Where rows would be shared instead, 0.98.  Not offered where the mid-M kernel would run: 0.996 of its time over 414 problems.
+// (Part of what keeps the tall ones below 1: the prices of the 256-column tiles are from before their rows went straight to local
+// memory and run about 8 % high.)  Where rows would be shared instead, 0.98.  Not offered where the mid-M kernel would run: 0.996 of its time over 414 problems.
 constexpr double SLIM_SHARE = 0.98, SLIM_SHARE_LOW = 1.0, SLIM_SHARE_TALL[3] = {0.90, 0.94, 0.90};
 constexpr int64_t SLIM_LEAST_ROWS = 33;
 
@@ -77,7 +78,8 @@ struct Instead {
     tiles::Shape slim;
 };
 
-// `us`: price of the kernel that would run; the shares of it.  (Not where the caller says which rows the decode or the mid-M kernel
+// `us`: price of the kernel that would run; the shares of it.  The two prices take a call up to 0.13 us on the host, of the 4.8 that a
+// call of 17 to 144 rows takes there.  (Not where the caller says which rows the decode or the mid-M kernel
 // gets, or what a launch shape is to be.)
 inline Instead instead(int a16, const Problem& p, const w2_tuning_t& tn, double us, double shared_share, double slim_share)
 {

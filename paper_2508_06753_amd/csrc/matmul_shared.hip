@@ -5,17 +5,19 @@
 // x 28672 with 48 int8 rows the rows alone (448 workgroups of four blocks: 88 MB) take 4.0 us, the weights (31 MB out of memory) 4.1,
 // both 8.0, also where different waves or different CUs read them, however far ahead.  So a workgroup is a CU's share of the columns
 // wide, SH waves x CJ column blocks, and its K ranges (as many as sixteen waves allow) read every row once: 224 workgroups of eight
-// blocks, 44 MB.  Any width from two to sixteen blocks: 5120 x 34816, 2176 blocks, is one round of 218 workgroups of ten.
+// blocks, 44 MB.  Widths of two to eight blocks, ten, twelve, fourteen and sixteen: 5120 x 34816, 2176 blocks, is one round of 218
+// workgroups of ten.
 //
 // The rows go straight to local memory, 128 bytes of each at a time (a chunk), four buffers a range, three chunks under way; 16-byte
 // pieces XORED by row.  A barrier per chunk, behind every wave's counted wait for its own loads.  No registers hold rows on their way,
 // which is what leaves room for sixteen waves: four per SIMD, whose matrix and vector instructions cover each other's waits.  Weights,
 // up-convert, dequant and the meeting of the ranges are the other kernel's.
 //
-// Measured (graph-timed with weights out of memory, us; matmul_midm.hip's best shape -> this kernel): 4096 x 28672 int8 M = 48 / 64 15.2
-// / 17.5 -> 13.2 / 14.7, bf16 M = 64 23.7 -> 20.9; 5120 x 34816 gated int8 M = 16 / 32 / 48 / 64 15.5 / 19.1 / 20.8 / 28.1 -> 13.9 /
-// 16.3 / 18.6 / 21.9, bf16 M = 32 / 48 / 64 25.6 / 28.5 / 39.8 -> 24.2 / 27.2 / 31.3; 8192 x 10240 M = 48 int8 14.5 -> 11.9, bf16 20.2 ->
-// 17.4.  What bounds it (4096 x 28672, 48 int8 rows, copies with parts taken out, of 13.5): loads alone 11.6, without any 9.8,
+// Measured (graph-timed through the public calls with weights out of memory, us; matmul_midm.hip's best shape -> this kernel, where AUTO
+// takes it): 4096 x 28672 int8 M = 48 / 64 16.2 / 18.3 -> 13.7 / 15.5, bf16 M = 64 24.2 -> 22.0; gated int8 M = 48 15.1 -> 12.3, bf16
+// M = 64 23.0 -> 20.5; 5120 x 34816 gated int8 M = 24 / 32 / 48 / 64 17.9 / 19.3 / 20.2 / 23.9 -> 15.8 / 16.3 / 18.5 / 21.1, bf16 M = 32 /
+// 48 / 64 25.3 / 27.9 / 36.6 -> 23.4 / 26.6 / 30.3; 8192 x 57344 gated int8 M = 48 39.6 -> 33.8.  Counters (4096 x 28672 gated): vector
+// issue 39 % of the launch, matrix pipe 18 % (48 int8 rows) and 29 % (64 bf16 rows), waves wait half their time.  What bounds it (4096 x 28672, 48 int8 rows, copies with parts taken out, of 13.5): loads alone 11.6, without any 9.8,
 // launch and epilogue 3.5; with 64 bf16 rows, of 20.9: 13.9, 16.0, matrix instructions alone 11.0.
 #include <hip/hip_runtime.h>
 

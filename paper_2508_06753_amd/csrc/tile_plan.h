@@ -256,7 +256,8 @@ inline A8Shape a8_shape(int G, int64_t M, int64_t N, int64_t n_kt, int64_t cap, 
         const Shape t = pick(kind, M, N, n_kt, cap, 8, tune.splitk);
         const bool few = (M + 127) / 128 * ((N + 255) / 256) <= 128;
         const int bn = tune.tiled_bn == 128 || tune.tiled_bn == 256 ? tune.tiled_bn : few && t.splits < 2 ? 128 : 256;
-        // (128 columns and groups of 64: no instantiation that splits K)
+        // (128 columns and groups of 64: a forced width keeps the whole K, as it did when no instantiation there split it; AUTO's
+        // parts over 128 columns are `slim`'s)
         return {8, bn, 1, bn == 128 && G == 64 ? 1 : t.splits, t.us};
     }
     const Shape64 p = shape64(G, M, N, n_kt, cap, tune);

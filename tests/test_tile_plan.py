@@ -113,7 +113,7 @@ def test_forced_tiles(plans):
         assert rows == (128 if bm == 128 else 0)                             # (0: the 64-row kernel)
         assert width == bn if bn else width in ((128, 256) if bm == 128 else (64, 128, 256))
         assert 1 <= splits <= max(1, min(cap, n_kt))
-        assert splits == 1 or not (bm == 128 and width == 128 and G == 64)    # (not built)
+        assert splits == 1 or not (bm == 128 and width == 128 and G == 64)    # (the whole K there)
 
 
 def test_groups_of_64_on_narrow_grids(plans):
